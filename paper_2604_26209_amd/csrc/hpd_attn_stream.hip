@@ -33,7 +33,8 @@
 //    memory operations of a wave complete in order, so a wave with a deep DMA queue cannot
 //    get a latency-critical load through.  The two roles run different code paths and meet
 //    at barriers only.  (The prefill attention, which is bound by the compute waves and far
-//    from saturating the memory pipeline, runs a shape without loader waves: see DenseShape.)
+//    from saturating the memory pipeline, has a kernel without loader waves:
+//    attn_prefill_kernel.)
 //  * Contraction (transposed):
 //        S^T[key,row] = K.Q^T   (A = K fragment, B = rotated, pre-scaled Q in registers)
 //        O^T[d,row]  += V^T.P^T (A = V fragment, B = P)
@@ -74,6 +75,7 @@
 //    second instantiation of the same kernel; see the comment at the kernel.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "hpd_internal.h"
 #include "hpd_device.h"
@@ -89,6 +91,8 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int D = 128;
 constexpr int SLOT_U4 = 16 * 64;  // one 32-key block: 8 K + 8 V fragments of 64 x 16 bytes
 constexpr float NEG_BIG = -1.0e30f;
+// read-only for the whole launch: a wave-uniform address is read through the scalar cache
+typedef __attribute__((address_space(4))) int32_t const_i32;
 
 // Two shapes of workgroup:
 //   wide    6 compute waves + 2 loaders, stages of two blocks: 128.5 KB of LDS, one workgroup
@@ -105,18 +109,11 @@ struct Shape {
   static constexpr int WAVES = CW + LW;
   static constexpr int STAGE_U4 = SB * SLOT_U4;
   static constexpr int STAGE_ROWS = STAGE_U4 / 16;        // 256-byte rows a stage can hold
-  static constexpr int LOADS_PER_ROUND = SB * 16 / (LW ? LW : CW);  // DMA instructions per loading wave per stage
+  static constexpr int LOADS_PER_ROUND = SB * 16 / LW;  // DMA instructions per loader wave per stage
   static constexpr int MAX_BLOCKS = CW;                   // row blocks per workgroup
 };
 using WideShape = Shape<6, 2, 2>;
 using NarrowShape = Shape<3, 1, 1>;
-//   dense   4 compute waves that also load (no loader waves), stages of one block, two
-//           workgroups per CU.  For the prefill attention, which is bound by the matrix and
-//           vector work of the compute waves: two compute waves on every SIMD (a wave overlaps
-//           its matrix and its vector instructions only with those of another wave on its
-//           SIMD), and the memory pipeline, far from saturated there, takes the 4 DMA
-//           instructions a wave issues per stage without holding it up.
-using DenseShape = Shape<4, 0, 1>;
 
 struct StreamArgs {
   hpd_dev_tables tb;
@@ -134,20 +131,6 @@ struct StreamArgs {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gptr),   \
                                    (__attribute__((address_space(3))) void*)(lptr), 16, 0, 2)
 
-// The same two instructions (M0 = LDS byte address of lane 0's 16 bytes, then the load) written
-// out, for waves that request blocks and also read them: the compiler makes every LDS read of a
-// wave wait for all loads-to-LDS the wave has in flight (it cannot tell the stage that is read
-// from the stages that are being filled), and the ring lives on loads that stay in flight across
-// the reads.  Which stage may be read is what the barriers of the rounds establish.
-__device__ __forceinline__ void dma16(const void* g, const void* l) {
-  const uint32_t la = (uint32_t)__builtin_amdgcn_readfirstlane(
-      (int32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)l));
-  uint32_t keep;  // M0 is the compiler's: put back what it held
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-               : "=&s"(keep)
-               : "v"(g), "s"(la)
-               : "memory");
-}
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
   floatx2 v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
@@ -262,8 +245,6 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
   constexpr int BPB = 32 / G;              // branches (PREFILL: tokens) per row block
   constexpr int QPR = G >= 8 ? 1 : 8 / G;  // branch quads (tail tiles per 8 positions) per row block
   constexpr int CWAVES = SH::CW, LOADERS = SH::LW, STAGE_BLOCKS = SH::SB, STAGE_U4 = SH::STAGE_U4;
-  constexpr bool SELF = LOADERS == 0;  // the compute waves issue the loads themselves
-  static_assert(!SELF || (STAGE_BLOCKS * 4 == CWAVES), "one quarter of a block per wave and stage");
   constexpr int LOADS_PER_ROUND = SH::LOADS_PER_ROUND, STAGE_ROWS = SH::STAGE_ROWS;
   static_assert(2 * STAGE_ROWS >= CWAVES * 32, "stages 2 and 3 must hold the query rows of a row group");
   static_assert(3 * LOADS_PER_ROUND <= 63, "three rounds in flight must fit the vmcnt counter");
@@ -598,27 +579,6 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
     }
   };
   const bool table_first = use_fmt && NB + n_full_tiles < 2 * STAGE_BLOCKS;
-  // ---- the dense shape (prefill: prefix blocks only): wave w issues quarter w % 4 of block
-  //      w / 4 of a stage - the same loads as a loader's (quarters 0, 1: the K rows 0..15,
-  //      16..31; quarters 2, 3: the V half), 4 per wave and stage
-  auto issue_quarter = [&](int32_t pos, uint4* dst_slot, int32_t qt) {
-    static_assert(!SELF || PREFILL, "the compute waves load prefix blocks only");
-    const int32_t gb = min(pos, NBT - 1);
-    char* const dst = reinterpret_cast<char*>(dst_slot);
-    const int32_t half = qt & 1;
-    int32_t slot0;
-    if (PLIST) slot0 = gb < NBh ? scalar_load(a.tb.fblk + 2 * (hoff + gb)) : doff + (gb - NBh) * 32;
-    else slot0 = gb < NBh ? hoff + gb * 32 : doff + (gb - NBh) * 32;
-    if (qt < 2) {
-      const char* const sK = kpool + (int64_t)slot0 * (D * 2) + half * 4096;
-      char* const dk = dst + half * 4096;
-      dma16(sK + kq[0], dk); dma16(sK + kq[1], dk + 1024); dma16(sK + kq[2], dk + 2048); dma16(sK + kq[3], dk + 3072);
-    } else {
-      const char* const sV = vpool + (int64_t)slot0 * (D * 2) + half * 1024;
-      char* const dv = dst + 8192 + half * 4096;
-      dma16(sV + vq, dv); dma16(sV + 4096 + vq, dv + 1024); dma16(sV + 512 + vq, dv + 2048); dma16(sV + 4608 + vq, dv + 3072);
-    }
-  };
   if (append_first || table_first) {
     if (!loader) {
       if (append_first) append_from(ap_first + (tid >> 3));
@@ -674,31 +634,6 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
   //      loaders leave alone until the second barrier): chunk c of row r at position
   //      c ^ (r & 15).  One wave fetches the (cos, sin) row of the shared position.  The new
   //      rows of the append are requested in the same breath.
-  // (dense shape: the waves request their quarters of rounds 0 and 1 first, of rounds 2 and 3
-  // when the query staging has given stages 2 and 3 back, and of round r + 3 behind the barrier
-  // of round r; before that barrier a wave waits for its own loads of round r.  The shape serves
-  // the prefill only: nothing is appended, so loads are the only vector memory operations a wave
-  // has in flight during the rounds and their count says which have landed.)
-  int32_t issued = 0;
-  auto issue_upto = [&](int32_t lim) {
-    if constexpr (SELF) {
-      for (; issued < min(NR, lim); ++issued) {
-        const int32_t x = issued & 3;
-        uint4* stage = x == 0 ? ring0 : (x == 1 ? ring1 : (x == 2 ? ring2 : ring3));
-        issue_quarter(issued * STAGE_BLOCKS + (wave >> 2), stage + (wave >> 2) * SLOT_U4, wave & 3);
-      }
-    }
-  };
-  auto own_loads_landed = [&](int32_t s1) {  // of the stages before s1
-    if constexpr (SELF) {
-      const int32_t newer = issued - s1;
-      if (newer >= 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * LOADS_PER_ROUND) : "memory");
-      else if (newer == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS_PER_ROUND) : "memory");
-      else if (newer == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS_PER_ROUND) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
-  };
-  issue_upto(2);
   const bool append_late = a.fused && !append_first;
   const bool append_mine = append_late && ap_first + (tid >> 3) < ap_end;
   NewRows new_rows = {};
@@ -746,7 +681,6 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave has its rows
   __builtin_amdgcn_s_barrier();        // stages 2 and 3 go back to the loaders
-  issue_upto(4);
 
   // ---- rotate the query: MFMA B operands in half precision (11 significant bits; the keys of
   //      the cache hold bf16 values in half format, so one pass of the f16 matrix instruction
@@ -911,10 +845,8 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
     const int32_t gb_h_part = (Hlen & 31) ? NBh - 1 : -1, gb_d_part = (Llen & 31) ? NB - 1 : -1;
     for (int32_t s0 = 0; s0 < s_tail; ++s0) {
       if (s0 == r_pub) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores of the append are complete
-      own_loads_landed(s0 + 1);
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): LDS reads of the previous round are done
       __builtin_amdgcn_s_barrier();
-      issue_upto(s0 + 4);
       const int32_t st = s0 & 3;
       const uint4* stage = st == 0 ? ring0 : (st == 1 ? ring1 : (st == 2 ? ring2 : ring3));
 #pragma nounroll
@@ -937,10 +869,8 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
   for (int32_t s0 = s_first; s0 < NR;) {
     const int32_t s1 = round_end(s0);
     if (s0 == r_pub) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores of the append are complete
-    own_loads_landed(s1);
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): LDS reads of the previous round are done
     __builtin_amdgcn_s_barrier();
-    issue_upto(s0 + 4);
     if (active) {
 #pragma nounroll
       for (int32_t gb = s0 * STAGE_BLOCKS; gb < min(s1 * STAGE_BLOCKS, NBT); ++gb) {
@@ -1160,6 +1090,324 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Attention of the prefix tokens (first inference step): the default kernel of
+// hpd_prefill_attention.  Units, masks, blocks, fragment order and arithmetic are those of
+// attn_stream_kernel's prefill modes; LIST = MODE_PREFILL_LIST.
+//
+// Every token is a query, so the time goes into the compute waves, and what bounds them is the
+// number of instructions a block costs: on GQA 64/8 x 128 with documents of 2048 tokens the
+// general kernel's 121 scalar and 126 vector instructions (16 of them MFMA) per row block and key
+// block took twice the cycles of the matrix work, and the chip, limited by power, lowers its clock
+// under this load (2.1 -> 1.6..1.8 GHz), so that an instruction saved counts twice.  Hence
+//  * four waves of 32 rows, two workgroups per CU: two waves on every SIMD, whose matrix and
+//    vector work overlap, and the start and the end of one workgroup under the stream of the other;
+//  * every wave loads: quarter w of a block is four instructions that share one LDS address and
+//    one scalar base, and a lane's four offsets are computed once.  The loads are written out
+//    because the compiler makes every LDS read of a wave wait for all loads-to-LDS the wave has in
+//    flight;
+//  * a round is two blocks, and the ring holds two rounds: one barrier per 64 keys, the next
+//    round in flight while one is consumed (it comes out of the L2: the row groups of a segment
+//    run on one XCD);
+//  * two blocks per step through scores, one check of the reference point, softmax and value
+//    product; a loop of its own for the blocks that all rows see alike (one path from one
+//    iteration to the next: with masked blocks as a second path in the loop the compiler
+//    copied the 64 accumulators in every round);
+//  * the score products start from minus the reference point of the row instead of 0, so that
+//    they come out as the exponents.
+// Measured (us per call with hpd_prefix_fill, one box; before = the general kernel with four waves
+// that load): 32 prompts x (64 + 512 tokens), 32/8 heads 205 -> 176; 16 prompts x (128 + 2 x 2048),
+// 64/8 heads 3306 -> 2744 (750 -> 904 TFLOP/s); literal mask, 16 ragged prompts of up to 8
+// documents 4506 -> 3714 (791 -> 960 TFLOP/s).  Without the last two points: 188 / 3023 / 4297.
+// ---------------------------------------------------------------------------------------
+constexpr int PREFILL_WAVES = 4;  // row blocks per workgroup
+template <int G, bool LIST>
+__global__ void __launch_bounds__(PREFILL_WAVES * 64, 2)
+attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
+                    const uint16_t* __restrict__ v_prefix, void* __restrict__ out) {
+  constexpr int BPB = 32 / G;       // tokens per row block (wave)
+  constexpr int TPG = PREFILL_WAVES * BPB;      // tokens per row group (workgroup)
+  constexpr uint32_t BLK = 16384;   // bytes of a block: 8 KB of K rows, 8 KB of V fragments
+  __shared__ uint4 ring[4 * SLOT_U4];
+
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int n = lane & 31, g2 = lane >> 5, r4 = lane >> 4, c16 = lane & 15;
+  // (unit, kv head) and row group of this workgroup: as in attn_stream_kernel
+  const int32_t rg = (blockIdx.x >> 3) % a.RG;
+  const int32_t grp = ((blockIdx.x >> 3) / a.RG) * 8 + (blockIdx.x & 7);
+  if (grp >= a.n_groups) return;
+  const int32_t hk = grp % a.Hkv, u = grp / a.Hkv;
+  const int32_t* desc = a.tb.funit_desc + (int64_t)u * 8;
+  const int32_t hoff = desc[0], Hlen = desc[1], doff = desc[2], row0 = desc[4], n_seg_tok = desc[5], seg_pos0 = desc[6];
+  const int32_t tok0 = rg * TPG;  // first token of the row group, counted in the segment
+  if (tok0 >= n_seg_tok) return;  // uniform over the workgroup
+  const int32_t n_tok = min(TPG, n_seg_tok - tok0);
+
+  const int32_t NBh = LIST ? Hlen : (Hlen + 31) >> 5;      // blocks the segment sees in full
+  const int32_t NB = NBh + ((tok0 + n_tok - 1) >> 5) + 1;  // ... and its own up to the last token
+  const int32_t NR = (NB + 1) >> 1;
+  const const_i32* const list = (const const_i32*)(uintptr_t)(a.tb.fblk + 2 * (int64_t)(LIST ? hoff : 0));
+
+  // ---- this wave's quarter of a block (K rows 0..15, K rows 16..31, V d-blocks 0..1, 2..3): one
+  //      base, four 32-bit offsets.  The instruction's offset field moves the address in memory
+  //      and the address in LDS alike, so one M0 serves the four.
+  const bool is_v = wave >= 2;
+  uint32_t vo[4];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) {
+    const uint32_t k_off = (uint32_t)(r4 * 256 + ((c16 ^ r4 ^ (4 * f)) << 4));  // + f * 1024
+    // the V fragments f lie 0, 4096, 512, 4608 bytes from the first; 2048 keeps the offset positive
+    const uint32_t v_off = (uint32_t)(((g2 * 128 + n) << 4) + 2048 + (f & 1) * 4096 + (f >> 1) * 512 - f * 1024);
+    vo[f] = is_v ? v_off : k_off;
+  }
+  const char* const src = (is_v ? reinterpret_cast<const char*>(v_prefix) + (wave & 1) * 1024 - 2048
+                                : reinterpret_cast<const char*>(k_prefix) + (wave & 1) * 4096) +
+                          (int64_t)hk * a.NP * (D * 2);
+  const uint32_t ring_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)ring);
+  auto slot_of = [&](int32_t gb) -> int32_t {  // first pool slot of a block
+    if (gb >= NBh) return doff + (gb - NBh) * 32;
+    return LIST ? list[2 * gb] : hoff + gb * 32;
+  };
+  auto issue = [&](int32_t slot0, uint32_t at) {
+    const char* const s = src + (int64_t)slot0 * (D * 2);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(ring_lds + at + (uint32_t)wave * 4096);
+    uint32_t keep;  // M0 is the compiler's: put back what it held
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %6\n\t"
+        "global_load_lds_dwordx4 %2, %6 offset:1024\n\t"
+        "global_load_lds_dwordx4 %3, %6 offset:2048\n\t"
+        "global_load_lds_dwordx4 %4, %6 offset:3072\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(keep)
+        : "v"(vo[0]), "v"(vo[1]), "v"(vo[2]), "v"(vo[3]), "s"(dst), "s"(s)
+        : "memory");
+  };
+  // a block past the last one re-loads the last one (never read)
+  auto issue_round = [&](int32_t sA, int32_t sB, int32_t r) {
+    const uint32_t at = (uint32_t)(r & 1) * (2 * BLK);
+    issue(sA, at);
+    issue(sB, at + BLK);
+  };
+  // ---- the query rows of the wave, straight into operand layout, and their positions
+  const int32_t row = wave * 32 + n;  // row within the row group
+  const int32_t my_tok = tok0 + min(row / G, n_tok - 1);
+  const bool active = wave * BPB < n_tok;  // the wave has rows
+  uint4 qraw[8];
+  {
+    const uint16_t* qp = q + ((int64_t)(row0 + my_tok) * a.Hq + hk * a.Gr + min(row % G, a.Gr - 1)) * D + g2 * 8;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) qraw[kk] = *reinterpret_cast<const uint4*>(qp + kk * 16);
+  }
+  const int32_t pos = (!LIST || seg_pos0 >= 0) ? seg_pos0 + my_tok : a.tb.skel_pos[my_tok - seg_pos0 - 1];
+  issue_round(slot_of(0), slot_of(min(1, NB - 1)), 0);
+  if (NR > 1) issue_round(slot_of(2), slot_of(min(3, NB - 1)), 1);
+  f16x8 Qf[8];
+  {
+    const float4* cs_row = reinterpret_cast<const float4*>(a.tb.rope + (int64_t)pos * (D / 2));
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      float lo[8], hi[8], rl[8], rh[8];
+      unpack8(qraw[kk], lo);
+      unpack8(qraw[kk + 4], hi);
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        const float4 cs = cs_row[kk * 8 + g2 * 4 + e2];
+        hpd::rope_pair(lo[2 * e2], hi[2 * e2], cs.x, cs.y, rl[2 * e2], rh[2 * e2]);
+        hpd::rope_pair(lo[2 * e2 + 1], hi[2 * e2 + 1], cs.z, cs.w, rl[2 * e2 + 1], rh[2 * e2 + 1]);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { rl[e] *= a.scale_log2; rh[e] *= a.scale_log2; }
+      Qf[kk] = pack8_half(rl);
+      Qf[kk + 4] = pack8_half(rh);
+    }
+  }
+
+  float l_lane = 0.f;
+  floatx16 minus_m;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) minus_m[i] = 0.f;
+  float slack = -INFINITY;
+  floatx16 acc[4];
+#pragma unroll
+  for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[blk][i] = 0.f;
+
+  const int32_t krow = ((n >> 4) << 4) | (((n >> 2) & 1) << 3) | (((n >> 3) & 1) << 2) | (n & 3);
+  const char* const rc = reinterpret_cast<const char*>(ring);
+  // N consecutive blocks of the ring at `at`: scores, softmax, value product
+  auto compute = [&](auto nc, uint32_t at, bool masked, uint32_t ok0, uint32_t ok1) __attribute__((always_inline)) {
+    constexpr int N = decltype(nc)::value;
+    float s[N][16];
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      floatx16 S;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) S[i] = minus_m[i];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const f16x8 kf = __builtin_bit_cast(f16x8, *reinterpret_cast<const uint4*>(
+            rc + at + (krow * 256 + (((kk * 2 + g2) ^ (krow & 15)) << 4)) + b * BLK));
+        S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, Qf[kk], S, 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[b][i] = S[i];
+    }
+    if (masked) {
+#pragma unroll
+      for (int b = 0; b < N; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[b][i] = ((b ? ok1 : ok0) >> i) & 1 ? s[b][i] : -INFINITY;
+    }
+    float bm = NEG_BIG;
+#pragma unroll
+    for (int b = 0; b < N; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[b][i]);
+    if (__any(bm > slack)) {
+      bm = fmaxf(bm, __shfl_xor(bm, 32));
+      // (the first block sets the reference point whatever its sign)
+      const float d = slack < 0.f ? bm : fmaxf(bm, 0.f);
+      const float alpha = fast_exp2(-d);
+      slack = MAX_SLACK;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) minus_m[i] -= d;
+#pragma unroll
+      for (int b = 0; b < N; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[b][i] -= d;
+      l_lane *= alpha;
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[blk][i] *= alpha;
+    }
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      uint4 vf[8];
+#pragma unroll
+      for (int f = 0; f < 8; ++f) vf[f] = *reinterpret_cast<const uint4*>(rc + at + lane * 16 + b * BLK + 8192 + f * 1024);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[b][i] = fast_exp2(s[b][i]);
+      const f16x8 P0 = pack8_half(s[b]), P1 = pack8_half(s[b] + 8);
+      const uint4 w0 = __builtin_bit_cast(uint4, P0), w1 = __builtin_bit_cast(uint4, P1);
+      float la = sum_half_pair(w0.x, l_lane), lb = sum_half_pair(w1.x, 0.f);
+      la = sum_half_pair(w0.y, la); lb = sum_half_pair(w1.y, lb);
+      la = sum_half_pair(w0.z, la); lb = sum_half_pair(w1.z, lb);
+      la = sum_half_pair(w0.w, la); lb = sum_half_pair(w1.w, lb);
+      l_lane = la + lb;
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk) {
+        acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, vf[blk * 2]), P0, acc[blk], 0, 0, 0);
+        acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, vf[blk * 2 + 1]), P1, acc[blk], 0, 0, 0);
+      }
+    }
+  };
+  auto first_bits = [](int32_t cnt) -> uint32_t { return (1u << min(max(cnt, 0), 8)) - 1u; };
+
+  const int32_t tok_first = tok0 + wave * BPB, tok_last = min(tok_first + BPB, tok0 + n_tok) - 1;
+  const int32_t plain_end = NBh + (tok0 >> 5);  // blocks from here on reach into the row group
+  const int32_t h_part = !LIST && (Hlen & 31) ? NBh - 1 : -1;  // the header's last block is partial
+  const int32_t r_plain = plain_end >> 1;  // rounds whose blocks all rows see alike
+  int32_t nA = 0, nB = 0;
+  auto open_round = [&](int32_t r) __attribute__((always_inline)) {
+    // (the round after the first was requested in front of the loop)
+    if (r == 0 && NR > 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): LDS reads of the previous round are done
+    __builtin_amdgcn_s_barrier();        // the round is in LDS; the other half of the ring is free
+    if (r >= 1 && r + 1 < NR) issue_round(nA, nB, r + 1);
+    // where the blocks of round r + 2 lie
+    if (r + 2 < NR) {
+      nA = slot_of(2 * r + 4);
+      nB = slot_of(min(2 * r + 5, NB - 1));
+    }
+  };
+  auto keys_of = [&](int32_t b) -> int32_t {  // keys of a block that the segment sees in full
+    if (b >= NBh) return 32;
+    return LIST ? list[2 * b + 1] : b == h_part ? Hlen & 31 : 32;
+  };
+  auto ok_bits = [&](int32_t valid) -> uint32_t {
+    return first_bits(valid - g2 * 8) | (first_bits(valid - 16 - g2 * 8) << 8);
+  };
+  for (int32_t r = 0; r < r_plain; ++r) {
+    open_round(r);
+    const int32_t vA = keys_of(2 * r), vB = keys_of(2 * r + 1);
+    const bool masked = (vA & vB) != 32;
+    uint32_t ok0 = 0, ok1 = 0;
+    if (masked) { ok0 = ok_bits(vA); ok1 = ok_bits(vB); }
+    compute(std::integral_constant<int, 2>{}, (uint32_t)(r & 1) * (2 * BLK), masked, ok0, ok1);
+  }
+  for (int32_t r = r_plain; r < NR; ++r) {
+    open_round(r);
+#pragma nounroll
+    for (int32_t b = 2 * r; b < min(2 * r + 2, NB); ++b) {
+      int32_t valid = keys_of(b);
+      bool masked = valid < 32;
+      if (b >= NBh) {  // causal inside the segment: the row of token x keeps keys 0 .. x
+        const int32_t k0 = (b - NBh) * 32;
+        if (k0 > tok_last) break;
+        masked = k0 + 31 > tok_first;
+        valid = my_tok - k0 + 1;
+      }
+      compute(std::integral_constant<int, 1>{}, (uint32_t)(b & 3) * BLK, masked, ok_bits(valid), 0u);
+    }
+  }
+  __syncthreads();  // the ring is dead from here on and gets reused
+  if (!active) return;
+
+  // ---- normalise and write: as the waves of attn_stream_kernel that hold whole rows
+  const float inv = 1.0f / (l_lane + __shfl_xor(l_lane, 32));
+  uint4* const mine = ring + wave * 1024;
+  typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+  const int32_t rows_here = n_tok * G;
+  if (a.out_f32) {
+    float4* rowp = reinterpret_cast<float4*>(mine) + n * 32;
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc)
+        rowp[(blk * 8 + cc * 2 + g2) ^ n] = make_float4(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv,
+                                                        acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv);
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+    for (int32_t i = 0; i < 16; ++i) {  // 2 rows per instruction
+      const int32_t rr = i * 2 + (lane >> 5), chunk = lane & 31, lrr = wave * 32 + rr;
+      if (lrr < rows_here && lrr % G < a.Gr) {
+        const uint4 v = mine[rr * 32 + (chunk ^ rr)];
+        const int64_t off = ((int64_t)(row0 + tok0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 4;
+        u4v vv = {v.x, v.y, v.z, v.w};
+        __builtin_nontemporal_store(vv, reinterpret_cast<u4v*>(reinterpret_cast<float*>(out) + off));
+      }
+    }
+  } else {
+    uint2* rowp = reinterpret_cast<uint2*>(mine) + n * 32;
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc)
+        rowp[(((blk * 4 + cc) ^ (n & 15)) << 1) | g2] =
+            make_uint2(cvt_pk_bf16(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv),
+                       cvt_pk_bf16(acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv));
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+    for (int32_t i = 0; i < 8; ++i) {  // 4 rows per instruction
+      const int32_t rr = i * 4 + (lane >> 4), chunk = lane & 15, lrr = wave * 32 + rr;
+      if (lrr < rows_here && lrr % G < a.Gr) {
+        const uint4 v = mine[rr * 16 + (chunk ^ (rr & 15))];
+        const int64_t off = ((int64_t)(row0 + tok0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 8;
+        u4v vv = {v.x, v.y, v.z, v.w};
+        __builtin_nontemporal_store(vv, reinterpret_cast<u4v*>(reinterpret_cast<uint16_t*>(out) + off));
+      }
+    }
+  }
+}
+
 template <int G, typename SH, int MODE>
 hipError_t launch_g(const StreamArgs& a, int64_t items, const void* q, const void* k_prefix,
                     const void* v_prefix, void* k_tail, void* v_tail, const void* k_new,
@@ -1167,6 +1415,14 @@ hipError_t launch_g(const StreamArgs& a, int64_t items, const void* q, const voi
   attn_stream_kernel<G, SH, MODE><<<dim3((unsigned)items), SH::WAVES * 64, 0, s>>>(
       a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail,
       (uint16_t*)v_tail, (const uint16_t*)k_new, (const uint16_t*)v_new, out);
+  return hipGetLastError();
+}
+
+template <int G, bool LIST>
+hipError_t launch_prefill(const StreamArgs& a, int64_t items, const void* q, const void* k_prefix,
+                          const void* v_prefix, void* out, hipStream_t s) {
+  attn_prefill_kernel<G, LIST><<<dim3((unsigned)items), PREFILL_WAVES * 64, 0, s>>>(
+      a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
   return hipGetLastError();
 }
 
@@ -1263,14 +1519,10 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
   const int64_t n_units = (int64_t)L->funit_desc.size() / 8;
   if (n_units == 0) return hipSuccess;
   const int32_t max_nblk = std::max(1, (L->fmax_rows * G + 31) / 32);
-  // Every token is a query, so a segment has many row groups, and a row group streams only the
-  // keys up to its last token: many short workgroups, whose starts and ends overlap better
-  // with two workgroups per CU (the narrow shape measured 3 % to 23 % faster than the wide one
-  // on the four bf16 configurations), and whose time goes into the compute waves' matrix and
-  // vector work, not into memory: the dense shape (0 % to 5 % faster than the narrow one).
-  // kernel_mode 3 / 4 force the wide / the narrow shape.
-  const bool narrow = L->kernel_mode == 4, wide = L->kernel_mode == 3, dense = !narrow && !wide;
-  const int32_t shape_blocks = narrow ? NarrowShape::MAX_BLOCKS : dense ? DenseShape::MAX_BLOCKS : WideShape::MAX_BLOCKS;
+  // kernel_mode 3 / 4 force the general kernel's wide / narrow shape; otherwise the prefill's own
+  // kernel, which is faster from the smallest batches measured to the largest (see there).
+  const bool narrow = L->kernel_mode == 4, wide = L->kernel_mode == 3, own = !narrow && !wide;
+  const int32_t shape_blocks = narrow ? NarrowShape::MAX_BLOCKS : own ? PREFILL_WAVES : WideShape::MAX_BLOCKS;
   a.RG = (max_nblk + shape_blocks - 1) / shape_blocks;
   a.n_groups = (int32_t)(n_units * a.Hkv);
   const int64_t items = ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
@@ -1279,8 +1531,7 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
 #define HPD_LAUNCH_M(GG, PP)                                                                   \
   (narrow ? launch_g<GG, NarrowShape, PP>(a, items, q, k_prefix, v_prefix, nullptr, nullptr,  \
                                           nullptr, nullptr, out, s)                           \
-   : dense ? launch_g<GG, DenseShape, PP>(a, items, q, k_prefix, v_prefix, nullptr, nullptr,  \
-                                          nullptr, nullptr, out, s)                           \
+   : own ? launch_prefill<GG, PP == MODE_PREFILL_LIST>(a, items, q, k_prefix, v_prefix, out, s) \
           : launch_g<GG, WideShape, PP>(a, items, q, k_prefix, v_prefix, nullptr, nullptr,    \
                                         nullptr, nullptr, out, s))
 #define HPD_LAUNCH(GG) (list ? HPD_LAUNCH_M(GG, MODE_PREFILL_LIST) : HPD_LAUNCH_M(GG, MODE_PREFILL))

@@ -709,10 +709,44 @@ def test_prefill_attention_bf16_all_kernels(g):
     block, segments of many row groups, empty headers, ragged ends."""
     wl = W.random_workload(92 + g, dtype="bf16", hq=8, hkv=8 // g, d=128, base=500000.0, t=2, p=3,
                            j_range=(1, 3), h_range=(0, 90), l_range=(1, 260 if g > 1 else 700))
-    for mode in (0, 1, 3, 4):  # 0: the default, the dense shape
+    for mode in (0, 1, 3, 4):  # 0: the prefill's own kernel
         _say(f"prefill bf16 G={g} mode {mode}: {wl.n_prefix_tokens} tokens")
         rel = _check_prefill(wl, mode, f"prefill_bf16_g{g}_m{mode}")
         _say(f"  worst err/rms {rel:.2e}")
+
+
+@pytest.mark.parametrize("literal", [False, True])
+@pytest.mark.parametrize("g", [1, 3, 4, 8])
+def test_prefill_attention_at_the_edges_of_its_blocks(g, literal):
+    """The prefill kernel's rounds of two 32-key blocks: no header, headers that end inside or at
+    the end of either block of a round, documents of one token, of a row group and one token more or
+    less, an odd and an even number of blocks; 3 query heads per kv head run with a padding row."""
+    grp = 128 // (4 if g == 3 else g)  # tokens per row group
+    header = [0, 1, 31, 32, 33, 64, 95]
+    per = [2, 1, 3, 2, 2, 1, 2]
+    doc = [1, grp, grp + 1, 31, 33, 2 * grp - 1, 32, 64, 65, 3 * grp + 5, 96, 1, 97]
+    n_doc = len(doc)
+    attr = np.arange(n_doc).astype(np.int32) * 11 % 40 + 1 if literal else None
+    from paper_2604_26209_amd import binding as B
+    for hkv in (1, 2):
+        wl = W.make_workload("edges", "bf16", g * hkv, hkv, 128, 500000.0, 2, header, per, doc, [1] * n_doc, [2] * n_doc)
+        _say(f"prefill edges G={g} hkv={hkv} literal={literal}: {wl.n_prefix_tokens} tokens")
+        rel = _check_prefill(wl, 0, f"prefill_edges_g{g}_{literal}", attr_len=attr)
+        _say(f"  worst err/rms {rel:.2e}")
+        # bf16 outputs are the fp32 outputs rounded to nearest even, nothing else
+        outs = []
+        for out_dtype, dt in ((B.HPD_OUT_F32, torch.float32), (B.HPD_OUT_SAME, torch.bfloat16)):
+            layout = B.layout_from_workload(wl, out_dtype=out_dtype,
+                                            **(dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=attr,
+                                                    mask_mode=B.HPD_MASK_PAPER) if literal else {}))
+            n_tok = int(layout.counts()[B.HPD_C_N_PREFIX_TOKENS])
+            inputs = H.Inputs(wl, layout.n_live(), "cuda", n_tok)
+            q = W.normal_values((n_tok, g * hkv, 128), 5, "cuda", "bf16")
+            kp, vp, _, _ = B.alloc_pools(layout)
+            B.hpd_prefix_fill(layout, inputs.k_raw, inputs.v_raw, kp, vp)
+            outs.append(torch.zeros((n_tok, g * hkv, 128), dtype=dt, device="cuda"))
+            B.hpd_prefill_attention(layout, q, kp, vp, outs[-1])
+        assert torch.equal(outs[0].to(torch.bfloat16), outs[1])
 
 
 def test_prefill_attention_literal_mask_fp32_generic():
