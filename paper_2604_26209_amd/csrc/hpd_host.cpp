@@ -609,6 +609,11 @@ int hpd_decode_attention(const hpd_layout* L, int32_t step, const void* q, const
   } else {
     // the generic kernel keeps one score per key in LDS
     if (hpd_generic_max_keys(L, step) > 15000) return HPD_E_UNSUPPORTED;
+    if (hpd_attention_f32_supported(L, k_prefix, v_prefix, k_tail)) {
+      HPD_HIP(hpd_launch_attention_stream(L, step, q, k_prefix, v_prefix, const_cast<void*>(k_tail),
+                                          const_cast<void*>(v_tail), nullptr, nullptr, out, (hipStream_t)stream));
+      return HPD_OK;
+    }
     HPD_HIP(hpd_launch_attention_generic(L, step, q, k_prefix, v_prefix, k_tail, v_tail, out,
                                          (hipStream_t)stream));
   }
@@ -656,6 +661,11 @@ int hpd_decode_step(const hpd_layout* L, int32_t step, const void* q, const void
     // one launch: the attention kernel rotates, stores and uses the new keys itself
     HPD_HIP(hpd_launch_attention_stream(L, step, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new,
                                         out, (hipStream_t)stream));
+    return HPD_OK;
+  }
+  if (hpd_attention_f32_supported(L, k_prefix, v_prefix, k_tail) && hpd_generic_max_keys(L, step) <= 15000) {
+    HPD_HIP(hpd_launch_attention_stream(L, step, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out,
+                                        (hipStream_t)stream));
     return HPD_OK;
   }
   rc = hpd_kv_append(L, step, k_new, v_new, k_tail, v_tail, nullptr, stream);

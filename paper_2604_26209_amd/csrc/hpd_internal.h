@@ -123,6 +123,20 @@ hipError_t hpd_launch_expand_mask(const int32_t* d_desc, int32_t S, int32_t pape
 hipError_t hpd_launch_finetune_mask(const int32_t* d_desc, int32_t S, int32_t* pos_out, uint8_t* mask_out,
                                     hipStream_t s);
 
+// fp32 decode attention (hpd_attn_f32.hip): one row group of 16 rows holds the query heads of at
+// least one branch; 16-byte loads from the pools.  kernel_mode 1 forces the generic kernel.
+constexpr int32_t HPD_F32_ROWS = 16;
+inline bool hpd_attention_f32_supported(const hpd_layout* L, const void* k_prefix, const void* v_prefix,
+                                        const void* k_tail) {
+  const int32_t D = L->cfg.head_dim;
+  return L->kernel_mode == 0 && L->cfg.dtype == HPD_F32 && L->cfg.mask_mode == HPD_MASK_BLOCK &&
+         (D == 32 || D == 64 || D == 128) && L->cfg.n_q_heads / L->cfg.n_kv_heads <= HPD_F32_ROWS &&
+         (((uintptr_t)k_prefix | (uintptr_t)v_prefix | (uintptr_t)k_tail) & 15) == 0;
+}
+hipError_t hpd_launch_attention_f32(const hpd_layout* L, int32_t step, const void* q, const void* k_prefix,
+                                    const void* v_prefix, void* k_tail, void* v_tail, const void* k_new,
+                                    const void* v_new, void* out, hipStream_t s);
+
 // most keys any row of the step has in the generic kernel (it keeps one score per key in LDS)
 int64_t hpd_generic_max_keys(const hpd_layout* L, int32_t step);
 
@@ -132,6 +146,7 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
 hipError_t hpd_launch_prefill_generic(const hpd_layout* L, const void* q, const void* k_prefix,
                                       const void* v_prefix, void* out, hipStream_t s);
 // k_new / v_new may be null: then the newest token is read from the tail pool like the others
+// fp32 layouts (where hpd_attention_f32_supported says so): hpd_launch_attention_f32
 // dynamic: work lists and live list from the device-side pruning state instead of the tables
 // built from branch_len
 hipError_t hpd_launch_attention_stream(const hpd_layout* L, int32_t step, const void* q,

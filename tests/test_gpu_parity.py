@@ -836,6 +836,54 @@ def test_mask_export_bit_exact():
         assert np.array_equal(m.cpu().numpy(), po.dense_mask())
 
 
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("g", [1, 3, 5, 16])
+def test_fp32_decode_kernel_at_the_edges_of_its_tiles(g, d):
+    """Row groups of 16 rows (16, 5, 3 and 1 branches), tiles of 16 keys: headers and documents around a
+    tile, no header, one branch, exactly one row group and one branch more, branches that end (so
+    that a document's live branches are no run of ids), tails of 1 to 12 positions.  Against the
+    oracle, the step call against the two-call sequence, and against the generic kernel (fp32 sums of
+    at most 200 terms of size 1 in another order: 1e-5)."""
+    hkv, per_group = 2, 16 // g
+    header, per, doc = [0, 1, 16, 33], [2, 1, 2, 1], [1, 15, 17, 160, 32, 47]
+    nbr = [1, per_group, per_group + 1, 2, 2 * per_group + 1, 3]
+    blen = 1 + np.arange(sum(nbr)) * 7 % 12
+    wl = W.make_workload("f32edges", "f32", g * hkv, hkv, d, 10000.0, 12, header, per, doc, nbr, blen)
+    _say(f"fp32 decode edges G={g} D={d}")
+    two = H.run_hip(wl)
+    worst = H.check_all(wl, two, label=f"f32_edges_g{g}_d{d}")
+    one = H.run_hip(wl, inputs=two["inputs"], fused=True)
+    gen = H.run_hip(wl, inputs=two["inputs"], kernel_mode=1)
+    for x, y, z in zip(two["out"], one["out"], gen["out"]):
+        assert torch.equal(x, y)
+        assert x.numel() == 0 or float((x - z).abs().max()) < 1e-5
+    _say(f"  max-abs against the oracle {worst:.2e}")
+
+
+def test_fp32_decode_kernel_keeps_infinite_values_in_their_branch():
+    """A branch whose newest value is infinite or NaN: the other branches' rows, which share its tile, stay as
+    they are without it."""
+    from paper_2604_26209_amd import binding as B
+    wl = W.make_workload("f32inf", "f32", 4, 2, 64, 10000.0, 4, [5], [1], [40], [11], [4] * 11)
+    layout = B.layout_from_workload(wl)
+    inputs = H.Inputs(wl, layout.n_live(), "cuda")
+    outs = []
+    for bad in (False, True):
+        kp, vp, kt, vt = B.alloc_pools(layout)
+        B.hpd_prefix_fill(layout, inputs.k_raw, inputs.v_raw, kp, vp)
+        v = [x.clone() for x in inputs.v_new]
+        if bad:
+            v[1][3, 0, 7], v[2][9, 1, 8] = float("inf"), float("nan")
+        for t in range(4):
+            out = torch.zeros(11, 4, 64, device="cuda")
+            B.hpd_decode_step(layout, t, inputs.q[t], inputs.k_new[t], v[t], kp, vp, kt, vt, out)
+        outs.append(out.cpu())
+    same = torch.ones(11, 4, 64, dtype=torch.bool)
+    same[3, :2, 7], same[9, 2:, 8] = False, False
+    assert torch.equal(outs[0][same], outs[1][same])
+    assert not torch.isfinite(outs[1][~same]).any()
+
+
 def test_kv_pools_hold_rotated_keys_at_reported_slots():
     """K tail and prefix pools against the oracle's cache (rotated K), through the
     documented pool layouts."""
