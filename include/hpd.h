@@ -362,8 +362,8 @@ int hpd_set_tail_pages(hpd_layout* layout, int32_t page_size, int32_t n_pages, c
  *   pos_out  : device int32 [S] or NULL
  *   mask_out : device uint8 [S][S] row-major (query row, key column) or NULL
  *   s_out    : host int64*, receives S = prompt_len + sum(attr_len) + sum(value_len)
- * Integer work only.  Allocates and frees a token table of 16 S bytes and synchronises the
- * stream: a data-preparation call, not a per-step one.  HPD_E_INVALID for lengths out of
+ * Integer work only.  Synchronises the stream (and, with more than 640 attributes, allocates and
+ * frees a table of 6 bytes each): a data-preparation call, not a per-step one.  HPD_E_INVALID for lengths out of
  * range, HPD_E_OVERFLOW if S exceeds 46000 or a position 2^30.
  */
 int hpd_finetune_mask(int32_t prompt_len, int32_t n_attr, const int32_t* attr_len,

@@ -842,25 +842,26 @@ int hpd_finetune_mask(int32_t prompt_len, int32_t n_attr, const int32_t* attr_le
   if (S > 46000 || S + (int64_t)n_attr * k_max > ((int64_t)1 << 30)) return HPD_E_OVERFLOW;
   *s_out = S;
   if (S == 0 || (!pos_out && !mask_out)) return HPD_OK;
-  // token table in the regular order; Algorithm 2 for the skeleton, end(a_n) + k for values
-  std::vector<int32_t> desc;
-  desc.reserve((size_t)S * 4);
-  for (int32_t i = 0; i < prompt_len; ++i) desc.insert(desc.end(), {0, -1, 0, i});
-  int32_t next = prompt_len, offset = 0;
-  for (int32_t n = 0; n < n_attr; ++n) {
-    for (int32_t i = 0; i < attr_len[n]; ++i) desc.insert(desc.end(), {1, n, 0, next++ + offset});
-    const int32_t end_pos = desc[desc.size() - 1];
-    for (int32_t k = 1; k <= value_len[n]; ++k) desc.insert(desc.end(), {2, n, k, end_pos + k});
-    offset += k_max;
-  }
-  int32_t* d_desc = nullptr;
+  // where every attribute's name and value tokens start in the regular order, and the name tokens in
+  // front of it
   hipStream_t s = (hipStream_t)stream;
-  HPD_HIP(hipMalloc((void**)&d_desc, desc.size() * sizeof(int32_t)));
-  hipError_t e = hipMemcpyAsync(d_desc, desc.data(), desc.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hpd_launch_finetune_mask(d_desc, (int32_t)S, pos_out, mask_out, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  (void)hipFree(d_desc);
-  if (e != hipSuccess) return hip_fail(e);
+  try {
+    std::vector<int32_t> table(3 + 3 * (size_t)n_attr);
+    table[0] = prompt_len; table[1] = n_attr; table[2] = k_max;
+    int32_t *first_name = table.data() + 3, *first_value = first_name + n_attr, *before = first_value + n_attr;
+    int32_t at = prompt_len, names = 0;
+    for (int32_t n = 0; n < n_attr; ++n) {
+      first_name[n] = at;
+      first_value[n] = at + attr_len[n];
+      before[n] = names;
+      at += attr_len[n] + value_len[n];
+      names += attr_len[n];
+    }
+    HPD_HIP(hpd_launch_finetune_mask(table.data(), (int32_t)S, pos_out, mask_out, s));
+  } catch (const std::bad_alloc&) {
+    return HPD_E_NOMEM;
+  }
+  HPD_HIP(hipStreamSynchronize(s));
   return HPD_OK;
 }
 

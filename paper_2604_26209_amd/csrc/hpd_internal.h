@@ -119,8 +119,9 @@ hipError_t hpd_launch_attention_generic(const hpd_layout* L, int32_t step, const
 hipError_t hpd_launch_expand_mask(const int32_t* d_desc, int32_t S, int32_t paper, uint8_t* mask_out,
                                   hipStream_t s);
 
-// desc[S][4] = (kind 0 prompt / 1 attribute / 2 value, attribute index, k, position ID)
-hipError_t hpd_launch_finetune_mask(const int32_t* d_desc, int32_t S, int32_t* pos_out, uint8_t* mask_out,
+// table (host): prompt tokens, attributes, k_max, then [3][attributes]: first name token, first value
+// token, name tokens of earlier attributes
+hipError_t hpd_launch_finetune_mask(const int32_t* table, int32_t S, int32_t* pos_out, uint8_t* mask_out,
                                     hipStream_t s);
 
 // fp32 decode attention (hpd_attn_f32.hip): one row group of 16 rows holds the query heads of at

@@ -4,6 +4,7 @@
 // in hpd_attn_stream.hip.
 #include <algorithm>
 #include <mutex>
+#include <vector>
 
 #include "hpd_internal.h"
 #include "hpd_device.h"
@@ -329,25 +330,75 @@ dynamic_prune_kernel(int32_t n_docs, int32_t B, int32_t next_step, const uint8_t
 }
 
 // ---------------------------------------------------------------------------------------
-// Fine-tuning mask (Section 4.4).  desc[S][4] = (kind, attribute, k, position ID) in the regular
-// token order; kind 0 prompt, 1 attribute, 2 value token.
+// Fine-tuning mask (Section 4.4): one byte per (query, key) in the regular token order.  The rule
+// - causal, attribute tokens never see values, value token k of attribute n does not see value
+// k' > k of an earlier attribute - is one comparison of two codes: a key is (attribute, k) with
+// k >= 1 for a value and 0 otherwise, a query is (attribute, k) for a value, (all attributes, 0)
+// for an attribute token, (none, 0) for the prompt; the key is hidden if its attribute and its k
+// are smaller resp. larger than the query's.
+// Bound by the bytes it writes.  A workgroup takes FT_ROWS queries x FT_KEYS keys: it expands the
+// attributes' start offsets into key codes in LDS, a thread then holds 16 keys and writes 16 bytes per
+// query (not aligned where S is no multiple of 16).  The offsets travel in the kernel's arguments
+// (FT_EMBED attributes at most, else in device memory), so that a call allocates and copies
+// nothing.  Measured on 4000
+// tokens, whole call with its synchronisation: 69 -> 33 us (before: a byte per thread, two launches, a
+// table of 16 bytes per token built, allocated, copied and freed by every call).
 // ---------------------------------------------------------------------------------------
-__global__ void finetune_mask_kernel(const int32_t* __restrict__ desc, int32_t S,
-                                     uint8_t* __restrict__ mask) {
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)S * S) return;
-  const int32_t qi = (int32_t)(gid / S), ki = (int32_t)(gid % S);
-  const int32_t qk = desc[qi * 4], qn = desc[qi * 4 + 1], qs = desc[qi * 4 + 2];
-  const int32_t kk = desc[ki * 4], kn = desc[ki * 4 + 1], ks = desc[ki * 4 + 2];
-  bool ok = ki <= qi;                                       // causal
-  if (kk == 2 && qk == 1) ok = false;                       // attributes never see values
-  if (kk == 2 && qk == 2 && kn < qn && ks > qs) ok = false;  // not generated yet
-  mask[gid] = ok ? 1 : 0;
-}
-
-__global__ void finetune_pos_kernel(const int32_t* __restrict__ desc, int32_t S, int32_t* __restrict__ pos) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < S) pos[i] = desc[i * 4 + 3];
+constexpr int FT_ROWS = 8, FT_KEYS = 4096, FT_EMBED = 640;
+struct FtOffsets {
+  uint16_t name[FT_EMBED], value[FT_EMBED], before[FT_EMBED];  // first name / value token, names of earlier attributes
+};
+template <bool EMBED>
+__global__ void __launch_bounds__(256)
+finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_attr, int32_t prompt_len, int32_t k_max,
+                     int32_t S, int32_t* __restrict__ pos, uint8_t* __restrict__ mask) {
+  __shared__ uint32_t key[FT_KEYS];   // attribute << 16 | k
+  __shared__ uint32_t query[FT_ROWS];
+  const int32_t tid = threadIdx.x, q0 = blockIdx.x * FT_ROWS, k0 = blockIdx.y * FT_KEYS;
+  for (int32_t i = tid; i < FT_KEYS; i += 256) key[i] = 0;
+  if (tid < FT_ROWS) query[tid] = 0;
+  if (pos && k0 == 0 && tid < FT_ROWS && q0 + tid < min(S, prompt_len)) pos[q0 + tid] = q0 + tid;
+  __syncthreads();
+  const uint16_t* const name = EMBED ? emb.name : dev;
+  const uint16_t* const value = EMBED ? emb.value : dev + n_attr;
+  const uint16_t* const before = EMBED ? emb.before : dev + 2 * n_attr;
+  for (int32_t a = tid; a < n_attr; a += 256) {
+    const int32_t ns = name[a], vs = value[a], ve = a + 1 < n_attr ? (int32_t)name[a + 1] : S;
+    for (int32_t i = max(vs, k0); i < min(ve, k0 + FT_KEYS); ++i) key[i - k0] = (uint32_t)a << 16 | (uint32_t)(i - vs + 1);
+    for (int32_t i = max(ns, q0); i < min(ve, q0 + FT_ROWS); ++i) {
+      query[i - q0] = i < vs ? 0xffff0000u : (uint32_t)a << 16 | (uint32_t)(i - vs + 1);
+      // a value continues from its attribute's last token
+      if (pos && k0 == 0) pos[i] = prompt_len + before[a] + a * k_max + (i - ns);
+    }
+  }
+  __syncthreads();
+  const int32_t kc = k0 + tid * 16;  // this thread's first key
+  if (!mask || kc >= S) return;
+  uint32_t code[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) code[e] = key[tid * 16 + e];
+#pragma unroll
+  for (int r = 0; r < FT_ROWS; ++r) {
+    const int32_t qi = q0 + r;
+    if (qi >= S) break;
+    const uint32_t qn = query[r] >> 16, qk = query[r] & 0xffffu;
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (kc <= qi) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const bool ok = kc + e <= qi && !((code[e] >> 16) < qn && (code[e] & 0xffffu) > qk);
+        w[e >> 2] |= (ok ? 1u : 0u) << (8 * (e & 3));
+      }
+    }
+    uint8_t* const dst = mask + (int64_t)qi * S + kc;
+    if (kc + 16 <= S) {
+      __builtin_memcpy(dst, w, 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (kc + e < S) dst[e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -674,11 +725,32 @@ hipError_t hpd_launch_expand_mask(const int32_t* d_desc, int32_t S, int32_t pape
   return hipGetLastError();
 }
 
-hipError_t hpd_launch_finetune_mask(const int32_t* d_desc, int32_t S, int32_t* pos_out, uint8_t* mask_out,
-                                    hipStream_t s) {
-  if (pos_out) finetune_pos_kernel<<<grid1d(S, 256), 256, 0, s>>>(d_desc, S, pos_out);
-  if (mask_out) finetune_mask_kernel<<<grid1d((int64_t)S * S, 256), 256, 0, s>>>(d_desc, S, mask_out);
-  return hipGetLastError();
+hipError_t hpd_launch_finetune_mask(const int32_t* table, int32_t S, int32_t* pos_out, uint8_t* mask_out, hipStream_t s) {
+  const int32_t prompt_len = table[0], n_attr = table[1], k_max = table[2];
+  const int32_t* off = table + 3;  // [3][n_attr], all below 2^16
+  const dim3 grid((unsigned)((S + FT_ROWS - 1) / FT_ROWS), mask_out ? (unsigned)((S + FT_KEYS - 1) / FT_KEYS) : 1u);
+  FtOffsets emb = {};
+  if (n_attr <= FT_EMBED) {
+    for (int32_t n = 0; n < n_attr; ++n) {
+      emb.name[n] = (uint16_t)off[n];
+      emb.value[n] = (uint16_t)off[n_attr + n];
+      emb.before[n] = (uint16_t)off[2 * n_attr + n];
+    }
+    finetune_mask_kernel<true><<<grid, 256, 0, s>>>(emb, nullptr, n_attr, prompt_len, k_max, S, pos_out, mask_out);
+    return hipGetLastError();
+  }
+  std::vector<uint16_t> host(off, off + 3 * (size_t)n_attr);
+  uint16_t* dev = nullptr;
+  hipError_t e = hipMalloc((void**)&dev, host.size() * sizeof(uint16_t));
+  if (e != hipSuccess) return e;
+  e = hipMemcpyAsync(dev, host.data(), host.size() * sizeof(uint16_t), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) {
+    finetune_mask_kernel<false><<<grid, 256, 0, s>>>(emb, dev, n_attr, prompt_len, k_max, S, pos_out, mask_out);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  (void)hipFree(dev);
+  return e;
 }
 
 // ---------------------------------------------------------------------------------------

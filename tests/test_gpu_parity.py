@@ -800,6 +800,36 @@ def test_prefix_fill_fast_kernel_equals_general_kernel(literal):
     assert bool((pools[0][0] != 3.0).any())
 
 
+@pytest.mark.parametrize("n_attr", [0, 1, 640, 641])
+@pytest.mark.parametrize("plen", [0, 15, 16, 4090])
+def test_finetune_mask_at_the_edges_of_its_blocks(plen, n_attr):
+    """Sequences that are no multiple of the 16 keys of a thread, of the 8 queries and 4096 keys of a workgroup,
+    the number of attributes around what travels in the kernel's arguments, with and without positions."""
+    from oracle import finetune_mask as F
+    from paper_2604_26209_amd import binding as B
+    al, vl = 1 + np.arange(n_attr) % 3, np.arange(n_attr) * 5 % 4
+    if n_attr == 1:
+        vl = np.array([37])
+    kmax = 40
+    s = plen + int(al.sum() + vl.sum())
+    _say(f"finetune mask edges: prompt {plen}, {n_attr} attributes, {s} tokens")
+    assert B.hpd_finetune_mask(plen, al, vl, kmax) == s
+    if s == 0:
+        return
+    pos = torch.full((s + 8,), -7, dtype=torch.int32, device="cuda")
+    m = torch.full((s * s + 64,), 9, dtype=torch.uint8, device="cuda")
+    B.hpd_finetune_mask(plen, al, vl, kmax, pos[:s], m[:s * s].view(s, s))
+    assert np.array_equal(pos[:s].cpu().numpy(), F.finetune_position_ids(plen, al, vl, kmax))
+    assert bool((pos[s:] == -7).all()) and bool((m[s * s:] == 9).all())
+    # the rule over codes (attribute, k) of all pairs, as in the docstring of the oracle's loop
+    owner = np.concatenate([np.full(plen, -1)] + [np.full(a + v, n) for n, (a, v) in enumerate(zip(al, vl))])
+    k = np.concatenate([np.zeros(plen, int)] + [np.r_[np.zeros(a, int), 1:v + 1] for a, v in zip(al, vl)])
+    value, name = k > 0, (k == 0) & (owner >= 0)
+    ok = np.tri(s, dtype=bool) & ~(value[None] & name[:, None])
+    ok &= ~(value[None] & value[:, None] & (owner[None] < owner[:, None]) & (k[None] > k[:, None]))
+    assert np.array_equal(m[:s * s].view(s, s).cpu().numpy(), ok.astype(np.uint8))
+
+
 def test_finetune_mask_and_positions_bit_exact():
     """hpd_finetune_mask (Section 4.4) against the loop oracle: mask and position IDs."""
     from oracle import finetune_mask as F
