@@ -269,6 +269,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
             L->pblk.push_back(L->seg_off[P + d] + i);
             L->pblk.push_back(std::min<int32_t>(HPD_KEY_BLOCK, doc_len[d] - i));
           }
+        L->pblk_docs.push_back((int32_t)(L->pblk.size() / 2) - L->pblk_ptr[p]);
         // then the blocks of the attribute names: a row keeps the names up to its own branch's,
         // so the second entry is 1000 + the index of the block's first name token
         for (int32_t i = 0; i < L->seg_len[P + n_docs + p]; i += HPD_KEY_BLOCK) {
@@ -296,7 +297,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
           const int32_t pb0 = L->prompt_branch_ptr[p];
           const int32_t desc[16] = {L->seg_off[p], L->seg_len[p], L->pblk_ptr[p],
                                     L->pblk_ptr[p + 1] - L->pblk_ptr[p], r0, nbl, pb0,
-                                    (bl - bf == nbl - 1) ? bf : -1, bl - pb0 + 1, 0, 0, 0, 0, 0, 0, 0};
+                                    (bl - bf == nbl - 1) ? bf : -1, bl - pb0 + 1, L->pblk_docs[p], 0, 0, 0, 0, 0, 0};
           L->punit_desc.insert(L->punit_desc.end(), desc, desc + 16);
           L->pmax_rows[t] = std::max(L->pmax_rows[t], nbl);
         }
@@ -385,7 +386,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
     //      prompt under the literal mask), the units with the most keys first.  Documents:
     //      {hoff, Hlen, doff, Llen, first branch, end of branches, position of step 0 | -1, 0};
     //      prompts: {hoff, Hlen, first entry of the block list, its blocks, first branch, end of
-    //      branches, 0, 0}
+    //      branches, document blocks of the list, 0}
     {
       const size_t nU = paper ? (size_t)P : (size_t)n_docs;
       std::vector<int32_t> order(nU);
@@ -401,7 +402,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
         if (paper) {
           const int32_t p = order[u];
           o[0] = L->seg_off[p]; o[1] = L->seg_len[p]; o[2] = L->pblk_ptr[p]; o[3] = L->pblk_ptr[p + 1] - L->pblk_ptr[p];
-          o[4] = L->prompt_branch_ptr[p]; o[5] = L->prompt_branch_ptr[p + 1];
+          o[4] = L->prompt_branch_ptr[p]; o[5] = L->prompt_branch_ptr[p + 1]; o[6] = L->pblk_docs[p];
         } else {
           const int32_t d = order[u], p = L->doc_prompt[d];
           o[0] = L->seg_off[p]; o[1] = L->seg_len[p]; o[2] = L->seg_off[L->P + d]; o[3] = L->seg_len[L->P + d];

@@ -30,7 +30,7 @@ struct hpd_dev_tables {
   const int32_t* branch_len;         // [B] steps a branch is decoded for
   // paper-literal mask only: work units are prompts
   const int32_t* pblk;        // [total document blocks][2] (first pool slot, keys) of every 32-key block of a prompt's documents
-  const int32_t* punit_desc;  // [total_punits][16] {hoff, Hlen, first pblk entry, document blocks, first live row, live branches, first branch of the prompt, first live branch id or -1, key branches (first .. last live), 0...}
+  const int32_t* punit_desc;  // [total_punits][16] {hoff, Hlen, first pblk entry, document blocks, first live row, live branches, first branch of the prompt, first live branch id or -1, key branches (first .. last live), document blocks without the names, 0...}
   // paper-literal mask only: the attribute-name (skeleton) tokens of a prompt are a segment of
   // their own (id P + n_docs + p), fed after the prompt's documents
   const int32_t* skel_pos;      // [total name tokens] position IDs (Algorithm 2), prompt by prompt; null without skeleton segments
@@ -72,7 +72,7 @@ struct hpd_layout {
   std::vector<int32_t> doc_prompt, branch_doc, branch_base_pos, branch_len;
   std::vector<int32_t> prompt_doc_ptr, prompt_branch_ptr;
   // paper-literal mask: document blocks per prompt, per-step prompt units
-  std::vector<int32_t> pblk_ptr, pblk, punit_ptr, punit_desc, pmax_rows;
+  std::vector<int32_t> pblk_ptr, pblk, pblk_docs, punit_ptr, punit_desc, pmax_rows;
   int32_t max_prompt_branches = 0;
   std::vector<int32_t> skel_pos, skel_off, skel_seg_off, skel_cum;
   std::vector<int32_t> funit_desc;  // prefix-token attention units, heaviest first

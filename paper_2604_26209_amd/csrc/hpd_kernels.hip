@@ -221,7 +221,8 @@ __global__ void expand_mask_kernel(const int32_t* __restrict__ desc, int32_t S, 
 // document.  The liveness of every branch is kept in LDS, one byte each, for the length of
 // the kernel; nothing the kernel writes to global memory is read back.
 // Literal mask (`len` given): the units are prompts - `fixed` holds {hoff, Hlen, first entry
-// of the prompt's block list, its blocks, first branch, end of branches, 0, 0} and a descriptor
+// of the prompt's block list, its blocks, first branch, end of branches, document blocks of the
+// list, 0} and a descriptor
 // has 16 words, as the host builds them - and since a finished branch stays visible to the
 // later ones, the number of tokens it reached is kept in `len` (the step budget while it runs).
 // ---------------------------------------------------------------------------------------
@@ -318,12 +319,13 @@ dynamic_prune_kernel(int32_t n_docs, int32_t B, int32_t next_step, const uint8_t
       desc[2 * u + 1] = make_int4(first, nb, fx1.z >= 0 ? fx1.z + next_step : -1, b_first);
     } else {
       // {hoff, Hlen, list entry, blocks | first live row, live branches, first branch of the
-      //  prompt, first live branch if consecutive | key branches: first .. last live | 0}
+      //  prompt, first live branch if consecutive | key branches: first .. last live, document
+      //  blocks of the list | 0}
       int32_t y = hi - 1;
       while (nb > 0 && !al[y]) --y;
       desc[4 * u] = fx0;
       desc[4 * u + 1] = make_int4(first, nb, lo, b_first);
-      desc[4 * u + 2] = make_int4(nb > 0 ? y - lo + 1 : 0, 0, 0, 0);
+      desc[4 * u + 2] = make_int4(nb > 0 ? y - lo + 1 : 0, fx1.z, 0, 0);
       desc[4 * u + 3] = make_int4(0, 0, 0, 0);
     }
   }
