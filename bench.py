@@ -222,7 +222,7 @@ def bench_prefill(args, wl, layout, B, W, torch, np, out_f32, attr_len=None):
                       "out_dtype": "f32" if tdt == torch.float32 else wl.dtype, "call": "hpd_prefill_attention"},
            "roofline": {"bound": "mfma", "achieved": round(tf, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                         "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
-                        "kernel": "attn_stream_kernel (prefill instantiation)", "launches": steps,
+                        "kernel": "attn_prefill_kernel", "launches": steps,
                         "avg_launch_us": round(dur_s / steps * 1e6, 2), "flops_per_launch": int(flops),
                         "algorithmic_bytes_per_launch": int(alg_bytes)}}
     print(json.dumps(rec))
@@ -424,6 +424,7 @@ def measure_decode(args, k, steps, warmup, B, W, torch, np, min_timed_s=0.0):
                 "traffic_source": (f"{traffic_src}: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of `bench.py --config {k}`, "
                                    "not measured by this run") if traffic_src else None,
                 "kernel": ("attn_stream_kernel" if stream_kernel else
+                           "attention_f32_kernel" if wl.dtype == "f32" and not paper and not args.kernel_mode else
                            "append_kernel + attention_generic_kernel (two launches per step)"),
                 "launches": len(launched), "avg_launch_us": round(dur_s / len(launched) * 1e6, 2),
                 "algorithmic_bytes_per_launch": int(alg / len(launched)),
@@ -607,7 +608,7 @@ def main():
             "traffic": rf["traffic"], "traffic_source": rf["traffic_source"]}
         if k == 1:
             per_config["1"]["note"] = ("the correctness configuration: 0.2 MB per step, bound by launch latency "
-                                       "(generic fp32 kernels, two launches per step)")
+                                       "(fp32 matrix instruction, one launch per step)")
     wl, paper, attr_len = head.pop("_workload")
     head["config"]["headline"] = ("configs[4] is the largest single-GPU configuration (2.6 GB of algorithmic bytes "
                                   "per launch) and the only one with every part of the path in it: stacked documents "

@@ -1125,7 +1125,7 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
 //    copied the 64 accumulators in every round);
 //  * the score products start from minus the reference point of the row instead of 0, so that
 //    they come out as the exponents.
-// Measured (us per call with hpd_prefix_fill, one box; before = the general kernel with four waves
+// Measured (us per call with hpd_prefix_fill, one card; before = the general kernel with four waves
 // that load): 32 prompts x (64 + 512 tokens), 32/8 heads 205 -> 176; 16 prompts x (128 + 2 x 2048),
 // 64/8 heads 3306 -> 2744 (750 -> 904 TFLOP/s); literal mask, 16 ragged prompts of up to 8
 // documents 4506 -> 3714 (791 -> 960 TFLOP/s).  Without the last two points: 188 / 3023 / 4297.
