@@ -1279,9 +1279,11 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
       for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[b][i]);
     if (__any(bm > slack)) {
       bm = fmaxf(bm, __shfl_xor(bm, 32));
-      // (the first block sets the reference point whatever its sign)
+      // The first block sets the reference point whatever its sign.  Sum and accumulators are
+      // empty there and have to stay so: 2^-d of a row whose first scores all lie below -128 is
+      // infinite, and infinity times 0 is NaN.
       const float d = slack < 0.f ? bm : fmaxf(bm, 0.f);
-      const float alpha = fast_exp2(-d);
+      const float alpha = slack < 0.f ? 0.f : fast_exp2(-d);
       slack = MAX_SLACK;
 #pragma unroll
       for (int i = 0; i < 16; ++i) minus_m[i] -= d;

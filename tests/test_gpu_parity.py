@@ -646,9 +646,10 @@ def test_paper_literal_mask_stream_kernel_shapes(g):
             assert torch.equal(x, y)
 
 
-def _check_prefill(wl, mode, label, out_f32=None, attr_len=None):
+def _check_prefill(wl, mode, label, out_f32=None, attr_len=None, change=None):
     """hpd_prefill_attention against the oracle's prefill_attention, all prompts.  With
-    `attr_len`: the literal mask (gap positions), whose prefix also holds the attribute names."""
+    `attr_len`: the literal mask (gap positions), whose prefix also holds the attribute names.
+    `change` maps (queries, keys) to the ones used."""
     from paper_2604_26209_amd import binding as B
     if out_f32 is None:
         out_f32 = wl.dtype == "bf16"
@@ -662,6 +663,8 @@ def _check_prefill(wl, mode, label, out_f32=None, attr_len=None):
     assert n_tok == wl.n_prefix_tokens + (int(np.sum(attr_len)) if paper else 0)
     inputs = H.Inputs(wl, layout.n_live(), "cuda", n_tok)
     q = W.normal_values((n_tok, wl.n_q_heads, wl.head_dim), wl.value_seed * 1000 + 3, "cuda", wl.dtype)
+    if change:
+        q, inputs.k_raw = change(q, inputs.k_raw)
     kp, vp, kt, vt = B.alloc_pools(layout)
     for x in (kp, vp):
         x.fill_(float("nan"))
@@ -747,6 +750,40 @@ def test_prefill_attention_at_the_edges_of_its_blocks(g, literal):
             outs.append(torch.zeros((n_tok, g * hkv, 128), dtype=dt, device="cuda"))
             B.hpd_prefill_attention(layout, q, kp, vp, outs[-1])
         assert torch.equal(outs[0].to(torch.bfloat16), outs[1])
+
+
+@pytest.mark.parametrize("literal", [False, True])
+@pytest.mark.parametrize("case", ["low", "very_low", "rising", "falling", "common_offset", "peaked_x8"])
+def test_prefill_score_ranges_of_the_online_softmax(case, literal):
+    """Prefill scores other than those of N(0,1).  Every score of a row near -150 or near -1000 in log2
+    units; plateaus of 40 keys that rise from -1000 to +300, or fall; every score near +16; rows that one
+    key or a few dominate.  Rows that start with one key (no header, the first header token) and rows behind a
+    header.  The offsets are in channel 63, whose rotation is small at these positions: the rounding of
+    the query there moves all keys of a plateau alike, so the tolerance stays the one of N(0,1) inputs.
+    The prefill's own kernel and the general kernel."""
+    wl = W.make_workload("scores", "bf16", 8, 2, 128, 500000.0, 2, [0, 1, 40, 129], [2, 2, 3, 1],
+                         [1, 200, 33, 97, 64, 5, 150, 31], [1] * 8, [2] * 8)
+    attr = np.arange(8).astype(np.int32) * 7 % 20 + 1 if literal else None
+
+    def change(q, k):
+        q, k = q.float(), k.float()
+        if case == "peaked_x8":
+            q = q * 8
+        elif case == "common_offset":
+            q, k = q + 1, k + 1
+        else:
+            a = 32.0 if case == "low" else 64.0
+            level = dict(low=[-37.0], very_low=[-122.0], rising=[-122.0, -61.0, -30.0, 0.0, 16.0, 37.0],
+                         falling=[37.0, 16.0, 0.0, -30.0, -61.0, -122.0])[case]
+            at = torch.arange(k.shape[0], device=k.device) // 40 % len(level)
+            q[..., 63] = a
+            k[..., 63] = torch.tensor(level, device=k.device)[at][:, None]
+        return q.to(torch.bfloat16), k.to(torch.bfloat16)
+
+    for mode in (0, 4):
+        _say(f"prefill score ranges: {case} literal={literal} mode {mode}")
+        rel = _check_prefill(wl, mode, f"prefill_{case}_{literal}_m{mode}", attr_len=attr, change=change)
+        _say(f"  worst err/rms {rel:.2e}")
 
 
 def test_prefill_attention_literal_mask_fp32_generic():
