@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import hpd_oracle as O
 from paper_2604_26209_amd import workloads as W
 
 import hpd_harness as H
@@ -784,6 +785,37 @@ def test_prefill_score_ranges_of_the_online_softmax(case, literal):
         _say(f"prefill score ranges: {case} literal={literal} mode {mode}")
         rel = _check_prefill(wl, mode, f"prefill_{case}_{literal}_m{mode}", attr_len=attr, change=change)
         _say(f"  worst err/rms {rel:.2e}")
+
+
+def test_prefill_scores_far_above_the_first_reference_point():
+    """192 keys with scores near -8356 in log2 units, then keys with scores near 0, which decide: their weights
+    must not carry the rounding of the first ones' scores (up to 5e-4 in every sum around 8000).  Error against
+    the oracle in 64 bits over the rows that see both, relative 2-norm; the general kernel, which adds every
+    score up from 0, is the measure.  10 %: right after the jump the largest weight of a row is 1 to within that
+    rounding instead of exactly, and is rounded to half as the others are.  (With the rounding: 2.4 times.)"""
+    from paper_2604_26209_amd import binding as B
+    n = 1000
+    wl = W.make_workload("jump", "bf16", 8, 2, 128, 500000.0, 2, [0], [1], [n], [1], [2])
+    err = {}
+    for mode in (0, 4):
+        layout = B.layout_from_workload(wl, out_dtype=B.HPD_OUT_F32)
+        B.hpd_set_kernel_mode(layout, mode)
+        inp = H.Inputs(wl, layout.n_live(), "cuda")
+        q = W.normal_values((n, 8, 128), 5, "cuda", "bf16")
+        q[..., 63] = 64.0
+        inp.k_raw[..., 63] = (torch.arange(n, device="cuda") < 192)[:, None] * -1024.0
+        kp, vp, _, _ = B.alloc_pools(layout)
+        B.hpd_prefix_fill(layout, inp.k_raw, inp.v_raw, kp, vp)
+        out = torch.full((n, 8, 128), float("nan"), device="cuda")
+        B.hpd_prefill_attention(layout, q, kp, vp, out)
+        orc = O.HPDOracle(wl.header_len, wl.doc_ptr, wl.doc_len, wl.branch_ptr, wl.branch_len, 8, 2, 128, 500000.0, 2,
+                          dtype=np.float64, cache_dtype="bf16")
+        orc.prefill({0: inp.k_raw.double().cpu().numpy()}, {0: inp.v_raw.double().cpu().numpy()})
+        want = orc.prefill_attention({0: q.double().cpu().numpy()})[0][192:]
+        got = out.double().cpu().numpy()[192:]
+        err[mode] = float(np.linalg.norm(got - want) / np.linalg.norm(want))
+    _say(f"prefill scores above the reference point: {err[0]:.3e}, general kernel {err[4]:.3e}")
+    assert err[0] <= 1.1 * err[4]
 
 
 def test_prefill_attention_literal_mask_fp32_generic():
