@@ -1467,8 +1467,6 @@ hipError_t hpd_launch_attention_stream(const hpd_layout* L, int32_t step, const 
                                        const void* k_prefix, const void* v_prefix, void* k_tail,
                                        void* v_tail, const void* k_new, const void* v_new, void* out,
                                        hipStream_t s, bool dynamic) {
-  if (L->cfg.dtype == HPD_F32)
-    return hpd_launch_attention_f32(L, step, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s);
   StreamArgs a;
   a.tb = L->dev;
   a.step = step; a.Hq = L->cfg.n_q_heads; a.Hkv = L->cfg.n_kv_heads;

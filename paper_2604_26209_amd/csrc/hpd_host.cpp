@@ -594,6 +594,10 @@ int hpd_kv_append(const hpd_layout* L, int32_t step, const void* k_new, const vo
   return HPD_OK;
 }
 
+// The generic kernel keeps one score per key in LDS.  The fp32 kernel does not, but it shares the
+// limit: whether a call is taken must not hang on the pools' alignment or on the kernel mode.
+static bool too_many_keys(const hpd_layout* L, int32_t step) { return hpd_generic_max_keys(L, step) > 15000; }
+
 int hpd_decode_attention(const hpd_layout* L, int32_t step, const void* q, const void* k_prefix,
                          const void* v_prefix, const void* k_tail, const void* v_tail, void* out,
                          void* stream) {
@@ -608,11 +612,10 @@ int hpd_decode_attention(const hpd_layout* L, int32_t step, const void* q, const
                                         const_cast<void*>(v_tail), nullptr, nullptr, out,
                                         (hipStream_t)stream));
   } else {
-    // the generic kernel keeps one score per key in LDS
-    if (hpd_generic_max_keys(L, step) > 15000) return HPD_E_UNSUPPORTED;
+    if (too_many_keys(L, step)) return HPD_E_UNSUPPORTED;
     if (hpd_attention_f32_supported(L, k_prefix, v_prefix, k_tail)) {
-      HPD_HIP(hpd_launch_attention_stream(L, step, q, k_prefix, v_prefix, const_cast<void*>(k_tail),
-                                          const_cast<void*>(v_tail), nullptr, nullptr, out, (hipStream_t)stream));
+      HPD_HIP(hpd_launch_attention_f32(L, step, q, k_prefix, v_prefix, const_cast<void*>(k_tail),
+                                       const_cast<void*>(v_tail), nullptr, nullptr, out, (hipStream_t)stream));
       return HPD_OK;
     }
     HPD_HIP(hpd_launch_attention_generic(L, step, q, k_prefix, v_prefix, k_tail, v_tail, out,
@@ -664,14 +667,15 @@ int hpd_decode_step(const hpd_layout* L, int32_t step, const void* q, const void
                                         out, (hipStream_t)stream));
     return HPD_OK;
   }
-  if (hpd_attention_f32_supported(L, k_prefix, v_prefix, k_tail) && hpd_generic_max_keys(L, step) <= 15000) {
-    HPD_HIP(hpd_launch_attention_stream(L, step, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out,
-                                        (hipStream_t)stream));
+  if (too_many_keys(L, step)) return HPD_E_UNSUPPORTED;  // before anything is appended
+  if (hpd_attention_f32_supported(L, k_prefix, v_prefix, k_tail)) {
+    HPD_HIP(hpd_launch_attention_f32(L, step, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out,
+                                     (hipStream_t)stream));
     return HPD_OK;
   }
-  rc = hpd_kv_append(L, step, k_new, v_new, k_tail, v_tail, nullptr, stream);
-  if (rc != HPD_OK) return rc;
-  return hpd_decode_attention(L, step, q, k_prefix, v_prefix, k_tail, v_tail, out, stream);
+  HPD_HIP(hpd_launch_append(L, step, k_new, v_new, k_tail, v_tail, nullptr, (hipStream_t)stream));
+  HPD_HIP(hpd_launch_attention_generic(L, step, q, k_prefix, v_prefix, k_tail, v_tail, out, (hipStream_t)stream));
+  return HPD_OK;
 }
 
 int hpd_expand_mask(const hpd_layout* L, int32_t prompt, int32_t step_hi, uint8_t* mask_out,

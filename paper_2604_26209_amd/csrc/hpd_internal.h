@@ -134,6 +134,7 @@ inline bool hpd_attention_f32_supported(const hpd_layout* L, const void* k_prefi
          (D == 32 || D == 64 || D == 128) && L->cfg.n_q_heads / L->cfg.n_kv_heads <= HPD_F32_ROWS &&
          (((uintptr_t)k_prefix | (uintptr_t)v_prefix | (uintptr_t)k_tail) & 15) == 0;
 }
+// k_new / v_new may be null, as in hpd_launch_attention_stream
 hipError_t hpd_launch_attention_f32(const hpd_layout* L, int32_t step, const void* q, const void* k_prefix,
                                     const void* v_prefix, void* k_tail, void* v_tail, const void* k_new,
                                     const void* v_new, void* out, hipStream_t s);
@@ -147,7 +148,6 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
 hipError_t hpd_launch_prefill_generic(const hpd_layout* L, const void* q, const void* k_prefix,
                                       const void* v_prefix, void* out, hipStream_t s);
 // k_new / v_new may be null: then the newest token is read from the tail pool like the others
-// fp32 layouts (where hpd_attention_f32_supported says so): hpd_launch_attention_f32
 // dynamic: work lists and live list from the device-side pruning state instead of the tables
 // built from branch_len
 hipError_t hpd_launch_attention_stream(const hpd_layout* L, int32_t step, const void* q,

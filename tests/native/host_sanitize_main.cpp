@@ -28,6 +28,8 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout*, const void*, const void*
 hipError_t hpd_launch_prefill_generic(const hpd_layout*, const void*, const void*, const void*, void*, hipStream_t) STUB()
 hipError_t hpd_launch_attention_stream(const hpd_layout*, int32_t, const void*, const void*, const void*, void*,
                                        void*, const void*, const void*, void*, hipStream_t, bool) STUB()
+hipError_t hpd_launch_attention_f32(const hpd_layout*, int32_t, const void*, const void*, const void*, void*, void*,
+                                    const void*, const void*, void*, hipStream_t) STUB()
 hipError_t hpd_launch_dynamic_prune(const hpd_layout*, int32_t, const uint8_t*, hipStream_t) STUB()
 hipError_t hpd_dynamic_scratch(int, void**, size_t*) STUB()
 

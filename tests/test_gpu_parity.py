@@ -959,6 +959,25 @@ def test_fp32_decode_kernel_at_the_edges_of_its_tiles(g, d):
     _say(f"  max-abs against the oracle {worst:.2e}")
 
 
+@pytest.mark.parametrize("dtype,mode", [("f32", 0), ("f32", 1), ("bf16", 1)])
+def test_a_refused_decode_step_leaves_the_tails_alone(dtype, mode):
+    """A step whose rows see more keys than the generic kernel's LDS holds is refused before its append."""
+    from paper_2604_26209_amd import binding as B
+    d = 128 if dtype == "bf16" else 32
+    wl = W.make_workload("too_long", dtype, 2, 1, d, 10000.0, 2, [0], [1], [15000], [3], [2] * 3)
+    layout = B.layout_from_workload(wl)
+    B.hpd_set_kernel_mode(layout, mode)
+    kp, vp, kt, vt = B.alloc_pools(layout)
+    for x in (kp, vp, kt, vt):
+        x.fill_(3.0)
+    inputs = H.Inputs(wl, layout.n_live(), "cuda")
+    out = torch.full_like(inputs.q[0], 3.0)
+    with pytest.raises(B.HpdError):
+        B.hpd_decode_step(layout, 0, inputs.q[0], inputs.k_new[0], inputs.v_new[0], kp, vp, kt, vt, out)
+    for x in (kt, vt, out):
+        assert bool((x == 3.0).all())
+
+
 def test_fp32_decode_kernel_keeps_infinite_values_in_their_branch():
     """A branch whose newest value is infinite or NaN: the other branches' rows, which share its tile, stay as
     they are without it."""
