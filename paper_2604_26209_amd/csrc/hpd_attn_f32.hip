@@ -29,14 +29,11 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int ROWS = HPD_F32_ROWS;  // rows (branch x query head) per workgroup
-// waves of a workgroup: at most 16, and their shares of the result fit 64 KB of LDS
 template <int D>
-constexpr int MAX_WAVES = 65536 / (ROWS * (D + 2) * 4) < 16 ? 65536 / (ROWS * (D + 2) * 4) : 16;
-
-template <int D>
-__global__ void __launch_bounds__(MAX_WAVES<D> * 64)
+__global__ void __launch_bounds__(hpd_f32_max_waves(D) * 64)
 attention_f32_kernel(hpd_dev_tables tb, const int32_t* __restrict__ units, const int32_t* __restrict__ live,
-                     int32_t step, int32_t Hq, int32_t Hkv, int32_t Tcap, int32_t RG, int64_t NP,
+                     const int2* __restrict__ groups, int32_t step, int32_t Hq, int32_t Hkv, int32_t Tcap, int32_t RG,
+                     int32_t BPG, int64_t NP,
                      const float* __restrict__ q, const float* __restrict__ k_prefix,
                      const float* __restrict__ v_prefix, float* k_tail, float* v_tail,
                      const float* __restrict__ k_new, const float* __restrict__ v_new, float* __restrict__ out) {
@@ -49,9 +46,17 @@ attention_f32_kernel(hpd_dev_tables tb, const int32_t* __restrict__ units, const
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, kq = lane >> 4;
 
-  const int32_t G = Hq / Hkv, BPG = ROWS / G;  // branches per row group
-  const int32_t rg = blockIdx.x % RG, grp = blockIdx.x / RG, hk = grp % Hkv;
-  const int32_t* desc = units + (int64_t)(grp / Hkv) * 8;
+  // BPG branches per row group; unit and row group from the list if the step has one
+  const int32_t G = Hq / Hkv;
+  int32_t rg, hk, u;
+  if (groups) {
+    const int2 g = groups[blockIdx.x / Hkv];
+    rg = g.y; hk = blockIdx.x % Hkv; u = g.x;
+  } else {
+    const int32_t grp = blockIdx.x / RG;
+    rg = blockIdx.x % RG; hk = grp % Hkv; u = grp / Hkv;
+  }
+  const int32_t* desc = units + (int64_t)u * 8;
   const int32_t hoff = desc[0], Hlen = desc[1], doff = desc[2], Llen = desc[3], row0 = desc[4], nb = desc[5], ub0 = desc[7];
   const int32_t br0 = rg * BPG;
   if (br0 >= nb) return;  // uniform over the workgroup
@@ -255,25 +260,15 @@ attention_f32_kernel(hpd_dev_tables tb, const int32_t* __restrict__ units, const
 template <int D>
 hipError_t launch(const hpd_layout* L, int32_t step, const void* q, const void* k_prefix, const void* v_prefix,
                   void* k_tail, void* v_tail, const void* k_new, const void* v_new, void* out, hipStream_t s) {
-  const int32_t Hq = L->cfg.n_q_heads, Hkv = L->cfg.n_kv_heads, G = Hq / Hkv, BPG = ROWS / G;
-  const int64_t n_units = L->unit_ptr[step + 1] - L->unit_ptr[step];
-  const int32_t RG = (L->max_rows[step] + BPG - 1) / BPG;
-  // a wave per tile of the longest unit: a wave that finds no tile only costs its share of the merge
-  int32_t tiles = 1;
-  for (int32_t u = L->unit_ptr[step]; u < L->unit_ptr[step + 1]; ++u) {
-    const int32_t d = L->unit_doc[u];
-    const int32_t t = (L->seg_len[L->doc_prompt[d]] + 15) / 16 + (L->seg_len[L->P + d] + 15) / 16;
-    tiles = std::max(tiles, t);
-    if (tiles >= MAX_WAVES<D>) break;
-  }
-  const int32_t tail_tiles = (std::min(BPG, L->max_rows[step]) * (step + 1) + 15) / 16;
-  const int32_t waves = std::min(MAX_WAVES<D>, tiles + tail_tiles);
-  const size_t lds = (size_t)waves * ROWS * (D + 2) * sizeof(float);
-  const int64_t grid = n_units * Hkv * RG;
+  const int32_t Hq = L->cfg.n_q_heads, Hkv = L->cfg.n_kv_heads;
+  const hpd_f32_step& st = L->f32_steps[step];
+  const size_t lds = (size_t)st.waves * ROWS * (D + 2) * sizeof(float);
+  const int64_t grid = st.groups * Hkv;
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  attention_f32_kernel<D><<<dim3((unsigned)grid), waves * 64, lds, s>>>(
-      L->dev, L->dev.unit_desc + (int64_t)L->unit_ptr[step] * 8, L->dev.live_branch + L->live_ptr[step], step, Hq, Hkv,
-      L->T, RG, L->NP, (const float*)q, (const float*)k_prefix, (const float*)v_prefix, (float*)k_tail, (float*)v_tail,
+  const int2* groups = st.rg ? nullptr : reinterpret_cast<const int2*>(L->dev.f32_groups) + st.list;
+  attention_f32_kernel<D><<<dim3((unsigned)grid), st.waves * 64, lds, s>>>(
+      L->dev, L->dev.unit_desc + (int64_t)L->unit_ptr[step] * 8, L->dev.live_branch + L->live_ptr[step], groups, step,
+      Hq, Hkv, L->T, st.rg, st.per_group, L->NP, (const float*)q, (const float*)k_prefix, (const float*)v_prefix, (float*)k_tail, (float*)v_tail,
       (const float*)k_new, (const float*)v_new, (float*)out);
   return hipGetLastError();
 }

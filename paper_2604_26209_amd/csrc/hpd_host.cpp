@@ -48,6 +48,49 @@ int validate_config(const hpd_config* c) {
   return HPD_OK;
 }
 
+// The steps of the fp32 decode kernel.  A launch of as many row groups for every unit as the unit with the most
+// branches needs is mostly empty workgroups where one document has many times the branches of the others, and an
+// empty one is not free: 2000 documents of one branch and one of 2000, 16/4 heads x 64, 5854 us, one workgroup per
+// row and head in the generic kernel 1020.  From twice the groups that exist on they are therefore listed: 218 us.
+// (A list costs one more dependent load, and in a step of a few workgroups every load shows.)
+void plan_f32(hpd_layout* L) {
+  const int32_t D = L->cfg.head_dim, G = L->cfg.n_q_heads / L->cfg.n_kv_heads;
+  if (L->cfg.dtype != HPD_F32 || paper_mode(L) || G > HPD_F32_ROWS || (D != 32 && D != 64 && D != 128)) return;
+  L->f32_steps.resize(L->T);
+  std::vector<int32_t> list, last;
+  for (int32_t t = 0; t < L->T; ++t) {
+    hpd_f32_step& s = L->f32_steps[t];
+    const int32_t u0 = L->unit_ptr[t], n_units = L->unit_ptr[t + 1] - u0;
+    auto desc = [&](int32_t u) { return L->unit_desc.data() + (size_t)(u0 + u) * 8; };
+    auto row_groups = [&](int32_t nb) { return (nb + s.per_group - 1) / s.per_group; };
+    auto prefix_tiles = [&](int32_t u) { return (int64_t)(desc(u)[1] + 15) / 16 + (desc(u)[3] + 15) / 16; };
+    auto tail_tiles = [&](int64_t nb) { return (nb * (t + 1) + 15) / 16; };
+    s.per_group = HPD_F32_ROWS / G;
+    int64_t exist = 0, most = 1;  // groups; tiles of the longest unit
+    for (int32_t u = 0; u < n_units; ++u) {
+      exist += row_groups(desc(u)[5]);
+      most = std::max(most, prefix_tiles(u));
+    }
+    // a wave per tile of the longest unit: a wave that finds no tile costs its share of the merge
+    most += tail_tiles(std::min(s.per_group, L->max_rows[t]));
+    s.rg = row_groups(L->max_rows[t]);
+    s.groups = (int64_t)n_units * s.rg;
+    if (s.groups > 2 * exist) {
+      s.rg = 0;
+      s.groups = exist;
+      list.clear();
+      for (int32_t u = 0; u < n_units; ++u)
+        for (int32_t g = 0; g < row_groups(desc(u)[5]); ++g) list.insert(list.end(), {u, g});
+      if (list != last) {  // (steps in a row that lose no branch share one)
+        L->f32_groups.insert(L->f32_groups.end(), list.begin(), list.end());
+        last = list;
+      }
+      s.list = L->f32_groups.size() / 2 - (size_t)exist;
+    }
+    s.waves = (int32_t)std::min<int64_t>(hpd_f32_max_waves(D), most);
+  }
+}
+
 // Copies a host vector into the device int arena and returns its device address.
 struct IntArena {
   std::vector<int32_t> host;
@@ -257,6 +300,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
       }
     }
     L->total_units = (int64_t)L->unit_doc.size();
+    plan_f32(L);
 
     // ---- paper-literal mask: the work unit is the prompt (its rows see every document and the
     //      tails of all earlier branches).  Document blocks of a prompt in stream order; per
@@ -443,7 +487,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
                  o_blen = A.add(L->branch_len), o_pblk = A.add(L->pblk), o_pdesc = A.add(L->punit_desc),
                  o_fdesc = A.add(L->funit_desc), o_spos = A.add(L->skel_pos), o_soff = A.add(L->skel_off),
                  o_sseg = A.add(L->skel_seg_off), o_scum = A.add(L->skel_cum), o_fblk = A.add(L->fblk),
-                 o_fill = A.add(L->fill_blk), o_dynfix = A.add(L->dyn_fixed);
+                 o_fill = A.add(L->fill_blk), o_dynfix = A.add(L->dyn_fixed), o_f32 = A.add(L->f32_groups);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&L->n_cus, hipDeviceAttributeMultiprocessorCount, L->device);
@@ -473,7 +517,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
     L->dev.prompt_doc_ptr = base + o_pdp; L->dev.prompt_branch_ptr = base + o_pbp;
     L->dev.branch_len = base + o_blen; L->dev.pblk = base + o_pblk; L->dev.punit_desc = base + o_pdesc;
     L->dev.funit_desc = base + o_fdesc; L->dev.fblk = base + o_fblk;
-    L->dev.fill_blk = base + o_fill;
+    L->dev.fill_blk = base + o_fill; L->dev.f32_groups = base + o_f32;
     L->dyn_fixed_dev = const_cast<int32_t*>(base) + o_dynfix;
     L->dev.skel_pos = paper_mode(L) ? base + o_spos : nullptr; L->dev.skel_off = base + o_soff;
     L->dev.skel_seg_off = base + o_sseg; L->dev.skel_cum = base + o_scum;

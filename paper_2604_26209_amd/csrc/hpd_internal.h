@@ -28,6 +28,7 @@ struct hpd_dev_tables {
   const int32_t* prompt_doc_ptr;     // [P+1] first document of each prompt
   const int32_t* prompt_branch_ptr;  // [P+1] first branch of each prompt
   const int32_t* branch_len;         // [B] steps a branch is decoded for
+  const int32_t* f32_groups;         // [..][2] (unit within the step, row group) of the steps that list them
   // paper-literal mask only: work units are prompts
   const int32_t* pblk;        // [total document blocks][2] (first pool slot, keys) of every 32-key block of a prompt's documents
   const int32_t* punit_desc;  // [total_punits][16] {hoff, Hlen, first pblk entry, document blocks, first live row, live branches, first branch of the prompt, first live branch id or -1, key branches (first .. last live), document blocks without the names, 0...}
@@ -61,6 +62,15 @@ __device__ __forceinline__ int64_t hpd_tail_row(const hpd_dev_tables& tb, int32_
   return ((((int64_t)pg * Hkv + hk)) << tb.page_shift) + (t & ((1 << tb.page_shift) - 1));
 }
 
+// One step of the fp32 decode kernel (hpd_attn_f32.hip): how its rows are cut into workgroups.
+struct hpd_f32_step {
+  int32_t per_group = 0;  // branches per row group
+  int32_t rg = 0;         // row groups of every unit (the most that one needs), or 0: `groups` are listed
+  int64_t groups = 0;     // workgroups per kv head
+  size_t list = 0;        // rg == 0: first (unit, row group) pair of the step in f32_groups
+  int32_t waves = 0;      // waves per workgroup
+};
+
 struct hpd_layout {
   hpd_config cfg;
   int32_t P = 0, n_docs = 0, B = 0, T = 0, n_seg = 0;
@@ -82,6 +92,8 @@ struct hpd_layout {
   int32_t fmax_list_blocks = 0;     // literal mask: most list blocks any segment sees in full
   std::vector<int32_t> live_ptr, live_branch, doc_live_ptr, unit_ptr, unit_doc, unit_desc;
   std::vector<int32_t> max_rows;  // [T] largest number of live branches of any document at step t
+  std::vector<hpd_f32_step> f32_steps;  // [T], empty where the fp32 kernel does not apply
+  std::vector<int32_t> f32_groups;      // [..][2]
   std::vector<float> rope;        // host copy of the (cos, sin) table
 
   // device-side pruning: state built by dynamic_prune_kernel (one allocation, d_dyn)
@@ -124,14 +136,16 @@ hipError_t hpd_launch_expand_mask(const int32_t* d_desc, int32_t S, int32_t pape
 hipError_t hpd_launch_finetune_mask(const int32_t* table, int32_t S, int32_t* pos_out, uint8_t* mask_out,
                                     hipStream_t s);
 
-// fp32 decode attention (hpd_attn_f32.hip): one row group of 16 rows holds the query heads of at
-// least one branch; 16-byte loads from the pools.  kernel_mode 1 forces the generic kernel.
+// fp32 decode attention (hpd_attn_f32.hip): block mask, 32, 64 or 128 channels; one row group of 16
+// rows holds the query heads of at least one branch; 16-byte loads from the pools.  kernel_mode 1 forces the generic kernel.
 constexpr int32_t HPD_F32_ROWS = 16;
+// waves of a workgroup: at most 16, and their shares of the result fit 64 KB of LDS
+constexpr int32_t hpd_f32_max_waves(int32_t D) {
+  return 65536 / (HPD_F32_ROWS * (D + 2) * 4) < 16 ? 65536 / (HPD_F32_ROWS * (D + 2) * 4) : 16;
+}
 inline bool hpd_attention_f32_supported(const hpd_layout* L, const void* k_prefix, const void* v_prefix,
                                         const void* k_tail) {
-  const int32_t D = L->cfg.head_dim;
-  return L->kernel_mode == 0 && L->cfg.dtype == HPD_F32 && L->cfg.mask_mode == HPD_MASK_BLOCK &&
-         (D == 32 || D == 64 || D == 128) && L->cfg.n_q_heads / L->cfg.n_kv_heads <= HPD_F32_ROWS &&
+  return L->kernel_mode == 0 && !L->f32_steps.empty() &&
          (((uintptr_t)k_prefix | (uintptr_t)v_prefix | (uintptr_t)k_tail) & 15) == 0;
 }
 // k_new / v_new may be null, as in hpd_launch_attention_stream

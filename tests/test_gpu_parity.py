@@ -959,6 +959,69 @@ def test_fp32_decode_kernel_at_the_edges_of_its_tiles(g, d):
     _say(f"  max-abs against the oracle {worst:.2e}")
 
 
+# fp32 batches whose rows fill the 16-row groups badly: heads, channels, documents, branches of each
+# document, steps
+F32_UNEVEN = {
+    "one_document_of_many_branches": (16, 4, 64, [40] * 10 + [64], [1] * 5 + [0] + [2] * 4 + [41], 5),
+}
+
+
+@pytest.mark.parametrize("case", F32_UNEVEN)
+def test_fp32_decode_of_uneven_batches(case):
+    """The ways in which an fp32 step is cut into workgroups: against the oracle, the step call against the two-call
+    sequence, and against the generic kernel (sums of at most 500 terms of size 1 in another order: 1e-5)."""
+    hq, hkv, d, doc, nbr, steps = F32_UNEVEN[case]
+    blen = 1 + np.arange(sum(nbr)) * 3 % steps
+    blen[-1] = steps
+    wl = W.make_workload("uneven", "f32", hq, hkv, d, 10000.0, steps, [20, 0], [len(doc) // 2, len(doc) - len(doc) // 2],
+                         doc, nbr, blen)
+    _say(f"fp32 decode, {case}")
+    two = H.run_hip(wl)
+    worst = H.check_all(wl, two, label=case)
+    one = H.run_hip(wl, inputs=two["inputs"], fused=True)
+    gen = H.run_hip(wl, inputs=two["inputs"], kernel_mode=1)
+    for x, y, z in zip(two["out"], one["out"], gen["out"]):
+        assert torch.equal(x, y)
+        assert x.numel() == 0 or float((x - z).abs().max()) < 1e-5
+    _say(f"  max-abs against the oracle {worst:.2e}")
+
+
+F32_UNEVEN_LARGE = {
+    "one_document_of_many_branches": (16, 4, 64, [64] * 1001, [1] * 1000 + [1000], 2),
+}
+
+
+@pytest.mark.parametrize("case", F32_UNEVEN_LARGE)
+def test_fp32_decode_of_uneven_batches_is_no_slower_than_the_generic_kernel(case):
+    """Where the default of an fp32 step cuts a batch badly it costs many times what the generic kernels take; 1.25 is
+    well above what two timings of the same call differ by."""
+    from paper_2604_26209_amd import binding as B
+    hq, hkv, d, doc, nbr, steps = F32_UNEVEN_LARGE[case]
+    wl = W.make_workload("uneven", "f32", hq, hkv, d, 10000.0, steps, [0], [len(doc)], doc, nbr, [steps] * sum(nbr))
+    layout = B.layout_from_workload(wl)
+    pools = B.alloc_pools(layout)
+    for x in pools:
+        x.normal_()
+    n = wl.n_branches
+    q, k, v = (torch.randn(n, h, d, device="cuda") for h in (hq, hkv, hkv))
+    out = torch.zeros_like(q)
+    us = {}
+    for mode in (0, 1, 0, 1):
+        B.hpd_set_kernel_mode(layout, mode)
+        call = lambda: B.hpd_decode_step(layout, steps - 1, q, k, v, *pools, out)
+        call()
+        start, end = torch.cuda.Event(True), torch.cuda.Event(True)
+        for _ in range(5):
+            start.record()
+            for _ in range(10):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            us[mode] = min(us.get(mode, 1e9), start.elapsed_time(end) * 100)
+    _say(f"fp32 decode, {case}: {us[0]:.1f} us, generic kernels {us[1]:.1f} us")
+    assert us[0] <= 1.25 * us[1]
+
+
 @pytest.mark.parametrize("dtype,mode", [("f32", 0), ("f32", 1), ("bf16", 1)])
 def test_a_refused_decode_step_leaves_the_tails_alone(dtype, mode):
     """A step whose rows see more keys than the generic kernel's LDS holds is refused before its append."""
