@@ -53,7 +53,7 @@ int validate_config(const hpd_config* c) {
 // empty one is not free: 2000 documents of one branch and one of 2000, 16/4 heads x 64, 5854 us, one workgroup per
 // row and head in the generic kernel 1020.  From twice the groups that exist on they are therefore listed: 218 us.
 // (A list costs one more dependent load, and in a step of a few workgroups every load shows.)
-void plan_f32(hpd_layout* L) {
+void plan_f32(hpd_layout* L, int32_t n_cus) {
   const int32_t D = L->cfg.head_dim, G = L->cfg.n_q_heads / L->cfg.n_kv_heads;
   if (L->cfg.dtype != HPD_F32 || paper_mode(L) || G > HPD_F32_ROWS || (D != 32 && D != 64 && D != 128)) return;
   L->f32_steps.resize(L->T);
@@ -66,12 +66,12 @@ void plan_f32(hpd_layout* L) {
     auto prefix_tiles = [&](int32_t u) { return (int64_t)(desc(u)[1] + 15) / 16 + (desc(u)[3] + 15) / 16; };
     auto tail_tiles = [&](int64_t nb) { return (nb * (t + 1) + 15) / 16; };
     s.per_group = HPD_F32_ROWS / G;
-    int64_t exist = 0, most = 1;  // groups; tiles of the longest unit
+    int64_t exist = 0, most = 1, all = 0;  // groups; tiles of the longest one and of all of them together
     for (int32_t u = 0; u < n_units; ++u) {
       exist += row_groups(desc(u)[5]);
       most = std::max(most, prefix_tiles(u));
+      all += row_groups(desc(u)[5]) * prefix_tiles(u) + tail_tiles(desc(u)[5]);
     }
-    // a wave per tile of the longest unit: a wave that finds no tile costs its share of the merge
     most += tail_tiles(std::min(s.per_group, L->max_rows[t]));
     s.rg = row_groups(L->max_rows[t]);
     s.groups = (int64_t)n_units * s.rg;
@@ -87,7 +87,13 @@ void plan_f32(hpd_layout* L) {
       }
       s.list = L->f32_groups.size() / 2 - (size_t)exist;
     }
-    s.waves = (int32_t)std::min<int64_t>(hpd_f32_max_waves(D), most);
+    // A wave per tile of an average group: the waves that a shorter group has no tile for hold LDS and registers
+    // that workgroups in the queue need (3000 documents of 20 keys and one of 3000, three branches each, 8/8 heads x
+    // 32: 674 us with a wave per tile of the longest group, 260 so, 302 in the generic kernels).  But not so few that the longest group
+    // is still at work when the others are done: a CU does about 8 tiles side by side.
+    const int64_t work = std::max<int64_t>(1, all * L->cfg.n_kv_heads);
+    const int64_t waves = std::max((all + exist - 1) / std::max<int64_t>(1, exist), 8 * most * n_cus / work);
+    s.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most, waves}));
   }
 }
 
@@ -300,7 +306,12 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
       }
     }
     L->total_units = (int64_t)L->unit_doc.size();
-    plan_f32(L);
+    {
+      int device = 0, n_cus = L->n_cus;
+      if (!(cfg->flags & HPD_FLAG_HOST_ONLY) && hipGetDevice(&device) == hipSuccess)
+        (void)hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, device);
+      plan_f32(L, n_cus);
+    }
 
     // ---- paper-literal mask: the work unit is the prompt (its rows see every document and the
     //      tails of all earlier branches).  Document blocks of a prompt in stream order; per
