@@ -67,12 +67,21 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     auto tail_tiles = [&](int64_t nb) { return (nb * (t + 1) + 15) / 16; };
     s.per_group = HPD_F32_ROWS / G;
     int64_t exist = 0, most = 1, all = 0;  // groups; tiles of the longest one and of all of them together
-    for (int32_t u = 0; u < n_units; ++u) {
-      exist += row_groups(desc(u)[5]);
-      most = std::max(most, prefix_tiles(u));
-      all += row_groups(desc(u)[5]) * prefix_tiles(u) + tail_tiles(desc(u)[5]);
+    for (;; s.per_group = (s.per_group + 1) / 2) {
+      int64_t prefix = 1;  // tiles of the longest unit
+      exist = all = 0;
+      for (int32_t u = 0; u < n_units; ++u) {
+        exist += row_groups(desc(u)[5]);
+        prefix = std::max(prefix, prefix_tiles(u));
+        all += row_groups(desc(u)[5]) * prefix_tiles(u) + tail_tiles(desc(u)[5]);
+      }
+      const int64_t tails = tail_tiles(std::min(s.per_group, L->max_rows[t]));
+      most = prefix + tails;
+      // Fewer branches per group where their tails are most of a group's keys and CUs are idle: a group
+      // streams the prefix once for its branches, but the tails of each (one document of 32 keys, 16 branches of
+      // 400 tokens, 4/4 heads x 64: one group per kv head 137 us, one per branch 16, generic kernels 50).
+      if (s.per_group == 1 || tails <= prefix || exist * L->cfg.n_kv_heads >= n_cus) break;
     }
-    most += tail_tiles(std::min(s.per_group, L->max_rows[t]));
     s.rg = row_groups(L->max_rows[t]);
     s.groups = (int64_t)n_units * s.rg;
     if (s.groups > 2 * exist) {

@@ -964,6 +964,7 @@ def test_fp32_decode_kernel_at_the_edges_of_its_tiles(g, d):
 F32_UNEVEN = {
     "one_document_of_many_branches": (16, 4, 64, [40] * 10 + [64], [1] * 5 + [0] + [2] * 4 + [41], 5),
     "one_long_document": (8, 8, 32, [3] * 299 + [400], [1] * 300, 3),
+    "tails_longer_than_the_document": (6, 2, 32, [17, 3], [11, 16], 40),
 }
 
 
@@ -990,6 +991,7 @@ def test_fp32_decode_of_uneven_batches(case):
 F32_UNEVEN_LARGE = {
     "one_document_of_many_branches": (16, 4, 64, [64] * 1001, [1] * 1000 + [1000], 2),
     "one_long_document": (8, 8, 32, [3000] + [20] * 3000, [3] * 3001, 2),
+    "tails_longer_than_the_document": (4, 4, 64, [32], [16], 401),
 }
 
 
