@@ -102,6 +102,18 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     // is still at work when the others are done: a CU does about 8 tiles side by side.
     const int64_t work = std::max<int64_t>(1, all * L->cfg.n_kv_heads);
     const int64_t waves = std::max((all + exist - 1) / std::max<int64_t>(1, exist), 8 * most * n_cus / work);
+    // Groups with one row in use of 16 (one branch per document, one query head per kv head) and few keys: the
+    // matrix work for the other rows, and the registers of 64 and 128 channels (four and two waves per SIMD),
+    // cost more than the generic kernel's loads as soon as workgroups queue up.  New / generic, 8/8 heads, us:
+    // 128 channels, documents of 3, 20, 60, 150 keys: 64 of them 9 / 12, 10 / 14, 20 / 26, 30 / 52; 128 of them
+    // 11 / 12, 21 / 18, 40 / 35, 57 / 70; 4000 of them 393 / 190, 728 / 431, 1451 / 936, 2140 / 2060.  64 channels: 200
+    // of them 9 / 13, 16 / 17, 30 / 33, 53 / 65; 4000 of them 156 / 125, 255 / 268, 629 / 520, 1068 / 1090.  32 channels: not
+    // slower.  Two rows in use: slower with 128 channels and a tile each of document and tail, 4000 of them 429 / 367.
+    const int64_t wgs = exist * L->cfg.n_kv_heads;
+    int64_t rows = 0;  // (row, tile) pairs in use over G
+    for (int32_t u = 0; u < n_units; ++u) rows += desc(u)[5] * (prefix_tiles(u) + tail_tiles(1));
+    s.generic = D >= 64 && ((2 * rows * G < 3 * all && all < (D == 128 ? 10 : 8) * exist && wgs > (D == 128 ? 3 : 8) * (int64_t)n_cus) ||
+                            (D == 128 && 2 * rows * G < 5 * all && all <= 2 * exist && wgs > 8 * (int64_t)n_cus));
     s.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most, waves}));
   }
 }
@@ -677,7 +689,7 @@ int hpd_decode_attention(const hpd_layout* L, int32_t step, const void* q, const
                                         (hipStream_t)stream));
   } else {
     if (too_many_keys(L, step)) return HPD_E_UNSUPPORTED;
-    if (hpd_attention_f32_supported(L, k_prefix, v_prefix, k_tail)) {
+    if (hpd_use_attention_f32(L, step, k_prefix, v_prefix, k_tail)) {
       HPD_HIP(hpd_launch_attention_f32(L, step, q, k_prefix, v_prefix, const_cast<void*>(k_tail),
                                        const_cast<void*>(v_tail), nullptr, nullptr, out, (hipStream_t)stream));
       return HPD_OK;
@@ -732,7 +744,7 @@ int hpd_decode_step(const hpd_layout* L, int32_t step, const void* q, const void
     return HPD_OK;
   }
   if (too_many_keys(L, step)) return HPD_E_UNSUPPORTED;  // before anything is appended
-  if (hpd_attention_f32_supported(L, k_prefix, v_prefix, k_tail)) {
+  if (hpd_use_attention_f32(L, step, k_prefix, v_prefix, k_tail)) {
     HPD_HIP(hpd_launch_attention_f32(L, step, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out,
                                      (hipStream_t)stream));
     return HPD_OK;

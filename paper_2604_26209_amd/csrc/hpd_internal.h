@@ -69,6 +69,7 @@ struct hpd_f32_step {
   int64_t groups = 0;     // workgroups per kv head
   size_t list = 0;        // rg == 0: first (unit, row group) pair of the step in f32_groups
   int32_t waves = 0;      // waves per workgroup
+  bool generic = false;   // the generic kernels are the faster ones for this step
 };
 
 struct hpd_layout {
@@ -143,9 +144,9 @@ constexpr int32_t HPD_F32_ROWS = 16;
 constexpr int32_t hpd_f32_max_waves(int32_t D) {
   return 65536 / (HPD_F32_ROWS * (D + 2) * 4) < 16 ? 65536 / (HPD_F32_ROWS * (D + 2) * 4) : 16;
 }
-inline bool hpd_attention_f32_supported(const hpd_layout* L, const void* k_prefix, const void* v_prefix,
-                                        const void* k_tail) {
-  return L->kernel_mode == 0 && !L->f32_steps.empty() &&
+inline bool hpd_use_attention_f32(const hpd_layout* L, int32_t step, const void* k_prefix, const void* v_prefix,
+                                  const void* k_tail) {
+  return L->kernel_mode == 0 && !L->f32_steps.empty() && !L->f32_steps[step].generic &&
          (((uintptr_t)k_prefix | (uintptr_t)v_prefix | (uintptr_t)k_tail) & 15) == 0;
 }
 // k_new / v_new may be null, as in hpd_launch_attention_stream

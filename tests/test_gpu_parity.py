@@ -965,6 +965,7 @@ F32_UNEVEN = {
     "one_document_of_many_branches": (16, 4, 64, [40] * 10 + [64], [1] * 5 + [0] + [2] * 4 + [41], 5),
     "one_long_document": (8, 8, 32, [3] * 299 + [400], [1] * 300, 3),
     "tails_longer_than_the_document": (6, 2, 32, [17, 3], [11, 16], 40),
+    "one_row_per_document": (8, 8, 128, [5] * 100, [1] * 100, 2),
 }
 
 
@@ -992,6 +993,7 @@ F32_UNEVEN_LARGE = {
     "one_document_of_many_branches": (16, 4, 64, [64] * 1001, [1] * 1000 + [1000], 2),
     "one_long_document": (8, 8, 32, [3000] + [20] * 3000, [3] * 3001, 2),
     "tails_longer_than_the_document": (4, 4, 64, [32], [16], 401),
+    "one_row_per_document": (8, 8, 128, [20] * 1000, [1] * 1000, 1),
 }
 
 
