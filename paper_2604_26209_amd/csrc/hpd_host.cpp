@@ -114,6 +114,11 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     for (int32_t u = 0; u < n_units; ++u) rows += desc(u)[5] * (prefix_tiles(u) + tail_tiles(1));
     s.generic = D >= 64 && ((2 * rows * G < 3 * all && all < (D == 128 ? 10 : 8) * exist && wgs > (D == 128 ? 3 : 8) * (int64_t)n_cus) ||
                             (D == 128 && 2 * rows * G < 5 * all && all <= 2 * exist && wgs > 8 * (int64_t)n_cus));
+    // 12 or more rows of 128 channels, but only the waves of two or three tiles to merge their shares: up to 16 outputs
+    // a thread, the longest part of such a step.  16/1 heads, documents of 3 keys: one 14.4 us, generic kernels 10.5; 60
+    // of them with one branch 14.8 / 11.1, with three 15.0 / 17.9.  20 keys: one 13.7 / 12.0, 30 of them 14.3 / 13.7.
+    const int64_t calls = (int64_t)(L->live_ptr[t + 1] - L->live_ptr[t]) * L->cfg.n_q_heads;
+    s.generic |= D == 128 && std::min(s.per_group, L->max_rows[t]) * G >= 12 && most <= 3 && calls <= (most <= 2 ? 6 : 1) * (int64_t)n_cus;
     s.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most, waves}));
   }
 }

@@ -965,14 +965,18 @@ F32_UNEVEN = {
     "one_document_of_many_branches": (16, 4, 64, [40] * 10 + [64], [1] * 5 + [0] + [2] * 4 + [41], 5),
     "one_long_document": (8, 8, 32, [3] * 299 + [400], [1] * 300, 3),
     "tails_longer_than_the_document": (6, 2, 32, [17, 3], [11, 16], 40),
-    "one_row_per_document": (8, 8, 128, [5] * 100, [1] * 100, 2),
+    "one_row_per_document": (8, 8, 128, [5] * 100, [1] * 100, 1),
+    "short_documents_of_many_heads": (16, 1, 128, [3], [2], 2),
 }
+
+F32_GENERIC = ("one_row_per_document", "short_documents_of_many_heads")
 
 
 @pytest.mark.parametrize("case", F32_UNEVEN)
 def test_fp32_decode_of_uneven_batches(case):
     """The ways in which an fp32 step is cut into workgroups: against the oracle, the step call against the two-call
-    sequence, and against the generic kernel (sums of at most 500 terms of size 1 in another order: 1e-5)."""
+    sequence, and against the generic kernel (sums of at most 500 terms of size 1 in another order: 1e-5), whose
+    bits tell which of the two kernels the layout's plan chose."""
     hq, hkv, d, doc, nbr, steps = F32_UNEVEN[case]
     blen = 1 + np.arange(sum(nbr)) * 3 % steps
     blen[-1] = steps
@@ -986,6 +990,7 @@ def test_fp32_decode_of_uneven_batches(case):
     for x, y, z in zip(two["out"], one["out"], gen["out"]):
         assert torch.equal(x, y)
         assert x.numel() == 0 or float((x - z).abs().max()) < 1e-5
+    assert all(torch.equal(x, z) for x, z in zip(two["out"], gen["out"])) == (case in F32_GENERIC)
     _say(f"  max-abs against the oracle {worst:.2e}")
 
 
