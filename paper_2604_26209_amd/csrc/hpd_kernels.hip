@@ -347,6 +347,7 @@ dynamic_prune_kernel(int32_t n_docs, int32_t B, int32_t next_step, const uint8_t
 // table of 16 bytes per token built, allocated, copied and freed by every call).
 // ---------------------------------------------------------------------------------------
 constexpr int FT_ROWS = 8, FT_KEYS = 4096, FT_EMBED = 640;
+constexpr int FT_LONG = 64, FT_LONGS = FT_KEYS / FT_LONG;
 struct FtOffsets {
   uint16_t name[FT_EMBED], value[FT_EMBED], before[FT_EMBED];  // first name / value token, names of earlier attributes
 };
@@ -356,9 +357,12 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
                      int32_t S, int32_t* __restrict__ pos, uint8_t* __restrict__ mask) {
   __shared__ uint32_t key[FT_KEYS];   // attribute << 16 | k
   __shared__ uint32_t query[FT_ROWS];
+  __shared__ int32_t longs[FT_LONGS], n_long;  // attributes with more than FT_LONG value tokens among the keys
   const int32_t tid = threadIdx.x, q0 = blockIdx.x * FT_ROWS, k0 = blockIdx.y * FT_KEYS;
-  for (int32_t i = tid; i < FT_KEYS; i += 256) key[i] = 0;
+  const int32_t n_key = mask ? min(FT_KEYS, S - k0) : 0;
+  for (int32_t i = tid; i < n_key; i += 256) key[i] = 0;
   if (tid < FT_ROWS) query[tid] = 0;
+  if (tid == 0) n_long = 0;
   if (pos && k0 == 0 && tid < FT_ROWS && q0 + tid < min(S, prompt_len)) pos[q0 + tid] = q0 + tid;
   __syncthreads();
   const uint16_t* const name = EMBED ? emb.name : dev;
@@ -366,7 +370,10 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
   const uint16_t* const before = EMBED ? emb.before : dev + 2 * n_attr;
   for (int32_t a = tid; a < n_attr; a += 256) {
     const int32_t ns = name[a], vs = value[a], ve = a + 1 < n_attr ? (int32_t)name[a + 1] : S;
-    for (int32_t i = max(vs, k0); i < min(ve, k0 + FT_KEYS); ++i) key[i - k0] = (uint32_t)a << 16 | (uint32_t)(i - vs + 1);
+    const int32_t lo = max(vs, k0), hi = min(ve, k0 + n_key);
+    if (hi - lo > FT_LONG) longs[atomicAdd(&n_long, 1)] = a;
+    else
+      for (int32_t i = lo; i < hi; ++i) key[i - k0] = (uint32_t)a << 16 | (uint32_t)(i - vs + 1);
     for (int32_t i = max(ns, q0); i < min(ve, q0 + FT_ROWS); ++i) {
       query[i - q0] = i < vs ? 0xffff0000u : (uint32_t)a << 16 | (uint32_t)(i - vs + 1);
       // a value continues from its attribute's last token
@@ -374,6 +381,15 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
     }
   }
   __syncthreads();
+  // a long value is expanded by the whole workgroup: by one thread it would be a chain of up to FT_KEYS writes to LDS
+  // (4000 tokens with one value of 3900: 193 us the call, 33 so)
+  if (n_long) {
+    for (int32_t j = 0; j < n_long; ++j) {
+      const int32_t a = longs[j], vs = value[a], ve = a + 1 < n_attr ? (int32_t)name[a + 1] : S;
+      for (int32_t i = max(vs, k0) + tid; i < min(ve, k0 + n_key); i += 256) key[i - k0] = (uint32_t)a << 16 | (uint32_t)(i - vs + 1);
+    }
+    __syncthreads();
+  }
   const int32_t kc = k0 + tid * 16;  // this thread's first key
   if (!mask || kc >= S) return;
   uint32_t code[16];

@@ -869,6 +869,16 @@ def test_prefix_fill_fast_kernel_equals_general_kernel(literal):
     assert bool((pools[0][0] != 3.0).any())
 
 
+def _finetune_mask_of_all_pairs(plen, al, vl):
+    """The rule over codes (attribute, k) of all pairs, as in the docstring of the oracle's loop."""
+    owner = np.concatenate([np.full(plen, -1)] + [np.full(a + v, n) for n, (a, v) in enumerate(zip(al, vl))])
+    k = np.concatenate([np.zeros(plen, int)] + [np.r_[np.zeros(a, int), 1:v + 1] for a, v in zip(al, vl)])
+    value, name = k > 0, (k == 0) & (owner >= 0)
+    ok = np.tri(len(k), dtype=bool) & ~(value[None] & name[:, None])
+    ok &= ~(value[None] & value[:, None] & (owner[None] < owner[:, None]) & (k[None] > k[:, None]))
+    return ok.astype(np.uint8)
+
+
 @pytest.mark.parametrize("n_attr", [0, 1, 640, 641])
 @pytest.mark.parametrize("plen", [0, 15, 16, 4090])
 def test_finetune_mask_at_the_edges_of_its_blocks(plen, n_attr):
@@ -890,13 +900,48 @@ def test_finetune_mask_at_the_edges_of_its_blocks(plen, n_attr):
     B.hpd_finetune_mask(plen, al, vl, kmax, pos[:s], m[:s * s].view(s, s))
     assert np.array_equal(pos[:s].cpu().numpy(), F.finetune_position_ids(plen, al, vl, kmax))
     assert bool((pos[s:] == -7).all()) and bool((m[s * s:] == 9).all())
-    # the rule over codes (attribute, k) of all pairs, as in the docstring of the oracle's loop
-    owner = np.concatenate([np.full(plen, -1)] + [np.full(a + v, n) for n, (a, v) in enumerate(zip(al, vl))])
-    k = np.concatenate([np.zeros(plen, int)] + [np.r_[np.zeros(a, int), 1:v + 1] for a, v in zip(al, vl)])
-    value, name = k > 0, (k == 0) & (owner >= 0)
-    ok = np.tri(s, dtype=bool) & ~(value[None] & name[:, None])
-    ok &= ~(value[None] & value[:, None] & (owner[None] < owner[:, None]) & (k[None] > k[:, None]))
-    assert np.array_equal(m[:s * s].view(s, s).cpu().numpy(), ok.astype(np.uint8))
+    assert np.array_equal(m[:s * s].view(s, s).cpu().numpy(), _finetune_mask_of_all_pairs(plen, al, vl))
+
+
+@pytest.mark.parametrize("n_attr", [7, 650])
+def test_finetune_mask_of_long_values(n_attr):
+    """Values around and far above the 64 tokens that one thread expands, across the 4096 keys of a workgroup; with a
+    mask only, with positions only, with the offsets in the kernel's arguments and in memory."""
+    from oracle import finetune_mask as F
+    from paper_2604_26209_amd import binding as B
+    al, vl = np.ones(n_attr, int), np.zeros(n_attr, int)
+    vl[:7] = [65, 64, 3900, 0, 300, 66, 1]
+    vl[-1] = 70
+    plen, kmax = 5, 4000
+    s = plen + int(al.sum() + vl.sum())
+    _say(f"finetune mask of long values: {n_attr} attributes, {s} tokens")
+    m = torch.full((s, s), 9, dtype=torch.uint8, device="cuda")
+    pos = torch.full((s,), -7, dtype=torch.int32, device="cuda")
+    B.hpd_finetune_mask(plen, al, vl, kmax, None, m)
+    B.hpd_finetune_mask(plen, al, vl, kmax, pos, None)
+    assert np.array_equal(pos.cpu().numpy(), F.finetune_position_ids(plen, al, vl, kmax))
+    assert np.array_equal(m.cpu().numpy(), _finetune_mask_of_all_pairs(plen, al, vl))
+
+
+def test_finetune_mask_of_one_long_value_takes_no_longer():
+    """The mask of 4004 tokens, all but a hundred of one value, against the same number of tokens in 128 attributes: the
+    bytes written are the same.  (One thread for the value: 6.7 times; 2 leaves room for two timings.)"""
+    from paper_2604_26209_amd import binding as B
+    m = torch.zeros(4004, 4004, dtype=torch.uint8, device="cuda")
+    us = []
+    for plen, al, vl, kmax in ((100, [4], [3900], 4000), (2596, [3] * 128, [8] * 128, 16)):
+        best = 1e9
+        for _ in range(20):
+            start, end = torch.cuda.Event(True), torch.cuda.Event(True)
+            start.record()
+            for _ in range(5):
+                B.hpd_finetune_mask(plen, al, vl, kmax, None, m)
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) * 200)
+        us.append(best)
+    _say(f"finetune mask: one value of 3900 tokens {us[0]:.1f} us, 128 attributes {us[1]:.1f} us")
+    assert us[0] <= 2 * us[1]
 
 
 def test_finetune_mask_and_positions_bit_exact():
