@@ -340,10 +340,10 @@ dynamic_prune_kernel(int32_t n_docs, int32_t B, int32_t next_step, const uint8_t
 // are smaller resp. larger than the query's.
 // Bound by the bytes it writes.  A workgroup takes FT_ROWS queries x FT_KEYS keys: it expands the
 // attributes' start offsets into key codes in LDS, a thread then holds 16 keys and writes 16 bytes per
-// query (not aligned where S is no multiple of 16).  The offsets travel in the kernel's arguments
+// query (not aligned where S is no multiple of 16; the last thread's keys then overlap its neighbour's).  The offsets travel in the kernel's arguments
 // (FT_EMBED attributes at most, else in device memory), so that a call allocates and copies
 // nothing.  Measured on 4000
-// tokens, whole call with its synchronisation: 69 -> 33 us (before: a byte per thread, two launches, a
+// tokens, whole call with its synchronisation: 69 -> 31 us, on 388 tokens 28.2 -> 26.9 (before: a byte per thread, two launches, a
 // table of 16 bytes per token built, allocated, copied and freed by every call).
 // ---------------------------------------------------------------------------------------
 constexpr int FT_ROWS = 8, FT_KEYS = 4096, FT_EMBED = 640;
@@ -370,6 +370,7 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
   const uint16_t* const before = EMBED ? emb.before : dev + 2 * n_attr;
   for (int32_t a = tid; a < n_attr; a += 256) {
     const int32_t ns = name[a], vs = value[a], ve = a + 1 < n_attr ? (int32_t)name[a + 1] : S;
+    const int32_t pos0 = prompt_len + before[a] + a * k_max;  // position of the attribute's first token
     const int32_t lo = max(vs, k0), hi = min(ve, k0 + n_key);
     if (hi - lo > FT_LONG) longs[atomicAdd(&n_long, 1)] = a;
     else
@@ -377,7 +378,7 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
     for (int32_t i = max(ns, q0); i < min(ve, q0 + FT_ROWS); ++i) {
       query[i - q0] = i < vs ? 0xffff0000u : (uint32_t)a << 16 | (uint32_t)(i - vs + 1);
       // a value continues from its attribute's last token
-      if (pos && k0 == 0) pos[i] = prompt_len + before[a] + a * k_max + (i - ns);
+      if (pos && k0 == 0) pos[i] = pos0 + (i - ns);
     }
   }
   __syncthreads();
@@ -390,11 +391,14 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
     }
     __syncthreads();
   }
-  const int32_t kc = k0 + tid * 16;  // this thread's first key
-  if (!mask || kc >= S) return;
+  if (tid * 16 >= n_key) return;
+  // this thread's 16 keys.  The last thread's end with the sequence and overlap its neighbour's (the same bytes): 16
+  // stores of a byte for each of the 8 queries took 2.5 us, more than a small call's 16-byte stores together.
+  const bool whole = n_key >= 16;
+  const int32_t kl = whole ? min(tid * 16, n_key - 16) : 0, kc = k0 + kl;
   uint32_t code[16];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) code[e] = key[tid * 16 + e];
+  for (int e = 0; e < 16; ++e) code[e] = key[kl + e];
 #pragma unroll
   for (int r = 0; r < FT_ROWS; ++r) {
     const int32_t qi = q0 + r;
@@ -409,12 +413,12 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
       }
     }
     uint8_t* const dst = mask + (int64_t)qi * S + kc;
-    if (kc + 16 <= S) {
+    if (whole) {
       __builtin_memcpy(dst, w, 16);
     } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e)
-        if (kc + e < S) dst[e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
+        if (e < n_key) dst[e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
     }
   }
 }

@@ -903,6 +903,20 @@ def test_finetune_mask_at_the_edges_of_its_blocks(plen, n_attr):
     assert np.array_equal(m[:s * s].view(s, s).cpu().numpy(), _finetune_mask_of_all_pairs(plen, al, vl))
 
 
+@pytest.mark.parametrize("s", [1, 15, 16, 17, 31, 388, 4097, 4111, 4112, 4113])
+def test_finetune_mask_of_any_number_of_tokens(s):
+    """Lengths around the 16 keys of a thread, alone and behind the 4096 keys of a workgroup, with a value at the end."""
+    from paper_2604_26209_amd import binding as B
+    al, vl = ([], []) if s < 3 else ([1, 1], [s // 3, 1]) if s < 17 else ([2, 1], [8, 5])
+    plen = s - sum(al) - sum(vl)
+    _say(f"finetune mask of {s} tokens")
+    m = torch.full((s * s + 64,), 9, dtype=torch.uint8, device="cuda")
+    B.hpd_finetune_mask(plen, al, vl, 40, None, m[:s * s].view(s, s))
+    assert bool((m[s * s:] == 9).all())
+    want = _finetune_mask_of_all_pairs(plen, np.array(al, int), np.array(vl, int))
+    assert np.array_equal(m[:s * s].view(s, s).cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("n_attr", [7, 650])
 def test_finetune_mask_of_long_values(n_attr):
     """Values around and far above the 64 tokens that one thread expands, across the 4096 keys of a workgroup; with a
