@@ -1124,9 +1124,9 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
 //    iteration to the next: with masked blocks as a second path in the loop the compiler
 //    copied the 64 accumulators in every round);
 //  * the score products start from minus the reference point of the row instead of 0, so that
-//    they come out as the exponents (and are formed again when the point moves: a block whose
-//    scores lie far above an old point would carry that point's rounding, 2.4 times the error
-//    against 64 bits after a jump of 8000; 0.4 % of the shortest of the calls below).
+//    they come out as the exponents (and are formed again when a large point moves towards 0: a
+//    block whose scores lie far above an old point would carry that point's rounding, 2.4 times
+//    the error against 64 bits after a jump of 8000).
 // Measured (us per call with hpd_prefix_fill, one card; before = the general kernel with four waves
 // that load): 32 prompts x (64 + 512 tokens), 32/8 heads 205 -> 176; 16 prompts x (128 + 2 x 2048),
 // 64/8 heads 3306 -> 2744 (750 -> 904 TFLOP/s); literal mask, 16 ragged prompts of up to 8
@@ -1287,22 +1287,24 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
       // The first block sets the reference point whatever its sign.  Sum and accumulators are
       // empty there and have to stay so: 2^-d of a row whose first scores all lie below -128 is
       // infinite, and infinity times 0 is NaN.
-      const bool first = slack < 0.f;  // of all rows of the wave or of none
+      const bool first = slack < 0.f;
       const float d = first ? bm : fmaxf(bm, 0.f);
       const float alpha = first ? 0.f : fast_exp2(-d);
       slack = MAX_SLACK;
+      // These scores were added up on top of the old reference point and carry its rounding.  Where it is farther
+      // from 0 than the new one and large (up to 128 that rounding is a sixteenth of the weights'), once
+      // more from there.  (Whenever the point moves: 2701 -> 2992 us on 16 prompts x (128 + 2 x 2048), 64/8 heads,
+      // queries 8 times as large.)
+      const float m_old = minus_m[0], m_new = m_old - d;
+      const bool again = __any(fabsf(m_old) > fmaxf(128.f, fabsf(m_new)));
 #pragma unroll
-      for (int i = 0; i < 16; ++i) minus_m[i] -= d;
-      if (__any(first)) {
+      for (int i = 0; i < 16; ++i) minus_m[i] = m_new;
+      const float shift = again ? 0.f : d;
+      if (again) scores();
 #pragma unroll
-        for (int b = 0; b < N; ++b)
+      for (int b = 0; b < N; ++b)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) s[b][i] -= d;
-      } else {
-        // These scores were added up on top of the old reference point and carry its rounding, the
-        // more the farther it lies below them: once more from the new one.
-        scores();
-      }
+        for (int i = 0; i < 16; ++i) s[b][i] -= shift;
       l_lane *= alpha;
 #pragma unroll
       for (int blk = 0; blk < 4; ++blk)
