@@ -323,23 +323,25 @@ class _PageAllocator:
         return self.table[live, t // self.ps].astype(np.int64) * self.ps + t % self.ps
 
 
-@pytest.mark.parametrize("case", ["stream_fused", "stream_two_call", "generic_f32", "dynamic"])
+@pytest.mark.parametrize("case", ["stream_fused", "stream_two_call", "f32", "generic_f32", "dynamic"])
 def test_paged_tails(case):
     """hpd_set_tail_pages: tail pools of n_pages pages (fewer than B * T slots; pages of ended
     branches are reused) against the contiguous pools: same outputs bit for bit, slots as the
     page table says, and within tolerance of the oracle."""
     from paper_2604_26209_amd import binding as B
     _say(f"paged tails: {case}")
-    f32 = case == "generic_f32"
+    f32 = case in ("f32", "generic_f32")  # the fp32 kernel, the generic one
+    mode = 1 if case == "generic_f32" else 0
     if f32:
         wl = W.random_workload(140, dtype="f32", hq=4, hkv=2, d=64, t=19, p=2, n_range=(1, 9))
     else:
         wl = W.random_workload(141, dtype="bf16", hq=8, hkv=2, d=128, base=500000.0, t=21, p=3,
                                j_range=(1, 3), n_range=(1, 14), h_range=(0, 80), l_range=(1, 200))
     ps = 8
-    ref = H.run_hip(wl, fused=(case != "stream_two_call"))
+    ref = H.run_hip(wl, fused=(case != "stream_two_call"), kernel_mode=mode)
     inputs = ref["inputs"]
     lay = B.layout_from_workload(wl, out_dtype=B.HPD_OUT_SAME if f32 else B.HPD_OUT_F32)
+    B.hpd_set_kernel_mode(lay, mode)
     alloc = _PageAllocator(wl, ps, seed=7)
     assert alloc.n_pages * ps < wl.n_branches * wl.max_new, "the case must save memory"
     table = torch.from_numpy(alloc.table).cuda()
@@ -1015,7 +1017,32 @@ def test_fp32_decode_kernel_at_the_edges_of_its_tiles(g, d):
     for x, y, z in zip(two["out"], one["out"], gen["out"]):
         assert torch.equal(x, y)
         assert x.numel() == 0 or float((x - z).abs().max()) < 1e-5
+    # it was the kernel of its own that ran: sums in another order are not the same bits throughout
+    assert not all(torch.equal(x, z) for x, z in zip(two["out"], gen["out"]))
     _say(f"  max-abs against the oracle {worst:.2e}")
+
+
+def test_fp32_decode_with_pools_off_16_bytes_runs_the_generic_kernel():
+    """The fp32 kernel loads 16 bytes at a time; pools that start 4 bytes off give the generic kernel's bits."""
+    from paper_2604_26209_amd import binding as B
+    wl = W.make_workload("off16", "f32", 8, 2, 64, 10000.0, 3, [20], [2], [50, 7], [5, 3], [3] * 8)
+    outs = {}
+    for mode, off in ((0, 0), (0, 1), (1, 0)):
+        layout = B.layout_from_workload(wl)
+        B.hpd_set_kernel_mode(layout, mode)
+        inputs = H.Inputs(wl, layout.n_live(), "cuda")
+        pools = []
+        for x in B.alloc_pools(layout):
+            pools.append(torch.zeros(x.numel() + 4, device="cuda")[off:off + x.numel()])
+        kp, vp, kt, vt = pools
+        B.hpd_prefix_fill(layout, inputs.k_raw, inputs.v_raw, kp, vp)
+        outs[mode, off] = []
+        for t in range(3):
+            out = torch.zeros_like(inputs.q[t])
+            B.hpd_decode_step(layout, t, inputs.q[t], inputs.k_new[t], inputs.v_new[t], kp, vp, kt, vt, out)
+            outs[mode, off].append(out)
+    same = [all(torch.equal(x, y) for x, y in zip(outs[0, off], outs[1, 0])) for off in (0, 1)]
+    assert same == [False, True]
 
 
 # fp32 batches whose rows fill the 16-row groups badly: heads, channels, documents, branches of each
