@@ -222,7 +222,9 @@ def bench_prefill(args, wl, layout, B, W, torch, np, out_f32, attr_len=None):
                       "out_dtype": "f32" if tdt == torch.float32 else wl.dtype, "call": "hpd_prefill_attention"},
            "roofline": {"bound": "mfma", "achieved": round(tf, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                         "frac": round(tf / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
-                        "kernel": "attn_prefill_kernel", "launches": steps,
+                        "kernel": ("attention_generic_kernel" if wl.dtype != "bf16" or wl.head_dim != 128 or args.kernel_mode == 1
+                                   else "attn_stream_kernel" if args.kernel_mode in (3, 4) else "attn_prefill_kernel"),
+                        "launches": steps,
                         "avg_launch_us": round(dur_s / steps * 1e6, 2), "flops_per_launch": int(flops),
                         "algorithmic_bytes_per_launch": int(alg_bytes)}}
     print(json.dumps(rec))

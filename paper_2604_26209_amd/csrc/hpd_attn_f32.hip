@@ -1,13 +1,16 @@
 // fp32 decode attention on the fp32 matrix instruction (gfx950): hpd_decode_attention and
 // hpd_decode_step of fp32 layouts under the block mask, 32, 64 or 128 channels, up to 16 query
-// heads per kv head.  Everything else in fp32 runs the generic kernel of hpd_kernels.hip.
+// heads per kv head.  Everything else in fp32 runs the generic kernel of hpd_kernels.hip, and so do the
+// steps for which the layout's plan (plan_f32 in hpd_host.cpp) finds it faster: few rows and few keys per
+// workgroup, and many workgroups.
 //
 // What bounds it is latency: a decode step of a small fp32 batch moves a few megabytes, and the
 // generic kernel (one workgroup per row and query head) spends its time in chains of dependent
 // 4-byte loads, one per key and thread.  Here a workgroup takes 16 rows (query heads of
-// consecutive live branches of one document) of one kv head, and its waves - as many as there are
-// tiles of 16 keys, at most 15 with 64 channels - share out the tiles: header, document, then the tails of the
-// group's branches, position by position.  A tile is two products with v_mfma_f32_16x16x4_f32,
+// consecutive live branches of one document) of one kv head, and its waves share out the tiles of 16 keys:
+// header, document, then the tails of the group's branches, position by position.  How many branches
+// and waves a workgroup has (at most 16, 15 and 7 waves with 32, 64 and 128 channels) and which row groups
+// are launched is the plan's, with the reasons and both sides' times there.  A tile is two products with v_mfma_f32_16x16x4_f32,
 //     S^T[key,row] = K.Q^T   and   O^T[channel,row] += V^T.P^T,
 // exact fp32 multiply-adds in both.  The K operand is one float4 per lane and 16 channels (the
 // four channels of a float4 are the lane's operands of four instructions), the scores come out with
@@ -17,8 +20,8 @@
 // The step call appends in the same launch: a branch belongs to exactly one row group, which
 // stores its new key and value in front of the prefix tiles and reads them behind a barrier.
 // Measured (us per hpd_decode_step, generic kernels and append launch -> this): 8 prompts x 12
-// branches, 16/4 heads x 64, 458 keys a row 118.9 -> 17.1 (10 MB); 4 branches, 4/4 heads x 64, 72
-// keys, 8 steps in a row 13.3 -> 8.8 each, most of it the launch.  Error against 64 bits over 26
+// branches, 16/4 heads x 64, 458 keys a row 119.2 -> 17.6 (10 MB); 4 branches, 4/4 heads x 64, 72
+// keys, 8 steps in a row 12.9 -> 8.3 each, most of it the launch.  Error against 64 bits over 26
 // batches: 1.3e-7 .. 2.1e-7, generic kernel 2.1e-7 .. 3.8e-7.
 #include <algorithm>
 

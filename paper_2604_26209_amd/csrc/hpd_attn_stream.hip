@@ -233,6 +233,8 @@ __device__ __forceinline__ void rotate16(uint4 raw_lo, uint4 raw_hi, const float
 // MODE_PREFILL_LIST = MODE_PREFILL under the literal mask: what a segment sees in full (the
 // header and the earlier documents of its prompt) is a list of blocks with a key count each
 // instead of the header's run of slots, and the names' positions come from a table.
+// (The two prefill modes run where hpd_set_kernel_mode forces a workgroup shape; the default is
+// attn_prefill_kernel.)
 enum { MODE_BLOCK = 0, MODE_PAPER = 1, MODE_PREFILL = 2, MODE_PAGED = 3, MODE_PREFILL_LIST = 4 };
 template <int G, typename SH, int MODE>
 __global__ void __launch_bounds__(SH::WAVES * 64, 2)
@@ -1128,9 +1130,16 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
 //    block whose scores lie far above an old point would carry that point's rounding, 2.4 times
 //    the error against 64 bits after a jump of 8000).
 // Measured (us per call with hpd_prefix_fill, one card; before = the general kernel with four waves
-// that load): 32 prompts x (64 + 512 tokens), 32/8 heads 205 -> 176; 16 prompts x (128 + 2 x 2048),
-// 64/8 heads 3306 -> 2744 (750 -> 904 TFLOP/s); literal mask, 16 ragged prompts of up to 8
-// documents 4506 -> 3714 (791 -> 960 TFLOP/s).  Without the last two points: 188 / 3023 / 4297.
+// that load): 32 prompts x (64 + 512 tokens), 32/8 heads 207 -> 177; 16 prompts x (128 + 2 x 2048),
+// 64/8 heads 3238 -> 2706 (766 -> 916 TFLOP/s); literal mask, 16 ragged prompts of up to 8
+// documents 4465 -> 3724 (799 -> 957 TFLOP/s).  Without the last two points: 188 / 3023 / 4297.
+// A wave whose rows lie behind the segment's end loads and meets the barriers, and its products are
+// thrown away; the general kernel gave it a share of the keys.  Calls of such segments are faster all the
+// same (us, before -> now, 32/8 heads): one prompt of 64 + 100 tokens 11.8 -> 8.3; 2 x (1000 + 300 documents
+// of 8, 16, 32 tokens) 1403 -> 1093, 1470 -> 1096, 1521 -> 1110; 1 x (8000 + 8) 649 -> 525; 16/16 heads, 2 x
+// (1000 + 300 x 32) 2670 -> 2041; literal mask, 16 x (64 + 4 x 500, 8 tokens of names) 785 -> 664.
+// The outputs differ from the general kernel's by rounding (relative 5e-4 in bf16): one reference point
+// per 64 keys.  Error against 64 bits on N(0,1) inputs, fp32 outputs: 2.42e-4, general kernel 2.44e-4.
 // ---------------------------------------------------------------------------------------
 constexpr int PREFILL_WAVES = 4;  // row blocks per workgroup
 template <int G, bool LIST>
@@ -1546,7 +1555,8 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
   if (n_units == 0) return hipSuccess;
   const int32_t max_nblk = std::max(1, (L->fmax_rows * G + 31) / 32);
   // kernel_mode 3 / 4 force the general kernel's wide / narrow shape; otherwise the prefill's own
-  // kernel, which is faster from the smallest batches measured to the largest (see there).
+  // kernel, which was faster in every call measured: one prompt of 200 tokens 13.6 -> 9.3 us, and the
+  // larger ones at the kernel.
   const bool narrow = L->kernel_mode == 4, wide = L->kernel_mode == 3, own = !narrow && !wide;
   const int32_t shape_blocks = narrow ? NarrowShape::MAX_BLOCKS : own ? PREFILL_WAVES : WideShape::MAX_BLOCKS;
   a.RG = (max_nblk + shape_blocks - 1) / shape_blocks;

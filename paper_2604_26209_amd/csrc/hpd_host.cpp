@@ -51,7 +51,7 @@ int validate_config(const hpd_config* c) {
 // The steps of the fp32 decode kernel.  A launch of as many row groups for every unit as the unit with the most
 // branches needs is mostly empty workgroups where one document has many times the branches of the others, and an
 // empty one is not free: 2000 documents of one branch and one of 2000, 16/4 heads x 64, 5854 us, one workgroup per
-// row and head in the generic kernel 1020.  From twice the groups that exist on they are therefore listed: 218 us.
+// row and head in the generic kernel 1020.  From twice the groups that exist on they are therefore listed: 254 us.
 // (A list costs one more dependent load, and in a step of a few workgroups every load shows.)
 void plan_f32(hpd_layout* L, int32_t n_cus) {
   const int32_t D = L->cfg.head_dim, G = L->cfg.n_q_heads / L->cfg.n_kv_heads;
@@ -98,8 +98,8 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     }
     // A wave per tile of an average group: the waves that a shorter group has no tile for hold LDS and registers
     // that workgroups in the queue need (3000 documents of 20 keys and one of 3000, three branches each, 8/8 heads x
-    // 32: 674 us with a wave per tile of the longest group, 260 so, 302 in the generic kernels).  But not so few that the longest group
-    // is still at work when the others are done: a CU does about 8 tiles side by side.
+    // 32: 674 us with a wave per tile of the longest group, 260 so, 302 in the generic kernels).  But not so few
+    // that the longest group is still at work when the others are done: a CU does about 8 tiles side by side.
     const int64_t work = std::max<int64_t>(1, all * L->cfg.n_kv_heads);
     const int64_t waves = std::max((all + exist - 1) / std::max<int64_t>(1, exist), 8 * most * n_cus / work);
     // Groups with one row in use of 16 (one branch per document, one query head per kv head) and few keys: the

@@ -1,7 +1,7 @@
 // HIP kernels (gfx950) for HPD masked decode attention: helper kernels (prefix fill,
 // positions, append, mask export) and the generic wave-reduction attention kernel that
-// covers fp32, odd shapes and serves as the fallback.  The MFMA shared-prefix kernel is
-// in hpd_attn_stream.hip.
+// covers odd shapes, what of fp32 hpd_attn_f32.hip does not, and serves as the fallback.  The
+// MFMA shared-prefix kernel and the prefill kernel are in hpd_attn_stream.hip.
 #include <algorithm>
 #include <mutex>
 #include <vector>
