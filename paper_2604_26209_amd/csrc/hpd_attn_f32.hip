@@ -271,8 +271,8 @@ hipError_t launch(const hpd_layout* L, int32_t step, const void* q, const void* 
   const int2* groups = st.rg ? nullptr : reinterpret_cast<const int2*>(L->dev.f32_groups) + st.list;
   attention_f32_kernel<D><<<dim3((unsigned)grid), st.waves * 64, lds, s>>>(
       L->dev, L->dev.unit_desc + (int64_t)L->unit_ptr[step] * 8, L->dev.live_branch + L->live_ptr[step], groups, step,
-      Hq, Hkv, L->T, st.rg, st.per_group, L->NP, (const float*)q, (const float*)k_prefix, (const float*)v_prefix, (float*)k_tail, (float*)v_tail,
-      (const float*)k_new, (const float*)v_new, (float*)out);
+      Hq, Hkv, L->T, st.rg, st.per_group, L->NP, (const float*)q, (const float*)k_prefix, (const float*)v_prefix,
+      (float*)k_tail, (float*)v_tail, (const float*)k_new, (const float*)v_new, (float*)out);
   return hipGetLastError();
 }
 

@@ -338,13 +338,15 @@ dynamic_prune_kernel(int32_t n_docs, int32_t B, int32_t next_step, const uint8_t
 // k >= 1 for a value and 0 otherwise, a query is (attribute, k) for a value, (all attributes, 0)
 // for an attribute token, (none, 0) for the prompt; the key is hidden if its attribute and its k
 // are smaller resp. larger than the query's.
-// Bound by the bytes it writes.  A workgroup takes FT_ROWS queries x FT_KEYS keys: it expands the
+// Bound by a chain of latencies - offsets, expansion, barrier - of which a call sees its own launch and wait
+// on top; the bytes it writes take 3 us at 4000 tokens.  A workgroup takes FT_ROWS queries x FT_KEYS keys: it expands the
 // attributes' start offsets into key codes in LDS, a thread then holds 16 keys and writes 16 bytes per
-// query (not aligned where S is no multiple of 16; the last thread's keys then overlap its neighbour's).  The offsets travel in the kernel's arguments
-// (FT_EMBED attributes at most, else in device memory), so that a call allocates and copies
-// nothing.  Measured on 4000
-// tokens, whole call with its synchronisation: 69 -> 31 us, on 388 tokens 28.2 -> 26.9 (before: a byte per thread, two launches, a
-// table of 16 bytes per token built, allocated, copied and freed by every call).
+// query (not aligned where S is no multiple of 16; the last thread's keys then overlap its
+// neighbour's).  The offsets travel in the kernel's arguments (FT_EMBED attributes at most, else in
+// device memory), so that a call allocates and copies nothing.  Measured, whole call with its
+// synchronisation, before -> now: 4000 tokens 69 -> 31 us (kernels alone 28.7 -> 12.2), 388 tokens 28.2 -> 26.9
+// (4.2 -> 9.2); before: a byte per thread, two launches, a table of 16 bytes per token built, allocated,
+// copied and freed by every call.
 // ---------------------------------------------------------------------------------------
 constexpr int FT_ROWS = 8, FT_KEYS = 4096, FT_EMBED = 640;
 constexpr int FT_LONG = 64, FT_LONGS = FT_KEYS / FT_LONG;

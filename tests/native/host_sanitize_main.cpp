@@ -52,6 +52,31 @@ static std::vector<T> query(const hpd_layout* L, int32_t what, size_t n) {
   return v;
 }
 
+// every row group of a step is launched exactly once: by its number, or by one pair of a list inside f32_groups
+static bool check_f32_steps(const hpd_layout* L) {
+  bool listed = false;
+  for (size_t t = 0; t < L->f32_steps.size(); ++t) {
+    const hpd_f32_step& s = L->f32_steps[t];
+    const int32_t G = L->cfg.n_q_heads / L->cfg.n_kv_heads, u0 = L->unit_ptr[t], n = L->unit_ptr[t + 1] - u0;
+    CHECK(s.per_group >= 1 && s.per_group * G <= HPD_F32_ROWS);
+    CHECK(s.waves >= 1 && s.waves <= hpd_f32_max_waves(L->cfg.head_dim));
+    auto groups = [&](int32_t u) { return (L->unit_desc[(size_t)(u0 + u) * 8 + 5] + s.per_group - 1) / s.per_group; };
+    int64_t exist = 0;
+    for (int32_t u = 0; u < n; ++u) exist += groups(u);
+    if (s.rg || n == 0) {
+      for (int32_t u = 0; u < n; ++u) CHECK(groups(u) <= s.rg);
+      CHECK(s.groups == (int64_t)n * s.rg);
+      continue;
+    }
+    listed = true;
+    CHECK(s.groups == exist && s.list * 2 + (size_t)exist * 2 <= L->f32_groups.size());
+    const int32_t* pair = L->f32_groups.data() + s.list * 2;
+    for (int32_t u = 0; u < n; ++u)
+      for (int32_t g = 0; g < groups(u); ++g, pair += 2) CHECK(pair[0] == u && pair[1] == g);
+  }
+  return listed;
+}
+
 int main() {
   std::mt19937 rng(26209);
   auto uni = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
@@ -103,6 +128,7 @@ int main() {
     CHECK(c[HPD_C_N_PROMPTS] == P && c[HPD_C_N_DOCS] == (int64_t)doc_len.size());
     const size_t B = (size_t)c[HPD_C_N_BRANCHES], T = (size_t)cfg.max_new;
     const size_t n_seg = (size_t)P + doc_len.size() + (paper ? P : 0);
+    check_f32_steps(L);
     query<int64_t>(L, HPD_Q_POOL_BYTES, 4);
     const auto n_live = query<int32_t>(L, HPD_Q_N_LIVE, T);
     int64_t total = 0;
@@ -135,6 +161,31 @@ int main() {
     CHECK(hpd_set_kernel_mode(L, 7) == HPD_E_INVALID);
     hpd_layout_free(L);
   }
+  // fp32 steps of batches with a few documents of many branches, whose row groups are listed: branches that end at
+  // different steps, documents that lose all of theirs
+  int with_list = 0;
+  for (int iter = 0; iter < 60; ++iter) {
+    hpd_config cfg{};
+    const int G = uni(1, 17);
+    cfg.n_kv_heads = uni(1, 3); cfg.n_q_heads = cfg.n_kv_heads * G;
+    cfg.head_dim = 32 << uni(0, 2); cfg.dtype = HPD_F32; cfg.rope_base = 10000.0; cfg.max_new = uni(1, 9);
+    cfg.flags = HPD_FLAG_HOST_ONLY;
+    const int n_docs = uni(1, 40);
+    std::vector<int32_t> doc_ptr{0, n_docs}, doc_len, branch_ptr{0}, branch_len;
+    for (int d = 0; d < n_docs; ++d) {
+      doc_len.push_back(uni(1, iter % 7 == 0 ? 900 : 40));
+      branch_ptr.push_back(branch_ptr.back() + (uni(0, 9) ? uni(0, 2) : uni(30, 200)));
+      while ((int)branch_len.size() < branch_ptr.back()) branch_len.push_back(uni(1, cfg.max_new));
+    }
+    const int32_t header = uni(0, 40), none = 1;
+    hpd_layout* L = nullptr;
+    CHECK(hpd_build_layout(&cfg, 1, &header, doc_ptr.data(), doc_len.data(), branch_ptr.data(),
+                           branch_len.empty() ? &none : branch_len.data(), nullptr, nullptr, &L) == HPD_OK);
+    CHECK(L->f32_steps.size() == (G <= HPD_F32_ROWS ? (size_t)cfg.max_new : 0));
+    with_list += check_f32_steps(L);
+    hpd_layout_free(L);
+  }
+  CHECK(with_list >= 10);
   // fine-tuning mask: sizes and argument checks (outputs NULL: nothing is launched)
   for (int iter = 0; iter < 200; ++iter) {
     const int n = uni(0, 12), k_max = uni(1, 9);
