@@ -64,7 +64,7 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     auto desc = [&](int32_t u) { return L->unit_desc.data() + (size_t)(u0 + u) * 8; };
     auto row_groups = [&](int32_t nb) { return (nb + s.per_group - 1) / s.per_group; };
     auto prefix_tiles = [&](int32_t u) { return (int64_t)(desc(u)[1] + 15) / 16 + (desc(u)[3] + 15) / 16; };
-    auto tail_tiles = [&](int64_t nb) { return (nb * (t + 1) + 15) / 16; };
+    auto tail_tiles = [&](int64_t nb) { return (nb * t + 15) / 16; };
     s.per_group = HPD_F32_ROWS / G;
     int64_t exist = 0, most = 1, all = 0;  // groups; tiles of the longest one and of all of them together
     for (;; s.per_group = (s.per_group + 1) / 2) {
@@ -84,7 +84,7 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     }
     s.rg = row_groups(L->max_rows[t]);
     s.groups = (int64_t)n_units * s.rg;
-    if (s.groups > 2 * exist) {
+    if (s.groups > 2 * exist || s.rg > 65535) {  // (the row groups of a unit are the grid's y)
       s.rg = 0;
       s.groups = exist;
       list.clear();
@@ -98,28 +98,32 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     }
     // A wave per tile of an average group: the waves that a shorter group has no tile for hold LDS and registers
     // that workgroups in the queue need (3000 documents of 20 keys and one of 3000, three branches each, 8/8 heads x
-    // 32: 674 us with a wave per tile of the longest group, 260 so, 302 in the generic kernels).  But not so few
-    // that the longest group is still at work when the others are done: a CU does about 8 tiles side by side.
-    const int64_t work = std::max<int64_t>(1, all * L->cfg.n_kv_heads);
+    // 32: 674 us with a wave per tile of the longest group, 260 so, 302 in the generic kernels; measured before the
+    // tiles went through LDS).  But not so few that the longest group is still at work when the others are done: a CU
+    // does about 8 tiles side by side.
+    const int64_t work = std::max<int64_t>(1, all * L->cfg.n_kv_heads), wgs = exist * L->cfg.n_kv_heads;
     const int64_t waves = std::max((all + exist - 1) / std::max<int64_t>(1, exist), 8 * most * n_cus / work);
-    // Groups with one row in use of 16 (one branch per document, one query head per kv head) and few keys: the
-    // matrix work for the other rows, and the registers of 64 and 128 channels (four and two waves per SIMD),
-    // cost more than the generic kernel's loads as soon as workgroups queue up.  New / generic, 8/8 heads, us:
-    // 128 channels, documents of 3, 20, 60, 150 keys: 64 of them 9 / 12, 10 / 14, 20 / 26, 30 / 52; 128 of them
-    // 11 / 12, 21 / 18, 40 / 35, 57 / 70; 4000 of them 393 / 190, 728 / 431, 1451 / 936, 2140 / 2060.  64 channels: 200
-    // of them 9 / 13, 16 / 17, 30 / 33, 53 / 65; 4000 of them 156 / 125, 255 / 268, 629 / 520, 1068 / 1090.  32 channels: not
-    // slower.  Two rows in use: slower with 128 channels and a tile each of document and tail, 4000 of them 429 / 367.
-    const int64_t wgs = exist * L->cfg.n_kv_heads;
+    // One more for the newest tokens, but for workgroups of one or two tiles that queue up, where the last wave takes them
+    // with its tile.  With it / without, us: 2000 documents of 64 keys, 1 branch, 16/4 heads x 64, 152 / 172; 300 of 64
+    // keys, 64/8 x 128, 212 / 255; 200 of 20 keys, 8/8 x 64, 11.8 / 12.8; but of 3 keys 11.2 / 8.6, and 4000 of 3 keys, 8/8
+    // x 32, 70 / 60.
+    const bool newest_wave = wgs <= n_cus || all > 2 * exist;
+    // 128 channels, groups with one row in use of 16 (one branch per document, one query head per kv head) and few keys:
+    // the matrix work for the other rows, and the registers (two waves per SIMD), cost more than the generic kernel's
+    // loads as soon as workgroups queue up.  This / generic, 8/8 heads, documents of 3, 20, 60, 150 keys, us: 64 of
+    // them 7 / 10, 8 / 14, 15 / 26, 24 / 53; 128 of them 9 / 12, 19 / 18, 38 / 36, 45 / 72; 4000 of them 267 / 228, 502 /
+    // 452, 1073 / 960, 1297 / 2085.  (64 channels: 4000 of them 122 / 136, 186 / 275, 467 / 526, 806 / 1102.)  Two rows in
+    // use: slower with a tile each of document and tail.
     int64_t rows = 0;  // (row, tile) pairs in use over G
     for (int32_t u = 0; u < n_units; ++u) rows += desc(u)[5] * (prefix_tiles(u) + tail_tiles(1));
-    s.generic = D >= 64 && ((2 * rows * G < 3 * all && all < (D == 128 ? 10 : 8) * exist && wgs > (D == 128 ? 3 : 8) * (int64_t)n_cus) ||
-                            (D == 128 && 2 * rows * G < 5 * all && all <= 2 * exist && wgs > 8 * (int64_t)n_cus));
-    // 12 or more rows of 128 channels, but only the waves of two or three tiles to merge their shares: up to 16 outputs
-    // a thread, the longest part of such a step.  16/1 heads, documents of 3 keys: one 14.4 us, generic kernels 10.5; 60
-    // of them with one branch 14.8 / 11.1, with three 15.0 / 17.9.  20 keys: one 13.7 / 12.0, 30 of them 14.3 / 13.7.
+    s.generic = D == 128 && ((2 * rows * G < 3 * all && all < 10 * exist && wgs > 3 * (int64_t)n_cus) ||
+                             (2 * rows * G < 5 * all && all <= 2 * exist && wgs > 8 * (int64_t)n_cus));
+    // So do the smallest steps, of one or two branches with 12 or more query heads and a tile or two, where the merge
+    // is the longest part: no difference (16/1 heads, one branch, 3 keys 9.4 / 9.2, one or two launches).  From three
+    // branches on this kernel is the faster one: 60 documents of 3 keys, one branch, 9.2 / 11.2, three 9.4 / 18.7.
     const int64_t calls = (int64_t)(L->live_ptr[t + 1] - L->live_ptr[t]) * L->cfg.n_q_heads;
-    s.generic |= D == 128 && std::min(s.per_group, L->max_rows[t]) * G >= 12 && most <= 3 && calls <= (most <= 2 ? 6 : 1) * (int64_t)n_cus;
-    s.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most, waves}));
+    s.generic |= D == 128 && std::min(s.per_group, L->max_rows[t]) * G >= 12 && most <= 2 && calls <= 32;
+    s.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most + newest_wave, waves + newest_wave}));
   }
 }
 

@@ -140,10 +140,9 @@ hipError_t hpd_launch_finetune_mask(const int32_t* table, int32_t S, int32_t* po
 // fp32 decode attention (hpd_attn_f32.hip): block mask, 32, 64 or 128 channels; one row group of 16
 // rows holds the query heads of at least one branch; 16-byte loads from the pools.  kernel_mode 1 forces the generic kernel.
 constexpr int32_t HPD_F32_ROWS = 16;
-// waves of a workgroup: at most 16, and their shares of the result fit 64 KB of LDS
-constexpr int32_t hpd_f32_max_waves(int32_t D) {
-  return 65536 / (HPD_F32_ROWS * (D + 2) * 4) < 16 ? 65536 / (HPD_F32_ROWS * (D + 2) * 4) : 16;
-}
+constexpr int32_t HPD_F32_PAD = 4;  // floats between the rows of a wave's share of the result in LDS
+// waves of a workgroup: at most 16, and their tiles fit 128 of the 160 KB of LDS
+constexpr int32_t hpd_f32_max_waves(int32_t D) { return 131072 / (128 * D) < 16 ? 131072 / (128 * D) : 16; }
 inline bool hpd_use_attention_f32(const hpd_layout* L, int32_t step, const void* k_prefix, const void* v_prefix,
                                   const void* k_tail) {
   return L->kernel_mode == 0 && !L->f32_steps.empty() && !L->f32_steps[step].generic &&

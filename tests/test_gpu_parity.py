@@ -1045,6 +1045,32 @@ def test_fp32_decode_with_pools_off_16_bytes_runs_the_generic_kernel():
     assert same == [False, True]
 
 
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_fp32_decode_with_tail_values_off_16_bytes_and_long_tails(d):
+    """Tail values that start 4 bytes off are fetched a float at a time: the bits of the aligned pool.  40 steps, so that
+    a tile holds the ends of branches of 1, 15, 16, 17 and more tokens; against the generic kernel (fp32 sums of at most 80
+    terms of size 1 in another order: 1e-5)."""
+    from paper_2604_26209_amd import binding as B
+    wl = W.make_workload("vtail4", "f32", 4, 2, d, 10000.0, 40, [3], [3], [40, 7, 1], [1, 5, 9], [40, 40, 1, 17, 40, 33] + [40] * 9)
+    _say(f"fp32 decode, tail values off 16 bytes, D={d}")
+    outs = {}
+    for mode, off in ((0, 0), (0, 1), (1, 0)):
+        layout = B.layout_from_workload(wl)
+        B.hpd_set_kernel_mode(layout, mode)
+        inputs = H.Inputs(wl, layout.n_live(), "cuda")
+        kp, vp, kt, vt = B.alloc_pools(layout)
+        vt = torch.full((vt.numel() + 4,), float("nan"), device="cuda")[off:off + vt.numel()]
+        B.hpd_prefix_fill(layout, inputs.k_raw, inputs.v_raw, kp, vp)
+        outs[mode, off] = []
+        for t in range(wl.max_new):
+            out = torch.zeros_like(inputs.q[t])
+            B.hpd_decode_step(layout, t, inputs.q[t], inputs.k_new[t], inputs.v_new[t], kp, vp, kt, vt, out)
+            outs[mode, off].append(out)
+    for x, y, z in zip(outs[0, 0], outs[0, 1], outs[1, 0]):
+        assert torch.equal(x, y)
+        assert float((x - z).abs().max()) < 1e-5
+
+
 # fp32 batches whose rows fill the 16-row groups badly: heads, channels, documents, branches of each
 # document, steps
 F32_UNEVEN = {
