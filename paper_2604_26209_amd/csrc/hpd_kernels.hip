@@ -338,18 +338,27 @@ dynamic_prune_kernel(int32_t n_docs, int32_t B, int32_t next_step, const uint8_t
 // k >= 1 for a value and 0 otherwise, a query is (attribute, k) for a value, (all attributes, 0)
 // for an attribute token, (none, 0) for the prompt; the key is hidden if its attribute and its k
 // are smaller resp. larger than the query's.
-// Bound by a chain of latencies - offsets, expansion, barrier - of which a call sees its own launch and wait
-// on top; the bytes it writes take 3 us at 4000 tokens.  A workgroup takes FT_ROWS queries x FT_KEYS keys: it expands the
-// attributes' start offsets into key codes in LDS, a thread then holds 16 keys and writes 16 bytes per
-// query (not aligned where S is no multiple of 16; the last thread's keys then overlap its
-// neighbour's).  The offsets travel in the kernel's arguments (FT_EMBED attributes at most, else in
-// device memory), so that a call allocates and copies nothing.  Measured, whole call with its
-// synchronisation, before -> now: 4000 tokens 69 -> 31 us (kernels alone 28.7 -> 12.2), 388 tokens 28.2 -> 26.9
-// (4.2 -> 9.2); before: a byte per thread, two launches, a table of 16 bytes per token built, allocated,
-// copied and freed by every call.
+// Bound by a chain of latencies - offsets, expansion, barrier - and the stores behind it (16 MB at 4000 tokens), of which a
+// call sees its own launch and wait on top.  A workgroup takes FT_ROWS queries x FT_KEYS keys: it expands the
+// attributes' start offsets into key codes in LDS, a thread then holds 16 keys.
+//  * Whatever the length of the sequence, a row is written in 16-byte units of the memory, not of the row: the row's
+//    first unit starts at its key s < 16, the same for all threads, and a thread's unit is made of its own 16 bytes and its
+//    neighbour's, shifted by s.  (So 63 lanes of a wave have a unit.)  The keys in front of the first and behind the last
+//    whole unit are bytes of a lane each.  Stores of 16 bytes at any address took 6 of the kernel's 9 us at 3919 tokens.
+//  * Most bytes are decided for a whole wave: keys behind the query, and in front of it where the query is of the prompt
+//    or none of the wave's 1024 keys is a value.  The others are worked out two keys at a time in 16-bit lanes.
+// The offsets travel in the kernel's arguments (FT_EMBED attributes at most, else in device memory), so that a call
+// allocates and copies nothing.  Measured, whole call with its synchronisation, a byte per thread -> 16 bytes at any
+// address -> this: 3919 tokens 69 -> 30.7 -> 27.1 us (kernels alone 28.7 -> 12.2 -> 8.5), 350 tokens 28.2 -> 27.1 -> 25.4,
+// 11168 tokens 53.6 -> 49.9, 43905 tokens 562 -> 534 (3.6 TB/s).  In the kernel of 3919 tokens the last store is issued 5.5 us
+// after the first wave starts; the rest is its launch and its end.
 // ---------------------------------------------------------------------------------------
-constexpr int FT_ROWS = 8, FT_KEYS = 4096, FT_EMBED = 640;
-constexpr int FT_LONG = 64, FT_LONGS = FT_KEYS / FT_LONG;
+constexpr int FT_ROWS = 8, FT_WAVE = 63 * 16, FT_KEYS = 4 * FT_WAVE, FT_SPAN = FT_KEYS + 16, FT_EMBED = 640;
+constexpr int FT_LONG = 64, FT_LONGS = FT_SPAN / FT_LONG;
+// Masks of up to so many bytes are written through the L2 (sc1): what is left in it is written back when the kernel
+// ends, and the wait for that is part of the call.  Through / not, us a call: 3919 tokens 27.1 / 28.5, 7268 44.3 / 45.8,
+// 12248 53.0 / 53.0; where the mask outgrows the Infinity Cache the L2 writes better: 26248 tokens 259 / 201, 43905 703 / 534.
+constexpr int64_t FT_THROUGH = (int64_t)128 << 20;
 struct FtOffsets {
   uint16_t name[FT_EMBED], value[FT_EMBED], before[FT_EMBED];  // first name / value token, names of earlier attributes
 };
@@ -357,12 +366,12 @@ template <bool EMBED>
 __global__ void __launch_bounds__(256)
 finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_attr, int32_t prompt_len, int32_t k_max,
                      int32_t S, int32_t* __restrict__ pos, uint8_t* __restrict__ mask) {
-  __shared__ uint32_t key[FT_KEYS];   // attribute << 16 | k
+  __shared__ __align__(16) uint32_t key[FT_SPAN];  // attribute << 16 | k
   __shared__ uint32_t query[FT_ROWS];
   __shared__ int32_t longs[FT_LONGS], n_long;  // attributes with more than FT_LONG value tokens among the keys
   const int32_t tid = threadIdx.x, q0 = blockIdx.x * FT_ROWS, k0 = blockIdx.y * FT_KEYS;
-  const int32_t n_key = mask ? min(FT_KEYS, S - k0) : 0;
-  for (int32_t i = tid; i < n_key; i += 256) key[i] = 0;
+  const int32_t n_key = mask ? min(FT_SPAN, S - k0) : 0;
+  for (int32_t i = tid; i < FT_SPAN / 4; i += 256) reinterpret_cast<uint4*>(key)[i] = make_uint4(0, 0, 0, 0);
   if (tid < FT_ROWS) query[tid] = 0;
   if (tid == 0) n_long = 0;
   if (pos && k0 == 0 && tid < FT_ROWS && q0 + tid < min(S, prompt_len)) pos[q0 + tid] = q0 + tid;
@@ -384,7 +393,7 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
     }
   }
   __syncthreads();
-  // a long value is expanded by the whole workgroup: by one thread it would be a chain of up to FT_KEYS writes to LDS
+  // a long value is expanded by the whole workgroup: by one thread it would be a chain of up to FT_SPAN writes to LDS
   // (4000 tokens with one value of 3900: 193 us the call, 33 so)
   if (n_long) {
     for (int32_t j = 0; j < n_long; ++j) {
@@ -393,34 +402,81 @@ finetune_mask_kernel(FtOffsets emb, const uint16_t* __restrict__ dev, int32_t n_
     }
     __syncthreads();
   }
-  if (tid * 16 >= n_key) return;
-  // this thread's 16 keys.  The last thread's end with the sequence and overlap its neighbour's (the same bytes): 16
-  // stores of a byte for each of the 8 queries took 2.5 us, more than a small call's 16-byte stores together.
-  const bool whole = n_key >= 16;
-  const int32_t kl = whole ? min(tid * 16, n_key - 16) : 0, kc = k0 + kl;
-  uint32_t code[16];
+  if (n_key == 0) return;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int32_t w0 = k0 + wave * FT_WAVE, kc = w0 + lane * 16;  // first key of the wave, of the lane
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u16x2 attr[8], k[8];
+  uint32_t any = 0;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) code[e] = key[kl + e];
-#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t x = key[kc - k0 + 2 * e], y = key[kc - k0 + 2 * e + 1];
+    attr[e] = __builtin_bit_cast(u16x2, (x >> 16) | (y & 0xffff0000u));
+    k[e] = __builtin_bit_cast(u16x2, (x & 0xffffu) | (y << 16));
+    any |= x | y;
+  }
+  const bool values = __any(any != 0);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(mask, 0, (uint32_t)S * (uint32_t)S, 0x00027000);
   for (int r = 0; r < FT_ROWS; ++r) {
     const int32_t qi = q0 + r;
     if (qi >= S) break;
-    const uint32_t qn = query[r] >> 16, qk = query[r] & 0xffffu;
-    uint32_t w[4] = {0, 0, 0, 0};
-    if (kc <= qi) {
+    uint8_t* const row = mask + (int64_t)qi * S;
+    const int32_t s = (int32_t)(-(uintptr_t)row & 15);  // key at the first 16-byte boundary
+    const uint32_t code = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)query[r]), qn = code >> 16, qk = code & 0xffffu;
+    if (w0 + s < S) {
+      uint32_t w[8];  // this lane's 16 keys, the next lane's
+      if (w0 > qi) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const bool ok = kc + e <= qi && !((code[e] >> 16) < qn && (code[e] & 0xffffu) > qk);
-        w[e >> 2] |= (ok ? 1u : 0u) << (8 * (e & 3));
+        for (int d = 0; d < 8; ++d) w[d] = 0;
+      } else if ((qn == 0 || !values) && w0 + 1023 <= qi) {
+#pragma unroll
+        for (int d = 0; d < 8; ++d) w[d] = 0x01010101u;
+      } else {
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+          const int32_t n = min(max(qi - kc + 1 - 4 * d, 0), 4);  // keys up to the query
+          w[d] = n > 0 ? 0x01010101u >> (8 * (4 - n)) : 0u;
+        }
+        if (qn != 0 && values) {
+          const u16x2 n2 = (u16x2)(uint16_t)qn, k2 = (u16x2)(uint16_t)qk, one = (u16x2)(uint16_t)1;
+          uint32_t hide[8];  // of an earlier attribute and a later step
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            hide[e] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_elementwise_min(
+                __builtin_elementwise_sub_sat(n2, attr[e]), __builtin_elementwise_sub_sat(k[e], k2)), one));
+#pragma unroll
+          for (int d = 0; d < 4; ++d) w[d] &= ~__builtin_amdgcn_perm(hide[2 * d + 1], hide[2 * d], 0x06040200u);
+        }
+#pragma unroll
+        for (int d = 0; d < 4; ++d) w[4 + d] = __shfl_down(w[d], 1);
+        if (s & 8) {
+#pragma unroll
+          for (int d = 0; d < 6; ++d) w[d] = w[d + 2];
+        }
+        if (s & 4) {
+#pragma unroll
+          for (int d = 0; d < 5; ++d) w[d] = w[d + 1];
+        }
+#pragma unroll
+        for (int d = 0; d < 4; ++d) w[d] = __builtin_amdgcn_alignbyte(w[d + 1], w[d], (uint32_t)s & 3u);
+      }
+      const u32x4 unit = {w[0], w[1], w[2], w[3]};
+      if (lane < 63 && kc + s + 16 <= S) {
+        const uint32_t at = (uint32_t)qi * (uint32_t)S + (uint32_t)(kc + s);
+        if ((int64_t)S * S <= FT_THROUGH) __builtin_amdgcn_raw_buffer_store_b128(unit, rsrc, at, 0, 16);
+        else __builtin_amdgcn_raw_buffer_store_b128(unit, rsrc, at, 0, 0);
       }
     }
-    uint8_t* const dst = mask + (int64_t)qi * S + kc;
-    if (whole) {
-      __builtin_memcpy(dst, w, 16);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (e < n_key) dst[e] = (uint8_t)(w[e >> 2] >> (8 * (e & 3)));
+    // the keys in front of the first whole unit, and (in the block that has their place) those behind the last one
+    if (r / 2 == wave && lane < 32) {
+      const int32_t units = S > s ? (S - s) / 16 : 0, last = s + 16 * units;
+      const int32_t e = lane < 16 ? lane : last + lane - 16;
+      const bool mine = lane < 16 ? k0 == 0 && e < min(s, S) : S > s && units / (FT_KEYS / 16) == (int32_t)blockIdx.y && e < S;
+      if (mine) {
+        const uint32_t x = key[e - k0];
+        row[e] = e <= qi && !((x >> 16) < qn && (x & 0xffffu) > qk);
+      }
     }
   }
 }
@@ -752,7 +808,8 @@ hipError_t hpd_launch_expand_mask(const int32_t* d_desc, int32_t S, int32_t pape
 hipError_t hpd_launch_finetune_mask(const int32_t* table, int32_t S, int32_t* pos_out, uint8_t* mask_out, hipStream_t s) {
   const int32_t prompt_len = table[0], n_attr = table[1], k_max = table[2];
   const int32_t* off = table + 3;  // [3][n_attr], all below 2^16
-  const dim3 grid((unsigned)((S + FT_ROWS - 1) / FT_ROWS), mask_out ? (unsigned)((S + FT_KEYS - 1) / FT_KEYS) : 1u);
+  // (a row's last, partial unit may be the first of a block of its own)
+  const dim3 grid((unsigned)((S + FT_ROWS - 1) / FT_ROWS), mask_out ? (unsigned)(S / FT_KEYS + 1) : 1u);
   FtOffsets emb = {};
   if (n_attr <= FT_EMBED) {
     for (int32_t n = 0; n < n_attr; ++n) {

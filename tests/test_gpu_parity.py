@@ -919,6 +919,33 @@ def test_finetune_mask_of_any_number_of_tokens(s):
     assert np.array_equal(m[:s * s].view(s, s).cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("s,off", [(16, 1), (17, 15), (1007, 3), (1008, 8), (1023, 12), (1024, 5), (1025, 0), (4031, 7), (4032, 1),
+                                   (4033, 14), (4047, 2), (4048, 9), (8065, 11), (11600, 6)])
+def test_finetune_mask_at_any_address(s, off):
+    """A mask that starts anywhere, of lengths around the 63 x 16 keys of a wave and the 4032 of a workgroup: rows begin
+    and end inside a 16-byte unit of the memory; the longest is written past the L2's write-through limit."""
+    from paper_2604_26209_amd import binding as B
+    n = s // 40
+    al, vl = 1 + np.arange(n) % 3, np.arange(n) * 7 % 30
+    plen = s - int(al.sum() + vl.sum())
+    _say(f"finetune mask of {s} tokens at byte {off}")
+    buf = torch.full((s * s + 64,), 9, dtype=torch.uint8, device="cuda")
+    m = buf[off:off + s * s]
+    assert B.hpd_finetune_mask(plen, al, vl, 40, None, m) == s
+    assert bool((buf[:off] == 9).all()) and bool((buf[off + s * s:] == 9).all())
+    owner = torch.full((s,), -1, dtype=torch.int32, device="cuda")
+    k, at = torch.zeros_like(owner), plen
+    for a, (x, y) in enumerate(zip(al.tolist(), vl.tolist())):
+        owner[at:at + x + y] = a
+        k[at + x:at + x + y] = torch.arange(1, y + 1, device="cuda")
+        at += x + y
+    i = torch.arange(s, device="cuda")
+    ok = i[None] <= i[:, None]
+    ok &= ~((k[None] > 0) & ((k == 0) & (owner >= 0))[:, None])
+    ok &= ~((k[None] > k[:, None]) & (k[:, None] > 0) & (owner[None] < owner[:, None]))
+    assert torch.equal(m.view(s, s), ok.to(torch.uint8))
+
+
 @pytest.mark.parametrize("n_attr", [7, 650])
 def test_finetune_mask_of_long_values(n_attr):
     """Values around and far above the 64 tokens that one thread expands, across the 4096 keys of a workgroup; with a
