@@ -1,0 +1,595 @@
+// Decode attention of launches with many rows per unit (gfx950, bf16, head_dim 128): the loop of the prefill kernel
+// (attn_prefill_kernel in hpd_attn_stream.hip: four waves of 32 rows that load and compute, two workgroups per CU, rounds
+// of two blocks) with the units, the append and the tails of attn_stream_kernel.  Which steps run it is plan_dense's.
+//
+// What bounds such a launch is the compute waves.  attn_stream_kernel has six of them on a CU's four SIMDs beside two
+// loaders: a block of 32 keys took 184 ns per row block and CU (70B-like, in-kernel timestamps), 129 ns here, and its one
+// workgroup per CU leaves the CU idle while it starts and ends (18 of 93 us), where here the other one works.
+//  * Block mask: a tail belongs to one wave's rows, so behind the shared blocks every wave fetches and works on the tiles
+//    of its own branches, through 16 KB of the ring that are its own: no barrier.  The keys of a tile are requested as soon
+//    as the scores of the one before are settled, its values when those have been read; the first tile's keys during
+//    the last round of the prefix.  Positions in the newest chunk follow its length, as there.
+//  * Literal mask: the tiles are shared blocks like the prefix (a wave skips those behind its last branch), with as few
+//    positions in the newest chunk as it holds.  A row group's last tiles are only its own, so the last row group of a
+//    prompt, which has the most, is started first.  Both blocks of a round of tiles at a time, as in the prefix: the
+//    compiler spills 55 registers, 440 us instead of 317.
+// Measured (us per hpd_decode_step, before -> now): 16 prompts x 2 documents of 2048 tokens, 48 branches, 64/8 heads 153 ->
+// 140 (768 workgroups on 512 places: half of the launch runs one per CU); literal mask, 64 prompts x 4 documents, 96
+// branches 359 -> 315..323; literal mask, 25 prompts x 3 documents of 84 tokens, 153 branches 307 -> 122.
+// Outputs differ from the other kernel's by rounding (relative 7e-4 in bf16); error against 64 bits 1.7e-3 for both.
+#include <algorithm>
+#include <type_traits>
+
+#include "hpd_attn_bf16.h"
+
+namespace {
+
+constexpr int DENSE_WAVES = 4;  // row blocks per workgroup
+
+template <int G, bool PAPER, bool PAGED>
+__global__ void __launch_bounds__(DENSE_WAVES * 64, 2)
+attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
+                  const uint16_t* __restrict__ v_prefix, uint16_t* __restrict__ k_tail, uint16_t* __restrict__ v_tail,
+                  const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, void* __restrict__ out) {
+  constexpr int BPB = 32 / G;  // branches per row block (wave)
+  constexpr int LG_G = G == 1 ? 0 : G == 2 ? 1 : G == 4 ? 2 : 3;
+  constexpr uint32_t BLK = 16384, HALF = 2 * BLK;  // bytes of a block (8 KB of K, 8 KB of V), of a round
+  __shared__ uint4 ring[4 * SLOT_U4];
+  constexpr int MAX_KEY_BRANCHES = 256;
+  __shared__ int32_t klen[PAPER ? MAX_KEY_BRANCHES : 1];  // tokens in memory of every key branch
+  // ids of the row group's branches where they are no run: a lookup in memory waits for the loads in front of it
+  __shared__ int32_t ids[PAPER ? 1 : DENSE_WAVES * BPB];
+
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int n = lane & 31, g2 = lane >> 5, r4 = lane >> 4, c16 = lane & 15;
+  // (unit, kv head) and row group of this workgroup, and the unit's descriptor: as in attn_stream_kernel
+  const int32_t rg = a.RG - 1 - (blockIdx.x >> 3) % a.RG;
+  const int32_t grp = ((blockIdx.x >> 3) / a.RG) * 8 + (blockIdx.x & 7);
+  if (grp >= a.n_groups) return;
+  const int32_t hk = grp % a.Hkv, u = grp / a.Hkv;
+  const int32_t* desc = (PAPER ? a.tb.punit_desc : a.tb.unit_desc) + (int64_t)u * (PAPER ? 16 : 8);
+  const int32_t hoff = desc[0], Hlen = desc[1], doff = desc[2], Llen = desc[3];
+  const int32_t row0 = desc[4], nb = desc[5], upos = PAPER ? -1 : desc[6], ub0 = desc[7];
+  const int32_t pb0 = PAPER ? desc[6] : 0;
+  const int32_t n_doc_blk = PAPER ? desc[9] : 0;
+  // the unit's row blocks, shared out evenly over the row groups that it needs
+  const int32_t nblk = (nb * G + 31) >> 5, n_rg = (nblk + DENSE_WAVES - 1) / DENSE_WAVES;
+  if (rg >= n_rg) return;  // uniform over the workgroup
+  const int32_t per_group = (nblk + n_rg - 1) / n_rg, first_blk = rg * per_group;
+  const int32_t nblk_here = min(per_group, nblk - first_blk);
+  if (nblk_here <= 0) return;
+  const int32_t br0 = first_blk * BPB, nbr_here = min(nb - br0, nblk_here * BPB);
+  const bool active = wave < nblk_here;  // the wave has rows
+  // global id of the unit's li-th live branch
+  auto unit_branch = [&](int32_t li) -> int32_t { return ub0 >= 0 ? ub0 + li : a.tb.live_branch[a.live_base + row0 + li]; };
+  const int32_t kb_end = PAPER ? __builtin_amdgcn_readfirstlane(unit_branch(br0 + nbr_here - 1)) - pb0 + 1 : 0;
+
+  // ---- what all rows share: NB prefix blocks; literal mask: then the tail tiles of the prompt's branches 0 .. kb_end-1
+  const int32_t NBh = (Hlen + 31) >> 5, NBd = PAPER ? Llen : (Llen + 31) >> 5, NB = NBh + NBd;
+  const int32_t NC = (a.step >> 3) + 1, newest = (a.step & 7) + 1;
+  const int32_t fmt_lg = newest <= 1 ? 0 : newest <= 2 ? 1 : newest <= 4 ? 2 : 3;
+  const int32_t NQ = PAPER ? (kb_end + 3) >> 2 : 0;
+  const int32_t n_full = PAPER ? (fmt_lg < 3 ? NQ * (NC - 1) : NQ * NC) : 0;
+  const int32_t NS = NB + (PAPER ? n_full + (fmt_lg < 3 ? (kb_end + (32 >> fmt_lg) - 1) >> (5 - fmt_lg) : 0) : 0);
+  const int32_t NR = (NS + 1) >> 1;
+  const const_i32* const list = (const const_i32*)(uintptr_t)(a.tb.pblk + 2 * (int64_t)(PAPER ? doff : 0));
+
+  // ---- loads: quarter `wave` of a block (K rows 0..15, K rows 16..31, V d-blocks 0..1, 2..3; tail tiles: V rows 0..15,
+  //      16..31)
+  const bool is_v = wave >= 2;
+  uint32_t vo[4];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) {
+    const uint32_t k_off = (uint32_t)(r4 * 256 + ((c16 ^ r4 ^ (4 * f)) << 4));  // + f * 1024
+    const uint32_t v_off = (uint32_t)(((g2 * 128 + n) << 4) + 2048 + (f & 1) * 4096 + (f >> 1) * 512 - f * 1024);
+    vo[f] = is_v ? v_off : k_off;
+  }
+  const char* const src = (is_v ? reinterpret_cast<const char*>(v_prefix) + (wave & 1) * 1024 - 2048
+                                : reinterpret_cast<const char*>(k_prefix) + (wave & 1) * 4096) +
+                          (int64_t)hk * a.NP * (D * 2);
+  const uint32_t ring_lds = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)ring);
+  auto issue_prefix = [&](int32_t slot0, uint32_t at) {
+    const char* const s = uniform(src + (int64_t)slot0 * (D * 2));
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(ring_lds + at + (uint32_t)wave * 4096);
+    uint32_t keep;  // M0 is the compiler's: put back what it held
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %6\n\t"
+        "global_load_lds_dwordx4 %2, %6 offset:1024\n\t"
+        "global_load_lds_dwordx4 %3, %6 offset:2048\n\t"
+        "global_load_lds_dwordx4 %4, %6 offset:3072\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(keep)
+        : "v"(vo[0]), "v"(vo[1]), "v"(vo[2]), "v"(vo[3]), "s"(dst), "s"(s)
+        : "memory");
+  };
+  // four rows-of-four: rows rw[0..3] of a pool, chunk ch[f] of each, to LDS bytes at .. at + 4095; streaming hint
+  auto issue_rows = [&](const uint16_t* pool, const uint32_t (&rw)[4], const uint32_t (&ch)[4], uint32_t at) {
+    const char* p[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) p[f] = reinterpret_cast<const char*>(pool) + ((uint64_t)rw[f] * (D * 2) + ch[f]) - f * 1024;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(ring_lds + at);
+    uint32_t keep;
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, off nt\n\t"
+        "global_load_lds_dwordx4 %2, off offset:1024 nt\n\t"
+        "global_load_lds_dwordx4 %3, off offset:2048 nt\n\t"
+        "global_load_lds_dwordx4 %4, off offset:3072 nt\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(keep)
+        : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "s"(dst)
+        : "memory");
+  };
+  // row (32 bits hold the rows of any pool that fits the memory) of token t of branch b
+  auto tail_row = [&](int32_t b, int32_t t) -> uint32_t {
+    if (PAGED) return (uint32_t)hpd_tail_row(a.tb, b, hk, a.Hkv, a.Tcap, t);
+    return ((uint32_t)b * (uint32_t)a.Hkv + (uint32_t)hk) * (uint32_t)a.Tcap + (uint32_t)t;
+  };
+  // literal mask, tail tile tt: key k is position c * 8 + k % 2^lg of branch tb0 + k / 2^lg
+  struct TileAt { int32_t c, tb0, lg; };
+  auto tile_at = [&](int32_t tt) -> TileAt {
+    if (tt < n_full) {
+      const int32_t c = tt / max(NQ, 1);
+      return {c, (tt - c * NQ) * 4, 3};
+    }
+    return {NC - 1, (tt - n_full) << (5 - fmt_lg), fmt_lg};
+  };
+  auto issue_tile = [&](int32_t tt, uint32_t at) {
+    const TileAt x = tile_at(tt);
+    uint32_t rw[4], ch[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const int32_t k = (wave & 1) * 16 + f * 4 + r4;
+      const int32_t j = min(x.tb0 + (k >> x.lg), kb_end - 1);
+      const int32_t pos = max(min(x.c * 8 + (k & ((1 << x.lg) - 1)), klen[j] - 1), 0);
+      rw[f] = tail_row(pb0 + j, pos);
+      ch[f] = (uint32_t)(is_v ? (c16 ^ (2 * r4)) << 4 : (c16 ^ r4 ^ (4 * f)) << 4);
+    }
+    issue_rows(is_v ? v_tail : k_tail, rw, ch, at + (uint32_t)wave * 4096);
+  };
+  auto slot_of = [&](int32_t gb) -> int32_t {  // first pool slot of a prefix block
+    if (gb < NBh) return hoff + gb * 32;
+    return PAPER ? list[2 * (gb - NBh)] : doff + (gb - NBh) * 32;
+  };
+  auto issue = [&](int32_t gb, int32_t slot, uint32_t at) {
+    if (!PAPER || gb < NB) issue_prefix(slot, at);
+    else issue_tile(gb - NB, at);
+  };
+  // (a block past the last one re-loads the last one, never read)
+  auto issue_round = [&](int32_t r, int32_t sA, int32_t sB) {
+    const uint32_t at = (uint32_t)(r & 1) * HALF;
+    issue(2 * r, sA, at);
+    issue(min(2 * r + 1, NS - 1), sB, at + BLK);
+  };
+  auto slot_clamped = [&](int32_t gb) -> int32_t { return NB > 0 ? slot_of(min(gb, NB - 1)) : 0; };
+
+  // ---- fused mode: append the newest tokens (the arithmetic of hpd_kv_append), 8 lanes per branch.  Literal mask:
+  //      all live branches up to the row group's last (the same bytes from every writer).
+  auto append = [&]() {
+    const int32_t ap_c = (tid & 7) * 8;
+    for (int32_t li = (PAPER ? 0 : br0) + (tid >> 3); li < br0 + nbr_here; li += DENSE_WAVES * 8) {
+      const int64_t noff = ((int64_t)(row0 + li) * a.Hkv + hk) * D;
+      const uint4 klo = *reinterpret_cast<const uint4*>(k_new + noff + ap_c);
+      const uint4 khi = *reinterpret_cast<const uint4*>(k_new + noff + 64 + ap_c);
+      const uint4 vlo = *reinterpret_cast<const uint4*>(v_new + noff + ap_c);
+      const uint4 vhi = *reinterpret_cast<const uint4*>(v_new + noff + 64 + ap_c);
+      const int32_t b = unit_branch(li);
+      const int32_t pos = upos >= 0 ? upos : a.tb.branch_base_pos[b] + 1 + a.step;
+      float rl[8], rh[8];
+      rotate16(klo, khi, a.tb.rope + (int64_t)pos * (D / 2), ap_c, rl, rh);
+      const int64_t trow = (int64_t)tail_row(b, a.step) * D;
+      *reinterpret_cast<uint4*>(k_tail + trow + ap_c) = pack8_key(rl);
+      *reinterpret_cast<uint4*>(k_tail + trow + 64 + ap_c) = pack8_key(rh);
+      *reinterpret_cast<uint4*>(v_tail + trow + ap_c) = cache8(vlo);
+      *reinterpret_cast<uint4*>(v_tail + trow + 64 + ap_c) = cache8(vhi);
+    }
+  };
+  if constexpr (PAPER) {
+    for (int32_t i = tid; i < kb_end; i += DENSE_WAVES * 64) klen[i] = min(a.step + 1, a.tb.branch_len[pb0 + i]);
+  }
+  if (!PAPER && ub0 < 0) {
+    for (int32_t i = tid; i < nbr_here; i += DENSE_WAVES * 64) ids[i] = unit_branch(br0 + i);
+  }
+  // rounds 0 and 1 are requested in front of the first barrier: with tail tiles among them the append comes before
+  const bool append_first = a.fused && PAPER && NB < 4;
+  if (PAPER && NB < 4) {
+    if (append_first) append();
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+
+  // ---- the query rows of the wave, straight into operand layout, and their position
+  const int32_t lb_row = wave * BPB + n / G;                       // this row's branch, counted in the row group
+  const int32_t my_lb = br0 + min(lb_row, nbr_here - 1);           // ... in the unit; rows behind the last repeat it
+  uint4 qraw[8];
+  {
+    const uint16_t* qp = q + ((int64_t)(row0 + my_lb) * a.Hq + hk * a.Gr + min(n % G, a.Gr - 1)) * D + g2 * 8;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) qraw[kk] = *reinterpret_cast<const uint4*>(qp + kk * 16);
+  }
+  const int32_t my_branch = unit_branch(my_lb);
+  const int32_t pos = upos >= 0 ? upos : a.tb.branch_base_pos[my_branch] + 1 + a.step;
+  if (NR > 0) issue_round(0, slot_clamped(0), slot_clamped(1));
+  if (NR > 1) issue_round(1, slot_clamped(2), slot_clamped(3));
+  f16x8 Qf[8];
+  {
+    const float4* cs_row = reinterpret_cast<const float4*>(a.tb.rope + (int64_t)pos * (D / 2));
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      float lo[8], hi[8], rl[8], rh[8];
+      unpack8(qraw[kk], lo);
+      unpack8(qraw[kk + 4], hi);
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        const float4 cs = cs_row[kk * 8 + g2 * 4 + e2];
+        hpd::rope_pair(lo[2 * e2], hi[2 * e2], cs.x, cs.y, rl[2 * e2], rh[2 * e2]);
+        hpd::rope_pair(lo[2 * e2 + 1], hi[2 * e2 + 1], cs.z, cs.w, rl[2 * e2 + 1], rh[2 * e2 + 1]);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { rl[e] *= a.scale_log2; rh[e] *= a.scale_log2; }
+      Qf[kk] = pack8_half(rl);
+      Qf[kk + 4] = pack8_half(rh);
+    }
+  }
+  if (a.fused && !append_first) append();
+
+  float l_lane = 0.f;
+  floatx16 minus_m;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) minus_m[i] = 0.f;
+  float slack = -INFINITY;
+  floatx16 acc[4];
+#pragma unroll
+  for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[blk][i] = 0.f;
+
+  const int32_t krow = ((n >> 4) << 4) | (((n >> 2) & 1) << 3) | (((n >> 3) & 1) << 2) | (n & 3);
+  const char* const rc = reinterpret_cast<const char*>(ring);
+  // Scores, softmax and value product as in attn_prefill_kernel.  N blocks whose K halves lie at `at`, `at` + BLK.
+  auto settle = [&](auto nc, float (&s)[decltype(nc)::value][16], uint32_t at, bool masked, uint32_t ok0, uint32_t ok1)
+      __attribute__((always_inline)) {
+    constexpr int N = decltype(nc)::value;
+    auto scores = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int b = 0; b < N; ++b) {
+        floatx16 S;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) S[i] = minus_m[i];
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+          const f16x8 kf = __builtin_bit_cast(f16x8, *reinterpret_cast<const uint4*>(
+              rc + at + (krow * 256 + (((kk * 2 + g2) ^ (krow & 15)) << 4)) + b * BLK));
+          S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, Qf[kk], S, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[b][i] = S[i];
+      }
+      if (masked) {
+#pragma unroll
+        for (int b = 0; b < N; ++b)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[b][i] = ((b ? ok1 : ok0) >> i) & 1 ? s[b][i] : -INFINITY;
+      }
+    };
+    scores();
+    float bm = NEG_BIG;
+#pragma unroll
+    for (int b = 0; b < N; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[b][i]);
+    if (__any(bm > slack)) {
+      bm = fmaxf(bm, __shfl_xor(bm, 32));
+      // (a row that has seen no key yet keeps its empty state)
+      const bool none = bm <= NEG_BIG, first = slack < 0.f;
+      const float d = none ? 0.f : first ? bm : fmaxf(bm, 0.f);
+      const float alpha = first ? 0.f : fast_exp2(-d);
+      slack = none && first ? slack : MAX_SLACK;
+      const float m_old = minus_m[0], m_new = m_old - d;
+      const bool again = __any(fabsf(m_old) > fmaxf(128.f, fabsf(m_new)));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) minus_m[i] = m_new;
+      const float shift = again ? 0.f : d;
+      if (again) scores();
+#pragma unroll
+      for (int b = 0; b < N; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[b][i] -= shift;
+      l_lane *= alpha;
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[blk][i] *= alpha;
+    }
+  };
+  auto weigh = [&](float (&s)[16], const uint4 (&vf)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]);
+    const f16x8 P0 = pack8_half(s), P1 = pack8_half(s + 8);
+    const uint4 w0 = __builtin_bit_cast(uint4, P0), w1 = __builtin_bit_cast(uint4, P1);
+    float la = sum_half_pair(w0.x, l_lane), lb = sum_half_pair(w1.x, 0.f);
+    la = sum_half_pair(w0.y, la); lb = sum_half_pair(w1.y, lb);
+    la = sum_half_pair(w0.z, la); lb = sum_half_pair(w1.z, lb);
+    la = sum_half_pair(w0.w, la); lb = sum_half_pair(w1.w, lb);
+    l_lane = la + lb;
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk) {
+      acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, vf[blk * 2]), P0, acc[blk], 0, 0, 0);
+      acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, vf[blk * 2 + 1]), P1, acc[blk], 0, 0, 0);
+    }
+  };
+  auto read_values = [&](uint32_t at, uint4 (&vf)[8]) __attribute__((always_inline)) {  // of a prefix block's V half
+#pragma unroll
+    for (int f = 0; f < 8; ++f) vf[f] = *reinterpret_cast<const uint4*>(rc + at + lane * 16 + f * 1024);
+  };
+  auto read_tail_values = [&](uint32_t at, uint4 (&vf)[8]) __attribute__((always_inline)) {  // as in attn_stream_kernel
+    const int tj = (lane >> 2) & 3, tr = lane & 3;
+    const int tx = ((lane >> 4) & 1) * 2 + (tr >> 1);
+    const char* vlane = rc + at + (g2 * 8 + tj) * 256 + (tr & 1) * 8;
+#pragma unroll
+    for (int f = 0; f < 8; ++f) {
+      const int chunk = ((f >> 1) * 4 + tx) ^ (2 * tj);
+      const char* p = vlane + (f & 1) * 4096 + chunk * 16;
+      const uint2 k03 = lds_read_tr16(p), k47 = lds_read_tr16(p + 4 * 256);
+      vf[f] = make_uint4(k03.x, k03.y, k47.x, k47.y);
+    }
+  };
+  // N blocks from `at` on, of which those of bit b in `tails` are tail tiles
+  auto compute = [&](auto nc, uint32_t at, bool masked, uint32_t ok0, uint32_t ok1, uint32_t tails) __attribute__((always_inline)) {
+    constexpr int N = decltype(nc)::value;
+    float s[N][16];
+    settle(nc, s, at, masked, ok0, ok1);
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      uint4 vf[8];
+      if ((tails >> b) & 1) read_tail_values(at + b * BLK + 8192, vf);
+      else read_values(at + b * BLK + 8192, vf);
+      weigh(s[b], vf);
+    }
+  };
+  auto first_bits = [](int32_t cnt) -> uint32_t { return (1u << min(max(cnt, 0), 8)) - 1u; };
+  auto ok_bits = [&](int32_t valid) -> uint32_t {
+    return first_bits(valid - g2 * 8) | (first_bits(valid - 16 - g2 * 8) << 8);
+  };
+
+  const int32_t h_part = (Hlen & 31) ? NBh - 1 : -1, d_part = !PAPER && (Llen & 31) ? NB - 1 : -1;
+  auto keys_of = [&](int32_t b) -> int32_t {  // of a prefix block
+    if (b == h_part) return Hlen & 31;
+    if (PAPER) return b < NBh ? 32 : list[2 * (b - NBh) + 1];
+    return b == d_part ? Llen & 31 : 32;
+  };
+  int32_t nA = slot_clamped(4), nB = slot_clamped(5);  // where the prefix blocks of the next round but one lie
+  auto open_round = [&](int32_t r) __attribute__((always_inline)) {
+    // (the round after the first was requested in front of the loop; so was the append, which is complete at barrier 1)
+    if (r == 0 && NR > 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): LDS reads of the previous round are done
+    __builtin_amdgcn_s_barrier();        // the round is in LDS; the other half of the ring is free
+    if (r >= 1 && r + 1 < NR) {
+      issue_round(r + 1, nA, nB);
+      nA = slot_clamped(2 * r + 4);
+      nB = slot_clamped(2 * r + 5);
+    }
+  };
+
+  // literal mask: the branch of this row and of the row block's last one, counted from the prompt's first, and the
+  // names they see
+  int32_t kb_row = 0, kb_row_min = 0, kb_row_max = 0, names_row = 0, names_max = 0;
+  if constexpr (PAPER) {
+    kb_row = my_branch - pb0;
+    kb_row_min = __builtin_amdgcn_readfirstlane(kb_row);
+    kb_row_max = __builtin_amdgcn_readfirstlane(unit_branch(br0 + min(wave * BPB + BPB - 1, nbr_here - 1))) - pb0;
+    names_row = a.tb.skel_cum[pb0 + kb_row];
+    names_max = __builtin_amdgcn_readfirstlane(a.tb.skel_cum[pb0 + kb_row_max]);
+  }
+  const int32_t r_plain = (PAPER ? NBh + n_doc_blk : NB) >> 1;  // rounds of blocks that all rows see alike
+  // ---- block mask: the tails of the wave's own branches, tile by tile, through 16 KB of the ring that are the wave's
+  const uint32_t hx = (uint32_t)(NR & 1) * HALF, hy = HALF - hx;  // the half that the last round does not use; its own
+  const uint32_t my_k = hx + (uint32_t)wave * 8192, my_v = hy + (uint32_t)wave * 8192;
+  const int32_t wb0 = wave * BPB, wnb = min(BPB, nbr_here - wb0);  // the wave's branches
+  const int32_t lg_new = max(fmt_lg, LG_G);
+  const int32_t n_quad = (wnb + 3) >> 2;
+  const int32_t n_own = PAPER ? 0 : n_quad * (NC - 1) + ((wnb + (32 >> lg_new) - 1) >> (5 - lg_new));
+  auto own_tile = [&](int32_t t) -> TileAt {
+    const int32_t nf = n_quad * (NC - 1);
+    if (t < nf) {
+      const int32_t c = n_quad == 1 ? t : t / n_quad;
+      return {c, wb0 + (t - c * n_quad) * 4, 3};
+    }
+    return {NC - 1, wb0 + ((t - nf) << (5 - lg_new)), lg_new};
+  };
+  // K or V half of own tile t: row k = 4 f + lane / 16 of it is position c * 8 + k % 2^lg of branch tb0 + k / 2^lg; what
+  // lies behind the last branch or position repeats the last one
+  auto issue_own = [&](const uint16_t* pool, bool v, uint32_t at, int32_t t) __attribute__((always_inline)) {
+    const TileAt x = own_tile(t);
+    int32_t r4 = lane >> 4, c16 = lane & 15;
+    asm volatile("" : "+v"(r4), "+v"(c16));  // (addresses kept from one tile for the next cost registers that the loop needs)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      uint32_t rw[4], ch[4];
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        const int32_t k = (4 * h + f) * 4 + r4;
+        const int32_t j = min(x.tb0 + (k >> x.lg), nbr_here - 1);
+        rw[f] = tail_row(ub0 >= 0 ? ub0 + br0 + j : ids[j], min(x.c * 8 + (k & ((1 << x.lg) - 1)), a.step));
+        ch[f] = (uint32_t)(v ? (c16 ^ (2 * r4)) << 4 : (c16 ^ r4 ^ (4 * f)) << 4);
+      }
+      issue_rows(pool, rw, ch, at + h * 4096);
+    }
+  };
+
+  if (!active) {  // a wave without rows loads
+    for (int32_t r = 0; r < NR; ++r) open_round(r);
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    if (NR == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    return;
+  }
+  for (int32_t r = 0; r < r_plain; ++r) {
+    open_round(r);
+    if (!PAPER && r == NR - 1) {
+      issue_own(k_tail, false, my_k, 0);
+    }
+    const int32_t vA = keys_of(2 * r), vB = keys_of(2 * r + 1);
+    const bool masked = (vA & vB) != 32;
+    uint32_t ok0 = 0, ok1 = 0;
+    if (masked) { ok0 = ok_bits(vA); ok1 = ok_bits(vB); }
+    compute(std::integral_constant<int, 2>{}, (uint32_t)(r & 1) * HALF, masked, ok0, ok1, 0u);
+  }
+  for (int32_t r = r_plain; r < NR; ++r) {
+    open_round(r);
+    if (!PAPER && r == NR - 1) {
+      issue_own(k_tail, false, my_k, 0);
+    }
+#pragma nounroll
+    for (int32_t b = 2 * r; b < min(2 * r + 2, NS); ++b) {
+      // what the rows see of the block: all of it, or what their bits say
+      uint32_t ok = 0;
+      bool masked = true;
+      const bool tail = PAPER && b >= NB;
+      if (!tail) {
+        int32_t valid = keys_of(b);
+        masked = valid < 32;
+        if (PAPER && valid >= 1000) {  // a block of attribute names: the row keeps those up to its own branch's
+          const int32_t k0 = valid - 1000;
+          if (k0 >= names_max) continue;
+          masked = true;
+          valid = names_row - k0;
+        }
+        ok = ok_bits(valid);
+      } else {
+        const TileAt x = tile_at(b - NB);
+        if (x.tb0 > kb_row_max) continue;
+        // a row keeps the tokens in memory of the branches up to its own
+        const int32_t j_lane = x.tb0 + (n >> x.lg);
+        masked = !__all(j_lane <= kb_row_min && klen[min(j_lane, kb_end - 1)] - x.c * 8 >= 1 << x.lg);
+        if (masked) {
+#pragma nounroll
+          for (int32_t i = 0; i < 16; i += 1 << x.lg) {
+            const int32_t j = x.tb0 + (((i >> 3) * 16 + g2 * 8 + (i & 7)) >> x.lg);
+            const int32_t cnt = j <= kb_row ? min(klen[min(j, kb_end - 1)] - x.c * 8, 1 << x.lg) : 0;
+            ok |= first_bits(cnt) << i;
+          }
+        }
+      }
+      compute(std::integral_constant<int, 1>{}, (uint32_t)(b & 3) * BLK, masked, ok, 0u, tail ? 1u : 0u);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  if (NR == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the append
+  __builtin_amdgcn_s_barrier();  // the ring is the waves' own from here on
+  if constexpr (!PAPER) {
+    if (NR == 0) {
+      issue_own(k_tail, false, my_k, 0);
+    }
+    issue_own(v_tail, true, my_v, 0);
+#pragma nounroll
+    for (int32_t t = 0; t < n_own; ++t) {
+      const TileAt x = own_tile(t);
+      const int32_t k0 = (lb_row - x.tb0) << x.lg;  // this row's first key in the tile
+      const int32_t lo = k0 - g2 * 8, hi = lo + min(a.step + 1 - x.c * 8, 1 << x.lg);
+      const uint32_t ok = (k0 >= 0 && k0 < 32) ? ((first_bits(hi) & ~first_bits(lo)) |
+                                                  ((first_bits(hi - 16) & ~first_bits(lo - 16)) << 8)) : 0u;
+      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // the keys have landed, the values may be on their way
+      float s[1][16];
+      settle(std::integral_constant<int, 1>{}, s, my_k, true, ok, 0u);
+      const bool more = t + 1 < n_own;
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      if (more) {
+        issue_own(k_tail, false, my_k, t + 1);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      uint4 vf[8];
+      read_tail_values(my_v, vf);
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      asm volatile("" ::: "memory");
+      if (more) issue_own(v_tail, true, my_v, t + 1);
+      weigh(s[0], vf);
+    }
+  }
+
+  // ---- normalise and write: as the waves of attn_stream_kernel that hold whole rows
+  const float inv = 1.0f / (l_lane + __shfl_xor(l_lane, 32));
+  char* const mine[2] = {reinterpret_cast<char*>(ring) + my_k, reinterpret_cast<char*>(ring) + my_v};
+  typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+  const int32_t rows_here = nbr_here * G;
+  if (a.out_f32) {  // 16 rows in each half
+    float4* rowp = reinterpret_cast<float4*>((n >> 4 ? mine[1] : mine[0]) + (n & 15) * 512);
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc)
+        rowp[(blk * 8 + cc * 2 + g2) ^ n] = make_float4(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv,
+                                                        acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv);
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+    for (int32_t i = 0; i < 16; ++i) {  // 2 rows per instruction
+      const int32_t rr = i * 2 + (lane >> 5), chunk = lane & 31, lrr = wave * 32 + rr;
+      if (lrr < rows_here && lrr % G < a.Gr) {
+        const uint4 v = reinterpret_cast<const uint4*>((rr >> 4 ? mine[1] : mine[0]) + (rr & 15) * 512)[chunk ^ rr];
+        const int64_t off = ((int64_t)(row0 + br0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 4;
+        u4v vv = {v.x, v.y, v.z, v.w};
+        __builtin_nontemporal_store(vv, reinterpret_cast<u4v*>(reinterpret_cast<float*>(out) + off));
+      }
+    }
+  } else {
+    uint2* rowp = reinterpret_cast<uint2*>(mine[0]) + n * 32;
+#pragma unroll
+    for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+      for (int cc = 0; cc < 4; ++cc)
+        rowp[(((blk * 4 + cc) ^ (n & 15)) << 1) | g2] =
+            make_uint2(cvt_pk_bf16(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv),
+                       cvt_pk_bf16(acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv));
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+    for (int32_t i = 0; i < 8; ++i) {  // 4 rows per instruction
+      const int32_t rr = i * 4 + (lane >> 4), chunk = lane & 15, lrr = wave * 32 + rr;
+      if (lrr < rows_here && lrr % G < a.Gr) {
+        const uint4 v = reinterpret_cast<const uint4*>(mine[0])[rr * 16 + (chunk ^ (rr & 15))];
+        const int64_t off = ((int64_t)(row0 + br0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 8;
+        u4v vv = {v.x, v.y, v.z, v.w};
+        __builtin_nontemporal_store(vv, reinterpret_cast<u4v*>(reinterpret_cast<uint16_t*>(out) + off));
+      }
+    }
+  }
+}
+
+template <int G, bool PAPER, bool PAGED>
+hipError_t launch_dense(const StreamArgs& a, int64_t items, const void* q, const void* k_prefix, const void* v_prefix,
+                        void* k_tail, void* v_tail, const void* k_new, const void* v_new, void* out, hipStream_t s) {
+  attn_dense_kernel<G, PAPER, PAGED><<<dim3((unsigned)items), DENSE_WAVES * 64, 0, s>>>(
+      a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail,
+      (const uint16_t*)k_new, (const uint16_t*)v_new, out);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32_t max_nblk, const void* q,
+                                      const void* k_prefix, const void* v_prefix, void* k_tail, void* v_tail,
+                                      const void* k_new, const void* v_new, void* out, hipStream_t s) {
+  a.RG = (max_nblk + DENSE_WAVES - 1) / DENSE_WAVES;
+  const int64_t items = ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
+  if (items > 0x7fffffff) return hipErrorInvalidValue;
+#define HPD_DENSE_M(GG, PP, TT) launch_dense<GG, PP, TT>(a, items, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s)
+#define HPD_DENSE(GG)                                                                   \
+  (paper ? a.tb.tail_pages ? HPD_DENSE_M(GG, true, true) : HPD_DENSE_M(GG, true, false) \
+         : a.tb.tail_pages ? HPD_DENSE_M(GG, false, true) : HPD_DENSE_M(GG, false, false))
+  switch (G) {
+    case 1: return HPD_DENSE(1);
+    case 2: return HPD_DENSE(2);
+    case 4: return HPD_DENSE(4);
+    case 8: return HPD_DENSE(8);
+    default: return hipErrorInvalidValue;
+  }
+#undef HPD_DENSE
+#undef HPD_DENSE_M
+}

@@ -127,6 +127,93 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
   }
 }
 
+// The steps that run attn_dense_kernel (hpd_attn_dense.hip).  Against the kernel with loader waves it has the faster
+// loop for many rows (four waves that load and compute, two workgroups per CU: 1.05 us per block of 32 keys for 2 x 128 rows of
+// a CU, the wide shape 1.15 us for 192), and the start and end of a workgroup under another's work; but it reads the prefix once
+// per 128 rows, and a wave without rows idles where the other kernel gives it a share of the keys.  Which one is faster
+// depends on how the units' rows divide, on their lengths and on how many workgroups there are, so both are estimated:
+// the time of a workgroup on its slot (a CU, or half of one), all of them over the slots, and a third of the longest for
+// the end of the launch; this kernel runs where the estimate promises a quarter and more.  Measured over 360 batches of
+// either mask (2 .. 64 branches, 1 .. 6 documents of 60 .. 3000 tokens, 1 .. 128 prompts; everywhere it would be 0.64 .. 2.5
+// times as fast): taken for 85 of them, 1.31 times the speed in the mean, from 0.92 (47 us instead of 43) to 2.5.
+void plan_dense(hpd_layout* L, int32_t n_cus) {
+  const int32_t Hkv = L->cfg.n_kv_heads, Gr = L->cfg.n_q_heads / Hkv;
+  if (L->cfg.dtype != HPD_BF16 || L->cfg.head_dim != 128 || Gr > 8) return;
+  const int32_t G = Gr <= 2 ? Gr : Gr <= 4 ? 4 : 8, BPB = 32 / G;  // rows per branch, branches per row block
+  const bool paper = paper_mode(L);
+  L->dense_steps.assign(L->T, 0);
+  auto ceil_div = [](int32_t a, int32_t b) { return (a + b - 1) / b; };
+  for (int32_t t = 0; t < L->T; ++t) {
+    const int32_t u0 = paper ? L->punit_ptr[t] : L->unit_ptr[t], n_units = (paper ? L->punit_ptr[t + 1] : L->unit_ptr[t + 1]) - u0;
+    const int32_t most = ceil_div((paper ? L->pmax_rows[t] : L->max_rows[t]) * G, 32);  // row blocks
+    // (up to three row blocks are one workgroup of the other kernel's narrow shape)
+    if (n_units == 0 || most < 4) continue;
+    const int32_t chunks = (t >> 3) + 1, newest = (t & 7) + 1, fmt = newest <= 1 ? 0 : newest <= 2 ? 1 : newest <= 4 ? 2 : 3;
+    const int32_t rg_wide = ceil_div(most, 6), rg_dense = ceil_div(most, 4);
+    const bool narrow = (int64_t)n_units * Hkv * rg_wide >= 2 * (int64_t)n_cus && most <= 6;
+    const int32_t rg_old = narrow ? ceil_div(most, 3) : rg_wide;
+    double sum_old = 0, sum = 0, longest_old = 0, longest = 0;  // us
+    int64_t seen = 0, rows = 0, blocks = 0, places = 0;  // branches whose tails are seen, live ones; row blocks, waves for them
+    int64_t wgs = 0;
+    for (int32_t u = u0; u < u0 + n_units; ++u) {
+      const int32_t* d = paper ? L->punit_desc.data() + (size_t)u * 16 : L->unit_desc.data() + (size_t)u * 8;
+      const int32_t nb = d[5], nblk = ceil_div(nb * G, 32), keys = paper ? d[8] : 0;  // keys: branches whose tails are seen
+      const int32_t prefix = ceil_div(d[1], 32) + (paper ? d[3] : ceil_div(d[3], 32));
+      seen += keys;
+      rows += nb;
+      // the kernel with loader waves
+      for (int32_t r = 0, per = ceil_div(nblk, rg_old); r < rg_old; ++r) {
+        const int32_t h = std::min(per, nblk - r * per);
+        double x = 0.7;  // a workgroup without rows
+        if (h > 0) {
+          const int32_t kg = narrow ? (h == 1 ? 3 : 1) : h == 1 ? 4 : h <= 3 ? 2 : 1;  // key groups
+          double tiles, busy;
+          if (paper) {
+            tiles = ceil_div((int32_t)std::ceil(keys * std::min(1.0, (double)(r * per + h) / nblk)), 4) * chunks;
+            busy = tiles / kg * 1.9;
+          } else {
+            const int32_t n = std::min(nb - r * per * BPB, h * BPB);
+            tiles = ceil_div(n, 4) * (chunks - 1) + ceil_div(n, 32 >> fmt);
+            busy = tiles / (h * kg);
+          }
+          static const double wide_block[7] = {0, 0.75, 0.75, 1.1, 0.8, 1.1, 1.15};
+          x = narrow ? 9 + 1.25 * prefix + 1.3 * busy + 0.25 * tiles : 11 + prefix * wide_block[h] + busy;
+          longest_old = std::max(longest_old, x);
+        }
+        sum_old += x * Hkv;
+      }
+      const int32_t n_rg = ceil_div(nblk, 4);
+      for (int32_t r = 0, per = ceil_div(nblk, n_rg); r < n_rg; ++r) {
+        const int32_t h = std::min(per, nblk - r * per);
+        if (h <= 0) continue;
+        double x = 10 + prefix * (h == 4 ? 1.05 : 1.3);
+        if (paper) {
+          const int32_t n = (int32_t)std::ceil(keys * std::min(1.0, (double)(r * per + h) / nblk));
+          x += 1.35 * (fmt < 3 ? ceil_div(n, 4) * (chunks - 1) + ceil_div(n, 32 >> fmt) : ceil_div(n, 4) * chunks);
+        } else {
+          const int32_t lg = std::max(fmt, G == 8 ? 3 : G == 4 ? 2 : G == 2 ? 1 : 0);
+          x += 1.2 * (ceil_div(std::min(BPB, nb), 4) * (chunks - 1) + ceil_div(BPB, 32 >> lg));
+        }
+        longest = std::max(longest, x);
+        sum += x * Hkv;
+        wgs += Hkv;
+        blocks += h;
+        places += 4;
+      }
+      sum += 0.5 * Hkv * (rg_dense - n_rg);
+    }
+    const int32_t slots = narrow ? 2 * n_cus : n_cus;
+    const double old_us = sum_old > longest_old * slots ? sum_old / slots + 0.35 * longest_old : longest_old;
+    const double us = wgs <= n_cus ? 0.75 * longest : wgs <= 2 * n_cus ? longest : sum / (2 * n_cus) + 0.35 * longest;
+    // (a launch of few workgroups is latency in either kernel.  What costs more than estimated: workgroups that are not
+    // full; under the literal mask launches of less than a workgroup per CU, and branches that have ended, whose tiles
+    // are masked key by key and whose rows are missing.)
+    const bool full = 5 * blocks >= 4 * places, ended = paper && 5 * seen > 6 * rows;
+    const double margin = ended ? 0.45 : paper && wgs <= n_cus ? 0.6 : full ? 0.8 : 0.65;
+    L->dense_steps[t] = wgs >= 64 && us < margin * old_us;
+  }
+}
+
 // Copies a host vector into the device int arena and returns its device address.
 struct IntArena {
   std::vector<int32_t> host;
@@ -336,12 +423,10 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
       }
     }
     L->total_units = (int64_t)L->unit_doc.size();
-    {
-      int device = 0, n_cus = L->n_cus;
-      if (!(cfg->flags & HPD_FLAG_HOST_ONLY) && hipGetDevice(&device) == hipSuccess)
-        (void)hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, device);
-      plan_f32(L, n_cus);
-    }
+    int device = 0, n_cus = L->n_cus;
+    if (!(cfg->flags & HPD_FLAG_HOST_ONLY) && hipGetDevice(&device) == hipSuccess)
+      (void)hipDeviceGetAttribute(&n_cus, hipDeviceAttributeMultiprocessorCount, device);
+    plan_f32(L, n_cus);
 
     // ---- paper-literal mask: the work unit is the prompt (its rows see every document and the
     //      tails of all earlier branches).  Document blocks of a prompt in stream order; per
@@ -389,6 +474,8 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
         L->punit_ptr[t + 1] = L->punit_ptr[t] + (int32_t)units.size();
       }
     }
+
+    plan_dense(L, n_cus);
 
     // ---- attention of the prefix tokens (first inference step, block mask): a unit per
     //      non-empty header and per document, the most expensive (tokens x keys) first

@@ -206,6 +206,94 @@ def test_stream_kernel_group_sizes_that_are_not_powers_of_two(g):
         _check_prefill(wl, 0, f"g{g}_prefill_m0", attr_len=attr if paper else None)
 
 
+@pytest.mark.parametrize("literal", [False, True])
+@pytest.mark.parametrize("g", [1, 2, 4, 5, 8])
+def test_decode_of_many_rows_per_unit(g, literal):
+    """The kernel for launches with many rows per unit: row blocks that do not fill a workgroup, documents around a block
+    of 32 keys and none, no header, branches that end (live ones that are no run of ids; under the literal mask tails of
+    several lengths in a tile), tails of 1 .. 11 positions, fp32 and bf16 outputs, paged tails.  Against the oracle, the
+    step call against the two-call sequence and against the other kernel (kernel mode 3: bits that differ tell that the
+    default was not that kernel)."""
+    from paper_2604_26209_amd import binding as B
+    pad = 1 << (g - 1).bit_length()
+    hkv, steps = 2, 11
+    if literal:
+        n = min(256, 9 * 32 // pad + 3) // 3
+        per, doc, nbr = [3] * 24, [1, 40, 32] * 24, [n, n + 1, n - 1] * 24
+        header = [0, 33, 64, 7] * 6
+    else:
+        n = 8 * 32 // pad
+        per, doc, nbr = [4] * 8, [1, 31, 64, 33] * 8, [n, n + 1, n - 1, 4 * 32 // pad] * 8
+        header = [0, 33, 64, 7, 0, 1, 32, 95]
+    blen = np.full(sum(nbr), steps)
+    blen[5::9] = 3
+    blen[7::11] = 8
+    attr = (1 + np.arange(sum(nbr)) % 4).astype(np.int32)
+    wl = W.make_workload("rows", "bf16", g * hkv, hkv, 128, 500000.0, steps, header, per, doc, nbr, blen)
+    kw = dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=attr, mask_mode=B.HPD_MASK_PAPER) if literal else {}
+    okw = dict(pos_mode="paper_gap", attr_len=attr, mask_mode="paper") if literal else {}
+    _say(f"many rows per unit: G={g} literal={literal}, {wl.n_branches} branches")
+    a = H.run_hip(wl, fused=True, **kw)
+    H.check_all(wl, a, prompts=[0, 1, 3], label=f"rows_g{g}_{literal}", **okw)
+    b = H.run_hip(wl, inputs=a["inputs"], **kw)
+    c = H.run_hip(wl, inputs=a["inputs"], fused=True, kernel_mode=3, **kw)
+    d = H.run_hip(wl, inputs=a["inputs"], fused=True, out_f32=False, **kw)
+    other = [not torch.equal(x, z) for x, z in zip(a["out"], c["out"])]
+    for x, y, z, w in zip(a["out"], b["out"], c["out"], d["out"]):
+        assert torch.equal(x, y)
+        assert torch.equal(x.to(torch.bfloat16), w)
+        # two roundings of queries and weights to 11 bits: as the bound against the oracle, of outputs of size 1
+        assert float((x - z).abs().max()) < H.BF16_TOL * float(x.square().mean().sqrt())
+    _say(f"  steps that ran it: {[t for t, o in enumerate(other) if o]}")
+    assert any(other)
+    # the same bits through a page table
+    lay = B.layout_from_workload(wl, out_dtype=B.HPD_OUT_F32, **kw)
+    table = torch.from_numpy(np.random.default_rng(g).permutation(2 * wl.n_branches).astype(np.int32).reshape(-1, 2)).cuda()
+    B.hpd_set_tail_pages(lay, 8, 2 * wl.n_branches, table)
+    inputs = a["inputs"]
+    pools = B.alloc_pools(lay)
+    B.hpd_prefix_fill(lay, inputs.k_raw, inputs.v_raw, pools[0], pools[1])
+    for t in range(steps):
+        out = torch.zeros_like(a["out"][t])
+        B.hpd_decode_step(lay, t, inputs.q[t], inputs.k_new[t], inputs.v_new[t], *pools, out)
+        assert torch.equal(out, a["out"][t]), f"step {t}: paged and contiguous outputs differ"
+
+
+@pytest.mark.parametrize("case", ["peaked_x4", "argmax_x16", "flat_div16", "common_offset", "negative_offset", "rising"])
+def test_score_ranges_of_decode_with_many_rows_per_unit(case):
+    """The inputs of test_score_ranges_of_the_online_softmax, and scores all near -16, for the kernel for many rows per
+    unit: against the oracle, and against the other kernel, whose bits differ.  That one rounds the same queries to the same
+    halves, so what is left are the weights' 11 bits: 2^-11 of a value, which is below 6.  Scores 16 times as wide are
+    compared with the other kernel only: there a query's 11 bits move a score of 60 by up to 60 * 2^-12, and of two keys that
+    tie each one's weight by a quarter of that, 2e-2 between values 5 apart, in some of these 10 000 rows (0.0213 x RMS in
+    either kernel, 2e-5 in the generic one, which keeps the query in fp32)."""
+    from paper_2604_26209_amd import binding as B
+    wl = W.make_workload("rows_ranges", "bf16", 16, 2, 128, 500000.0, 4, [40] * 8, [4] * 8, [50, 200, 97, 33] * 8, [40] * 32,
+                         [4] * 1280)
+    lay = B.layout_from_workload(wl)
+    inp = H.Inputs(wl, lay.n_live(), "cuda", lay.counts()[B.HPD_C_N_PREFIX_TOKENS])
+    bf = lambda x: x.float().to(torch.bfloat16)
+    if case in ("peaked_x4", "argmax_x16", "flat_div16"):
+        inp.q = [bf(x.float() * dict(peaked_x4=4.0, argmax_x16=16.0, flat_div16=1.0 / 16)[case]) for x in inp.q]
+    elif case == "rising":
+        n = inp.k_raw.shape[0]
+        inp.k_raw = bf(inp.k_raw.float() + torch.arange(n, device="cuda")[:, None, None] % 500 * (4.0 / 500))
+        inp.k_new = [bf(x.float() + 4.0 + 0.3 * t) for t, x in enumerate(inp.k_new)]
+        inp.q = [bf(x.float() * 0.5 + 1.0) for x in inp.q]
+    else:
+        sign = 1.0 if case == "common_offset" else -1.0
+        inp.q = [bf(x.float() + 1.0) for x in inp.q]
+        inp.k_raw = bf(inp.k_raw.float() + sign)
+        inp.k_new = [bf(x.float() + sign) for x in inp.k_new]
+    _say(f"score ranges, many rows: {case}")
+    a = H.run_hip(wl, inputs=inp, fused=True)
+    if case != "argmax_x16":
+        H.check_all(wl, a, prompts=[0, 5], label=f"rows_{case}")
+    c = H.run_hip(wl, inputs=inp, fused=True, kernel_mode=3)
+    assert any(not torch.equal(x, z) for x, z in zip(a["out"], c["out"]))
+    assert all(float((x - z).abs().max()) < 6 * 2.0 ** -11 for x, z in zip(a["out"], c["out"]))
+
+
 @pytest.mark.parametrize("seed,kw", [(120, dict(hq=8, hkv=2, p=3, j_range=(1, 4), n_range=(1, 14), l_range=(1, 200))),
                                      (121, dict(hq=8, hkv=8, p=2, j_range=(2, 3), n_range=(3, 40), l_range=(1, 90))),
                                      (122, dict(hq=16, hkv=2, p=2, j_range=(1, 2), n_range=(1, 30), l_range=(30, 300)))])
