@@ -87,15 +87,6 @@ __device__ __forceinline__ float sum_half_pair(uint32_t w, float c) {
   return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, w), __builtin_bit_cast(f16x2, 0x3c003c00u), c, false);
 }
 
-// ds_read_b64_tr_b16: within each 16 lanes, lane i receives element i % 4 of the 8 bytes that the
-// lanes 4*j + i/4 (j = 0..3) address, in the order of j: a 4 x 16 transpose of 2-byte elements.
-typedef short short4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint2 lds_read_tr16(const char* p) {
-  const short4v v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) short4v*)(uintptr_t)p);
-  return __builtin_bit_cast(uint2, v);
-}
-
 // A 32-bit word at a wave-uniform address through the scalar data cache (read only).  The
 // loaders use it for table lookups: a vector load would have to wait for every DMA instruction
 // in front of it, because vector memory operations of a wave complete in order.

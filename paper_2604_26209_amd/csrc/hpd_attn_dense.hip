@@ -333,7 +333,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     for (int f = 0; f < 8; ++f) {
       const int chunk = ((f >> 1) * 4 + tx) ^ (2 * tj);
       const char* p = vlane + (f & 1) * 4096 + chunk * 16;
-      const uint2 k03 = lds_read_tr16(p), k47 = lds_read_tr16(p + 4 * 256);
+      const uint2 k03 = hpd::lds_read_tr16(p), k47 = hpd::lds_read_tr16(p + 4 * 256);
       vf[f] = make_uint4(k03.x, k03.y, k47.x, k47.y);
     }
   };

@@ -99,4 +99,13 @@ __device__ __forceinline__ void load8_cache(const bf16_t* p, float out[8]) {
   out[6] = cache_bits_to_float(a.w & 0xffffu); out[7] = cache_bits_to_float(a.w >> 16);
 }
 
+// ds_read_b64_tr_b16: within each 16 lanes, lane i receives element i % 4 of the 8 bytes that the
+// lanes 4*j + i/4 (j = 0..3) address, in the order of j: a 4 x 16 transpose of 2-byte elements.
+typedef short short4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 lds_read_tr16(const void* p) {
+  const short4v v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) short4v*)(uintptr_t)p);
+  return __builtin_bit_cast(uint2, v);
+}
+
 }  // namespace hpd

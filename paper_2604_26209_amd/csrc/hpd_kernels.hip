@@ -56,20 +56,27 @@ __global__ void prefix_fill_kernel(hpd_dev_tables tb, int32_t n_seg, int32_t P, 
   v_prefix[(vblk + i + half) * 8 + (slot & 7)] = hpd::cache_from_float<T>(hpd::to_float(v_raw[src + i + half]));
 }
 
-// The same for bf16 with 128 channels, the shape the streaming attention kernel serves: one
-// 256-thread workgroup per (32-slot block of the pools, kv head), a wave per 8 slots.  Rows move
-// as 16-byte pieces (8 lanes per K row); the 8-key interleave of the V pool is a transpose of
-// 8 rows x 128 channels through LDS, written back as one contiguous 2 KB run per wave.  Slots
-// behind the segment's end get V = 0 (what prefix_pad_kernel does for the general kernel).
-// fill_blk[b] = (segment that owns block b | -1, raw index of the block's first token).
+// The same for bf16 with 128 channels, the shape the streaming attention kernel serves: a 256-thread workgroup per
+// (32-slot block of the pools, HPW kv heads), a wave per 8 slots.  Bound by memory; what kept it from its rate were the
+// instructions between the loads and the stores.  Rows move as 16-byte pieces (8 lanes per K row); the 8-key interleave of
+// the V pool is a transpose of 8 rows x 128 channels through LDS, 4 transposing reads a lane (32 two-byte reads before),
+// written back as one contiguous 2 KB run per wave; a key pair is rounded by one conversion.  Slots behind the segment's
+// end get V = 0 (what prefix_pad_kernel does for the general kernel).  fill_blk[b] = (segment that owns block b | -1, raw
+// index of the block's first token).  us, 8 kv heads, before -> now: 4608 tokens 10.4 -> 8.7, 18432 40.4 -> 34.2, 67584 124.6 ->
+// 107.5, 520192 922 -> 798 (4.6 -> 5.3 TB/s read and written, a plain copy 5.6).
+// FILL_FOUR: from so many (block, kv head) on a workgroup takes four heads, with one set of angles and 16 loads in flight a
+// thread.  One head / four, the rounding as before: 46848 tokens x 16 heads 153 / 150, 67584 x 8 110 / 109, 520192 x 8 837 /
+// 799; 18432 x 8 34.0 / 35.2, 4608 x 8 9.3 / 11.6.
+constexpr int64_t FILL_FOUR = 16384;
+template <int HPW>
 __global__ void __launch_bounds__(256)
 prefix_fill_bf16_128_kernel(hpd_dev_tables tb, int32_t n_seg, int32_t P, int32_t Hkv, int64_t NP,
                             const int32_t* __restrict__ fill_blk, const uint16_t* __restrict__ k_raw,
                             const uint16_t* __restrict__ v_raw, uint16_t* __restrict__ k_prefix,
                             uint16_t* __restrict__ v_prefix) {
-  constexpr int D = 128;
-  __shared__ uint16_t vt[4][8][D];
-  const int32_t blk = blockIdx.x / Hkv, h = blockIdx.x % Hkv;
+  constexpr int D = 128, PITCH = D + 64;  // (the 4 rows of a transposing read lie in two halves of the banks)
+  __shared__ __align__(16) uint16_t vt[4][8][PITCH];
+  const int32_t hg = Hkv / HPW, blk = blockIdx.x / hg, h0 = blockIdx.x % hg * HPW;
   const int32_t sid = fill_blk[2 * blk];
   if (sid < 0) return;  // uniform over the workgroup
   const int32_t raw0 = fill_blk[2 * blk + 1];
@@ -78,51 +85,68 @@ prefix_fill_bf16_128_kernel(hpd_dev_tables tb, int32_t n_seg, int32_t P, int32_t
   const int32_t idx = idx0 + wave * 8 + r;
   const bool valid = idx < len;
   const int64_t slot = (int64_t)blk * 32 + wave * 8 + r;
-  uint4 vlo = make_uint4(0, 0, 0, 0), vhi = vlo;
+  uint4 klo[HPW], khi[HPW], vlo[HPW], vhi[HPW];
+#pragma unroll
+  for (int i = 0; i < HPW; ++i) {
+    vlo[i] = vhi[i] = make_uint4(0, 0, 0, 0);
+    if (valid) {
+      const int64_t src = ((int64_t)(raw0 + wave * 8 + r) * Hkv + h0 + i) * D + cc * 8;
+      klo[i] = *reinterpret_cast<const uint4*>(k_raw + src);
+      khi[i] = *reinterpret_cast<const uint4*>(k_raw + src + 64);
+      vlo[i] = *reinterpret_cast<const uint4*>(v_raw + src);
+      vhi[i] = *reinterpret_cast<const uint4*>(v_raw + src + 64);
+    }
+  }
+  auto bf16_pair = [](float x, float y) -> uint32_t {  // rounded to nearest even: v_cvt_pk_bf16_f32
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{x, y}), bf16x2));
+  };
   if (valid) {
-    const int64_t src = ((int64_t)(raw0 + wave * 8 + r) * Hkv + h) * D;
-    const uint4 klo = *reinterpret_cast<const uint4*>(k_raw + src + cc * 8);
-    const uint4 khi = *reinterpret_cast<const uint4*>(k_raw + src + 64 + cc * 8);
-    vlo = *reinterpret_cast<const uint4*>(v_raw + src + cc * 8);
-    vhi = *reinterpret_cast<const uint4*>(v_raw + src + 64 + cc * 8);
     const bool skeleton = tb.skel_pos != nullptr && sid >= n_seg - P;
     const int32_t pos = skeleton ? tb.skel_pos[tb.skel_off[sid - (n_seg - P)] + idx] : tb.seg_pos0[sid] + idx;
     const float4* cs = reinterpret_cast<const float4*>(tb.rope + (int64_t)pos * (D / 2) + cc * 8);
-    const uint32_t lo[4] = {klo.x, klo.y, klo.z, klo.w}, hi[4] = {khi.x, khi.y, khi.z, khi.w};
-    uint32_t olo[4], ohi[4];
+    const float4 c4[4] = {cs[0], cs[1], cs[2], cs[3]};  // (cos, sin) of pairs 2 e, 2 e + 1
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      const float4 c4 = cs[e2];  // (cos, sin) of pairs 2*e2, 2*e2 + 1
-      float a0, b0, a1, b1;
-      hpd::rope_pair(hpd::bf16_bits_to_float(lo[e2] & 0xffffu), hpd::bf16_bits_to_float(hi[e2] & 0xffffu),
-                     c4.x, c4.y, a0, b0);
-      hpd::rope_pair(hpd::bf16_bits_to_float(lo[e2] >> 16), hpd::bf16_bits_to_float(hi[e2] >> 16),
-                     c4.z, c4.w, a1, b1);
-      olo[e2] = hpd::cache_bits_pair(hpd::bf16_bits_to_float(hpd::float_to_bf16_bits(a0)),
-                                   hpd::bf16_bits_to_float(hpd::float_to_bf16_bits(a1)));
-      ohi[e2] = hpd::cache_bits_pair(hpd::bf16_bits_to_float(hpd::float_to_bf16_bits(b0)),
-                                   hpd::bf16_bits_to_float(hpd::float_to_bf16_bits(b1)));
+    for (int i = 0; i < HPW; ++i) {
+      const uint32_t lo[4] = {klo[i].x, klo[i].y, klo[i].z, klo[i].w}, hi[4] = {khi[i].x, khi[i].y, khi[i].z, khi[i].w};
+      uint32_t olo[4], ohi[4];
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        float a0, b0, a1, b1;
+        hpd::rope_pair(hpd::bf16_bits_to_float(lo[e2] & 0xffffu), hpd::bf16_bits_to_float(hi[e2] & 0xffffu),
+                       c4[e2].x, c4[e2].y, a0, b0);
+        hpd::rope_pair(hpd::bf16_bits_to_float(lo[e2] >> 16), hpd::bf16_bits_to_float(hi[e2] >> 16),
+                       c4[e2].z, c4[e2].w, a1, b1);
+        olo[e2] = hpd::cache_bits_from_bf16_pair(bf16_pair(a0, a1));
+        ohi[e2] = hpd::cache_bits_from_bf16_pair(bf16_pair(b0, b1));
+      }
+      uint16_t* kd = k_prefix + ((int64_t)(h0 + i) * NP + slot) * D;
+      *reinterpret_cast<uint4*>(kd + cc * 8) = make_uint4(olo[0], olo[1], olo[2], olo[3]);
+      *reinterpret_cast<uint4*>(kd + 64 + cc * 8) = make_uint4(ohi[0], ohi[1], ohi[2], ohi[3]);
     }
-    uint16_t* kd = k_prefix + ((int64_t)h * NP + slot) * D;
-    *reinterpret_cast<uint4*>(kd + cc * 8) = make_uint4(olo[0], olo[1], olo[2], olo[3]);
-    *reinterpret_cast<uint4*>(kd + 64 + cc * 8) = make_uint4(ohi[0], ohi[1], ohi[2], ohi[3]);
   }
-  vlo = make_uint4(hpd::cache_bits_from_bf16_pair(vlo.x), hpd::cache_bits_from_bf16_pair(vlo.y),
-                   hpd::cache_bits_from_bf16_pair(vlo.z), hpd::cache_bits_from_bf16_pair(vlo.w));
-  vhi = make_uint4(hpd::cache_bits_from_bf16_pair(vhi.x), hpd::cache_bits_from_bf16_pair(vhi.y),
-                   hpd::cache_bits_from_bf16_pair(vhi.z), hpd::cache_bits_from_bf16_pair(vhi.w));
-  *reinterpret_cast<uint4*>(&vt[wave][r][cc * 8]) = vlo;
-  *reinterpret_cast<uint4*>(&vt[wave][r][64 + cc * 8]) = vhi;
-  __syncthreads();
-  uint16_t* vd = v_prefix + (((int64_t)h * (NP / 8) + (int64_t)blk * 4 + wave) * D) * 8;
+  auto cache4 = [](uint4 w) {
+    return make_uint4(hpd::cache_bits_from_bf16_pair(w.x), hpd::cache_bits_from_bf16_pair(w.y),
+                      hpd::cache_bits_from_bf16_pair(w.z), hpd::cache_bits_from_bf16_pair(w.w));
+  };
+  // values: the wave's 8 tokens, turned through its own part of LDS.  In a transposing read lane 4 j + q of 16 addresses
+  // channels 4 q .. +3 of token j, and lane i receives channel i of 4 tokens.
+  const uint16_t* const rd = &vt[wave][(lane >> 2) & 3][(lane >> 4) * 16 + (lane & 3) * 4];
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    const int c = half * 64 + lane;
-    uint32_t w[4];
+  for (int i = 0; i < HPW; ++i) {
+    *reinterpret_cast<uint4*>(&vt[wave][r][cc * 8]) = cache4(vlo[i]);
+    *reinterpret_cast<uint4*>(&vt[wave][r][64 + cc * 8]) = cache4(vhi[i]);
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+    __builtin_amdgcn_wave_barrier();
+    uint16_t* vd = v_prefix + (((int64_t)(h0 + i) * (NP / 8) + (int64_t)blk * 4 + wave) * D) * 8;
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2)
-      w[e2] = (uint32_t)vt[wave][2 * e2][c] | ((uint32_t)vt[wave][2 * e2 + 1][c] << 16);
-    *reinterpret_cast<uint4*>(vd + (int64_t)c * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int half = 0; half < 2; ++half) {
+      const uint2 t03 = hpd::lds_read_tr16(rd + half * 64), t47 = hpd::lds_read_tr16(rd + half * 64 + 4 * PITCH);
+      *reinterpret_cast<uint4*>(vd + (int64_t)(half * 64 + lane) * 8) = make_uint4(t03.x, t03.y, t47.x, t47.y);
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -683,7 +707,8 @@ hipError_t hpd_launch_prefix_fill(const hpd_layout* L, const void* k_raw, const 
   if (L->cfg.dtype == HPD_BF16 && L->cfg.head_dim == 128 && L->kernel_mode != 1 && L->dev.fill_blk) {
     const int64_t items = (L->NP / HPD_KEY_BLOCK) * L->cfg.n_kv_heads;
     if (items > 0x7fffffff) return hipErrorInvalidValue;
-    prefix_fill_bf16_128_kernel<<<dim3((unsigned)items), 256, 0, s>>>(
+    const bool four = L->cfg.n_kv_heads % 4 == 0 && items >= FILL_FOUR;
+    (four ? prefix_fill_bf16_128_kernel<4> : prefix_fill_bf16_128_kernel<1>)<<<dim3((unsigned)(four ? items / 4 : items)), 256, 0, s>>>(
         L->dev, L->n_seg, L->P, L->cfg.n_kv_heads, L->NP, L->dev.fill_blk, (const uint16_t*)k_raw,
         (const uint16_t*)v_raw, (uint16_t*)k_prefix, (uint16_t*)v_prefix);
     return hipGetLastError();

@@ -959,6 +959,27 @@ def test_prefix_fill_fast_kernel_equals_general_kernel(literal):
     assert bool((pools[0][0] != 3.0).any())
 
 
+@pytest.mark.parametrize("hkv,docs", [(4, 300), (12, 100), (6, 200), (16, 40)])
+def test_prefix_fill_of_large_batches_equals_general_kernel(hkv, docs):
+    """Launches of 16384 (block, kv head) and more, four heads a workgroup where the heads divide by four (6 do not, and 16
+    x 40 documents stay below): the bits of the element-wise kernel, infinities included, in ragged segments."""
+    from paper_2604_26209_amd import binding as B
+    doc = [1 + 977 * i % 1500 for i in range(docs)]
+    wl = W.make_workload("fill", "bf16", hkv, hkv, 128, 500000.0, 2, [0, 45], [docs // 2, docs - docs // 2], doc, [1] * docs, [2] * docs)
+    pools = []
+    for mode in (0, 1):
+        lay = B.layout_from_workload(wl)
+        B.hpd_set_kernel_mode(lay, mode)
+        k_raw, v_raw = (W.normal_values((wl.n_prefix_tokens, hkv, 128), i, "cuda", "bf16") for i in (1, 2))
+        k_raw[3, 1, 5], v_raw[7, 0, 70], v_raw[8, 1, 3] = float("inf"), float("-inf"), 1e-30
+        kp, vp, _, _ = B.alloc_pools(lay)
+        kp.fill_(3.0), vp.fill_(3.0)
+        B.hpd_prefix_fill(lay, k_raw, v_raw, kp, vp)
+        pools.append((kp.view(torch.int16), vp.view(torch.int16)))
+    _say(f"prefix fill, {wl.n_prefix_tokens} tokens x {hkv} heads: {pools[0][0].numel() // (32 * 128)} (block, kv head)")
+    assert torch.equal(pools[0][0], pools[1][0]) and torch.equal(pools[0][1], pools[1][1])
+
+
 def _finetune_mask_of_all_pairs(plen, al, vl):
     """The rule over codes (attribute, k) of all pairs, as in the docstring of the oracle's loop."""
     owner = np.concatenate([np.full(plen, -1)] + [np.full(a + v, n) for n, (a, v) in enumerate(zip(al, vl))])
