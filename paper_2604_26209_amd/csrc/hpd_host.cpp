@@ -205,12 +205,12 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
     const int32_t slots = narrow ? 2 * n_cus : n_cus;
     const double old_us = sum_old > longest_old * slots ? sum_old / slots + 0.35 * longest_old : longest_old;
     const double us = wgs <= n_cus ? 0.75 * longest : wgs <= 2 * n_cus ? longest : sum / (2 * n_cus) + 0.35 * longest;
-    // (a launch of few workgroups is latency in either kernel.  What costs more than estimated: workgroups that are not
-    // full; under the literal mask launches of less than a workgroup per CU, and branches that have ended, whose tiles
-    // are masked key by key and whose rows are missing.)
+    // What costs more than estimated: workgroups that are not full, launches of less than a workgroup per CU, and under the
+    // literal mask branches that have ended, whose tiles are masked key by key and whose rows are missing.  And a short
+    // launch is latency in either kernel (12.6 us became 14.4).
     const bool full = 5 * blocks >= 4 * places, ended = paper && 5 * seen > 6 * rows;
-    const double margin = ended ? 0.45 : paper && wgs <= n_cus ? 0.6 : full ? 0.8 : 0.65;
-    L->dense_steps[t] = wgs >= 64 && us < margin * old_us;
+    const double margin = ended ? 0.45 : wgs <= n_cus ? 0.6 : full ? 0.8 : 0.65;
+    L->dense_steps[t] = old_us > 22 && us < margin * old_us;
   }
 }
 
