@@ -48,7 +48,7 @@ MIN_TIMED_S = 0.3    # per_config entries other than the headline are timed at l
 # rocprofv3 counter summaries (FETCH_SIZE / WRITE_SIZE, scaled by a 1 GiB copy) of
 # `bench.py --config k`: the line "total traffic X MB per launch" is what roofline.traffic quotes
 PROFILE_OF_CONFIG = {2: "profiles/attn_stream_cfg2_llama3_8b.txt", 3: "profiles/attn_stream_cfg3_stacked.txt",
-                     4: "profiles/attn_stream_cfg4_long_70b.txt", 5: "profiles/attn_stream_cfg5_ragged.txt"}
+                     4: "profiles/attn_dense_cfg4_long_70b.txt", 5: "profiles/attn_stream_cfg5_ragged.txt"}
 
 
 def profiled_traffic(k):
@@ -425,7 +425,8 @@ def measure_decode(args, k, steps, warmup, B, W, torch, np, min_timed_s=0.0):
                 "traffic": traffic,
                 "traffic_source": (f"{traffic_src}: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of `bench.py --config {k}`, "
                                    "not measured by this run") if traffic_src else None,
-                "kernel": ("attn_stream_kernel" if stream_kernel else
+                "kernel": ("attn_stream_kernel" if stream_kernel and args.kernel_mode in (3, 4) else
+                           "attn_stream_kernel or, in steps of many rows per unit, attn_dense_kernel" if stream_kernel else
                            "attention_f32_kernel" if wl.dtype == "f32" and not paper and not args.kernel_mode else
                            "append_kernel + attention_generic_kernel (two launches per step)"),
                 "launches": len(launched), "avg_launch_us": round(dur_s / len(launched) * 1e6, 2),

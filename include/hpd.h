@@ -373,8 +373,9 @@ int hpd_finetune_mask(int32_t prompt_len, int32_t n_attr, const int32_t* attr_le
 /* Selects the attention kernel: 0 = automatic (bf16: as 2 where that is allowed; fp32 decode under
  * HPD_MASK_BLOCK with head_dim 32, 64 or 128, up to 16 query heads per kv head and pools that start on
  * 16 bytes: a kernel on the fp32 matrix instruction, or the generic one for the steps for which the layout
- * finds that faster), 1 = generic wave-reduction kernel for everything, 2 = LDS-streaming MFMA kernel, workgroup shape chosen per launch (decode: wide
- * or narrow; hpd_prefill_attention: a kernel of its own), 3 / 4 = the same with the wide / the
+ * finds that faster), 1 = generic wave-reduction kernel for everything, 2 = LDS-streaming MFMA kernels, chosen per launch (decode: the
+ * wide or narrow workgroup shape, or a kernel of its own for steps of many rows per document or prompt, which
+ * hpd_dynamic_step does not use; hpd_prefill_attention: a kernel of its own), 3 / 4 = the same with the wide / the
  * narrow workgroup shape forced for both calls (2..4 return HPD_E_UNSUPPORTED if
  * the shape does not allow the kernel: it needs bf16, head_dim 128 and a group size of 1,
  * 2, 4 or 8, and under HPD_MASK_PAPER at most 256 branches and 512 blocks of 32 keys per
