@@ -3,6 +3,7 @@ host-side layout logic (no GPU call) agrees bit-for-bit with the oracle's intege
 import ctypes
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -222,3 +223,21 @@ def test_rope_table_covers_the_step_budget_not_only_the_announced_lengths():
     lay = _host_layout(wl, B.HPD_POS_PAPER_GAP, attr_len=attr)
     base = B.hpd_layout_query(lay, B.HPD_Q_BRANCH_BASE_POS).astype(np.int64)
     assert int(lay.counts()[B.HPD_C_MAX_POS]) == int(base.max()) + T
+
+
+def test_layout_of_one_wide_unit_among_many_is_built_in_linear_time():
+    """One document with many branches among thousands with one: the plan of the decode kernels (head_dim 128) looks at the
+    row groups that exist, not at those of the widest unit for every unit.  Against the same batch with 64 channels,
+    which that plan does not look at: a build of up to three times the time, where the walk over all of them took more
+    than ten times."""
+    n, wide, best = 20000, 200000, {}
+    for d in (64, 128):
+        wl = W.make_workload("wide", "bf16", 64, 8, d, 10000.0, 8, [4] * (n + 1), [1] * (n + 1), [20] * (n + 1), [1] * n + [wide],
+                             np.full(n + wide, 8))
+        times = []
+        for _ in range(3):
+            t0 = time.perf_counter()
+            _host_layout(wl)
+            times.append(time.perf_counter() - t0)
+        best[d] = min(times)
+    assert best[128] < 3 * best[64], best
