@@ -124,12 +124,17 @@ def _ptr(x):
     return x.data_ptr()
 
 
+# (not part of torch's public interface: where a torch has one of them no longer, the public call is used)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(s):
     if s is None:
         # (once the GPU is in use: the handle alone.  Asking whether there is a GPU and making a Stream object were 3.6 of
         # the 8.8 us that the host spends on a decode step; so 0.3.)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream and _device and torch.cuda.is_initialized():
+            return _raw_stream(_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(s, int):
         return s

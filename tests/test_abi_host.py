@@ -1,12 +1,15 @@
 """CPU-only checks of the C-ABI library: it loads, exports every declared symbol, and its
 host-side layout logic (no GPU call) agrees bit-for-bit with the oracle's integers."""
 import ctypes
+import importlib.util
 import os
 import re
 import time
+import types
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import hpd_oracle as O
 from paper_2604_26209_amd import binding as B
@@ -241,3 +244,16 @@ def test_layout_of_one_wide_unit_among_many_is_built_in_linear_time():
             times.append(time.perf_counter() - t0)
         best[d] = min(times)
     assert best[128] < 3 * best[64], best
+
+
+@pytest.mark.parametrize("name", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torchs_private_functions(name, monkeypatch):
+    """The binding takes the current stream's handle from two private functions of torch; without them from the public call."""
+    monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("binding_copy", B.__file__)
+    copy = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(copy)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=26209))
+    assert copy._stream(None) == 26209
