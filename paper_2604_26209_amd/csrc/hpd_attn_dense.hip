@@ -39,6 +39,11 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
   __shared__ int32_t klen[PAPER ? MAX_KEY_BRANCHES : 1];  // tokens in memory of every key branch
   // ids of the row group's branches where they are no run: a lookup in memory waits for the loads in front of it
   __shared__ int32_t ids[PAPER ? 1 : DENSE_WAVES * BPB];
+  // paged tails: what the page table says for the branches of the tiles that a wave loads next (of its next round or own
+  // tile, by the parity of that).  They come by DMA in front of the tile before: looked up when a tile is requested,
+  // every lookup waited for all loads of the wave in flight, as its address is needed (16 branches of 125 tokens, a
+  // document of 141: 380 us, the other kernel 152).
+  __shared__ int32_t page_of[PAGED ? DENSE_WAVES : 1][2][64];
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -128,6 +133,20 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     if (PAGED) return (uint32_t)hpd_tail_row(a.tb, b, hk, a.Hkv, a.Tcap, t);
     return ((uint32_t)b * (uint32_t)a.Hkv + (uint32_t)hk) * (uint32_t)a.Tcap + (uint32_t)t;
   };
+  // paged: the page table's entry for the page of token t of branch b, one per lane, to page_of[wave][half]
+  auto request_pages = [&](int32_t half, int32_t b, int32_t t) __attribute__((always_inline)) {
+    const int32_t* const p = a.tb.tail_pages + (int64_t)b * a.tb.pages_per_branch + (t >> a.tb.page_shift);
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(
+        (__attribute__((address_space(3))) int32_t*)page_of[wave][half]));
+    uint32_t keep;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(keep) : "v"(p), "s"(dst) : "memory");
+  };
+  // ... and the row of token t (as in hpd_tail_row) of the branch that lane l asked for
+  auto paged_row = [&](int32_t half, int32_t l, int32_t t) -> uint32_t {
+    const uint32_t pg = (uint32_t)min(max(page_of[wave][half][l], 0), a.tb.n_pages - 1);
+    return ((pg * (uint32_t)a.Hkv + (uint32_t)hk) << a.tb.page_shift) + (uint32_t)(t & ((1 << a.tb.page_shift) - 1));
+  };
   // literal mask, tail tile tt: key k is position c * 8 + k % 2^lg of branch tb0 + k / 2^lg
   struct TileAt { int32_t c, tb0, lg; };
   auto tile_at = [&](int32_t tt) -> TileAt {
@@ -137,15 +156,22 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     }
     return {NC - 1, (tt - n_full) << (5 - fmt_lg), fmt_lg};
   };
-  auto issue_tile = [&](int32_t tt, uint32_t at) {
-    const TileAt x = tile_at(tt);
+  // (a branch's positions in a tile are those of one chunk of 8, or its last token: they lie in one page)
+  auto round_pages = [&](int32_t r) __attribute__((always_inline)) {  // of both tiles of round r
+    if (r >= NR || 2 * r + 1 < NB) return;
+    const TileAt x = tile_at(max(2 * r - NB, 0)), y = tile_at(min(2 * r + 1, NS - 1) - NB);
+    const int32_t c = g2 ? y.c : x.c, j = min((g2 ? y.tb0 : x.tb0) + n, kb_end - 1);
+    request_pages(r & 1, pb0 + j, max(min(c * 8, klen[j] - 1), 0));
+  };
+  auto issue_tile = [&](int32_t gb, uint32_t at) {
+    const TileAt x = tile_at(gb - NB);
     uint32_t rw[4], ch[4];
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
       const int32_t k = (wave & 1) * 16 + f * 4 + r4;
       const int32_t j = min(x.tb0 + (k >> x.lg), kb_end - 1);
       const int32_t pos = max(min(x.c * 8 + (k & ((1 << x.lg) - 1)), klen[j] - 1), 0);
-      rw[f] = tail_row(pb0 + j, pos);
+      rw[f] = PAGED ? paged_row((gb >> 1) & 1, (gb & 1) * 32 + (k >> x.lg), pos) : tail_row(pb0 + j, pos);
       ch[f] = (uint32_t)(is_v ? (c16 ^ (2 * r4)) << 4 : (c16 ^ r4 ^ (4 * f)) << 4);
     }
     issue_rows(is_v ? v_tail : k_tail, rw, ch, at + (uint32_t)wave * 4096);
@@ -156,7 +182,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
   };
   auto issue = [&](int32_t gb, int32_t slot, uint32_t at) {
     if (!PAPER || gb < NB) issue_prefix(slot, at);
-    else issue_tile(gb - NB, at);
+    else issue_tile(gb, at);
   };
   // (a block past the last one re-loads the last one, never read)
   auto issue_round = [&](int32_t r, int32_t sA, int32_t sB) {
@@ -199,6 +225,36 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     if (append_first) append();
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
+    if (PAGED) {
+      round_pages(0);
+      round_pages(1);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+  }
+
+  // ---- block mask: the tails of the wave's own branches, tile by tile, through 16 KB of the ring that are the wave's
+  const uint32_t hx = (uint32_t)(NR & 1) * HALF, hy = HALF - hx;  // the half that the last round does not use; its own
+  const uint32_t my_k = hx + (uint32_t)wave * 8192, my_v = hy + (uint32_t)wave * 8192;
+  const int32_t wb0 = wave * BPB, wnb = min(BPB, nbr_here - wb0);  // the wave's branches
+  const int32_t lg_new = max(fmt_lg, LG_G);
+  const int32_t n_quad = (wnb + 3) >> 2;
+  const int32_t n_own = PAPER ? 0 : n_quad * (NC - 1) + ((wnb + (32 >> lg_new) - 1) >> (5 - lg_new));
+  auto own_tile = [&](int32_t t) -> TileAt {
+    const int32_t nf = n_quad * (NC - 1);
+    if (t < nf) {
+      const int32_t c = n_quad == 1 ? t : t / n_quad;
+      return {c, wb0 + (t - c * n_quad) * 4, 3};
+    }
+    return {NC - 1, wb0 + ((t - nf) << (5 - lg_new)), lg_new};
+  };
+  auto own_pages = [&](int32_t t) __attribute__((always_inline)) {
+    const TileAt x = own_tile(t);
+    const int32_t j = min(x.tb0 + n, nbr_here - 1);
+    request_pages(t & 1, t < 2 ? unit_branch(br0 + j) : ub0 >= 0 ? ub0 + br0 + j : ids[j], x.c * 8);
+  };
+  if (PAGED && !PAPER && active) {
+    own_pages(0);
+    if (n_own > 1) own_pages(1);
   }
 
   // ---- the query rows of the wave, straight into operand layout, and their position
@@ -373,6 +429,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
       nA = slot_clamped(2 * r + 4);
       nB = slot_clamped(2 * r + 5);
     }
+    if (PAPER && PAGED) round_pages(r + 2);
   };
 
   // literal mask: the branch of this row and of the row block's last one, counted from the prompt's first, and the
@@ -386,21 +443,6 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     names_max = __builtin_amdgcn_readfirstlane(a.tb.skel_cum[pb0 + kb_row_max]);
   }
   const int32_t r_plain = (PAPER ? NBh + n_doc_blk : NB) >> 1;  // rounds of blocks that all rows see alike
-  // ---- block mask: the tails of the wave's own branches, tile by tile, through 16 KB of the ring that are the wave's
-  const uint32_t hx = (uint32_t)(NR & 1) * HALF, hy = HALF - hx;  // the half that the last round does not use; its own
-  const uint32_t my_k = hx + (uint32_t)wave * 8192, my_v = hy + (uint32_t)wave * 8192;
-  const int32_t wb0 = wave * BPB, wnb = min(BPB, nbr_here - wb0);  // the wave's branches
-  const int32_t lg_new = max(fmt_lg, LG_G);
-  const int32_t n_quad = (wnb + 3) >> 2;
-  const int32_t n_own = PAPER ? 0 : n_quad * (NC - 1) + ((wnb + (32 >> lg_new) - 1) >> (5 - lg_new));
-  auto own_tile = [&](int32_t t) -> TileAt {
-    const int32_t nf = n_quad * (NC - 1);
-    if (t < nf) {
-      const int32_t c = n_quad == 1 ? t : t / n_quad;
-      return {c, wb0 + (t - c * n_quad) * 4, 3};
-    }
-    return {NC - 1, wb0 + ((t - nf) << (5 - lg_new)), lg_new};
-  };
   // K or V half of own tile t: row k = 4 f + lane / 16 of it is position c * 8 + k % 2^lg of branch tb0 + k / 2^lg; what
   // lies behind the last branch or position repeats the last one
   auto issue_own = [&](const uint16_t* pool, bool v, uint32_t at, int32_t t) __attribute__((always_inline)) {
@@ -413,8 +455,8 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
         const int32_t k = (4 * h + f) * 4 + r4;
-        const int32_t j = min(x.tb0 + (k >> x.lg), nbr_here - 1);
-        rw[f] = tail_row(ub0 >= 0 ? ub0 + br0 + j : ids[j], min(x.c * 8 + (k & ((1 << x.lg) - 1)), a.step));
+        const int32_t j = min(x.tb0 + (k >> x.lg), nbr_here - 1), pos = min(x.c * 8 + (k & ((1 << x.lg) - 1)), a.step);
+        rw[f] = PAGED ? paged_row(t & 1, k >> x.lg, pos) : tail_row(ub0 >= 0 ? ub0 + br0 + j : ids[j], pos);
         ch[f] = (uint32_t)(v ? (c16 ^ (2 * r4)) << 4 : (c16 ^ r4 ^ (4 * f)) << 4);
       }
       issue_rows(pool, rw, ch, at + h * 4096);
@@ -499,6 +541,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
       const bool more = t + 1 < n_own;
       __builtin_amdgcn_s_waitcnt(0xc07f);
       if (more) {
+        if (PAGED && t + 2 < n_own) own_pages(t + 2);  // (in front of the keys: they have landed when those have)
         issue_own(k_tail, false, my_k, t + 1);
         asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
       } else {

@@ -259,6 +259,44 @@ def test_decode_of_many_rows_per_unit(g, literal):
         assert torch.equal(out, a["out"][t]), f"step {t}: paged and contiguous outputs differ"
 
 
+def _us_in_turn(calls):
+    """us per call of each of the calls, timed in turn: the least of five times ten."""
+    us = [1e9] * len(calls)
+    for _ in range(5):
+        for i, call in enumerate(calls):
+            call()
+            start, end = torch.cuda.Event(True), torch.cuda.Event(True)
+            start.record()
+            for _ in range(10):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            us[i] = min(us[i], start.elapsed_time(end) * 100)
+    return us
+
+
+@pytest.mark.parametrize("literal", [False, True])
+def test_decode_of_many_rows_per_unit_takes_no_longer_through_a_page_table(literal):
+    """Steps with a long tail that run the kernel for many rows per unit: the page table's entries are there when a tile is
+    requested.  Looked up at that time they made these steps take 1.35 and 1.55 times as long; 1.2 is well above what two
+    timings of the same call differ by."""
+    from paper_2604_26209_amd import binding as B
+    hq, hkv, steps, t, docs, per, doc, n = (32, 4, 32, 17, 54, 6, 45, 37) if literal else (64, 8, 48, 44, 64, 1, 141, 16)
+    wl = W.make_workload("rows_pages", "bf16", hq, hkv, 128, 500000.0, steps, [0] * (docs // per), [per] * (docs // per), [doc] * docs,
+                         [n] * docs, [steps] * (n * docs))
+    kw = dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=np.ones(n * docs, np.int32), mask_mode=B.HPD_MASK_PAPER) if literal else {}
+    lay = [B.layout_from_workload(wl, **kw) for _ in range(2)]
+    pages = steps // 8 * wl.n_branches
+    table = torch.randperm(pages, device="cuda").to(torch.int32).view(wl.n_branches, -1).contiguous()
+    B.hpd_set_tail_pages(lay[1], 8, pages, table)
+    pools = [x.normal_() for x in B.alloc_pools(lay[0])]
+    q, k, v = (torch.randn(wl.n_branches, h, 128, device="cuda").bfloat16() for h in (hq, hkv, hkv))
+    out = torch.zeros_like(q)
+    us = _us_in_turn([lambda x=x: B.hpd_decode_step(x, t, q, k, v, *pools, out) for x in lay])
+    _say(f"many rows per unit, literal={literal}: {us[0]:.1f} us, through a page table {us[1]:.1f} us")
+    assert us[1] < 1.2 * us[0]
+
+
 @pytest.mark.parametrize("case", ["peaked_x4", "argmax_x16", "flat_div16", "common_offset", "negative_offset", "rising"])
 def test_score_ranges_of_decode_with_many_rows_per_unit(case):
     """The inputs of test_score_ranges_of_the_online_softmax, and scores all near -16, for the kernel for many rows per
