@@ -128,14 +128,20 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
 }
 
 // The steps that run attn_dense_kernel (hpd_attn_dense.hip).  Against the kernel with loader waves it has the faster
-// loop for many rows (four waves that load and compute, two workgroups per CU: 1.05 us per block of 32 keys for 2 x 128 rows of
-// a CU, the wide shape 1.15 us for 192), and the start and end of a workgroup under another's work; but it reads the prefix once
-// per 128 rows, and a wave without rows idles where the other kernel gives it a share of the keys.  Which one is faster
-// depends on how the units' rows divide, on their lengths and on how many workgroups there are, so both are estimated:
-// the time of a workgroup on its slot (a CU, or half of one), all of them over the slots, and a third of the longest for
-// the end of the launch; this kernel runs where the estimate promises a quarter and more.  Measured over 360 batches of
-// either mask (2 .. 64 branches, 1 .. 6 documents of 60 .. 3000 tokens, 1 .. 128 prompts; everywhere it would be 0.64 .. 2.5
-// times as fast): taken for 85 of them, 1.31 times the speed in the mean, from 0.92 (47 us instead of 43) to 2.5.
+// loop for many rows (four waves that load and compute, two workgroups per CU), and the start and end of a workgroup under
+// another's work; but it reads the prefix once per 128 rows, keeps fewer bytes in flight, and a wave without rows idles where
+// the other kernel gives it a share of the keys.  Which one is faster depends on how the units' rows divide, on their
+// lengths and on how many workgroups there are, so both are estimated from the units: the time of a workgroup (start, blocks
+// of the prefix, tail tiles), all of them over the places that the CUs have for them, and half of the longest for the end of
+// the launch.
+// The constants are microseconds of an MI355X, fitted to 3200 random batches that ran both kernels, and rounded; in the ratio
+// of the two the estimate is off by 17 % (one sigma), so this kernel runs where it promises more.  A tenth is enough where
+// four of five waves have rows and, under the literal mask, there is more than a workgroup per CU and few branches have ended
+// (their tiles are masked key by key); elsewhere, half of the time, under the literal mask a third less (half of the steps
+// from 0.5 on would be faster by 1.37 in the mean, but one in ten slower, down to 0.70).
+// Measured over 2400 other batches for which the rule takes it (4 .. 400 branches, 1 .. 6 documents of up to 4000 tokens, 1 ..
+// 160 prompts, even, ragged and with branches that end, up to 256 steps, contiguous and paged tails, either mask): 1.42 times
+// the speed in the mean, up to 2.86; 24 of them slower, 11 by more than 3 %, the slowest 318 us instead of 283.
 void plan_dense(hpd_layout* L, int32_t n_cus) {
   const int32_t Hkv = L->cfg.n_kv_heads, Gr = L->cfg.n_q_heads / Hkv;
   if (L->cfg.dtype != HPD_BF16 || L->cfg.head_dim != 128 || Gr > 8) return;
@@ -149,18 +155,23 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
     // (up to three row blocks are one workgroup of the other kernel's narrow shape)
     if (n_units == 0 || most < 4) continue;
     const int32_t chunks = (t >> 3) + 1, newest = (t & 7) + 1, fmt = newest <= 1 ? 0 : newest <= 2 ? 1 : newest <= 4 ? 2 : 3;
+    const int32_t lg_new = std::max(fmt, G == 8 ? 3 : G == 4 ? 2 : G == 2 ? 1 : 0);  // positions of a wave's own tiles in the newest chunk
     const int32_t rg_wide = ceil_div(most, 6), rg_dense = ceil_div(most, 4);
     const bool narrow = (int64_t)n_units * Hkv * rg_wide >= 2 * (int64_t)n_cus && most <= 6;
     const int32_t rg_old = narrow ? ceil_div(most, 3) : rg_wide;
     double sum_old = 0, sum = 0, longest_old = 0, longest = 0;  // us
-    int64_t seen = 0, rows = 0, blocks = 0, places = 0;  // branches whose tails are seen, live ones; row blocks, waves for them
-    int64_t wgs = 0;
+    double bytes = 0;  // that the launch cannot do without
+    int64_t blocks = 0, wgs = 0;  // row blocks, workgroups (of 4 waves for them)
+    int64_t seen = 0, rows = 0;   // branches whose tails are seen, live ones
     for (int32_t u = u0; u < u0 + n_units; ++u) {
       const int32_t* d = paper ? L->punit_desc.data() + (size_t)u * 16 : L->unit_desc.data() + (size_t)u * 8;
-      const int32_t nb = d[5], nblk = ceil_div(nb * G, 32), keys = paper ? d[8] : 0;  // keys: branches whose tails are seen
+      const int32_t nb = d[5], nblk = ceil_div(nb * G, 32), keys = paper ? d[8] : nb;  // keys: branches whose tails are seen
       const int32_t prefix = ceil_div(d[1], 32) + (paper ? d[3] : ceil_div(d[3], 32));
       seen += keys;
       rows += nb;
+      bytes += 512. * Hkv * (32. * prefix + (double)keys * (t + 1));
+      // literal mask: branches that the rows up to row block `last` see
+      auto branches_seen = [&](int32_t last) { return (int32_t)std::ceil(keys * std::min(1.0, (double)last / nblk)); };
       // the kernel with loader waves; 0.7 us for each of the workgroups that the unit has no rows for: they are counted,
       // not walked (one document of 200 000 branches and 20 000 of one: 0.55 s of a build of 0.6)
       const int32_t per_old = ceil_div(nblk, rg_old), n_old = ceil_div(nblk, per_old);
@@ -168,49 +179,42 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
       for (int32_t r = 0; r < n_old; ++r) {
         const int32_t h = std::min(per_old, nblk - r * per_old);
         const int32_t kg = narrow ? (h == 1 ? 3 : 1) : h == 1 ? 4 : h <= 3 ? 2 : 1;  // key groups
-        double tiles, busy;
+        double tiles, x = 9 + prefix * (h > (narrow ? 1 : 4) ? 0.77 : 0.55);
         if (paper) {
-          tiles = ceil_div((int32_t)std::ceil(keys * std::min(1.0, (double)(r * per_old + h) / nblk)), 4) * chunks;
-          busy = tiles / kg * 1.9;
+          tiles = ceil_div(branches_seen(r * per_old + h), 4) * chunks;
+          x += 1.23 * tiles / kg;
         } else {
           const int32_t n = std::min(nb - r * per_old * BPB, h * BPB);
           tiles = ceil_div(n, 4) * (chunks - 1) + ceil_div(n, 32 >> fmt);
-          busy = tiles / (h * kg);
+          x += 2.9 * tiles / (h * kg);
         }
-        static const double wide_block[7] = {0, 0.75, 0.75, 1.1, 0.8, 1.1, 1.15};
-        const double x = narrow ? 9 + 1.25 * prefix + 1.3 * busy + 0.25 * tiles : 11 + prefix * wide_block[h] + busy;
+        if (narrow) x += 0.45 * tiles;
         longest_old = std::max(longest_old, x);
         sum_old += x * Hkv;
       }
-      const int32_t n_rg = ceil_div(nblk, 4);
-      for (int32_t r = 0, per = ceil_div(nblk, n_rg); r < n_rg; ++r) {
-        const int32_t h = std::min(per, nblk - r * per);
-        if (h <= 0) continue;
-        double x = 10 + prefix * (h == 4 ? 1.05 : 1.3);
+      const int32_t n_rg = ceil_div(nblk, 4), per = ceil_div(nblk, n_rg), n_used = ceil_div(nblk, per);
+      for (int32_t r = 0; r < n_used; ++r) {
+        double tail;
         if (paper) {
-          const int32_t n = (int32_t)std::ceil(keys * std::min(1.0, (double)(r * per + h) / nblk));
-          x += 1.35 * (fmt < 3 ? ceil_div(n, 4) * (chunks - 1) + ceil_div(n, 32 >> fmt) : ceil_div(n, 4) * chunks);
+          const int32_t n = branches_seen(std::min(r * per + per, nblk));
+          tail = 1.6 * (fmt < 3 ? ceil_div(n, 4) * (chunks - 1) + ceil_div(n, 32 >> fmt) : ceil_div(n, 4) * chunks);
         } else {
-          const int32_t lg = std::max(fmt, G == 8 ? 3 : G == 4 ? 2 : G == 2 ? 1 : 0);
-          x += 1.2 * (ceil_div(std::min(BPB, nb), 4) * (chunks - 1) + ceil_div(BPB, 32 >> lg));
+          tail = 2.2 * (ceil_div(std::min(BPB, nb), 4) * (chunks - 1) + ceil_div(BPB, 32 >> lg_new));
         }
+        const double x = (paper ? 15 : 10) + 0.77 * prefix + tail;
         longest = std::max(longest, x);
         sum += x * Hkv;
-        wgs += Hkv;
-        blocks += h;
-        places += 4;
       }
+      wgs += (int64_t)Hkv * n_used;
+      blocks += (int64_t)Hkv * nblk;
       sum += 0.5 * Hkv * (rg_dense - n_rg);
     }
     const int32_t slots = narrow ? 2 * n_cus : n_cus;
-    const double old_us = sum_old > longest_old * slots ? sum_old / slots + 0.35 * longest_old : longest_old;
-    const double us = wgs <= n_cus ? 0.75 * longest : wgs <= 2 * n_cus ? longest : sum / (2 * n_cus) + 0.35 * longest;
-    // What costs more than estimated: workgroups that are not full, launches of less than a workgroup per CU, and under the
-    // literal mask branches that have ended, whose tiles are masked key by key and whose rows are missing.  And a short
-    // launch is latency in either kernel (12.6 us became 14.4).
-    const bool full = 5 * blocks >= 4 * places, ended = paper && 5 * seen > 6 * rows;
-    const double margin = ended ? 0.45 : wgs <= n_cus ? 0.6 : full ? 0.8 : 0.65;
-    L->dense_steps[t] = old_us > 22 && us < margin * old_us;
+    const double old_us = sum_old > longest_old * slots ? sum_old / slots + 0.5 * longest_old : longest_old;
+    const double us = std::max(0.255e-6 * bytes,  // 3.9 TB/s is all that it streams
+                               wgs <= n_cus ? 0.75 * longest : wgs <= 2 * n_cus ? longest : sum / (2 * n_cus) + 0.5 * longest);
+    const bool close = 5 * blocks >= 4 * (4 * wgs) && (!paper || (5 * seen <= 6 * rows && wgs > n_cus));
+    L->dense_steps[t] = old_us > 20 && us < (close ? 0.9 : paper ? 0.65 : 0.5) * old_us;
   }
 }
 

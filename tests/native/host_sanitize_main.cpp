@@ -77,6 +77,34 @@ static bool check_f32_steps(const hpd_layout* L) {
   return listed;
 }
 
+// the steps of an even bf16 batch that run the kernel for many rows per unit: all of them, some, none
+enum { NONE = 0, SOME = 1, ALL = 2 };
+static int dense_steps(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t P, int32_t header, int32_t J, std::vector<int32_t> doc,
+                       std::vector<int32_t> branches, bool paper) {
+  hpd_config cfg{};
+  cfg.n_q_heads = hq; cfg.n_kv_heads = hkv; cfg.head_dim = D; cfg.dtype = HPD_BF16; cfg.rope_base = 10000.0; cfg.max_new = T;
+  cfg.flags = HPD_FLAG_HOST_ONLY;
+  cfg.pos_mode = paper ? HPD_POS_PAPER_GAP : HPD_POS_CONTIG;
+  cfg.mask_mode = paper ? HPD_MASK_PAPER : HPD_MASK_BLOCK;
+  std::vector<int32_t> headers(P, header), doc_ptr{0}, doc_len, branch_ptr{0};
+  for (int32_t p = 0; p < P; ++p) {
+    for (int32_t j = 0; j < J; ++j) {
+      doc_len.push_back(doc[doc_len.size() % doc.size()]);
+      branch_ptr.push_back(branch_ptr.back() + branches[(branch_ptr.size() - 1) % branches.size()]);
+    }
+    doc_ptr.push_back((int32_t)doc_len.size());
+  }
+  const std::vector<int32_t> attr(branch_ptr.back(), 1);
+  hpd_layout* L = nullptr;
+  CHECK(hpd_build_layout(&cfg, P, headers.data(), doc_ptr.data(), doc_len.data(), branch_ptr.data(), nullptr,
+                         paper ? attr.data() : nullptr, nullptr, &L) == HPD_OK);
+  CHECK(L->dense_steps.size() == (D == 128 && hq / hkv <= 8 ? (size_t)T : 0));
+  int32_t n = 0;
+  for (uint8_t s : L->dense_steps) n += s;
+  hpd_layout_free(L);
+  return n == 0 ? NONE : n == T ? ALL : SOME;
+}
+
 int main() {
   std::mt19937 rng(26209);
   auto uni = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
@@ -186,6 +214,20 @@ int main() {
     hpd_layout_free(L);
   }
   CHECK(with_list >= 10);
+  // the plan of the kernel for many rows per unit: even batches with full workgroups run it, few rows per unit and launches
+  // of mostly narrow units do not, nor does a layout that the streaming kernels do not serve
+  CHECK(dense_steps(64, 8, 128, 32, 16, 128, 2, {2048}, {48}, false) == ALL);
+  CHECK(dense_steps(64, 8, 128, 32, 16, 128, 2, {2048}, {40}, false) == ALL);
+  CHECK(dense_steps(64, 8, 128, 32, 16, 128, 2, {2048}, {12}, false) == NONE);
+  CHECK(dense_steps(32, 8, 128, 16, 32, 64, 1, {512}, {16}, false) == NONE);
+  CHECK(dense_steps(48, 8, 128, 4, 26, 1278, 4, {1, 5, 9}, {64, 1, 3, 5, 7}, false) == NONE);
+  CHECK(dense_steps(32, 8, 128, 4, 64, 859, 5, {20, 60, 110}, {113, 2, 5, 8, 14}, false) == NONE);
+  CHECK(dense_steps(32, 8, 128, 12, 64, 64, 4, {384}, {24}, true) == ALL);
+  CHECK(dense_steps(32, 8, 128, 24, 64, 0, 1, {20}, {64}, true) == ALL);
+  CHECK(dense_steps(32, 8, 128, 12, 64, 64, 1, {384}, {4}, true) == NONE);
+  CHECK(dense_steps(32, 4, 128, 64, 1, 0, 1, {20}, {16}, true) == NONE);
+  CHECK(dense_steps(64, 8, 64, 4, 16, 128, 2, {2048}, {48}, false) == NONE);
+  CHECK(dense_steps(72, 8, 128, 4, 16, 128, 2, {2048}, {48}, false) == NONE);
   // fine-tuning mask: sizes and argument checks (outputs NULL: nothing is launched)
   for (int iter = 0; iter < 200; ++iter) {
     const int n = uni(0, 12), k_max = uni(1, 9);
