@@ -209,12 +209,15 @@ attention_f32_kernel(hpd_dev_tables tb, const int32_t* __restrict__ units, const
         dma2(v_lds + f * 1024, v_tail + ((uint64_t)rows[f] * D + channel(r0, 4 * my_pos)),
              v_tail + ((uint64_t)rows[f + 1] * D + channel(r1, 4 * my_pos)));
       }
-    } else {  // a float per lane
-      const int32_t t0 = 16 * (t - nh - nd);
+    } else {  // a float per lane; the lanes that requested a row's keys have its place in the pools
+#pragma unroll
+      for (int f = 0; f < NJ; ++f) {
 #pragma nounroll
-      for (int32_t first = 0; first < 16 * D; first += 64) {
-        const int32_t row = (first + x) / D, i = min(t0 + row, n_tail - 1), b = tail_branch(i);
-        dma_dword(v_lds + 4 * first, v_tail + ((uint64_t)tail_row(b, i - b * step) * D + channel(row, (first + x) % D)));
+        for (int32_t first = f * 256; first < f * 256 + 256; first += 64) {
+          const int32_t row = (first + x) / D;
+          const uint32_t at = __shfl(rows[f], (row % RPI) * CH);
+          dma_dword(v_lds + 4 * first, v_tail + ((uint64_t)at * D + channel(row, (first + x) % D)));
+        }
       }
     }
   };
