@@ -1287,6 +1287,23 @@ def test_fp32_decode_with_tail_values_off_16_bytes_takes_little_longer(d, page):
     assert us[1] < 1.6 * us[0]
 
 
+def test_fp32_decode_of_two_units_uses_the_whole_chip():
+    """The row groups of a (unit, kv head) run on one XCD to share its L2, but not where that leaves XCDs without work: two
+    documents take less time than eight (on an XCD each, they took the same)."""
+    from paper_2604_26209_amd import binding as B
+    steps, n, calls = 64, 50, []
+    for docs in (2, 8):
+        wl = W.make_workload("xcds", "f32", 16, 1, 64, 10000.0, steps, [100] * docs, [1] * docs, [600] * docs, [n] * docs, [steps] * (docs * n))
+        lay = B.layout_from_workload(wl)
+        pools = [x.normal_() for x in B.alloc_pools(lay)]
+        q, k, v = (torch.randn(wl.n_branches, h, 64, device="cuda") for h in (16, 1, 1))
+        out = torch.zeros_like(q)
+        calls.append(lambda lay=lay, q=q, k=k, v=v, pools=pools, out=out: B.hpd_decode_step(lay, 55, q, k, v, *pools, out))
+    us = _us_in_turn(calls)
+    _say(f"fp32 decode, two units {us[0]:.1f} us, eight {us[1]:.1f} us")
+    assert us[0] < 0.85 * us[1]
+
+
 # fp32 batches whose rows fill the 16-row groups badly: heads, channels, documents, branches of each
 # document, steps
 F32_UNEVEN = {
