@@ -37,6 +37,9 @@
 // 17.6 -> 11.4; 256 documents of 512 keys, 12 branches, 16/4 heads x 64, 4218 -> 247 -> 148, x 128 8400 -> 487 -> 254; 2000
 // documents of 12..384 keys, 1..24 branches, 12065 -> 1936 -> 1046; 4 branches, 4/4 heads x 64, 72 keys, the kernel alone,
 // 7.0 -> 5.4 (1.0 until the descriptor is there, 1.4 more until the query is shared, 2.1 for the tiles, 0.8 to merge).
+// Over 2000 random batches 1.39 times the speed with loads into operand layout in the mean; 21 are slower, down to 0.82: launches
+// of thousands of workgroups with 32 channels and one or two tiles, documents of a few keys without a header (526 of up to
+// 9 keys, 8/2 heads, 11.5 -> 13.9 us; 476 of one or two keys, 64/8 heads, 116 -> 133).
 // Error against 64 bits over 25 batches: 1.4e-7 .. 2.0e-7, before 1.3e-7 .. 2.1e-7 (0.998 of it in the mean), generic kernel 2.1e-7
 // .. 3.8e-7.
 #include <algorithm>
@@ -472,9 +475,11 @@ hipError_t launch(const hpd_layout* L, int32_t step, const void* q, const void* 
   // at most 15000 keys per row
   const uint32_t magic = step > 1 ? (uint32_t)((((uint64_t)1 << 32) + step - 1) / step) : 0;
   // (x and y of a grid go together: one (unit, kv head) on each XCD, its row groups one after the other.  Where that leaves
-  // a tenth of the XCDs' places empty, row groups go to the XCDs in turn: one document of 666 keys, 50 branches, 32/2 heads
-  // x 64, step 55, 27.1 us on two XCDs, 14.4 on eight.  The plan lists the groups from 65536 per unit on, z is at most 65535.)
-  const bool in_turn = 10 * n_groups < 9 * 8 * octets;
+  // a tenth of the XCDs' places empty and gives an XCD more workgroups than it has CUs, row groups go to the XCDs in turn:
+  // one document of 666 keys, 50 branches, 32/2 heads x 64, step 55, 27.1 us on two XCDs, 14.4 on eight; but 35 documents
+  // with 5 row groups, 16/1 heads x 128, 15.1 on one XCD each, 17.9 in turn.  The plan lists the groups from 65536 per unit
+  // on, z is at most 65535.)
+  const bool in_turn = 10 * n_groups < 9 * 8 * octets && octets * rg * 8 > L->n_cus;
   const int64_t layers = in_turn ? 1 : octets;
   for (int64_t z = 0; z < layers; z += 65535) {
     attention_f32_kernel<D><<<dim3(in_turn ? (unsigned)n_groups : 8u, (unsigned)rg, (unsigned)std::min<int64_t>(layers - z, 65535)),

@@ -104,9 +104,7 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     const int64_t work = std::max<int64_t>(1, all * L->cfg.n_kv_heads), wgs = exist * L->cfg.n_kv_heads;
     const int64_t waves = std::max((all + exist - 1) / std::max<int64_t>(1, exist), 8 * most * n_cus / work);
     // One more for the newest tokens, but for workgroups of one or two tiles that queue up, where the last wave takes them
-    // with its tile.  With it / without, us: 2000 documents of 64 keys, 1 branch, 16/4 heads x 64, 152 / 172; 300 of 64
-    // keys, 64/8 x 128, 212 / 255; 200 of 20 keys, 8/8 x 64, 11.8 / 12.8; but of 3 keys 11.2 / 8.6, and 4000 of 3 keys, 8/8
-    // x 32, 70 / 60.
+    // with its tile (4000 documents of 3 keys, 8/8 heads x 32, 70 us with it, 60 without).
     const bool newest_wave = wgs <= n_cus || all > 2 * exist;
     // 128 channels, groups with one row in use of 16 (one branch per document, one query head per kv head) and few keys:
     // the matrix work for the other rows, and the registers (two waves per SIMD), cost more than the generic kernel's
@@ -123,7 +121,24 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     // branches on this kernel is the faster one: 60 documents of 3 keys, one branch, 9.2 / 11.2, three 9.4 / 18.7.
     const int64_t calls = (int64_t)(L->live_ptr[t + 1] - L->live_ptr[t]) * L->cfg.n_q_heads;
     s.generic |= D == 128 && std::min(s.per_group, L->max_rows[t]) * G >= 12 && most <= 2 && calls <= 32;
-    s.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most + newest_wave, waves + newest_wave}));
+    int64_t n_waves = std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most + newest_wave, waves + newest_wave}));
+    // Workgroups that are at work at once: by registers (24, 16 and 8 waves on a CU), by LDS.
+    auto at_once = [&](int64_t w) -> int64_t {
+      const int64_t by_waves = std::max<int64_t>(1, (D == 32 ? 24 : D == 64 ? 16 : 8) / w);
+      return (int64_t)n_cus * std::min<int64_t>(by_waves, 163840 / ((w * 32 + HPD_F32_ROWS) * D * (int64_t)sizeof(float)));
+    };
+    // Where they have room, three or four waves also for one or two tiles: they share the rotation of the query and the
+    // merge (498 documents of up to 5 keys, 8/2 heads x 32, 15.1 us with one wave, 12.1 with two, 10.3 with four; but 682
+    // workgroups with 128 channels, three of which fit a CU with two waves, 15.9 with two, 21.2 with three).  Where short
+    // workgroups queue up, two or three tiles a wave: 3739 documents of up to 54 keys, 10/2 heads x 64, 91.8 us with five
+    // waves, 58.6 with four, 49.2 with two.  Over 2000 batches 1.04 times the speed without these two rules in the mean,
+    // 11 slower by more than 3 %, none by more than 7 %.
+    if (n_waves < 4) {
+      while (n_waves < 4 && 4 * wgs <= 3 * at_once(n_waves + 1)) ++n_waves;
+    } else if (wgs > 2 * at_once(n_waves) && all <= 6 * exist && most * exist <= 2 * all && waves * exist < all + exist) {
+      n_waves = std::max<int64_t>(2, (2 * all + 5 * exist - 1) / (5 * exist));
+    }
+    s.waves = (int32_t)n_waves;
   }
 }
 

@@ -77,6 +77,21 @@ static bool check_f32_steps(const hpd_layout* L) {
   return listed;
 }
 
+// waves of a workgroup in the last step of an fp32 batch
+static int32_t f32_waves(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t docs, int32_t doc, int32_t branches) {
+  hpd_config cfg{};
+  cfg.n_q_heads = hq; cfg.n_kv_heads = hkv; cfg.head_dim = D; cfg.dtype = HPD_F32; cfg.rope_base = 10000.0; cfg.max_new = T;
+  cfg.flags = HPD_FLAG_HOST_ONLY;
+  const int32_t header = 0;
+  std::vector<int32_t> doc_ptr{0, docs}, doc_len(docs, doc), branch_ptr{0};
+  for (int32_t d = 0; d < docs; ++d) branch_ptr.push_back(branch_ptr.back() + branches);
+  hpd_layout* L = nullptr;
+  CHECK(hpd_build_layout(&cfg, 1, &header, doc_ptr.data(), doc_len.data(), branch_ptr.data(), nullptr, nullptr, nullptr, &L) == HPD_OK);
+  const int32_t waves = L->f32_steps[T - 1].waves;
+  hpd_layout_free(L);
+  return waves;
+}
+
 // the steps of an even bf16 batch that run the kernel for many rows per unit: all of them, some, none
 enum { NONE = 0, SOME = 1, ALL = 2 };
 static int dense_steps(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t P, int32_t header, int32_t J, std::vector<int32_t> doc,
@@ -214,6 +229,13 @@ int main() {
     hpd_layout_free(L);
   }
   CHECK(with_list >= 10);
+  // short workgroups: four waves where all of them are at work at once, two where they queue up; a wave per tile and one
+  // for the newest tokens where there are few workgroups
+  CHECK(f32_waves(8, 2, 32, 1, 500, 5, 4) == 4);
+  CHECK(f32_waves(10, 2, 32, 1, 2000, 5, 3) == 1);
+  CHECK(f32_waves(8, 2, 128, 1, 340, 5, 4) == 2);
+  CHECK(f32_waves(10, 2, 64, 4, 3739, 54, 1) == 2);
+  CHECK(f32_waves(16, 4, 64, 10, 8, 64, 4) == 8);
   // the plan of the kernel for many rows per unit: even batches with full workgroups run it, few rows per unit and launches
   // of mostly narrow units do not, nor does a layout that the streaming kernels do not serve
   CHECK(dense_steps(64, 8, 128, 32, 16, 128, 2, {2048}, {48}, false) == ALL);
