@@ -361,16 +361,20 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
         for (int i = 0; i < 16; ++i) acc[blk][i] *= alpha;
     }
   };
-  auto weigh = [&](float (&s)[16], const uint4 (&vf)[8]) __attribute__((always_inline)) {
+  // the weights, rounded to halves, and their sum
+  auto weights = [&](float (&s)[16], f16x8& P0, f16x8& P1) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) s[i] = fast_exp2(s[i]);
-    const f16x8 P0 = pack8_half(s), P1 = pack8_half(s + 8);
+    P0 = pack8_half(s);
+    P1 = pack8_half(s + 8);
     const uint4 w0 = __builtin_bit_cast(uint4, P0), w1 = __builtin_bit_cast(uint4, P1);
     float la = sum_half_pair(w0.x, l_lane), lb = sum_half_pair(w1.x, 0.f);
     la = sum_half_pair(w0.y, la); lb = sum_half_pair(w1.y, lb);
     la = sum_half_pair(w0.z, la); lb = sum_half_pair(w1.z, lb);
     la = sum_half_pair(w0.w, la); lb = sum_half_pair(w1.w, lb);
     l_lane = la + lb;
+  };
+  auto value_product = [&](const f16x8& P0, const f16x8& P1, const uint4 (&vf)[8]) __attribute__((always_inline)) {
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk) {
       acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, vf[blk * 2]), P0, acc[blk], 0, 0, 0);
@@ -393,17 +397,67 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
       vf[f] = make_uint4(k03.x, k03.y, k47.x, k47.y);
     }
   };
-  // N blocks from `at` on, of which those of bit b in `tails` are tail tiles
-  auto compute = [&](auto nc, uint32_t at, bool masked, uint32_t ok0, uint32_t ok1, uint32_t tails) __attribute__((always_inline)) {
+  // literal mask: the branch of this row and of the row block's last one, counted from the prompt's first, and the
+  // names they see
+  int32_t kb_row = 0, kb_row_min = 0, kb_row_max = 0, names_row = 0, names_max = 0;
+  if constexpr (PAPER) {
+    kb_row = my_branch - pb0;
+    kb_row_min = __builtin_amdgcn_readfirstlane(kb_row);
+    kb_row_max = __builtin_amdgcn_readfirstlane(unit_branch(br0 + min(wave * BPB + BPB - 1, nbr_here - 1))) - pb0;
+    names_row = a.tb.skel_cum[pb0 + kb_row];
+    names_max = __builtin_amdgcn_readfirstlane(a.tb.skel_cum[pb0 + kb_row_max]);
+  }
+  // Literal mask: an infinite or NaN value of a branch must not reach the rows of earlier ones as 0 * value.  Where a tile
+  // that not all rows see alike has one, the product takes zeros in its place, and the rows that see it add it.  (A
+  // token's value before it is weighted: what matters is that it is not finite.)
+  auto non_finite = [](uint32_t half) -> bool { return (half & 0x7c00u) == 0x7c00u; };
+  auto take_out_non_finite = [&](int32_t tile, uint32_t at, uint4 (&vf)[8]) __attribute__((always_inline)) {
+    f16x2 z = {(_Float16)0, (_Float16)0};
+    const f16x2 zero = z;
+#pragma unroll
+    for (int f = 0; f < 8; ++f) {  // (a finite value times zero is zero)
+      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].x), zero, z);
+      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].y), zero, z);
+      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].z), zero, z);
+      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].w), zero, z);
+    }
+    if (!__any(!(z[0] == zero[0] && z[1] == zero[1]))) return;
+    auto finite_pair = [&](uint32_t w) -> uint32_t {
+      return w & ((non_finite(w) ? 0u : 0xffffu) | (non_finite(w >> 16) ? 0u : 0xffff0000u));
+    };
+#pragma unroll
+    for (int f = 0; f < 8; ++f) vf[f] = make_uint4(finite_pair(vf[f].x), finite_pair(vf[f].y), finite_pair(vf[f].z), finite_pair(vf[f].w));
+    const TileAt x = tile_at(tile);
+#pragma nounroll
+    for (int32_t k = 0; k < 32; ++k) {
+      const int32_t j = x.tb0 + (k >> x.lg);
+      const bool sees = j <= kb_row && (k & ((1 << x.lg) - 1)) < klen[min(j, kb_end - 1)] - x.c * 8;
+#pragma unroll
+      for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+        for (int cc = 0; cc < 4; ++cc) {  // channels blk * 32 + cc * 8 + g2 * 4 + 0 .. 3 of key k
+          const uint2 v = *reinterpret_cast<const uint2*>(rc + at + k * 256 + (((blk * 4 + cc) ^ (2 * (k & 3))) << 4) + g2 * 8);
+          const uint32_t h[4] = {v.x & 0xffffu, v.x >> 16, v.y & 0xffffu, v.y >> 16};
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (sees && non_finite(h[e])) acc[blk][cc * 4 + e] += hpd::cache_bits_to_float(h[e]);
+        }
+    }
+  };
+  // N blocks from `at` on; tile >= 0: a tail tile of the literal mask (N = 1)
+  auto compute = [&](auto nc, uint32_t at, bool masked, uint32_t ok0, uint32_t ok1, int32_t tile) __attribute__((always_inline)) {
     constexpr int N = decltype(nc)::value;
     float s[N][16];
     settle(nc, s, at, masked, ok0, ok1);
 #pragma unroll
     for (int b = 0; b < N; ++b) {
       uint4 vf[8];
-      if ((tails >> b) & 1) read_tail_values(at + b * BLK + 8192, vf);
+      if (tile >= 0) read_tail_values(at + b * BLK + 8192, vf);
       else read_values(at + b * BLK + 8192, vf);
-      weigh(s[b], vf);
+      f16x8 P0, P1;
+      weights(s[b], P0, P1);
+      if (PAPER && N == 1 && masked && tile >= 0) take_out_non_finite(tile, at + 8192, vf);
+      value_product(P0, P1, vf);
     }
   };
   auto first_bits = [](int32_t cnt) -> uint32_t { return (1u << min(max(cnt, 0), 8)) - 1u; };
@@ -432,16 +486,6 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     if (PAPER && PAGED) round_pages(r + 2);
   };
 
-  // literal mask: the branch of this row and of the row block's last one, counted from the prompt's first, and the
-  // names they see
-  int32_t kb_row = 0, kb_row_min = 0, kb_row_max = 0, names_row = 0, names_max = 0;
-  if constexpr (PAPER) {
-    kb_row = my_branch - pb0;
-    kb_row_min = __builtin_amdgcn_readfirstlane(kb_row);
-    kb_row_max = __builtin_amdgcn_readfirstlane(unit_branch(br0 + min(wave * BPB + BPB - 1, nbr_here - 1))) - pb0;
-    names_row = a.tb.skel_cum[pb0 + kb_row];
-    names_max = __builtin_amdgcn_readfirstlane(a.tb.skel_cum[pb0 + kb_row_max]);
-  }
   const int32_t r_plain = (PAPER ? NBh + n_doc_blk : NB) >> 1;  // rounds of blocks that all rows see alike
   // K or V half of own tile t: row k = 4 f + lane / 16 of it is position c * 8 + k % 2^lg of branch tb0 + k / 2^lg; what
   // lies behind the last branch or position repeats the last one
@@ -479,7 +523,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     const bool masked = (vA & vB) != 32;
     uint32_t ok0 = 0, ok1 = 0;
     if (masked) { ok0 = ok_bits(vA); ok1 = ok_bits(vB); }
-    compute(std::integral_constant<int, 2>{}, (uint32_t)(r & 1) * HALF, masked, ok0, ok1, 0u);
+    compute(std::integral_constant<int, 2>{}, (uint32_t)(r & 1) * HALF, masked, ok0, ok1, -1);
   }
   for (int32_t r = r_plain; r < NR; ++r) {
     open_round(r);
@@ -517,7 +561,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
           }
         }
       }
-      compute(std::integral_constant<int, 1>{}, (uint32_t)(b & 3) * BLK, masked, ok, 0u, tail ? 1u : 0u);
+      compute(std::integral_constant<int, 1>{}, (uint32_t)(b & 3) * BLK, masked, ok, 0u, tail ? b - NB : -1);
     }
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -552,7 +596,9 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
       __builtin_amdgcn_s_waitcnt(0xc07f);
       asm volatile("" ::: "memory");
       if (more) issue_own(v_tail, true, my_v, t + 1);
-      weigh(s[0], vf);
+      f16x8 P0, P1;
+      weights(s[0], P0, P1);
+      value_product(P0, P1, vf);
     }
   }
 

@@ -318,6 +318,92 @@ def test_uneven_decode_batches_run_the_faster_kernel(case, mode):
     assert us[0] < 1.08 * us[1]
 
 
+@pytest.mark.parametrize("case", ["two_blocks", "header", "names", "names_g2"])
+def test_literal_decode_of_many_rows_and_few_shared_blocks(case):
+    """Prompts whose header, document and names are two, three or five blocks of 32 keys: with fewer than four, tail tiles are
+    among the first loads and the append comes in front of them.  26 steps: all tail formats, in chunks one to four; pools
+    of NaN; branches that end.  Against the oracle, the two-call sequence, pages of 8 to 32 tokens (the same bits), and the
+    other kernel, whose bits differ in every step."""
+    from paper_2604_26209_amd import binding as B
+    hq, header, n = {"two_blocks": (64, 0, 32), "header": (64, 7, 32), "names": (32, 0, 64), "names_g2": (16, 0, 128)}[case]
+    prompts, steps = 48, 26
+    blen = np.full(prompts * n, steps)
+    blen[4::11] = 13
+    attr = np.ones(prompts * n, np.int32)
+    wl = W.make_workload("few_blocks", "bf16", hq, 8, 128, 500000.0, steps, [header] * prompts, [1] * prompts, [20] * prompts, [n] * prompts, blen)
+    kw = dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=attr, mask_mode=B.HPD_MASK_PAPER)
+    _say(f"literal mask, few shared blocks: {case}")
+    a = H.run_hip(wl, fused=True, **kw)
+    H.check_all(wl, a, prompts=[0, 31], label=case, pos_mode="paper_gap", attr_len=attr, mask_mode="paper")
+    b = H.run_hip(wl, inputs=a["inputs"], **kw)
+    c = H.run_hip(wl, inputs=a["inputs"], fused=True, kernel_mode=3, **kw)
+    for t, (x, y, z) in enumerate(zip(a["out"], b["out"], c["out"])):
+        assert torch.equal(x, y), f"step {t}: step call and two calls differ"
+        assert not torch.equal(x, z), f"step {t} did not run the kernel for many rows"
+        assert float((x - z).abs().max()) < H.BF16_TOL * float(x.square().mean().sqrt())
+    for page in (8, 16, 32):
+        lay = B.layout_from_workload(wl, out_dtype=B.HPD_OUT_F32, **kw)
+        per = -(-steps // page)
+        table = torch.from_numpy(np.random.default_rng(page).permutation(per * wl.n_branches).astype(np.int32).reshape(-1, per)).cuda()
+        B.hpd_set_tail_pages(lay, page, per * wl.n_branches, table)
+        pools = [x.fill_(float("nan")) for x in B.alloc_pools(lay)]
+        inputs = a["inputs"]
+        B.hpd_prefix_fill(lay, inputs.k_raw, inputs.v_raw, pools[0], pools[1])
+        for t in range(steps):
+            out = torch.zeros_like(a["out"][t])
+            B.hpd_decode_step(lay, t, inputs.q[t], inputs.k_new[t], inputs.v_new[t], *pools, out)
+            assert torch.equal(out, a["out"][t]), f"step {t}: pages of {page} and contiguous tails differ"
+
+
+@pytest.mark.parametrize("page", [16, 32, 64])
+def test_block_mask_decode_of_many_rows_through_large_pages(page):
+    """Steps of several chunks per page, live branches that are no run of ids: the bits of contiguous tails."""
+    from paper_2604_26209_amd import binding as B
+    docs, n, steps = 64, 16, 70
+    blen = np.full(docs * n, steps)
+    blen[5::9] = 30
+    wl = W.make_workload("large_pages", "bf16", 64, 8, 128, 500000.0, steps, [33] * docs, [1] * docs, [40] * docs, [n] * docs, blen)
+    lay = [B.layout_from_workload(wl, out_dtype=B.HPD_OUT_F32) for _ in range(2)]
+    per = -(-steps // page)
+    table = torch.randperm(per * wl.n_branches, device="cuda").to(torch.int32).view(-1, per).contiguous()
+    B.hpd_set_tail_pages(lay[1], page, per * wl.n_branches, table)
+    inputs = H.Inputs(wl, lay[0].n_live(), "cuda")
+    pools = [[x.fill_(float("nan")) for x in B.alloc_pools(x)] for x in lay]
+    _say(f"block mask, pages of {page}")
+    for x, p in zip(lay, pools):
+        B.hpd_prefix_fill(x, inputs.k_raw, inputs.v_raw, p[0], p[1])
+    for t in range(steps):
+        outs = []
+        for x, p in zip(lay, pools):
+            outs.append(torch.zeros(inputs.q[t].shape, device="cuda"))
+            B.hpd_decode_step(x, t, inputs.q[t], inputs.k_new[t], inputs.v_new[t], *p, outs[-1])
+        assert bool(torch.isfinite(outs[0]).all()) and torch.equal(*outs), f"step {t}"
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("literal", [False, True])
+def test_non_finite_values_of_a_branch_in_decode_with_many_rows(literal, value):
+    """One value of one branch at one step.  Literal mask: the outputs that are not finite are those of the generic kernel: rows of
+    the branch and of later ones.  Block mask: no rows but those that the streaming kernel has (branches that share a tile
+    of 32 keys with it).  All others keep the bits of a run without it."""
+    from paper_2604_26209_amd import binding as B
+    prompts, n, steps, at = 48, 32, 12, 2
+    attr = np.ones(prompts * n, np.int32)
+    wl = W.make_workload("non_finite", "bf16", 64, 8, 128, 500000.0, steps, [7] * prompts, [1] * prompts, [40] * prompts, [n] * prompts,
+                         np.full(prompts * n, steps))
+    kw = dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=attr, mask_mode=B.HPD_MASK_PAPER) if literal else {}
+    _say(f"non-finite value, literal={literal}: {value}")
+    clean = H.run_hip(wl, fused=True, **kw)
+    inputs = clean["inputs"]
+    inputs.v_new[at][3 * n + 5, 1, 3] = value
+    a = H.run_hip(wl, inputs=inputs, fused=True, **kw)
+    ref = H.run_hip(wl, inputs=inputs, fused=True, kernel_mode=1 if literal else 3, **kw)
+    for t in range(steps):
+        bad, may = (~torch.isfinite(x["out"][t]) for x in (a, ref))
+        assert bool((bad & ~may).sum() == 0) and torch.equal(a["out"][t][~bad], clean["out"][t][~bad]), f"step {t}"
+        assert bool(bad[3 * n + 5].any()) == (t >= at) and (not literal or torch.equal(bad, may)), f"step {t}"
+
+
 @pytest.mark.parametrize("case", ["peaked_x4", "argmax_x16", "flat_div16", "common_offset", "negative_offset", "rising"])
 def test_score_ranges_of_decode_with_many_rows_per_unit(case):
     """The inputs of test_score_ranges_of_the_online_softmax, and scores all near -16, for the kernel for many rows per
