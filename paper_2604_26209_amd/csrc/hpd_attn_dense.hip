@@ -71,7 +71,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
   auto unit_branch = [&](int32_t li) -> int32_t { return ub0 >= 0 ? ub0 + li : a.tb.live_branch[a.live_base + row0 + li]; };
   const int32_t kb_end = PAPER ? __builtin_amdgcn_readfirstlane(unit_branch(br0 + nbr_here - 1)) - pb0 + 1 : 0;
 
-  // ---- what all rows share: NB prefix blocks; literal mask: then the tail tiles of the prompt's branches 0 .. kb_end-1
+  // ---- what all rows share: NB prefix blocks, at least one, as a document has a token; literal mask: then the tail tiles of the prompt's branches 0 .. kb_end-1
   const int32_t NBh = (Hlen + 31) >> 5, NBd = PAPER ? Llen : (Llen + 31) >> 5, NB = NBh + NBd;
   const int32_t NC = (a.step >> 3) + 1, newest = (a.step & 7) + 1;
   const int32_t fmt_lg = newest <= 1 ? 0 : newest <= 2 ? 1 : newest <= 4 ? 2 : 3;
@@ -190,7 +190,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     issue(2 * r, sA, at);
     issue(min(2 * r + 1, NS - 1), sB, at + BLK);
   };
-  auto slot_clamped = [&](int32_t gb) -> int32_t { return NB > 0 ? slot_of(min(gb, NB - 1)) : 0; };
+  auto slot_clamped = [&](int32_t gb) -> int32_t { return slot_of(min(gb, NB - 1)); };
 
   // ---- fused mode: append the newest tokens (the arithmetic of hpd_kv_append), 8 lanes per branch.  Literal mask:
   //      all live branches up to the row group's last (the same bytes from every writer).
@@ -268,7 +268,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
   }
   const int32_t my_branch = unit_branch(my_lb);
   const int32_t pos = upos >= 0 ? upos : a.tb.branch_base_pos[my_branch] + 1 + a.step;
-  if (NR > 0) issue_round(0, slot_clamped(0), slot_clamped(1));
+  issue_round(0, slot_clamped(0), slot_clamped(1));
   if (NR > 1) issue_round(1, slot_clamped(2), slot_clamped(3));
   f16x8 Qf[8];
   {
@@ -510,7 +510,6 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
   if (!active) {  // a wave without rows loads
     for (int32_t r = 0; r < NR; ++r) open_round(r);
     __builtin_amdgcn_s_waitcnt(0xc07f);
-    if (NR == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     return;
   }
@@ -565,12 +564,8 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     }
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);
-  if (NR == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the append
   __builtin_amdgcn_s_barrier();  // the ring is the waves' own from here on
   if constexpr (!PAPER) {
-    if (NR == 0) {
-      issue_own(k_tail, false, my_k, 0);
-    }
     issue_own(v_tail, true, my_v, 0);
 #pragma nounroll
     for (int32_t t = 0; t < n_own; ++t) {
