@@ -116,6 +116,11 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     for (int32_t u = 0; u < n_units; ++u) rows += desc(u)[5] * (prefix_tiles(u) + tail_tiles(1));
     s.generic = D == 128 && ((2 * rows * G < 3 * all && all < 10 * exist && wgs > 3 * (int64_t)n_cus) ||
                              (2 * rows * G < 5 * all && all <= 2 * exist && wgs > 8 * (int64_t)n_cus));
+    // So do the smallest steps, of one or two branches with 12 or more query heads and a tile or two, where the merge
+    // is the longest part: no difference (16/1 heads, one branch, 3 keys 9.4 / 9.2, one or two launches).  From three
+    // branches on this kernel is the faster one: 60 documents of 3 keys, one branch, 9.2 / 11.2, three 9.4 / 18.7.
+    const int64_t calls = (int64_t)(L->live_ptr[t + 1] - L->live_ptr[t]) * L->cfg.n_q_heads;
+    s.generic |= D == 128 && std::min(s.per_group, L->max_rows[t]) * G >= 12 && most <= 2 && calls <= 32;
     int64_t n_waves = std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most + newest_wave, waves + newest_wave}));
     // Workgroups that are at work at once: by registers (24, 16 and 8 waves on a CU), by LDS.
     auto at_once = [&](int64_t w) -> int64_t {

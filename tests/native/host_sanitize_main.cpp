@@ -77,7 +77,7 @@ static bool check_f32_steps(const hpd_layout* L) {
   return listed;
 }
 
-// waves of a workgroup in the last step of an fp32 batch, 0 if the generic kernels take it
+// waves of a workgroup in the last step of an fp32 batch
 static int32_t f32_waves(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t docs, int32_t doc, int32_t branches) {
   hpd_config cfg{};
   cfg.n_q_heads = hq; cfg.n_kv_heads = hkv; cfg.head_dim = D; cfg.dtype = HPD_F32; cfg.rope_base = 10000.0; cfg.max_new = T;
@@ -87,7 +87,7 @@ static int32_t f32_waves(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t 
   for (int32_t d = 0; d < docs; ++d) branch_ptr.push_back(branch_ptr.back() + branches);
   hpd_layout* L = nullptr;
   CHECK(hpd_build_layout(&cfg, 1, &header, doc_ptr.data(), doc_len.data(), branch_ptr.data(), nullptr, nullptr, nullptr, &L) == HPD_OK);
-  const int32_t waves = L->f32_steps[T - 1].generic ? 0 : L->f32_steps[T - 1].waves;
+  const int32_t waves = L->f32_steps[T - 1].waves;
   hpd_layout_free(L);
   return waves;
 }
@@ -236,9 +236,6 @@ int main() {
   CHECK(f32_waves(8, 2, 128, 1, 340, 5, 4) == 2);
   CHECK(f32_waves(10, 2, 64, 4, 3739, 54, 1) == 2);
   CHECK(f32_waves(16, 4, 64, 10, 8, 64, 4) == 8);
-  // the smallest steps of 128 channels are the fp32 kernel's; lone rows that queue up the generic kernels'
-  CHECK(f32_waves(16, 1, 128, 1, 1, 3, 1) == 4);
-  CHECK(f32_waves(8, 8, 128, 1, 4000, 20, 1) == 0);
   // the plan of the kernel for many rows per unit: even batches with full workgroups run it, few rows per unit and launches
   // of mostly narrow units do not, nor does a layout that the streaming kernels do not serve
   CHECK(dense_steps(64, 8, 128, 32, 16, 128, 2, {2048}, {48}, false) == ALL);
