@@ -408,7 +408,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     names_max = __builtin_amdgcn_readfirstlane(a.tb.skel_cum[pb0 + kb_row_max]);
   }
   // Literal mask: an infinite or NaN value of a branch must not reach the rows of earlier ones as 0 * value.  Where a tile
-  // that not all rows see alike has one, the product takes zeros in its place, and the rows that see it add it.  (A
+  // with branches that not all rows see has one, the product takes zeros in its place, and the rows that see it add it.  (A
   // token's value before it is weighted: what matters is that it is not finite.)
   auto non_finite = [](uint32_t half) -> bool { return (half & 0x7c00u) == 0x7c00u; };
   auto take_out_non_finite = [&](int32_t tile, uint32_t at, uint4 (&vf)[8]) __attribute__((always_inline)) {
@@ -444,8 +444,9 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
         }
     }
   };
-  // N blocks from `at` on; tile >= 0: a tail tile of the literal mask (N = 1)
-  auto compute = [&](auto nc, uint32_t at, bool masked, uint32_t ok0, uint32_t ok1, int32_t tile) __attribute__((always_inline)) {
+  // N blocks from `at` on; tile >= 0: a tail tile of the literal mask (N = 1); later: with branches that a row does not see
+  auto compute = [&](auto nc, uint32_t at, bool masked, uint32_t ok0, uint32_t ok1, int32_t tile,
+                     bool later) __attribute__((always_inline)) {
     constexpr int N = decltype(nc)::value;
     float s[N][16];
     settle(nc, s, at, masked, ok0, ok1);
@@ -456,7 +457,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
       else read_values(at + b * BLK + 8192, vf);
       f16x8 P0, P1;
       weights(s[b], P0, P1);
-      if (PAPER && N == 1 && masked && tile >= 0) take_out_non_finite(tile, at + 8192, vf);
+      if (PAPER && N == 1 && later) take_out_non_finite(tile, at + 8192, vf);
       value_product(P0, P1, vf);
     }
   };
@@ -522,7 +523,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     const bool masked = (vA & vB) != 32;
     uint32_t ok0 = 0, ok1 = 0;
     if (masked) { ok0 = ok_bits(vA); ok1 = ok_bits(vB); }
-    compute(std::integral_constant<int, 2>{}, (uint32_t)(r & 1) * HALF, masked, ok0, ok1, -1);
+    compute(std::integral_constant<int, 2>{}, (uint32_t)(r & 1) * HALF, masked, ok0, ok1, -1, false);
   }
   for (int32_t r = r_plain; r < NR; ++r) {
     open_round(r);
@@ -533,7 +534,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
     for (int32_t b = 2 * r; b < min(2 * r + 2, NS); ++b) {
       // what the rows see of the block: all of it, or what their bits say
       uint32_t ok = 0;
-      bool masked = true;
+      bool masked = true, later = false;
       const bool tail = PAPER && b >= NB;
       if (!tail) {
         int32_t valid = keys_of(b);
@@ -548,6 +549,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
       } else {
         const TileAt x = tile_at(b - NB);
         if (x.tb0 > kb_row_max) continue;
+        later = x.tb0 + (31 >> x.lg) > kb_row_min;
         // a row keeps the tokens in memory of the branches up to its own
         const int32_t j_lane = x.tb0 + (n >> x.lg);
         masked = !__all(j_lane <= kb_row_min && klen[min(j_lane, kb_end - 1)] - x.c * 8 >= 1 << x.lg);
@@ -560,7 +562,7 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
           }
         }
       }
-      compute(std::integral_constant<int, 1>{}, (uint32_t)(b & 3) * BLK, masked, ok, 0u, tail ? b - NB : -1);
+      compute(std::integral_constant<int, 1>{}, (uint32_t)(b & 3) * BLK, masked, ok, 0u, tail ? b - NB : -1, later);
     }
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);
