@@ -412,16 +412,17 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
   // token's value before it is weighted: what matters is that it is not finite.)
   auto non_finite = [](uint32_t half) -> bool { return (half & 0x7c00u) == 0x7c00u; };
   auto take_out_non_finite = [&](int32_t tile, uint32_t at, uint4 (&vf)[8]) __attribute__((always_inline)) {
-    f16x2 z = {(_Float16)0, (_Float16)0};
-    const f16x2 zero = z;
+    const f16x2 zero = {(_Float16)0, (_Float16)0};
+    f16x2 z[4] = {zero, zero, zero, zero};
 #pragma unroll
     for (int f = 0; f < 8; ++f) {  // (a finite value times zero is zero)
-      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].x), zero, z);
-      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].y), zero, z);
-      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].z), zero, z);
-      z = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].w), zero, z);
+      z[0] = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].x), zero, z[0]);
+      z[1] = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].y), zero, z[1]);
+      z[2] = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].z), zero, z[2]);
+      z[3] = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].w), zero, z[3]);
     }
-    if (!__any(!(z[0] == zero[0] && z[1] == zero[1]))) return;
+    const f16x2 sum = (z[0] + z[1]) + (z[2] + z[3]);
+    if (!__any(!((float)sum[0] + (float)sum[1] == 0.f))) return;
     auto finite_pair = [&](uint32_t w) -> uint32_t {
       return w & ((non_finite(w) ? 0u : 0xffffu) | (non_finite(w >> 16) ? 0u : 0xffff0000u));
     };
