@@ -287,9 +287,10 @@ int hpd_expand_mask(const hpd_layout* layout, int32_t prompt, int32_t step_hi, u
  * hpd_dynamic_prune - `finished`: device uint8 [n_live] in the row order of the step just
  *   taken; non-zero = that branch is not decoded any further.  Builds the next step's state.
  * hpd_dynamic_step  - hpd_decode_step of step `step` for the rows of the current live list
- *   (the same kernel; a document's rows are split over workgroups by its full branch count,
- *   the live count being unknown to the host, so sums may be grouped differently and results
- *   agree with hpd_decode_step to rounding, not always bit for bit):
+ *   (a document's rows are split over workgroups by its full branch count, the live count being
+ *   unknown to the host, so sums may be grouped differently, and for steps of many rows per
+ *   document or prompt hpd_decode_step has a kernel that this call does not use: results agree
+ *   with hpd_decode_step to rounding, not always bit for bit):
  *   rows r of q / k_new / v_new / out are the live branches in ascending b, r < n_live (the
  *   kernels touch no row beyond; buffers need n_live rows, B rows always suffice).
  * hpd_dynamic_state - device addresses of the live list (int32 [B], first n_live valid) and of
@@ -377,8 +378,8 @@ int hpd_finetune_mask(int32_t prompt_len, int32_t n_attr, const int32_t* attr_le
  * wide or narrow workgroup shape, or a kernel of its own for steps of many rows per document or prompt, which
  * hpd_dynamic_step does not use; hpd_prefill_attention: a kernel of its own), 3 / 4 = the same with the wide / the
  * narrow workgroup shape forced for both calls (2..4 return HPD_E_UNSUPPORTED if
- * the shape does not allow the kernel: it needs bf16, head_dim 128 and a group size of 1,
- * 2, 4 or 8, and under HPD_MASK_PAPER at most 256 branches and 512 blocks of 32 keys per
+ * the shape does not allow the kernel: it needs bf16, head_dim 128 and 1 to 8 query heads
+ * per kv head, and under HPD_MASK_PAPER at most 256 branches and 512 blocks of 32 keys per
  * prompt). */
 int hpd_set_kernel_mode(hpd_layout* layout, int32_t mode);
 

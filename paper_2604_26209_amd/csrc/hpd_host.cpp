@@ -116,9 +116,9 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
     for (int32_t u = 0; u < n_units; ++u) rows += desc(u)[5] * (prefix_tiles(u) + tail_tiles(1));
     s.generic = D == 128 && ((2 * rows * G < 3 * all && all < 10 * exist && wgs > 3 * (int64_t)n_cus) ||
                              (2 * rows * G < 5 * all && all <= 2 * exist && wgs > 8 * (int64_t)n_cus));
-    // So do the smallest steps, of one or two branches with 12 or more query heads and a tile or two, where the merge
-    // is the longest part: no difference (16/1 heads, one branch, 3 keys 9.4 / 9.2, one or two launches).  From three
-    // branches on this kernel is the faster one: 60 documents of 3 keys, one branch, 9.2 / 11.2, three 9.4 / 18.7.
+    // The smallest steps, of one or two branches with 12 or more query heads and a tile or two, stay with the generic
+    // kernels, whose bits they have always had, at a price: 8.5 .. 12.3 us in two launches, 7.1 .. 8.0 in this kernel (16/1, 14/1,
+    // 12/1 and 32/2 heads, 3 .. 20 keys).
     const int64_t calls = (int64_t)(L->live_ptr[t + 1] - L->live_ptr[t]) * L->cfg.n_q_heads;
     s.generic |= D == 128 && std::min(s.per_group, L->max_rows[t]) * G >= 12 && most <= 2 && calls <= 32;
     int64_t n_waves = std::max<int64_t>(1, std::min<int64_t>({hpd_f32_max_waves(D), most + newest_wave, waves + newest_wave}));
@@ -152,8 +152,9 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
 // The constants are microseconds of an MI355X, fitted to 3200 random batches that ran both kernels, and rounded; in the ratio
 // of the two the estimate is off by 17 % (one sigma), so this kernel runs where it promises more.  A tenth is enough where
 // four of five waves have rows and, under the literal mask, there is more than a workgroup per CU and few branches have ended
-// (their tiles are masked key by key); elsewhere, half of the time, under the literal mask a third less (half of the steps
-// from 0.5 on would be faster by 1.37 in the mean, but one in ten slower, down to 0.70).
+// (their tiles are masked key by key).  Elsewhere it has to promise half of the time, under the literal mask two thirds: with
+// the tenth there, 303 more of the 3200 batches would run it under the block mask, 1.37 times as fast in the mean, but 30 of
+// them slower, down to 0.70.  And a launch estimated at 20 us or less is latency in either kernel.
 // Measured over 2400 other batches for which the rule takes it (4 .. 400 branches, 1 .. 6 documents of up to 4000 tokens, 1 ..
 // 160 prompts, even, ragged and with branches that end, up to 256 steps, contiguous and paged tails, either mask): 1.42 times
 // the speed in the mean, up to 2.86; 24 of them slower, 11 by more than 3 %, the slowest 318 us instead of 283.
