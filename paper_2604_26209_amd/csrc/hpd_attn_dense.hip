@@ -13,8 +13,8 @@
 //    positions in the newest chunk as it holds.  A row group's last tiles are only its own, so the last row group of a
 //    prompt, which has the most, is started first.  Both blocks of a round of tiles at a time, as in the prefix: the
 //    compiler spills 55 registers, 440 us instead of 317.
-//  * Paged tails: the page table's entries for a tile come by DMA a tile ahead; 1.38 times the speed of the other kernel in the
-//    mean where the plan takes it, contiguous 1.37 (block mask), 1.52 and 1.54 (literal mask).
+//  * Paged tails: the page table's entries for a tile come by DMA a tile ahead; 1.39 times the speed of the other kernel in the
+//    mean where the plan takes it, contiguous 1.35 (block mask), 1.46 and 1.50 (literal mask).
 // Measured (us per hpd_decode_step, the other kernel -> this): 16 prompts x 2 documents of 2048 tokens, 48 branches, 64/8 heads,
 // step 17, 160 -> 138 (768 workgroups on 512 places: half of the launch runs one per CU); literal mask, 64 prompts x 4 documents of
 // 384 tokens, 96 branches, 32/8 heads, step 7, 369 -> 324; 25 prompts x 3 documents of 84 tokens, 153 branches, step 15, 488 -> 271.

@@ -152,12 +152,12 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
 // The constants are microseconds of an MI355X, fitted to 3200 random batches that ran both kernels, and rounded; in the ratio
 // of the two the estimate is off by 17 % (one sigma), so this kernel runs where it promises more.  A tenth is enough where
 // four of five waves have rows and, under the literal mask, there is more than a workgroup per CU and few branches have ended
-// (their tiles are masked key by key).  Elsewhere it has to promise half of the time, under the literal mask two thirds: with
-// the tenth there, 303 more of the 3200 batches would run it under the block mask, 1.37 times as fast in the mean, but 30 of
-// them slower, down to 0.70.  And a launch estimated at 20 us or less is latency in either kernel.
-// Measured over 2400 other batches for which the rule takes it (4 .. 400 branches, 1 .. 6 documents of up to 4000 tokens, 1 ..
-// 160 prompts, even, ragged and with branches that end, up to 256 steps, contiguous and paged tails, either mask): 1.42 times
-// the speed in the mean, up to 2.86; 24 of them slower, 11 by more than 3 %, the slowest 318 us instead of 283.
+// (their tiles are masked key by key).  Elsewhere it has to promise a bit more than half of the time, under the literal mask
+// three quarters: with the tenth there, about 300 more of the 3200 batches would run it under the block mask, 1.37 times as
+// fast in the mean, but one in ten of them slower, down to 0.70.  And a launch estimated at 20 us or less is latency in either kernel.
+// Measured over 2800 other batches for which the rule takes it (4 .. 400 branches, 1 .. 6 documents of up to 4000 tokens, 1 ..
+// 160 prompts, even, ragged and with branches that end, up to 256 steps, contiguous and paged tails, either mask): 1.41 times
+// the speed in the mean, up to 3.28; 26 of them slower, 14 by more than 3 %, the slowest 63 us instead of 52.
 void plan_dense(hpd_layout* L, int32_t n_cus) {
   const int32_t Hkv = L->cfg.n_kv_heads, Gr = L->cfg.n_q_heads / Hkv;
   if (L->cfg.dtype != HPD_BF16 || L->cfg.head_dim != 128 || Gr > 8) return;
@@ -230,7 +230,7 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
     const double us = std::max(0.255e-6 * bytes,  // 3.9 TB/s is all that it streams
                                wgs <= n_cus ? 0.75 * longest : wgs <= 2 * n_cus ? longest : sum / (2 * n_cus) + 0.5 * longest);
     const bool close = 5 * blocks >= 4 * (4 * wgs) && (!paper || (5 * seen <= 6 * rows && wgs > n_cus));
-    L->dense_steps[t] = old_us > 20 && us < (close ? 0.9 : paper ? 0.65 : 0.5) * old_us;
+    L->dense_steps[t] = old_us > 20 && us < (close ? 0.9 : paper ? 0.72 : 0.55) * old_us;
   }
 }
 
