@@ -997,63 +997,67 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
 // general kernel's 121 scalar and 126 vector instructions (16 of them MFMA) per row block and key
 // block took twice the cycles of the matrix work, and the chip, limited by power, lowers its clock
 // under this load (2.1 -> 1.6..1.8 GHz), so that an instruction saved counts twice.  Hence
-//  * four waves of 32 rows, two workgroups per CU: two waves on every SIMD, whose matrix and
-//    vector work overlap, and the start and the end of one workgroup under the stream of the other;
+//  * four waves of 32 rows, three workgroups per CU: three waves on every SIMD, whose matrix and vector work overlap, and
+//    the start and the end of a workgroup (9 of 36 us, in-kernel timestamps) under the streams of the others.  That leaves a
+//    wave 168 registers and a workgroup three blocks of LDS: a round is one block of 32 keys, two more are in flight, and the
+//    addresses of the eight K fragments are formed from one for every block.  Launches of up to two workgroups per CU have a
+//    shape of their own (WGS = 2): rounds of two blocks, the ring holds two, one barrier and one check of the reference point
+//    per 64 keys;
 //  * every wave loads: quarter w of a block is four instructions that share one LDS address and
 //    one scalar base, and a lane's four offsets are computed once.  The loads are written out
 //    because the compiler makes every LDS read of a wave wait for all loads-to-LDS the wave has in
-//    flight;
-//  * a round is two blocks, and the ring holds two rounds: one barrier per 64 keys, the next
-//    round in flight while one is consumed (it comes out of the L2: the row groups of a segment
-//    run on one XCD);
-//  * two blocks per step through scores, one check of the reference point, softmax and value
-//    product; a loop of its own for the blocks that all rows see alike (one path from one
-//    iteration to the next: with masked blocks as a second path in the loop the compiler
-//    copied the 64 accumulators in every round);
+//    flight.  (They come out of the L2: the row groups of a segment run on one XCD);
+//  * one workgroup per row group that exists, from a list (list_prefill_groups), the longest first: with a grid of (unit, row
+//    groups of the longest segment) two thirds of the workgroups of a ragged batch had nothing to do, and the longest came last;
+//  * a loop of its own for the blocks that all rows see alike (one path from one iteration to the next: with masked
+//    blocks as a second path in the loop the compiler copied the 64 accumulators in every round);
 //  * the score products start from minus the reference point of the row instead of 0, so that
 //    they come out as the exponents (and are formed again when a large point moves towards 0: a
 //    block whose scores lie far above an old point would carry that point's rounding, 2.4 times
 //    the error against 64 bits after a jump of 8000).
-// Measured (us per call with hpd_prefix_fill, one card; before = the general kernel with four waves
-// that load): 32 prompts x (64 + 512 tokens), 32/8 heads 207 -> 177; 16 prompts x (128 + 2 x 2048),
-// 64/8 heads 3238 -> 2706 (766 -> 916 TFLOP/s); literal mask, 16 ragged prompts of up to 8
-// documents 4465 -> 3724 (799 -> 957 TFLOP/s).  Without the last two points: 188 / 3023 / 4297.
+// What is left is power: on operands like these the chip holds 1.64 PFLOP/s with nothing but the matrix instructions, 1.38 with
+// the LDS reads of their operands, 1.20 with the softmax, 1.13 with the loads to LDS (loops without start and end, clock
+// 1.6-1.7 of 2.4 GHz: cycles saved lower the clock, only work saved gains), and a launch waits for the XCD whose clock is
+// lowest (5 % below the highest).
+// Measured (us per call with hpd_prefix_fill, one card; the general kernel -> rounds of two blocks, two workgroups per CU, unit
+// after unit -> this): 32 prompts x (64 + 512 tokens), 32/8 heads 207 -> 175 -> 162; 16 prompts x (128 + 2 x 2048),
+// 64/8 heads 3238 -> 2763 -> 2582; literal mask, 16 ragged prompts of up to 8 documents 4465 -> 3742 -> 3524.
 // A wave whose rows lie behind the segment's end loads and meets the barriers, and its products are
 // thrown away; the general kernel gave it a share of the keys.  Calls of such segments are faster all the
-// same (us, before -> now, 32/8 heads): one prompt of 64 + 100 tokens 11.8 -> 8.3; 2 x (1000 + 300 documents
+// same (us, the general kernel -> rounds of two blocks, 32/8 heads): one prompt of 64 + 100 tokens 11.8 -> 8.3; 2 x (1000 + 300 documents
 // of 8, 16, 32 tokens) 1403 -> 1093, 1470 -> 1096, 1521 -> 1110; 1 x (8000 + 8) 649 -> 525; 16/16 heads, 2 x
 // (1000 + 300 x 32) 2670 -> 2041; literal mask, 16 x (64 + 4 x 500, 8 tokens of names) 785 -> 664.
-// The outputs differ from the general kernel's by rounding (relative 5e-4 in bf16): one reference point
-// per 64 keys.  Error against 64 bits on N(0,1) inputs, fp32 outputs: 2.42e-4, general kernel 2.44e-4.
+// The outputs differ from the general kernel's by rounding (relative 5e-4 in bf16).  Error against 64 bits on N(0,1) inputs, fp32 outputs: 2.42e-4, general kernel 2.44e-4.
 // ---------------------------------------------------------------------------------------
-constexpr int PREFILL_WAVES = 4;  // row blocks per workgroup
-template <int G, bool LIST>
-__global__ void __launch_bounds__(PREFILL_WAVES * 64, 2)
+constexpr int PREFILL_WAVES = HPD_PREFILL_ROWS / 32;  // row blocks per workgroup
+// WGS = workgroups per CU
+template <int G, bool LIST, int WGS>
+__global__ void __launch_bounds__(PREFILL_WAVES * 64, WGS)
 attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
                     const uint16_t* __restrict__ v_prefix, void* __restrict__ out) {
   constexpr int BPB = 32 / G;       // tokens per row block (wave)
   constexpr int TPG = PREFILL_WAVES * BPB;      // tokens per row group (workgroup)
   constexpr uint32_t BLK = 16384;   // bytes of a block: 8 KB of K rows, 8 KB of V fragments
-  __shared__ uint4 ring[4 * SLOT_U4];
+  constexpr int SB = WGS == 2 ? 2 : 1;         // blocks per round
+  constexpr int SLOTS = WGS == 2 ? 4 : 3;      // blocks in the ring
+  __shared__ uint4 ring[SLOTS * SLOT_U4];
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int n = lane & 31, g2 = lane >> 5, r4 = lane >> 4, c16 = lane & 15;
-  // (unit, kv head) and row group of this workgroup: as in attn_stream_kernel
-  const int32_t rg = (blockIdx.x >> 3) % a.RG;
-  const int32_t grp = ((blockIdx.x >> 3) / a.RG) * 8 + (blockIdx.x & 7);
-  if (grp >= a.n_groups) return;
-  const int32_t hk = grp % a.Hkv, u = grp / a.Hkv;
-  const int32_t* desc = a.tb.funit_desc + (int64_t)u * 8;
+  // row group and kv head of this workgroup.  Workgroup b runs on XCD b % 8; the list keeps the row groups of one (unit,
+  // kv head), which read the same keys, on one of them.
+  const int32_t hk = blockIdx.x % a.Hkv, entry = blockIdx.x / a.Hkv;
+  const int32_t* desc = a.tb.fgroup_desc + (int64_t)entry * 8;
   const int32_t hoff = desc[0], Hlen = desc[1], doff = desc[2], row0 = desc[4], n_seg_tok = desc[5], seg_pos0 = desc[6];
-  const int32_t tok0 = rg * TPG;  // first token of the row group, counted in the segment
-  if (tok0 >= n_seg_tok) return;  // uniform over the workgroup
+  const int32_t tok0 = desc[7];  // first token of the row group, counted in the segment
+  if (n_seg_tok == 0) return;    // uniform over the workgroup
   const int32_t n_tok = min(TPG, n_seg_tok - tok0);
 
   const int32_t NBh = LIST ? Hlen : (Hlen + 31) >> 5;      // blocks the segment sees in full
   const int32_t NB = NBh + ((tok0 + n_tok - 1) >> 5) + 1;  // ... and its own up to the last token
-  const int32_t NR = (NB + 1) >> 1;
+  const int32_t NR = (NB + SB - 1) / SB;                   // rounds
   const const_i32* const list = (const const_i32*)(uintptr_t)(a.tb.fblk + 2 * (int64_t)(LIST ? hoff : 0));
 
   // ---- this wave's quarter of a block (K rows 0..15, K rows 16..31, V d-blocks 0..1, 2..3): one
@@ -1091,12 +1095,6 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
         : "v"(vo[0]), "v"(vo[1]), "v"(vo[2]), "v"(vo[3]), "s"(dst), "s"(s)
         : "memory");
   };
-  // a block past the last one re-loads the last one (never read)
-  auto issue_round = [&](int32_t sA, int32_t sB, int32_t r) {
-    const uint32_t at = (uint32_t)(r & 1) * (2 * BLK);
-    issue(sA, at);
-    issue(sB, at + BLK);
-  };
   // ---- the query rows of the wave, straight into operand layout, and their positions
   const int32_t row = wave * 32 + n;  // row within the row group
   const int32_t my_tok = tok0 + min(row / G, n_tok - 1);
@@ -1108,8 +1106,13 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
     for (int kk = 0; kk < 8; ++kk) qraw[kk] = *reinterpret_cast<const uint4*>(qp + kk * 16);
   }
   const int32_t pos = (!LIST || seg_pos0 >= 0) ? seg_pos0 + my_tok : a.tb.skel_pos[my_tok - seg_pos0 - 1];
+  // a block past the last one re-loads the last one (never read)
+  auto issue_round = [&](int32_t sA, int32_t sB, uint32_t at) {
+    issue(sA, at);
+    if (SB == 2) issue(sB, at + BLK);
+  };
   issue_round(slot_of(0), slot_of(min(1, NB - 1)), 0);
-  if (NR > 1) issue_round(slot_of(2), slot_of(min(3, NB - 1)), 1);
+  if (NR > 1) issue_round(slot_of(SB), slot_of(min(3, NB - 1)), SB * BLK);
   f16x8 Qf[8];
   {
     const float4* cs_row = reinterpret_cast<const float4*>(a.tb.rope + (int64_t)pos * (D / 2));
@@ -1144,11 +1147,14 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
 
   const int32_t krow = ((n >> 4) << 4) | (((n >> 2) & 1) << 3) | (((n >> 3) & 1) << 2) | (n & 3);
   const char* const rc = reinterpret_cast<const char*>(ring);
+  const uint32_t k_lane = (uint32_t)(krow * 256 + ((g2 ^ (krow & 15)) << 4));  // fragment kk lies at k_lane ^ (kk << 5)
   // N consecutive blocks of the ring at `at`: scores, softmax, value product
   auto compute = [&](auto nc, uint32_t at, bool masked, uint32_t ok0, uint32_t ok1) __attribute__((always_inline)) {
     constexpr int N = decltype(nc)::value;
     float s[N][16];
     auto scores = [&]() __attribute__((always_inline)) {
+      uint32_t base = k_lane + at;
+      if (WGS == 3) asm volatile("" : "+v"(base));  // (eight addresses kept from one block for the next are eight registers)
 #pragma unroll
       for (int b = 0; b < N; ++b) {
         floatx16 S;
@@ -1157,7 +1163,7 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
           const f16x8 kf = __builtin_bit_cast(f16x8, *reinterpret_cast<const uint4*>(
-              rc + at + (krow * 256 + (((kk * 2 + g2) ^ (krow & 15)) << 4)) + b * BLK));
+              rc + (WGS == 3 ? base ^ (kk << 5) : at + (k_lane ^ (kk << 5))) + b * BLK));
           S = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, Qf[kk], S, 0, 0, 0);
         }
 #pragma unroll
@@ -1231,21 +1237,32 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
   const int32_t tok_first = tok0 + wave * BPB, tok_last = min(tok_first + BPB, tok0 + n_tok) - 1;
   const int32_t plain_end = NBh + (tok0 >> 5);  // blocks from here on reach into the row group
   const int32_t h_part = !LIST && (Hlen & 31) ? NBh - 1 : -1;  // the header's last block is partial
-  const int32_t r_plain = plain_end >> 1;  // rounds whose blocks all rows see alike
+  const int32_t r_plain = plain_end / SB;  // rounds whose blocks all rows see alike
+  // where the blocks of the round that is requested next lie
   int32_t nA = 0, nB = 0;
-  auto open_round = [&](int32_t r) __attribute__((always_inline)) {
-    // (the round after the first was requested in front of the loop)
-    if (r == 0 && NR > 1) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  if (SB == 1 && NR > 2) nA = slot_of(2);
+  // at: where round r lies in the ring
+  auto open_round = [&](int32_t r, uint32_t at) __attribute__((always_inline)) {
+    // (rounds 0 and 1 were requested in front of the loop; a round is 4 * SB loads of the wave)
+    const bool newer = SB == 2 ? r == 0 && NR > 1 : r + 1 < NR;
+    if (newer) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * SB) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): LDS reads of the previous round are done
-    __builtin_amdgcn_s_barrier();        // the round is in LDS; the other half of the ring is free
-    if (r >= 1 && r + 1 < NR) issue_round(nA, nB, r + 1);
-    // where the blocks of round r + 2 lie
-    if (r + 2 < NR) {
-      nA = slot_of(2 * r + 4);
-      nB = slot_of(min(2 * r + 5, NB - 1));
+    __builtin_amdgcn_s_barrier();        // the round is in LDS; the slots of the round before are free
+    if constexpr (SB == 2) {
+      if (r >= 1 && r + 1 < NR) issue_round(nA, nB, at ^ (2 * BLK));
+      if (r + 2 < NR) {
+        nA = slot_of(2 * r + 4);
+        nB = slot_of(min(2 * r + 5, NB - 1));
+      }
+    } else {
+      if (r + 2 < NR) {
+        issue(nA, at == 0 ? 2 * BLK : at - BLK);
+        nA = slot_of(min(r + 3, NB - 1));
+      }
     }
   };
+  auto behind = [&](uint32_t at) -> uint32_t { return at == (SLOTS - SB) * BLK ? 0u : at + SB * BLK; };
   auto keys_of = [&](int32_t b) -> int32_t {  // keys of a block that the segment sees in full
     if (b >= NBh) return 32;
     return LIST ? list[2 * b + 1] : b == h_part ? Hlen & 31 : 32;
@@ -1253,18 +1270,23 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
   auto ok_bits = [&](int32_t valid) -> uint32_t {
     return first_bits(valid - g2 * 8) | (first_bits(valid - 16 - g2 * 8) << 8);
   };
+  uint32_t at = 0;
+#pragma nounroll
   for (int32_t r = 0; r < r_plain; ++r) {
-    open_round(r);
-    const int32_t vA = keys_of(2 * r), vB = keys_of(2 * r + 1);
+    open_round(r, at);
+    const int32_t vA = keys_of(SB * r), vB = SB == 2 ? keys_of(2 * r + 1) : 32;
     const bool masked = (vA & vB) != 32;
     uint32_t ok0 = 0, ok1 = 0;
     if (masked) { ok0 = ok_bits(vA); ok1 = ok_bits(vB); }
-    compute(std::integral_constant<int, 2>{}, (uint32_t)(r & 1) * (2 * BLK), masked, ok0, ok1);
+    compute(std::integral_constant<int, SB>{}, at, masked, ok0, ok1);
+    at = behind(at);
   }
-  for (int32_t r = r_plain; r < NR; ++r) {
-    open_round(r);
 #pragma nounroll
-    for (int32_t b = 2 * r; b < min(2 * r + 2, NB); ++b) {
+  for (int32_t r = r_plain; r < NR; ++r) {
+    open_round(r, at);
+#pragma nounroll
+    for (int32_t j = 0; j < SB && SB * r + j < NB; ++j) {
+      const int32_t b = SB * r + j;
       int32_t valid = keys_of(b);
       bool masked = valid < 32;
       if (b >= NBh) {  // causal inside the segment: the row of token x keeps keys 0 .. x
@@ -1273,36 +1295,44 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
         masked = k0 + 31 > tok_first;
         valid = my_tok - k0 + 1;
       }
-      compute(std::integral_constant<int, 1>{}, (uint32_t)(b & 3) * BLK, masked, ok_bits(valid), 0u);
+      compute(std::integral_constant<int, 1>{}, at + j * BLK, masked, ok_bits(valid), 0u);
     }
+    at = behind(at);
   }
   __syncthreads();  // the ring is dead from here on and gets reused
   if (!active) return;
 
   // ---- normalise and write: as the waves of attn_stream_kernel that hold whole rows
   const float inv = 1.0f / (l_lane + __shfl_xor(l_lane, 32));
-  uint4* const mine = ring + wave * 1024;
+  uint4* const mine = ring + wave * 512;  // 8 KB
   typedef uint32_t u4v __attribute__((ext_vector_type(4)));
   const int32_t rows_here = n_tok * G;
   if (a.out_f32) {
-    float4* rowp = reinterpret_cast<float4*>(mine) + n * 32;
+#pragma nounroll
+    for (int half = 0; half < 2; ++half) {  // 16 rows at a time
+      if (n >> 4 == half) {
+        float4* rowp = reinterpret_cast<float4*>(mine) + (n & 15) * 32;
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk)
+        for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-      for (int cc = 0; cc < 4; ++cc)
-        rowp[(blk * 8 + cc * 2 + g2) ^ n] = make_float4(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv,
-                                                        acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv);
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll 4
-    for (int32_t i = 0; i < 16; ++i) {  // 2 rows per instruction
-      const int32_t rr = i * 2 + (lane >> 5), chunk = lane & 31, lrr = wave * 32 + rr;
-      if (lrr < rows_here && lrr % G < a.Gr) {
-        const uint4 v = mine[rr * 32 + (chunk ^ rr)];
-        const int64_t off = ((int64_t)(row0 + tok0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 4;
-        u4v vv = {v.x, v.y, v.z, v.w};
-        __builtin_nontemporal_store(vv, reinterpret_cast<u4v*>(reinterpret_cast<float*>(out) + off));
+          for (int cc = 0; cc < 4; ++cc)
+            rowp[(blk * 8 + cc * 2 + g2) ^ n] = make_float4(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv,
+                                                            acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv);
       }
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+      for (int32_t i = 0; i < 8; ++i) {  // 2 rows per instruction
+        const int32_t rr = half * 16 + i * 2 + (lane >> 5), chunk = lane & 31, lrr = wave * 32 + rr;
+        if (lrr < rows_here && lrr % G < a.Gr) {
+          const uint4 v = mine[(rr & 15) * 32 + (chunk ^ rr)];
+          const int64_t off = ((int64_t)(row0 + tok0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 4;
+          u4v vv = {v.x, v.y, v.z, v.w};
+          __builtin_nontemporal_store(vv, reinterpret_cast<u4v*>(reinterpret_cast<float*>(out) + off));
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      __builtin_amdgcn_wave_barrier();
     }
   } else {
     uint2* rowp = reinterpret_cast<uint2*>(mine) + n * 32;
@@ -1339,10 +1369,14 @@ hipError_t launch_g(const StreamArgs& a, int64_t items, const void* q, const voi
 }
 
 template <int G, bool LIST>
-hipError_t launch_prefill(const StreamArgs& a, int64_t items, const void* q, const void* k_prefix,
+hipError_t launch_prefill(const StreamArgs& a, int64_t items, bool three, const void* q, const void* k_prefix,
                           const void* v_prefix, void* out, hipStream_t s) {
-  attn_prefill_kernel<G, LIST><<<dim3((unsigned)items), PREFILL_WAVES * 64, 0, s>>>(
-      a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
+  if (three)
+    attn_prefill_kernel<G, LIST, 3><<<dim3((unsigned)items), PREFILL_WAVES * 64, 0, s>>>(
+        a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
+  else
+    attn_prefill_kernel<G, LIST, 2><<<dim3((unsigned)items), PREFILL_WAVES * 64, 0, s>>>(
+        a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
   return hipGetLastError();
 }
 
@@ -1449,13 +1483,16 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
   const int32_t shape_blocks = narrow ? NarrowShape::MAX_BLOCKS : own ? PREFILL_WAVES : WideShape::MAX_BLOCKS;
   a.RG = (max_nblk + shape_blocks - 1) / shape_blocks;
   a.n_groups = (int32_t)(n_units * a.Hkv);
-  const int64_t items = ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
+  const int64_t items = own ? (int64_t)L->fgroup_desc.size() / 8 * a.Hkv : ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
   if (items > 0x7fffffff) return hipErrorInvalidValue;
   const bool list = L->cfg.mask_mode == HPD_MASK_PAPER;
+  // Up to two workgroups per CU none is a third, and rounds of two blocks are the faster ones (time of the kernel before over
+  // two / three per CU: up to 256 row groups 1.03 / 1.01, 256-320 1.14 / 1.13, 450-512 1.22 / 1.23; above: 512-768 1.15 / 1.28).
+  const bool three = L->prefill_groups > 2 * (int64_t)L->n_cus;
 #define HPD_LAUNCH_M(GG, PP)                                                                   \
   (narrow ? launch_g<GG, NarrowShape, PP>(a, items, q, k_prefix, v_prefix, nullptr, nullptr,  \
                                           nullptr, nullptr, out, s)                           \
-   : own ? launch_prefill<GG, PP == MODE_PREFILL_LIST>(a, items, q, k_prefix, v_prefix, out, s) \
+   : own ? launch_prefill<GG, PP == MODE_PREFILL_LIST>(a, items, three, q, k_prefix, v_prefix, out, s) \
           : launch_g<GG, WideShape, PP>(a, items, q, k_prefix, v_prefix, nullptr, nullptr,    \
                                         nullptr, nullptr, out, s))
 #define HPD_LAUNCH(GG) (list ? HPD_LAUNCH_M(GG, MODE_PREFILL_LIST) : HPD_LAUNCH_M(GG, MODE_PREFILL))

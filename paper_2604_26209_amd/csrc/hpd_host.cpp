@@ -234,6 +234,58 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
   }
 }
 
+// Row groups of attn_prefill_kernel, one record of 8 words each: the unit's descriptor with the row group's first token
+// in its last word.  The later a row group lies in its segment, the more keys it has.
+//  * Few row groups (up to 16 per CU; 2 or 3 run at a time): the longest of all first.  Against unit after unit (time before ->
+//    now, geometric means of random batches with that many row groups): 512-1000 1.25 -> 1.33, 1000-2000 1.21 -> 1.30, 2000-4000
+//    1.24 -> 1.26.
+//  * Up to two per CU: all start at once, the second half where the first one's workgroups are, in their order.  The shortest
+//    join each other - the longest of them the shortest -, and the longest have a CU to themselves: 1.05-1.17 -> 1.14-1.22
+//    (280 row groups of one prompt of 115 + 345 tokens, literal mask: 17.4 us -> 16.2).
+//  * More than 16: unit after unit, so that the row groups that run at a time read the same keys out of the L2 (all of 28000 row
+//    groups longest first: 3349 us, unit after unit 2078); the heaviest unit first, in each the longest row group first.
+// Workgroup b runs on XCD b % 8, and takes kv head b % Hkv of record b / Hkv: with fewer than 8 kv heads the records are dealt
+// to 8 / gcd(8, Hkv) lanes in turn, and the row groups of a unit stay in one lane, hence those of a (unit, kv head) on one XCD.
+void list_prefill_groups(hpd_layout* L, int32_t n_cus) {
+  const int32_t Gr = L->cfg.n_q_heads / L->cfg.n_kv_heads, Hkv = L->cfg.n_kv_heads;
+  if (L->cfg.dtype != HPD_BF16 || L->cfg.head_dim != 128 || Gr > 8) return;
+  const int32_t per = HPD_PREFILL_ROWS / (Gr <= 2 ? Gr : Gr <= 4 ? 4 : 8);  // tokens per row group
+  const bool list = L->cfg.mask_mode == HPD_MASK_PAPER;
+  const size_t n_units = L->funit_desc.size() / 8;
+  auto ceil_div = [](int32_t a, int32_t b) { return (a + b - 1) / b; };
+  for (size_t u = 0; u < n_units; ++u) L->prefill_groups += (int64_t)ceil_div(L->funit_desc[u * 8 + 5], per) * Hkv;
+  struct Item { int32_t blocks, unit, tok; };
+  struct Lane { std::vector<Item> items; int64_t load = 0; };
+  std::vector<Lane> lanes(8 / std::gcd(8, Hkv));
+  for (size_t u = 0; u < n_units; ++u) {
+    const int32_t* d = L->funit_desc.data() + u * 8;
+    Lane& to = *std::min_element(lanes.begin(), lanes.end(), [](const Lane& x, const Lane& y) { return x.load < y.load; });
+    for (int32_t t = (d[5] - 1) / per * per; t >= 0; t -= per) {
+      const int32_t blocks = (list ? d[1] : ceil_div(d[1], HPD_KEY_BLOCK)) + ceil_div(std::min(t + per, d[5]), HPD_KEY_BLOCK);
+      to.items.push_back({blocks, (int32_t)u, t});
+      to.load += blocks + 6;  // (its start and end take as long as about 6 blocks)
+    }
+  }
+  size_t most = 0;
+  for (Lane& l : lanes) {
+    if (L->prefill_groups <= 16 * (int64_t)n_cus)
+      std::stable_sort(l.items.begin(), l.items.end(), [](const Item& x, const Item& y) { return x.blocks > y.blocks; });
+    const size_t row = (size_t)n_cus / lanes.size() / Hkv, n = l.items.size();  // records of a lane for one workgroup on every CU
+    if (n > row && n <= 2 * row) {
+      std::reverse(l.items.begin() + row, l.items.end());
+      std::rotate(l.items.begin(), l.items.begin() + (2 * row - n), l.items.begin() + row);
+    }
+    most = std::max(most, l.items.size());
+  }
+  L->fgroup_desc.assign(most * lanes.size() * 8, 0);
+  for (size_t i = 0; i < lanes.size(); ++i)
+    for (size_t k = 0; k < lanes[i].items.size(); ++k) {
+      int32_t* o = L->fgroup_desc.data() + (k * lanes.size() + i) * 8;
+      std::copy_n(L->funit_desc.data() + (size_t)lanes[i].items[k].unit * 8, 8, o);
+      o[7] = lanes[i].items[k].tok;
+    }
+}
+
 // Copies a host vector into the device int arena and returns its device address.
 struct IntArena {
   std::vector<int32_t> host;
@@ -560,6 +612,8 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
       }
     }
 
+    list_prefill_groups(L, n_cus);
+
     // ---- for hpd_prefix_fill: which segment owns a 32-slot block of the pools, and where its
     //      first token sits in the input order
     {
@@ -635,7 +689,8 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
                  o_blen = A.add(L->branch_len), o_pblk = A.add(L->pblk), o_pdesc = A.add(L->punit_desc),
                  o_fdesc = A.add(L->funit_desc), o_spos = A.add(L->skel_pos), o_soff = A.add(L->skel_off),
                  o_sseg = A.add(L->skel_seg_off), o_scum = A.add(L->skel_cum), o_fblk = A.add(L->fblk),
-                 o_fill = A.add(L->fill_blk), o_dynfix = A.add(L->dyn_fixed), o_f32 = A.add(L->f32_groups);
+                 o_fill = A.add(L->fill_blk), o_dynfix = A.add(L->dyn_fixed), o_f32 = A.add(L->f32_groups),
+                 o_fgrp = A.add(L->fgroup_desc);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&L->n_cus, hipDeviceAttributeMultiprocessorCount, L->device);
@@ -665,6 +720,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
     L->dev.prompt_doc_ptr = base + o_pdp; L->dev.prompt_branch_ptr = base + o_pbp;
     L->dev.branch_len = base + o_blen; L->dev.pblk = base + o_pblk; L->dev.punit_desc = base + o_pdesc;
     L->dev.funit_desc = base + o_fdesc; L->dev.fblk = base + o_fblk;
+    L->dev.fgroup_desc = base + o_fgrp;
     L->dev.fill_blk = base + o_fill; L->dev.f32_groups = base + o_f32;
     L->dyn_fixed_dev = const_cast<int32_t*>(base) + o_dynfix;
     L->dev.skel_pos = paper_mode(L) ? base + o_spos : nullptr; L->dev.skel_off = base + o_soff;

@@ -40,6 +40,9 @@ struct hpd_dev_tables {
   const int32_t* skel_cum;      // [B] name tokens of the prompt's branches up to and including b
   // attention of the prefix tokens (block mask): one unit per non-empty header / document
   const int32_t* funit_desc;  // [n_funits][8] {hoff, Hlen (0 for a header), first slot, tokens, first token in q / out order, tokens, position ID of the first token, 0}
+  // row groups of attn_prefill_kernel, [..][8]: a unit's words and, last, the row group's first token in the segment;
+  // records without tokens fill up
+  const int32_t* fgroup_desc;
   // the same under the literal mask: one unit per non-empty header / document / names segment,
   // {first entry of the prompt in fblk, list blocks seen in full, first slot, tokens, first token in
   //  q / out order, tokens, position ID of the first token | -(1 + first entry in skel_pos), 0}
@@ -87,6 +90,8 @@ struct hpd_layout {
   int32_t max_prompt_branches = 0;
   std::vector<int32_t> skel_pos, skel_off, skel_seg_off, skel_cum;
   std::vector<int32_t> funit_desc;  // prefix-token attention units, heaviest first
+  std::vector<int32_t> fgroup_desc;  // row groups of attn_prefill_kernel
+  int64_t prefill_groups = 0;        // ... over all kv heads
   std::vector<int32_t> fblk;        // literal mask: header and document blocks of every prompt
   std::vector<int32_t> fill_blk;    // owner and first raw token of every 32-slot block of the prefix pools
   int32_t fmax_rows = 0;            // most tokens of any segment
@@ -140,6 +145,7 @@ hipError_t hpd_launch_finetune_mask(const int32_t* table, int32_t S, int32_t* po
 
 // fp32 decode attention (hpd_attn_f32.hip): block mask, 32, 64 or 128 channels; one row group of 16
 // rows holds the query heads of at least one branch; 16-byte loads from the pools.  kernel_mode 1 forces the generic kernel.
+constexpr int32_t HPD_PREFILL_ROWS = 128;  // query rows per workgroup of attn_prefill_kernel
 constexpr int32_t HPD_F32_ROWS = 16;
 constexpr int32_t HPD_F32_PAD = 4;  // floats between the rows of a wave's share of the result in LDS
 // waves of a workgroup: at most 16, and their tiles fit 128 of the 160 KB of LDS

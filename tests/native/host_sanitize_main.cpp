@@ -4,6 +4,7 @@
 // reported size, the host-side argument checks of the other entry points.  The kernel
 // launchers are stubbed out: nothing here may reach them.  Exit code 0 = no finding; a
 // sanitizer report aborts the program.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -94,6 +95,38 @@ static int32_t f32_waves(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t 
 
 // the steps of an even bf16 batch that run the kernel for many rows per unit: all of them, some, none
 enum { NONE = 0, SOME = 1, ALL = 2 };
+// attn_prefill_kernel's list: every row group of every segment once, with its segment's words; the row groups of a segment are
+// dealt to one XCD for every kv head (workgroup b: record b / Hkv, kv head b % Hkv, XCD b % 8)
+static void check_prefill_groups(const hpd_layout* L) {
+  const int32_t Hkv = L->cfg.n_kv_heads, Gr = L->cfg.n_q_heads / Hkv;
+  if (L->cfg.dtype != HPD_BF16 || L->cfg.head_dim != 128 || Gr > 8) {
+    CHECK(L->fgroup_desc.empty());
+    return;
+  }
+  const int32_t per = 128 / (Gr <= 2 ? Gr : Gr <= 4 ? 4 : 8);
+  const size_t n_units = L->funit_desc.size() / 8;
+  std::vector<std::vector<int>> seen(n_units), xcd(n_units, std::vector<int>(Hkv, -1));
+  int64_t n = 0;
+  for (size_t u = 0; u < n_units; ++u) seen[u].assign((L->funit_desc[u * 8 + 5] + per - 1) / per, 0);
+  for (size_t r = 0; r < L->fgroup_desc.size() / 8; ++r) {
+    const int32_t* d = L->fgroup_desc.data() + r * 8;
+    if (d[5] == 0) continue;
+    size_t u = 0;  // (a segment is told by its first pool slot and its kind)
+    while (u < n_units && !std::equal(d, d + 7, L->funit_desc.data() + u * 8)) ++u;
+    CHECK(u < n_units && d[7] % per == 0 && d[7] >= 0 && d[7] < d[5]);
+    ++seen[u][d[7] / per];
+    for (int32_t hk = 0; hk < Hkv; ++hk, ++n) {
+      int& x = xcd[u][hk];
+      const int now = (int)((r * Hkv + hk) % 8);
+      CHECK(x < 0 || x == now);
+      x = now;
+    }
+  }
+  for (auto& s : seen)
+    for (int c : s) CHECK(c == 1);
+  CHECK(n == L->prefill_groups);
+}
+
 static int dense_steps(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t P, int32_t header, int32_t J, std::vector<int32_t> doc,
                        std::vector<int32_t> branches, bool paper) {
   hpd_config cfg{};
@@ -118,6 +151,43 @@ static int dense_steps(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t P,
   for (uint8_t s : L->dense_steps) n += s;
   hpd_layout_free(L);
   return n == 0 ? NONE : n == T ? ALL : SOME;
+}
+
+// random batches of the bf16 kernels' shape, from fewer row groups than CUs to more than 16 per CU
+static void prefill_lists() {
+  std::mt19937 rng(30);
+  auto uni = [&](int lo, int hi) { return std::uniform_int_distribution<int>(lo, hi)(rng); };
+  int64_t fewest = 1 << 30, most = 0;
+  for (int iter = 0; iter < 60; ++iter) {
+    hpd_config cfg{};
+    const int hkvs[] = {1, 2, 3, 4, 6, 8, 12, 16};
+    cfg.n_kv_heads = hkvs[iter % 8]; cfg.n_q_heads = cfg.n_kv_heads * uni(1, 8);
+    cfg.head_dim = 128; cfg.dtype = HPD_BF16; cfg.rope_base = 500000.0; cfg.max_new = 2; cfg.flags = HPD_FLAG_HOST_ONLY;
+    const bool paper = iter % 3 == 0;
+    cfg.pos_mode = paper ? HPD_POS_PAPER_GAP : HPD_POS_CONTIG;
+    cfg.mask_mode = paper ? HPD_MASK_PAPER : HPD_MASK_BLOCK;
+    const int P = 1 << uni(0, 6), longest = 1 << uni(0, 11);
+    std::vector<int32_t> header, doc_ptr{0}, doc_len, branch_ptr{0}, attr;
+    doc_len.reserve(1);  // (so that its address is one without documents)
+    for (int p = 0; p < P; ++p) {
+      header.push_back(uni(0, 3) ? uni(1, 200) : 0);
+      for (int j = uni(0, 3); j > 0; --j) {
+        doc_len.push_back(uni(1, longest));
+        branch_ptr.push_back(branch_ptr.back() + uni(0, 3));
+      }
+      doc_ptr.push_back((int32_t)doc_len.size());
+    }
+    for (int32_t b = 0; b < branch_ptr.back(); ++b) attr.push_back(uni(1, 40));
+    attr.push_back(1);  // (so that its address is one where no branch is)
+    hpd_layout* L = nullptr;
+    CHECK(hpd_build_layout(&cfg, P, header.data(), doc_ptr.data(), doc_len.data(), branch_ptr.data(), nullptr,
+                           paper ? attr.data() : nullptr, nullptr, &L) == HPD_OK);
+    check_prefill_groups(L);
+    fewest = std::min(fewest, L->prefill_groups);
+    most = std::max(most, L->prefill_groups);
+    hpd_layout_free(L);
+  }
+  CHECK(fewest < 256 && most > 16 * 256);
 }
 
 int main() {
@@ -172,6 +242,7 @@ int main() {
     const size_t B = (size_t)c[HPD_C_N_BRANCHES], T = (size_t)cfg.max_new;
     const size_t n_seg = (size_t)P + doc_len.size() + (paper ? P : 0);
     check_f32_steps(L);
+    check_prefill_groups(L);
     query<int64_t>(L, HPD_Q_POOL_BYTES, 4);
     const auto n_live = query<int32_t>(L, HPD_Q_N_LIVE, T);
     int64_t total = 0;
@@ -229,6 +300,7 @@ int main() {
     hpd_layout_free(L);
   }
   CHECK(with_list >= 10);
+  prefill_lists();
   // short workgroups: four waves where all of them are at work at once, two where they queue up; a wave per tile and one
   // for the newest tokens where there are few workgroups
   CHECK(f32_waves(8, 2, 32, 1, 500, 5, 4) == 4);

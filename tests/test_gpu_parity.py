@@ -1014,6 +1014,26 @@ def test_prefill_attention_at_the_edges_of_its_blocks(g, literal):
 
 
 @pytest.mark.parametrize("literal", [False, True])
+@pytest.mark.parametrize("g,hkv", [(1, 16), (3, 6), (4, 8), (8, 3)])
+def test_prefill_attention_with_three_workgroups_per_cu(g, hkv, literal):
+    """The same edges in a launch of more than two row groups per CU, which runs rounds of one block; a number of kv heads
+    that is no multiple of 8 deals the row groups to several lanes."""
+    grp = 128 // (4 if g == 3 else g)
+    header, doc = [0, 1, 31, 32, 33, 64, 95], [1, grp, grp + 1, 31, 33, 2 * grp - 1, 32, 64, 65, 3 * grp + 5, 96, 1, 97]
+    per = [2, 1, 3, 2, 2, 1, 2]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    once = sum(-(-n // grp) for n in header + doc) * hkv
+    n = 2 * cus // once + 1
+    n_doc = len(doc) * n
+    attr = np.arange(n_doc).astype(np.int32) * 11 % 40 + 1 if literal else None
+    wl = W.make_workload("three", "bf16", g * hkv, hkv, 128, 500000.0, 2, header * n, per * n, doc * n, [1] * n_doc, [2] * n_doc)
+    _say(f"prefill three per CU G={g} hkv={hkv} literal={literal}: {wl.n_prefix_tokens} tokens, {once * n} row groups")
+    for change in (None, lambda q, k: (q * 8, k)):  # (and rows that a few keys dominate: the reference point moves often)
+        rel = _check_prefill(wl, 0, f"prefill_three_g{g}_{literal}", attr_len=attr, change=change)
+        _say(f"  worst err/rms {rel:.2e}")
+
+
+@pytest.mark.parametrize("literal", [False, True])
 @pytest.mark.parametrize("case", ["low", "very_low", "rising", "falling", "common_offset", "peaked_x8"])
 def test_prefill_score_ranges_of_the_online_softmax(case, literal):
     """Prefill scores other than those of N(0,1).  Every score of a row near -150 or near -1000 in log2
