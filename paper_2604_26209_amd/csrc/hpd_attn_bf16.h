@@ -9,13 +9,14 @@ struct StreamArgs {
   hpd_dev_tables tb;
   int32_t step, Hq, Hkv, Tcap, RG, n_groups, out_f32, fused, live_base;
   int32_t Gr;  // query heads per kv head; the kernel's G is the next power of two (padding rows are neither loaded nor stored)
+  int32_t at_once;  // attn_dense_kernel: all workgroups run at a time, if three per CU do
   int64_t NP;
   float scale_log2;
 };
 
 // decode attention of launches with many rows per unit (hpd_attn_dense.hip); G, max_nblk: the kernel's rows per branch,
-// the most row blocks of any unit
-hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32_t max_nblk, const void* q,
+// the most row blocks of any unit; workgroups: those that have rows
+hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32_t max_nblk, int32_t workgroups, int32_t n_cus, const void* q,
                                       const void* k_prefix, const void* v_prefix, void* k_tail, void* v_tail,
                                       const void* k_new, const void* v_new, void* out, hipStream_t s);
 

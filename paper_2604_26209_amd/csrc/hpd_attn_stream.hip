@@ -1271,7 +1271,6 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
     return first_bits(valid - g2 * 8) | (first_bits(valid - 16 - g2 * 8) << 8);
   };
   uint32_t at = 0;
-#pragma nounroll
   for (int32_t r = 0; r < r_plain; ++r) {
     open_round(r, at);
     const int32_t vA = keys_of(SB * r), vB = SB == 2 ? keys_of(2 * r + 1) : 32;
@@ -1281,7 +1280,6 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
     compute(std::integral_constant<int, SB>{}, at, masked, ok0, ok1);
     at = behind(at);
   }
-#pragma nounroll
   for (int32_t r = r_plain; r < NR; ++r) {
     open_round(r, at);
 #pragma nounroll
@@ -1441,7 +1439,7 @@ hipError_t hpd_launch_attention_stream(const hpd_layout* L, int32_t step, const 
   a.n_groups = (int32_t)(n_units * a.Hkv);
   // the plan is that of the layout's own lists; a launch on the device-side ones has the rows that are left by then
   const bool dense = !dynamic && (L->kernel_mode == 0 || L->kernel_mode == 2) && L->dense_steps[step];
-  if (dense) return hpd_launch_attention_dense(a, G, paper, max_nblk, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s);
+  if (dense) return hpd_launch_attention_dense(a, G, paper, max_nblk, L->dense_workgroups[step], L->n_cus, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s);
   const int64_t items = ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
 #define HPD_LAUNCH_M(GG, PP)                                                                            \
   (narrow ? launch_g<GG, NarrowShape, PP>(a, items, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s) \

@@ -164,6 +164,7 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
   const int32_t G = Gr <= 2 ? Gr : Gr <= 4 ? 4 : 8, BPB = 32 / G;  // rows per branch, branches per row block
   const bool paper = paper_mode(L);
   L->dense_steps.assign(L->T, 0);
+  L->dense_workgroups.assign(L->T, 0);
   auto ceil_div = [](int32_t a, int32_t b) { return (a + b - 1) / b; };
   for (int32_t t = 0; t < L->T; ++t) {
     const int32_t u0 = paper ? L->punit_ptr[t] : L->unit_ptr[t], n_units = (paper ? L->punit_ptr[t + 1] : L->unit_ptr[t + 1]) - u0;
@@ -230,6 +231,7 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
     const double us = std::max(0.255e-6 * bytes,  // 3.9 TB/s is all that it streams
                                wgs <= n_cus ? 0.75 * longest : wgs <= 2 * n_cus ? longest : sum / (2 * n_cus) + 0.5 * longest);
     const bool close = 5 * blocks >= 4 * (4 * wgs) && (!paper || (5 * seen <= 6 * rows && wgs > n_cus));
+    L->dense_workgroups[t] = (int32_t)std::min<int64_t>(wgs, std::numeric_limits<int32_t>::max());
     L->dense_steps[t] = old_us > 20 && us < (close ? 0.9 : paper ? 0.72 : 0.55) * old_us;
   }
 }

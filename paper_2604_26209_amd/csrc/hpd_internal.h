@@ -101,6 +101,7 @@ struct hpd_layout {
   std::vector<hpd_f32_step> f32_steps;  // [T], empty where the fp32 kernel does not apply
   std::vector<int32_t> f32_groups;      // [..][2]
   std::vector<uint8_t> dense_steps;     // [T] the step runs attn_dense_kernel; empty where it does not apply
+  std::vector<int32_t> dense_workgroups;  // [T] ... and the workgroups with rows that it has then
   std::vector<float> rope;        // host copy of the (cos, sin) table
 
   // device-side pruning: state built by dynamic_prune_kernel (one allocation, d_dyn)

@@ -276,6 +276,53 @@ def test_decode_of_many_rows_per_unit(g, literal):
 
 
 @pytest.mark.parametrize("literal", [False, True])
+@pytest.mark.parametrize("g,of_cus", [(1, 1.5), (8, 2.5), (3, 2.5), (8, 5), (1, 5)])
+def test_decode_of_many_rows_per_unit_by_workgroups_per_cu(g, of_cus, literal):
+    """The kernel for many rows per unit in launches of 1.5 workgroups per CU (two at a time), of 2.5 (three, priorities by
+    progress) and of 5 (three).  Documents of one token and around one block, row blocks that do not fill a workgroup, branches that
+    end, 21 steps: three chunks of tails, so that every piece of LDS that three workgroups per CU leave a wave holds keys and
+    values; pools of NaN.  Oracle, two-call sequence and pages of 8 tokens (the same bits), the other kernel."""
+    from paper_2604_26209_amd import binding as B
+    pad = 1 << (g - 1).bit_length()
+    hkv, steps, n = 8, 21, 8 * 32 // pad  # eight row blocks, the last not always full: two workgroups
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    prompts = int(of_cus * cus / (2 * hkv))
+    docs = [1] * prompts if literal else [2] * (prompts // 2)
+    header = [[0, 33, 64, 7, 95][i % 5] for i in range(len(docs))]
+    doc = [[1, 31, 64, 33, 97, 32][i % 6] for i in range(sum(docs))]
+    nbr = [n - i % 3 % 2 for i in range(sum(docs))]
+    blen = np.full(sum(nbr), steps)
+    blen[5::9] = 14
+    blen[7::11] = 18
+    attr = (1 + np.arange(sum(nbr)) % 4).astype(np.int32)
+    wl = W.make_workload("per_cu", "bf16", g * hkv, hkv, 128, 500000.0, steps, header, docs, doc, nbr, blen)
+    kw = dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=attr, mask_mode=B.HPD_MASK_PAPER) if literal else {}
+    okw = dict(pos_mode="paper_gap", attr_len=attr, mask_mode="paper") if literal else {}
+    _say(f"many rows per unit, {of_cus} workgroups per CU: G={g} literal={literal}, {wl.n_branches} branches")
+    a = H.run_hip(wl, fused=True, **kw)
+    H.check_all(wl, a, prompts=[0, len(docs) - 1], label=f"per_cu_g{g}_{literal}", **okw)
+    b = H.run_hip(wl, inputs=a["inputs"], **kw)
+    c = H.run_hip(wl, inputs=a["inputs"], fused=True, kernel_mode=3, **kw)
+    inputs = a["inputs"]
+    lay = B.layout_from_workload(wl, out_dtype=B.HPD_OUT_F32, **kw)
+    table = torch.from_numpy(np.random.default_rng(g).permutation(3 * wl.n_branches).astype(np.int32).reshape(-1, 3)).cuda()
+    B.hpd_set_tail_pages(lay, 8, 3 * wl.n_branches, table)
+    pools = [x.fill_(float("nan")) for x in B.alloc_pools(lay)]
+    B.hpd_prefix_fill(lay, inputs.k_raw, inputs.v_raw, pools[0], pools[1])
+    ran = []
+    for t, (x, y, z) in enumerate(zip(a["out"], b["out"], c["out"])):
+        assert torch.equal(x, y), f"step {t}: step call and two calls differ"
+        ran.append(not torch.equal(x, z))
+        # two roundings of queries and weights to 11 bits, of outputs of size 1
+        assert float((x - z).abs().max()) < H.BF16_TOL * float(x.square().mean().sqrt()), f"step {t}"
+        out = torch.zeros_like(x)
+        B.hpd_decode_step(lay, t, inputs.q[t], inputs.k_new[t], inputs.v_new[t], *pools, out)
+        assert torch.equal(out, x), f"step {t}: paged and contiguous outputs differ"
+    _say(f"  steps that ran it: {[t for t, r in enumerate(ran) if r]}")
+    assert sum(ran) >= 3
+
+
+@pytest.mark.parametrize("literal", [False, True])
 def test_decode_of_many_rows_per_unit_takes_no_longer_through_a_page_table(literal):
     """Steps with a long tail that run the kernel for many rows per unit: the page table's entries are there when a tile is
     requested.  Looked up at that time they made these steps take 1.44 and 1.55 times as long; 1.2 is well above what two
