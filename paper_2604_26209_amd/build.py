@@ -13,6 +13,8 @@ SOURCES = ["hpd_host.cpp", "hpd_kernels.hip", "hpd_attn_stream.hip", "hpd_attn_d
 # packed fp32 instructions are switched off for all device code
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first arguments of a kernel are in registers when it starts: what its first lookup needs stands in front
+         "-mllvm", "-amdgpu-kernarg-preload-count=8",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]
 
 

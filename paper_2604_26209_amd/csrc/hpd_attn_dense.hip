@@ -72,7 +72,8 @@ struct MinusPoint<3> {
 
 template <int G, bool PAPER, bool PAGED, int WGS>
 __global__ void __launch_bounds__(DENSE_WAVES * 64, WGS)
-attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
+attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t row_groups, int32_t kv_heads, StreamArgs a,
+                  const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
                   const uint16_t* __restrict__ v_prefix, uint16_t* __restrict__ k_tail, uint16_t* __restrict__ v_tail,
                   const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, void* __restrict__ out) {
   constexpr int BPB = 32 / G;  // branches per row block (wave)
@@ -99,11 +100,11 @@ attn_dense_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* 
   const int n = lane & 31, g2 = lane >> 5, r4 = lane >> 4, c16 = lane & 15;
   // (unit, kv head) and row group of this workgroup, and the unit's descriptor: as in attn_stream_kernel
   if (WGS == 3 && a.at_once) __builtin_amdgcn_s_setprio(3);
-  const int32_t rg = a.RG - 1 - (blockIdx.x >> 3) % a.RG;
-  const int32_t grp = ((blockIdx.x >> 3) / a.RG) * 8 + (blockIdx.x & 7);
-  if (grp >= a.n_groups) return;
-  const int32_t hk = grp % a.Hkv, u = grp / a.Hkv;
-  const int32_t* desc = (PAPER ? a.tb.punit_desc : a.tb.unit_desc) + (int64_t)u * (PAPER ? 16 : 8);
+  const int32_t rg = row_groups - 1 - (blockIdx.x >> 3) % row_groups;
+  const int32_t grp = ((blockIdx.x >> 3) / row_groups) * 8 + (blockIdx.x & 7);
+  if (grp >= n_groups) return;
+  const int32_t hk = grp % kv_heads, u = grp / kv_heads;
+  const int32_t* desc = descs + (int64_t)u * (PAPER ? 16 : 8);
   const int32_t hoff = desc[0], Hlen = desc[1], doff = desc[2], Llen = desc[3];
   const int32_t row0 = desc[4], nb = desc[5], upos = PAPER ? -1 : desc[6], ub0 = desc[7];
   const int32_t pb0 = PAPER ? desc[6] : 0;
@@ -835,11 +836,11 @@ hipError_t launch_dense(const StreamArgs& a, int64_t items, bool three, const vo
                         void* k_tail, void* v_tail, const void* k_new, const void* v_new, void* out, hipStream_t s) {
   if (three)
     attn_dense_kernel<G, PAPER, PAGED, 3><<<dim3((unsigned)items), DENSE_WAVES * 64, 0, s>>>(
-        a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail,
+        PAPER ? a.tb.punit_desc : a.tb.unit_desc, a.n_groups, a.RG, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail,
         (const uint16_t*)k_new, (const uint16_t*)v_new, out);
   else
     attn_dense_kernel<G, PAPER, PAGED, 2><<<dim3((unsigned)items), DENSE_WAVES * 64, 0, s>>>(
-        a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail,
+        PAPER ? a.tb.punit_desc : a.tb.unit_desc, a.n_groups, a.RG, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail,
         (const uint16_t*)k_new, (const uint16_t*)v_new, out);
   return hipGetLastError();
 }

@@ -22,6 +22,7 @@
 //    operand layout.  A load straight into operand layout has its 16 rows in 16 consecutive lanes: the memory pipeline
 //    takes such an instruction apart lane by lane (82 cycles each were measured, for data in the L2; whole rows 16),
 //    and 250 KB of K and V took 10 us;
+//  * what the descriptor's lookup takes are the first arguments, in registers when the kernel starts (11.4 -> 11.1 us);
 //  * a wave requests its first tile as soon as it has the unit's descriptor, in front of the query, and the
 //    next tile as soon as it has read the one it works on;
 //  * the query is rotated once, by all waves together, and shared through LDS (in operand layout from memory in every
@@ -105,9 +106,9 @@ __device__ __forceinline__ void dma_dword(uint32_t lds, const float* p) {  // 25
 
 template <int D>
 __global__ void __launch_bounds__(hpd_f32_max_waves(D) * 64, D == 32 ? 6 : D == 64 ? 4 : 2)
-attention_f32_kernel(hpd_dev_tables tb, const int32_t* __restrict__ units, const int32_t* __restrict__ live,
-                     const int2* __restrict__ groups, int32_t step, uint32_t step_magic, int32_t Hq, int32_t Hkv, int32_t G,
-                     uint32_t g_magic, int32_t Tcap, int32_t group0, int32_t n_groups, int32_t BPG, int64_t NP,
+attention_f32_kernel(const int32_t* __restrict__ units, const int2* __restrict__ groups, int32_t group0, int32_t width, int32_t n_groups, int32_t Hkv,
+                     int32_t BPG, hpd_dev_tables tb, const int32_t* __restrict__ live, int32_t step, uint32_t step_magic, int32_t Hq,
+                     int32_t G, uint32_t g_magic, int32_t Tcap, int64_t NP,
                      const float* __restrict__ q, const float* __restrict__ k_prefix,
                      const float* __restrict__ v_prefix, float* k_tail, float* v_tail,
                      const float* __restrict__ k_new, const float* __restrict__ v_new, float* __restrict__ out) {
@@ -123,7 +124,7 @@ attention_f32_kernel(hpd_dev_tables tb, const int32_t* __restrict__ units, const
 
   // BPG branches per row group; unit and row group from the list if the step has one, otherwise from the workgroup's
   // number (it runs on XCD number % 8)
-  const int32_t item = (group0 + blockIdx.z) * gridDim.x + blockIdx.x;
+  const int32_t item = (group0 + blockIdx.z) * width + blockIdx.x;
   if (item >= n_groups) return;  // the grid is padded to a multiple of 8 (unit, kv head)
   const int32_t hk = item % Hkv;
   int32_t u = item / Hkv, rg = blockIdx.y;
@@ -484,8 +485,9 @@ hipError_t launch(const hpd_layout* L, int32_t step, const void* q, const void* 
   for (int64_t z = 0; z < layers; z += 65535) {
     attention_f32_kernel<D><<<dim3(in_turn ? (unsigned)n_groups : 8u, (unsigned)rg, (unsigned)std::min<int64_t>(layers - z, 65535)),
                               st.waves * 64, lds, s>>>(
-        L->dev, L->dev.unit_desc + (int64_t)L->unit_ptr[step] * 8, L->dev.live_branch + L->live_ptr[step], groups, step, magic,
-        Hq, Hkv, G, (uint32_t)(256 + G - 1) / G, L->T, (int32_t)z, (int32_t)n_groups, st.per_group, L->NP, (const float*)q,
+        L->dev.unit_desc + (int64_t)L->unit_ptr[step] * 8, groups, (int32_t)z, in_turn ? (int32_t)n_groups : 8, (int32_t)n_groups, Hkv,
+        st.per_group, L->dev, L->dev.live_branch + L->live_ptr[step], step, magic, Hq, G, (uint32_t)(256 + G - 1) / G, L->T, L->NP,
+        (const float*)q,
         (const float*)k_prefix, (const float*)v_prefix, (float*)k_tail, (float*)v_tail, (const float*)k_new,
         (const float*)v_new, (float*)out);
     const hipError_t e = hipGetLastError();

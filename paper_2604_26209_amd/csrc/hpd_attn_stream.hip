@@ -123,7 +123,8 @@ using NarrowShape = Shape<3, 1, 1>;
 // attn_prefill_kernel.)
 template <int G, typename SH, int MODE>
 __global__ void __launch_bounds__(SH::WAVES * 64, 2)
-attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
+attn_stream_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t row_groups, int32_t kv_heads, StreamArgs a,
+                   const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
                    const uint16_t* __restrict__ v_prefix, uint16_t* __restrict__ k_tail,
                    uint16_t* __restrict__ v_tail, const uint16_t* __restrict__ k_new,
                    const uint16_t* __restrict__ v_new, void* __restrict__ out) {
@@ -158,11 +159,11 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
   // Workgroup b runs on XCD b % 8, and every XCD has an L2 of its own: the row groups of one
   // (unit, kv head), which stream the same prefix, get indices 8 apart - same XCD, dispatched
   // together - so that the second one finds the blocks in that L2.
-  const int32_t rg = (blockIdx.x >> 3) % a.RG;
-  const int32_t grp = ((blockIdx.x >> 3) / a.RG) * 8 + (blockIdx.x & 7);  // (unit, kv head)
-  if (grp >= a.n_groups) return;  // the grid is padded to a multiple of 8 groups
-  const int32_t hk = grp % a.Hkv;
-  const int32_t u = grp / a.Hkv;
+  const int32_t rg = (blockIdx.x >> 3) % row_groups;
+  const int32_t grp = ((blockIdx.x >> 3) / row_groups) * 8 + (blockIdx.x & 7);  // (unit, kv head)
+  if (grp >= n_groups) return;  // the grid is padded to a multiple of 8 groups
+  const int32_t hk = grp % kv_heads;
+  const int32_t u = grp / kv_heads;
   // PAPER: {hoff, Hlen, first entry of the prompt's block list, document blocks, first live
   //         row, live branches, first branch of the prompt, first live branch | -1, key branches,
   //         document blocks that are no attribute names}
@@ -170,8 +171,7 @@ attn_stream_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t*
   //         token in the order of q / out, tokens again, position ID of the first token, 0}
   // PLIST:  {first entry of the prompt's block list, list blocks the segment sees in full, then
   //         as PREFILL; for the names the position entry is -(1 + first entry in skel_pos)}
-  const int32_t* desc = (PAPER ? a.tb.punit_desc : PREFILL ? a.tb.funit_desc : a.tb.unit_desc) +
-                        (int64_t)u * (PAPER ? 16 : 8);  // pre-offset to this step by the host
+  const int32_t* desc = descs + (int64_t)u * (PAPER ? 16 : 8);
   const int32_t hoff = desc[0], Hlen = desc[1], doff = desc[2], Llen = desc[3];
   const int32_t row0_live = desc[4], nb = desc[5], upos = (PAPER || PREFILL) ? -1 : desc[6], ub0 = desc[7];
   const int32_t pb0 = PAPER ? desc[6] : 0;
@@ -1033,7 +1033,7 @@ constexpr int PREFILL_WAVES = HPD_PREFILL_ROWS / 32;  // row blocks per workgrou
 // WGS = workgroups per CU
 template <int G, bool LIST, int WGS>
 __global__ void __launch_bounds__(PREFILL_WAVES * 64, WGS)
-attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
+attn_prefill_kernel(const int32_t* __restrict__ descs, int32_t kv_heads, StreamArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_prefix,
                     const uint16_t* __restrict__ v_prefix, void* __restrict__ out) {
   constexpr int BPB = 32 / G;       // tokens per row block (wave)
   constexpr int TPG = PREFILL_WAVES * BPB;      // tokens per row group (workgroup)
@@ -1048,8 +1048,8 @@ attn_prefill_kernel(StreamArgs a, const uint16_t* __restrict__ q, const uint16_t
   const int n = lane & 31, g2 = lane >> 5, r4 = lane >> 4, c16 = lane & 15;
   // row group and kv head of this workgroup.  Workgroup b runs on XCD b % 8; the list keeps the row groups of one (unit,
   // kv head), which read the same keys, on one of them.
-  const int32_t hk = blockIdx.x % a.Hkv, entry = blockIdx.x / a.Hkv;
-  const int32_t* desc = a.tb.fgroup_desc + (int64_t)entry * 8;
+  const int32_t hk = blockIdx.x % kv_heads, entry = blockIdx.x / kv_heads;
+  const int32_t* desc = descs + (int64_t)entry * 8;
   const int32_t hoff = desc[0], Hlen = desc[1], doff = desc[2], row0 = desc[4], n_seg_tok = desc[5], seg_pos0 = desc[6];
   const int32_t tok0 = desc[7];  // first token of the row group, counted in the segment
   if (n_seg_tok == 0) return;    // uniform over the workgroup
@@ -1360,8 +1360,9 @@ template <int G, typename SH, int MODE>
 hipError_t launch_g(const StreamArgs& a, int64_t items, const void* q, const void* k_prefix,
                     const void* v_prefix, void* k_tail, void* v_tail, const void* k_new,
                     const void* v_new, void* out, hipStream_t s) {
+  const int32_t* descs = MODE == MODE_PAPER ? a.tb.punit_desc : MODE == MODE_PREFILL || MODE == MODE_PREFILL_LIST ? a.tb.funit_desc : a.tb.unit_desc;
   attn_stream_kernel<G, SH, MODE><<<dim3((unsigned)items), SH::WAVES * 64, 0, s>>>(
-      a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail,
+      descs, a.n_groups, a.RG, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail,
       (uint16_t*)v_tail, (const uint16_t*)k_new, (const uint16_t*)v_new, out);
   return hipGetLastError();
 }
@@ -1371,10 +1372,10 @@ hipError_t launch_prefill(const StreamArgs& a, int64_t items, bool three, const 
                           const void* v_prefix, void* out, hipStream_t s) {
   if (three)
     attn_prefill_kernel<G, LIST, 3><<<dim3((unsigned)items), PREFILL_WAVES * 64, 0, s>>>(
-        a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
+        a.tb.fgroup_desc, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
   else
     attn_prefill_kernel<G, LIST, 2><<<dim3((unsigned)items), PREFILL_WAVES * 64, 0, s>>>(
-        a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
+        a.tb.fgroup_desc, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, out);
   return hipGetLastError();
 }
 
