@@ -238,12 +238,12 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
 
 // Row groups of attn_prefill_kernel, one record of 8 words each: the unit's descriptor with the row group's first token
 // in its last word.  The later a row group lies in its segment, the more keys it has.
-//  * Few row groups (up to 16 per CU; 2 or 3 run at a time): the longest of all first.  Against unit after unit (time before ->
-//    now, geometric means of random batches with that many row groups): 512-1000 1.25 -> 1.33, 1000-2000 1.21 -> 1.30, 2000-4000
-//    1.24 -> 1.26.
+//  * Few row groups (up to 16 per CU; 2 or 3 run at a time): the longest of all first.  Times the speed of a grid of (unit, row
+//    groups of the longest segment), unit after unit / longest first, geometric means of random batches with that many row
+//    groups: 512-1000 1.25 / 1.33, 1000-2000 1.21 / 1.30, 2000-4000 1.24 / 1.26.
 //  * Up to two per CU: all start at once, the second half where the first one's workgroups are, in their order.  The shortest
-//    join each other - the longest of them the shortest -, and the longest have a CU to themselves: 1.05-1.17 -> 1.14-1.22
-//    (280 row groups of one prompt of 115 + 345 tokens, literal mask: 17.4 us -> 16.2).
+//    join each other - the longest of them the shortest -, and the longest have a CU to themselves: longest first 1.05-1.17, so
+//    1.14-1.22 (280 row groups of one prompt of 115 + 345 tokens, literal mask: 17.4 us, so 16.2).
 //  * More than 16: unit after unit, so that the row groups that run at a time read the same keys out of the L2 (all of 28000 row
 //    groups longest first: 3349 us, unit after unit 2078); the heaviest unit first, in each the longest row group first.
 // Workgroup b runs on XCD b % 8, and takes kv head b % Hkv of record b / Hkv: with fewer than 8 kv heads the records are dealt
