@@ -156,7 +156,8 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
 // three quarters: with the tenth there, about 300 more of the 3200 batches would run it under the block mask, 1.37 times as
 // fast in the mean, but one in ten of them slower, down to 0.70.  And a launch estimated at 20 us or less is latency in either kernel.
 // Measured over 2800 other batches for which the rule takes it (4 .. 400 branches, 1 .. 6 documents of up to 4000 tokens, 1 ..
-// 160 prompts, even, ragged and with branches that end, up to 256 steps, contiguous and paged tails, either mask): 1.41 times
+// 160 prompts, even, ragged and with branches that end, up to 256 steps, contiguous and paged tails, either mask; two workgroups
+// per CU in every launch, as for the fit: what the third adds from 512 workgroups on is left as margin): 1.41 times
 // the speed in the mean, up to 3.28; 26 of them slower, 14 by more than 3 %, the slowest 63 us instead of 52.
 void plan_dense(hpd_layout* L, int32_t n_cus) {
   const int32_t Hkv = L->cfg.n_kv_heads, Gr = L->cfg.n_q_heads / Hkv;
