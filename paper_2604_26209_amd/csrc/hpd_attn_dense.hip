@@ -859,7 +859,9 @@ hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32
   // 0.98 / 0.90, 512-768 0.98 / 1.04 | 0.99 / 1.09, 768-1024 0.98 / 0.95 | 0.98 / 0.97, 1024-3000 0.98 / 1.03 | 0.99 / 1.08,
   // more 0.99 / 1.07 | 1.00 / 1.09.
   const int64_t cu = n_cus;
-  const bool three = (workgroups > 2 * cu && workgroups <= 3 * cu) || workgroups > 4 * cu;
+  // In the first of these the grid has to have few workgroups without rows, which upset where the others go (three / two per CU,
+  // 512-768 workgroups: up to 1.3 times as many in the grid 1.17, more 1.02, down to 0.86).
+  const bool three = (workgroups > 2 * cu && workgroups <= 3 * cu && 4 * items <= 5 * (int64_t)workgroups) || workgroups > 4 * cu;
   a.at_once = workgroups <= 3 * cu;
 #define HPD_DENSE_M(GG, PP, TT) launch_dense<GG, PP, TT>(a, items, three, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s)
 #define HPD_DENSE(GG)                                                                   \
