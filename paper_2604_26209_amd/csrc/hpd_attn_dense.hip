@@ -8,7 +8,10 @@
 //  * Two or three workgroups per CU (WGS; the rule is at the launch), as in the prefill: rounds of two blocks and a ring of four, or
 //    rounds of one block, a ring of three, 168 registers.  For those what only the tails need of a lane is formed behind the prefix
 //    (again()), a row's branch waits in LDS, a tile's values are read 16 keys at a time, and the start value of the scores is
-//    two registers (MinusPoint).
+//    two registers (MinusPoint).  No register may be left over for scratch memory: the compiler does not see the loads that are
+//    written out, so at a reload the wave waits for all of them.  One to eight registers there, four in the loop over a wave's own
+//    tiles (16/8 heads) and one in the loop over the tiles of the literal mask, cost 1.6 % in the mean of 1131 random batches, 16/8
+//    heads 4 %.
 //  * Launches that run all at a time: a wave lowers its priority as it goes.  With equal ones the oldest workgroup of a CU is always
 //    served first and the last is left alone for the last fifth of the launch (16 x 2 documents below: 145.7 -> 131.4 us from
 //    the first wave to the last); where workgroups follow each other the same costs 3 %.
@@ -688,7 +691,8 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
         if (x.tb0 > kb_row_max) continue;
         later = x.tb0 + (31 >> x.lg) > kb_row_min;
         // a row keeps the tokens in memory of the branches up to its own
-        const int32_t j_lane = x.tb0 + (n >> x.lg);
+        const int lane_t = again(lane), g2 = lane_t >> 5;
+        const int32_t j_lane = x.tb0 + ((lane_t & 31) >> x.lg);
         masked = !__all(j_lane <= kb_row_min && klen[min(j_lane, kb_end - 1)] - x.c * 8 >= 1 << x.lg);
         if (masked) {
 #pragma nounroll
@@ -776,6 +780,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   }
 
   // ---- normalise and write: as the waves of attn_stream_kernel that hold whole rows
+  const int lane_o = again(lane), n_o = lane_o & 31, g2_o = lane_o >> 5;
   const float inv = 1.0f / (l_lane + __shfl_xor(l_lane, 32));
   uint4* const mine = reinterpret_cast<uint4*>(reinterpret_cast<char*>(ring) + my_free);  // 8 KB
   typedef uint32_t u4v __attribute__((ext_vector_type(4)));
@@ -783,20 +788,20 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   if (a.out_f32) {
 #pragma nounroll
     for (int half = 0; half < 2; ++half) {  // 16 rows at a time
-      if (n >> 4 == half) {
-        float4* rowp = reinterpret_cast<float4*>(mine) + (n & 15) * 32;
+      if (n_o >> 4 == half) {
+        float4* rowp = reinterpret_cast<float4*>(mine) + (n_o & 15) * 32;
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
           for (int cc = 0; cc < 4; ++cc)
-            rowp[(blk * 8 + cc * 2 + g2) ^ n] = make_float4(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv,
+            rowp[(blk * 8 + cc * 2 + g2_o) ^ n_o] = make_float4(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv,
                                                             acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv);
       }
       __builtin_amdgcn_s_waitcnt(0xc07f);
       __builtin_amdgcn_wave_barrier();
 #pragma unroll 4
       for (int32_t i = 0; i < 8; ++i) {  // 2 rows per instruction
-        const int32_t rr = half * 16 + i * 2 + (lane >> 5), chunk = lane & 31, lrr = wave * 32 + rr;
+        const int32_t rr = half * 16 + i * 2 + (lane_o >> 5), chunk = lane_o & 31, lrr = wave * 32 + rr;
         if (lrr < rows_here && lrr % G < a.Gr) {
           const uint4 v = mine[(rr & 15) * 32 + (chunk ^ rr)];
           const int64_t off = ((int64_t)(row0 + br0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 4;
@@ -808,19 +813,19 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
       __builtin_amdgcn_wave_barrier();
     }
   } else {
-    uint2* rowp = reinterpret_cast<uint2*>(mine) + n * 32;
+    uint2* rowp = reinterpret_cast<uint2*>(mine) + n_o * 32;
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
       for (int cc = 0; cc < 4; ++cc)
-        rowp[(((blk * 4 + cc) ^ (n & 15)) << 1) | g2] =
+        rowp[(((blk * 4 + cc) ^ (n_o & 15)) << 1) | g2_o] =
             make_uint2(cvt_pk_bf16(acc[blk][cc * 4 + 0] * inv, acc[blk][cc * 4 + 1] * inv),
                        cvt_pk_bf16(acc[blk][cc * 4 + 2] * inv, acc[blk][cc * 4 + 3] * inv));
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_wave_barrier();
 #pragma unroll 4
     for (int32_t i = 0; i < 8; ++i) {  // 4 rows per instruction
-      const int32_t rr = i * 4 + (lane >> 4), chunk = lane & 15, lrr = wave * 32 + rr;
+      const int32_t rr = i * 4 + (lane_o >> 4), chunk = lane_o & 15, lrr = wave * 32 + rr;
       if (lrr < rows_here && lrr % G < a.Gr) {
         const uint4 v = mine[rr * 16 + (chunk ^ (rr & 15))];
         const int64_t off = ((int64_t)(row0 + br0 + lrr / G) * a.Hq + hk * a.Gr + lrr % G) * D + chunk * 8;

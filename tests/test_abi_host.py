@@ -4,6 +4,7 @@ import ctypes
 import importlib.util
 import os
 import re
+import struct
 import time
 import types
 
@@ -34,6 +35,28 @@ def test_library_exports_every_declared_symbol():
     for name in peaks:
         assert hasattr(lib, name), name
     assert sorted(f for f in os.listdir(os.path.join(ROOT, "include")) if f.endswith(".h")) == ["hpd.h", "hpd_peaks.h"]
+
+
+def _kernel_metadata(path):
+    """The records of the kernels in a library: the note that the compiler leaves in each of its GPU code objects."""
+    msgpack = pytest.importorskip("msgpack")
+    data, at, name = open(path, "rb").read(), 0, b"AMDGPU\0\0"
+    while (at := data.find(name, at)) >= 0:
+        name_size, size, kind = struct.unpack_from("<III", data, at - 12)
+        at += len(name)
+        if (name_size, kind) == (7, 32):
+            yield from msgpack.unpackb(data[at:at + size])["amdhsa.kernels"]
+
+
+def test_kernels_keep_no_registers_in_scratch_memory():
+    """The compiler does not see the loads that the attention kernels write out, so where it reloads a register inside their
+    loops it waits for all of them."""
+    kernels = list(_kernel_metadata(B.LIB_PATH))
+    for part in ("attn_dense_kernel", "attn_prefill_kernel", "attn_stream_kernel", "attention_f32_kernel"):
+        assert any(part in k[".name"] for k in kernels), part
+    spilled = [(k[".name"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in kernels
+               if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]]
+    assert not spilled
 
 
 def _host_layout(wl, pos_mode=B.HPD_POS_CONTIG, attr_len=None):
