@@ -249,6 +249,10 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
 //    groups longest first: 3349 us, unit after unit 2078); the heaviest unit first, in each the longest row group first.
 // Workgroup b runs on XCD b % 8, and takes kv head b % Hkv of record b / Hkv: with fewer than 8 kv heads the records are dealt
 // to 8 / gcd(8, Hkv) lanes in turn, and the row groups of a unit stay in one lane, hence those of a (unit, kv head) on one XCD.
+// More than 16 row groups per CU are written straight to their places; collected and copied twice, they made building slower by up to a
+// third.  What is left is one pass over the memory (ms of hpd_build_layout, without the list -> collected -> so: 256 x 2 x 4000
+// tokens, 64/8 heads 3.97 -> 4.52 -> 4.18; 1000 x 4 x 500, 32/8 heads 1.20 -> 1.57 -> 1.24; that one has the sorting of the documents
+// once instead of once per step in its favour).
 void list_prefill_groups(hpd_layout* L, int32_t n_cus) {
   const int32_t Gr = L->cfg.n_q_heads / L->cfg.n_kv_heads, Hkv = L->cfg.n_kv_heads;
   if (L->cfg.dtype != HPD_BF16 || L->cfg.head_dim != 128 || Gr > 8) return;
@@ -256,37 +260,64 @@ void list_prefill_groups(hpd_layout* L, int32_t n_cus) {
   const bool list = L->cfg.mask_mode == HPD_MASK_PAPER;
   const size_t n_units = L->funit_desc.size() / 8;
   auto ceil_div = [](int32_t a, int32_t b) { return (a + b - 1) / b; };
-  for (size_t u = 0; u < n_units; ++u) L->prefill_groups += (int64_t)ceil_div(L->funit_desc[u * 8 + 5], per) * Hkv;
-  struct Item { int32_t blocks, unit, tok; };
-  struct Lane { std::vector<Item> items; int64_t load = 0; };
+  auto unit = [&](size_t u) { return L->funit_desc.data() + u * 8; };
+  auto groups = [&](size_t u) { return ceil_div(unit(u)[5], per); };
+  auto seen_in_full = [&](size_t u) { return list ? unit(u)[1] : ceil_div(unit(u)[1], HPD_KEY_BLOCK); };  // blocks
+  struct Lane { int64_t load = 0, n = 0; };
   std::vector<Lane> lanes(8 / std::gcd(8, Hkv));
+  std::vector<uint8_t> lane_of(lanes.size() > 1 ? n_units : 0);
   for (size_t u = 0; u < n_units; ++u) {
-    const int32_t* d = L->funit_desc.data() + u * 8;
-    Lane& to = *std::min_element(lanes.begin(), lanes.end(), [](const Lane& x, const Lane& y) { return x.load < y.load; });
-    for (int32_t t = (d[5] - 1) / per * per; t >= 0; t -= per) {
-      const int32_t blocks = (list ? d[1] : ceil_div(d[1], HPD_KEY_BLOCK)) + ceil_div(std::min(t + per, d[5]), HPD_KEY_BLOCK);
-      to.items.push_back({blocks, (int32_t)u, t});
-      to.load += blocks + 6;  // (its start and end take as long as about 6 blocks)
+    size_t to = 0;
+    if (!lane_of.empty()) {
+      for (size_t i = 1; i < lanes.size(); ++i)
+        if (lanes[i].load < lanes[to].load) to = i;
+      lane_of[u] = (uint8_t)to;
+      // the blocks of all row groups; a row group's start and end take as long as about 6
+      const int64_t m = groups(u) - 1;  // full ones: 1, 1, 2, 2 .. own blocks with 16 tokens each, else multiples of per / 32
+      lanes[to].load += (m + 1) * (seen_in_full(u) + 6) + ceil_div(unit(u)[5], HPD_KEY_BLOCK) +
+                        (per < HPD_KEY_BLOCK ? (m + 1) * (m + 1) / 4 : per / HPD_KEY_BLOCK * (m * (m + 1) / 2));
     }
+    lanes[to].n += groups(u);
   }
-  size_t most = 0;
-  for (Lane& l : lanes) {
-    if (L->prefill_groups <= 16 * (int64_t)n_cus)
-      std::stable_sort(l.items.begin(), l.items.end(), [](const Item& x, const Item& y) { return x.blocks > y.blocks; });
-    const size_t row = (size_t)n_cus / lanes.size() / Hkv, n = l.items.size();  // records of a lane for one workgroup on every CU
+  int64_t most = 0, all = 0;
+  for (const Lane& l : lanes) {
+    most = std::max(most, l.n);
+    all += l.n;
+  }
+  L->prefill_groups = all * Hkv;
+  L->fgroup_desc.resize(most * lanes.size() * 8);
+  auto put = [&](size_t lane, size_t k, size_t u, int32_t tok) {
+    int32_t* o = L->fgroup_desc.data() + (k * lanes.size() + lane) * 8;
+    std::copy_n(unit(u), 7, o);
+    o[7] = tok;
+  };
+  auto lane = [&](size_t u) -> size_t { return lane_of.empty() ? 0 : lane_of[u]; };
+  if (L->prefill_groups > 16 * (int64_t)n_cus) {  // many: every record straight to its place
+    std::vector<int32_t*> next(lanes.size());
+    for (size_t i = 0; i < lanes.size(); ++i) next[i] = L->fgroup_desc.data() + i * 8;
+    for (size_t u = 0; u < n_units; ++u) {
+      int32_t d[8], *o = next[lane(u)];
+      std::copy_n(unit(u), 8, d);
+      for (d[7] = (groups(u) - 1) * per; d[7] >= 0; d[7] -= per, o += lanes.size() * 8) std::memcpy(o, d, sizeof(d));
+      next[lane(u)] = o;
+    }
+    return;
+  }
+  struct Item { int32_t blocks, unit, tok; };
+  std::vector<Item> items;
+  for (size_t i = 0; i < lanes.size(); ++i) {
+    items.clear();
+    for (size_t u = 0; u < n_units; ++u)
+      for (int32_t t = (groups(u) - 1) * per; t >= 0 && lane(u) == i; t -= per)
+        items.push_back({seen_in_full(u) + ceil_div(std::min(t + per, unit(u)[5]), HPD_KEY_BLOCK), (int32_t)u, t});
+    std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.blocks > y.blocks; });
+    const size_t row = (size_t)n_cus / lanes.size() / Hkv, n = items.size();  // records of a lane for one workgroup on every CU
     if (n > row && n <= 2 * row) {
-      std::reverse(l.items.begin() + row, l.items.end());
-      std::rotate(l.items.begin(), l.items.begin() + (2 * row - n), l.items.begin() + row);
+      std::reverse(items.begin() + row, items.end());
+      std::rotate(items.begin(), items.begin() + (2 * row - n), items.begin() + row);
     }
-    most = std::max(most, l.items.size());
+    for (size_t k = 0; k < n; ++k) put(i, k, items[k].unit, items[k].tok);
   }
-  L->fgroup_desc.assign(most * lanes.size() * 8, 0);
-  for (size_t i = 0; i < lanes.size(); ++i)
-    for (size_t k = 0; k < lanes[i].items.size(); ++k) {
-      int32_t* o = L->fgroup_desc.data() + (k * lanes.size() + i) * 8;
-      std::copy_n(L->funit_desc.data() + (size_t)lanes[i].items[k].unit * 8, 8, o);
-      o[7] = lanes[i].items[k].tok;
-    }
 }
 
 // Copies a host vector into the device int arena and returns its device address.
@@ -460,28 +491,26 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
     L->doc_live_ptr.assign((size_t)T * (n_docs + 1), 0);
     L->unit_ptr.assign(T + 1, 0);
     L->max_rows.assign(T, 0);
+    // heaviest documents first: cost ~ keys streamed
+    std::vector<int64_t> doc_keys(n_docs);
+    for (int32_t d = 0; d < n_docs; ++d) doc_keys[d] = (int64_t)header_len[L->doc_prompt[d]] + doc_len[d];
+    std::vector<int32_t> heaviest(n_docs);
+    std::iota(heaviest.begin(), heaviest.end(), 0);
+    std::stable_sort(heaviest.begin(), heaviest.end(), [&](int32_t a, int32_t b) { return doc_keys[a] > doc_keys[b]; });
     for (int32_t t = 0; t < T; ++t) {
       int32_t w = L->live_ptr[t];
       int32_t* dlp = &L->doc_live_ptr[(size_t)t * (n_docs + 1)];
-      std::vector<int32_t> units;
       for (int32_t d = 0; d < n_docs; ++d) {
         dlp[d] = w - L->live_ptr[t];
         for (int32_t b = branch_ptr[d]; b < branch_ptr[d + 1]; ++b)
           if (L->branch_len[b] > t) L->live_branch[w++] = b;
         const int32_t nb = w - L->live_ptr[t] - dlp[d];
-        if (nb > 0) units.push_back(d);
         L->max_rows[t] = std::max(L->max_rows[t], nb);
       }
       dlp[n_docs] = w - L->live_ptr[t];
-      // heaviest documents first: cost ~ keys streamed
-      std::stable_sort(units.begin(), units.end(), [&](int32_t a, int32_t b) {
-        const int64_t ca = (int64_t)header_len[L->doc_prompt[a]] + doc_len[a];
-        const int64_t cb = (int64_t)header_len[L->doc_prompt[b]] + doc_len[b];
-        return ca > cb;
-      });
-      L->unit_doc.insert(L->unit_doc.end(), units.begin(), units.end());
-      L->unit_ptr[t + 1] = (int32_t)L->unit_doc.size();
-      for (int32_t d : units) {
+      for (int32_t d : heaviest) {
+        if (dlp[d + 1] == dlp[d]) continue;
+        L->unit_doc.push_back(d);
         const int32_t p = L->doc_prompt[d];
         // all live branches of a document share one position in the contiguous mode
         int32_t pos = -1;
@@ -496,6 +525,7 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
                                  dlp[d], nbl, pos, b_first};
         L->unit_desc.insert(L->unit_desc.end(), desc, desc + 8);
       }
+      L->unit_ptr[t + 1] = (int32_t)L->unit_doc.size();
     }
     L->total_units = (int64_t)L->unit_doc.size();
     int device = 0, n_cus = L->n_cus;
@@ -692,15 +722,20 @@ int hpd_build_layout(const hpd_config* cfg, int32_t n_prompts, const int32_t* he
                  o_blen = A.add(L->branch_len), o_pblk = A.add(L->pblk), o_pdesc = A.add(L->punit_desc),
                  o_fdesc = A.add(L->funit_desc), o_spos = A.add(L->skel_pos), o_soff = A.add(L->skel_off),
                  o_sseg = A.add(L->skel_seg_off), o_scum = A.add(L->skel_cum), o_fblk = A.add(L->fblk),
-                 o_fill = A.add(L->fill_blk), o_dynfix = A.add(L->dyn_fixed), o_f32 = A.add(L->f32_groups),
-                 o_fgrp = A.add(L->fgroup_desc);
+                 o_fill = A.add(L->fill_blk), o_dynfix = A.add(L->dyn_fixed), o_f32 = A.add(L->f32_groups);
+    // (a long list goes behind the others as it is: a second transfer is 10 us, one more copy of it on the host more than that)
+    const size_t n_fgrp = L->fgroup_desc.size() > 1 << 16 ? L->fgroup_desc.size() : 0;
+    const size_t o_fgrp = n_fgrp ? A.host.size() : A.add(L->fgroup_desc);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipGetDevice(&L->device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&L->n_cus, hipDeviceAttributeMultiprocessorCount, L->device);
-    if (e == hipSuccess) e = hipMalloc(&L->d_ints, A.host.size() * sizeof(int32_t));
+    if (e == hipSuccess) e = hipMalloc(&L->d_ints, (A.host.size() + n_fgrp) * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc(&L->d_rope, L->rope.size() * sizeof(float));
     if (e == hipSuccess)
       e = hipMemcpyAsync(L->d_ints, A.host.data(), A.host.size() * sizeof(int32_t),
+                         hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && n_fgrp)
+      e = hipMemcpyAsync((int32_t*)L->d_ints + o_fgrp, L->fgroup_desc.data(), n_fgrp * sizeof(int32_t),
                          hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
       e = hipMemcpyAsync(L->d_rope, L->rope.data(), L->rope.size() * sizeof(float),

@@ -1080,6 +1080,28 @@ def test_prefill_attention_with_three_workgroups_per_cu(g, hkv, literal):
         _say(f"  worst err/rms {rel:.2e}")
 
 
+@pytest.mark.parametrize("hkv", [1, 2])
+def test_prefill_attention_of_a_list_of_row_groups_that_is_uploaded_by_itself(hkv):
+    """More than 8192 row groups of 16 tokens per kv head, in several lanes: against the general kernel, which has no list."""
+    from paper_2604_26209_amd import binding as B
+    per, n = 12, 90
+    doc = [113 + i % 16 for i in range(per * n)]
+    wl = W.make_workload("long_list", "bf16", 8 * hkv, hkv, 128, 500000.0, 2, [33] * n, [per] * n, doc, [1] * len(doc), [2] * len(doc))
+    q = W.normal_values((wl.n_prefix_tokens, 8 * hkv, 128), 5, "cuda", "bf16")
+    k, v = (W.normal_values((wl.n_prefix_tokens, hkv, 128), seed, "cuda", "bf16") for seed in (6, 7))
+    _say(f"prefill, long list, hkv={hkv}: {wl.n_prefix_tokens} tokens")
+    outs = []
+    for mode in (0, 3):
+        lay = B.layout_from_workload(wl, out_dtype=B.HPD_OUT_F32)
+        B.hpd_set_kernel_mode(lay, mode)
+        kp, vp, _, _ = B.alloc_pools(lay)
+        B.hpd_prefix_fill(lay, k, v, kp, vp)
+        outs.append(torch.zeros(q.shape, device="cuda"))
+        B.hpd_prefill_attention(lay, q, kp, vp, outs[-1])
+    # two roundings of queries and weights to 11 bits, of outputs of size 1
+    assert float((outs[0] - outs[1]).abs().max()) < H.BF16_TOL * float(outs[1].square().mean().sqrt())
+
+
 @pytest.mark.parametrize("literal", [False, True])
 @pytest.mark.parametrize("case", ["low", "very_low", "rising", "falling", "common_offset", "peaked_x8"])
 def test_prefill_score_ranges_of_the_online_softmax(case, literal):
