@@ -8,6 +8,9 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
+#include <limits>
+#include <numeric>
 #include <random>
 #include <vector>
 
@@ -125,6 +128,45 @@ static void check_prefill_groups(const hpd_layout* L) {
   for (auto& s : seen)
     for (int c : s) CHECK(c == 1);
   CHECK(n == L->prefill_groups);
+  // the order of each lane, and that the lanes are as even as their units allow
+  const size_t lanes = 8 / std::gcd(8, Hkv), row = (size_t)L->n_cus / lanes / Hkv;
+  auto blocks = [&](const int32_t* d, int32_t tok) {
+    return (L->cfg.mask_mode == HPD_MASK_PAPER ? d[1] : (d[1] + 31) / 32) + (std::min(tok + per, d[5]) + 31) / 32;
+  };
+  int64_t heaviest = 0, least = std::numeric_limits<int64_t>::max(), greatest = 0;
+  for (size_t u = 0; u < n_units; ++u) {
+    int64_t load = 0;
+    for (int32_t t = 0; t < L->funit_desc[u * 8 + 5]; t += per) load += blocks(L->funit_desc.data() + u * 8, t) + 6;
+    heaviest = std::max(heaviest, load);
+  }
+  for (size_t i = 0; i < lanes; ++i) {
+    std::vector<const int32_t*> of;
+    for (size_t r = i; r < L->fgroup_desc.size() / 8; r += lanes)
+      if (L->fgroup_desc[r * 8 + 5]) of.push_back(L->fgroup_desc.data() + r * 8);
+    std::vector<int32_t> b;
+    int64_t load = 0;
+    for (const int32_t* d : of) {
+      b.push_back(blocks(d, d[7]));
+      load += b.back() + 6;
+    }
+    least = std::min(least, load);
+    greatest = std::max(greatest, load);
+    if (L->prefill_groups > 16 * (int64_t)L->n_cus) {  // unit after unit, each from its last row group to its first
+      for (size_t k = 1; k < of.size(); ++k)
+        CHECK(std::equal(of[k], of[k] + 7, of[k - 1]) ? of[k][7] == of[k - 1][7] - per
+                                                      : of[k - 1][7] == 0 && of[k][7] + per >= of[k][5]);
+      continue;
+    }
+    std::vector<int32_t> want = b;
+    std::sort(want.begin(), want.end(), std::greater<int32_t>());
+    if (of.size() > row && of.size() <= 2 * row) {  // the first that shares its CU is the longest of them, with the shortest of all
+      const std::vector<int32_t> longest = want;
+      for (size_t k = 0; k < of.size(); ++k)
+        want[k] = k < row ? longest[(2 * row - of.size() + k) % row] : longest[of.size() - 1 - (k - row)];
+    }
+    CHECK(b == want);
+  }
+  CHECK(n_units == 0 || greatest - least <= heaviest);
 }
 
 static int dense_steps(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t P, int32_t header, int32_t J, std::vector<int32_t> doc,
