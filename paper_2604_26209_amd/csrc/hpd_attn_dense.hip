@@ -134,7 +134,8 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   const int32_t NR = (NS + SB - 1) / SB;  // rounds
   const const_i32* const list = (const const_i32*)(uintptr_t)(a.tb.pblk + 2 * (int64_t)(PAPER ? doff : 0));
 
-  // what only the tails need of the lane is formed where they need it: kept through the loops it costs registers
+  // What only the tails need of the lane is formed where they need it: kept through the loops it costs registers.  (The literal mask
+  // with two workgroups per CU has them: forming it again there, and looking for non-finite values 16 keys at a time, cost 1 to 2 %.)
   auto again = [](int lane) -> int { asm volatile("" : "+v"(lane)); return lane; };
   // ---- loads: quarter `wave` of a block (K rows 0..15, K rows 16..31, V d-blocks 0..1, 2..3; tail tiles: V rows 0..15,
   //      16..31)
@@ -220,14 +221,14 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   };
   auto issue_tile = [&](int32_t gb, uint32_t at) {
     const TileAt x = tile_at(gb - NB);
-    const int lane_t = again(lane), r4 = lane_t >> 4, c16 = lane_t & 15;
+    const int lane_t = WGS == 3 ? again(lane) : lane, r4 = lane_t >> 4, c16 = lane_t & 15;
     uint32_t rw[4], ch[4];
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
       const int32_t k = (wave & 1) * 16 + f * 4 + r4;
       const int32_t j = min(x.tb0 + (k >> x.lg), kb_end - 1);
       const int32_t pos = max(min(x.c * 8 + (k & ((1 << x.lg) - 1)), klen[j] - 1), 0);
-      rw[f] = PAGED ? paged_row((gb / SB) & 1, gb % SB * 32 + (k >> x.lg), pos) : tail_row(pb0 + j, pos);
+      rw[f] = PAGED ? paged_row((SB == 2 ? gb >> 1 : gb) & 1, (SB == 2 ? (gb & 1) * 32 : 0) + (k >> x.lg), pos) : tail_row(pb0 + j, pos);
       ch[f] = (uint32_t)(is_v ? (c16 ^ (2 * r4)) << 4 : (c16 ^ r4 ^ (4 * f)) << 4);
     }
     issue_rows(is_v ? v_tail : k_tail, rw, ch, at + (uint32_t)wave * 4096);
@@ -487,11 +488,14 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   // with branches that not all rows see has one, the product takes zeros in its place, and the rows that see it add it.  (A
   // token's value before it is weighted: what matters is that it is not finite.)
   auto non_finite = [](uint32_t half) -> bool { return (half & 0x7c00u) == 0x7c00u; };
-  auto take_out_non_finite = [&](int32_t tile, uint32_t at, int32_t h, uint4 (&vf)[4]) __attribute__((always_inline)) {  // keys 16 h ..
+  // vf: N fragments, of keys k0 .. k0 + 4 * N - 1.
+  auto take_out_non_finite = [&](auto nc, int32_t tile, uint32_t at, int32_t k0, uint4 (&vf)[decltype(nc)::value])
+      __attribute__((always_inline)) {
+    constexpr int N = decltype(nc)::value;
     const f16x2 zero = {(_Float16)0, (_Float16)0};
     f16x2 z[4] = {zero, zero, zero, zero};
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {  // (a finite value times zero is zero)
+    for (int f = 0; f < N; ++f) {  // (a finite value times zero is zero)
       z[0] = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].x), zero, z[0]);
       z[1] = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].y), zero, z[1]);
       z[2] = __builtin_elementwise_fma(__builtin_bit_cast(f16x2, vf[f].z), zero, z[2]);
@@ -503,11 +507,11 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
       return w & ((non_finite(w) ? 0u : 0xffffu) | (non_finite(w >> 16) ? 0u : 0xffff0000u));
     };
 #pragma unroll
-    for (int f = 0; f < 4; ++f) vf[f] = make_uint4(finite_pair(vf[f].x), finite_pair(vf[f].y), finite_pair(vf[f].z), finite_pair(vf[f].w));
+    for (int f = 0; f < N; ++f) vf[f] = make_uint4(finite_pair(vf[f].x), finite_pair(vf[f].y), finite_pair(vf[f].z), finite_pair(vf[f].w));
     const TileAt x = tile_at(tile);
-    const int g2 = again(lane) >> 5;
+    const int g2 = (WGS == 3 ? again(lane) : lane) >> 5;
 #pragma nounroll
-    for (int32_t k = 16 * h; k < 16 * h + 16; ++k) {
+    for (int32_t k = k0; k < k0 + 4 * N; ++k) {
       const int32_t j = x.tb0 + (k >> x.lg);
       const bool sees = j <= kb_row && (k & ((1 << x.lg) - 1)) < klen[min(j, kb_end - 1)] - x.c * 8;
 #pragma unroll
@@ -542,7 +546,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
           for (int blk = 0; blk < 4; ++blk)
             vf[blk] = *reinterpret_cast<const uint4*>(rc + at + lane_t * 16 + 8192 + (2 * blk + h) * 1024);
         }
-        if (later) take_out_non_finite(tile, at + 8192, h, vf);
+        if (later) take_out_non_finite(std::integral_constant<int, 4>{}, tile, at + 8192, 16 * h, vf);
         half_product(P[h], vf);
       }
       return;
@@ -554,15 +558,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
       else read_values(at + b * BLK + 8192, vf);
       f16x8 P0, P1;
       weights(s[b], P0, P1);
-      if (PAPER && N == 1 && later) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          uint4 half[4] = {vf[h], vf[2 + h], vf[4 + h], vf[6 + h]};
-          take_out_non_finite(tile, at + 8192, h, half);
-#pragma unroll
-          for (int blk = 0; blk < 4; ++blk) vf[2 * blk + h] = half[blk];
-        }
-      }
+      if (PAPER && N == 1 && later) take_out_non_finite(std::integral_constant<int, 8>{}, tile, at + 8192, 0, vf);
       value_product(P0, P1, vf);
     }
   };
@@ -670,8 +666,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
     open_round(r, at);
     if (!PAPER && r == NR - 1) issue_own_keys(my_free, my_free + 4096, 0, own_tile(0));
 #pragma nounroll
-    for (int32_t i = 0; i < SB && SB * r + i < NS; ++i) {
-      const int32_t b = SB * r + i;
+    for (int32_t b = SB * r; b < min(SB * r + SB, NS); ++b) {
       // what the rows see of the block: all of it, or what their bits say
       uint32_t ok = 0;
       bool masked = true, later = false;
@@ -691,7 +686,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
         if (x.tb0 > kb_row_max) continue;
         later = x.tb0 + (31 >> x.lg) > kb_row_min;
         // a row keeps the tokens in memory of the branches up to its own
-        const int lane_t = again(lane), g2 = lane_t >> 5;
+        const int lane_t = WGS == 3 ? again(lane) : lane, g2 = lane_t >> 5;
         const int32_t j_lane = x.tb0 + ((lane_t & 31) >> x.lg);
         masked = !__all(j_lane <= kb_row_min && klen[min(j_lane, kb_end - 1)] - x.c * 8 >= 1 << x.lg);
         if (masked) {
@@ -703,7 +698,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
           }
         }
       }
-      compute(std::integral_constant<int, 1>{}, at + i * BLK, masked, ok, 0u, tail ? b - NB : -1, later);
+      compute(std::integral_constant<int, 1>{}, SB == 2 ? (uint32_t)(b & 3) * BLK : at, masked, ok, 0u, tail ? b - NB : -1, later);
     }
     at = behind(at);
   }
@@ -859,13 +854,12 @@ hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32
   const int64_t items = ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
   if (items > 0x7fffffff) return hipErrorInvalidValue;
   // Three workgroups per CU where all of them run at a time that two per CU would leave to a second round, and from more than
-  // four per CU on; between them the third would only leave a longer last round.  Time of the kernel that had two per CU alone
-  // over two / three per CU (geometric means of random batches, block mask | literal mask): up to 512 workgroups 0.98 / 0.90 |
-  // 0.98 / 0.90, 512-768 0.98 / 1.04 | 0.99 / 1.09, 768-1024 0.98 / 0.95 | 0.98 / 0.97, 1024-3000 0.98 / 1.03 | 0.99 / 1.08,
-  // more 0.99 / 1.07 | 1.00 / 1.09.
+  // four per CU on; between them the third would only leave a longer last round.  Time with two per CU over time with three,
+  // geometric means of 3220 random batches, block mask | literal mask: up to 256 workgroups 0.90 | 0.88, 256-512 0.97 | 0.96, 512-768
+  // 1.12 | 1.19, 768-1024 0.97 | 0.99, 1024-1600 1.05 | 1.07, 1600-3000 1.07 | 1.09, more 1.11 | 1.10.  In the first of these ranges the
+  // grid has to have few workgroups without rows, which upset where the others go: the figures are for up to 1.25 times as many in
+  // the grid; with more 1.04 | 1.03, in a quarter of them below 0.97, down to 0.84.
   const int64_t cu = n_cus;
-  // In the first of these the grid has to have few workgroups without rows, which upset where the others go (three / two per CU,
-  // 512-768 workgroups: up to 1.3 times as many in the grid 1.17, more 1.02, down to 0.86).
   const bool three = (workgroups > 2 * cu && workgroups <= 3 * cu && 4 * items <= 5 * (int64_t)workgroups) || workgroups > 4 * cu;
   a.at_once = workgroups <= 3 * cu;
 #define HPD_DENSE_M(GG, PP, TT) launch_dense<GG, PP, TT>(a, items, three, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s)

@@ -365,23 +365,24 @@ def test_uneven_decode_batches_run_the_faster_kernel(case, mode):
     assert us[0] < 1.08 * us[1]
 
 
+@pytest.mark.parametrize("prompts", [24, 48])
 @pytest.mark.parametrize("case", ["two_blocks", "header", "names", "names_g2"])
-def test_literal_decode_of_many_rows_and_few_shared_blocks(case):
+def test_literal_decode_of_many_rows_and_few_shared_blocks(case, prompts):
     """Prompts whose header, document and names are two, three or five blocks of 32 keys: with fewer than four, tail tiles are
     among the first loads and the append comes in front of them.  26 steps: all tail formats, in chunks one to four; pools
-    of NaN; branches that end.  Against the oracle, the two-call sequence, pages of 8 to 32 tokens (the same bits), and the
-    other kernel, whose bits differ in every step."""
+    of NaN; branches that end.  384 workgroups, two per CU at a time, and 768, three.  Against the oracle, the two-call sequence, pages
+    of 8 to 32 tokens (the same bits), and the other kernel, whose bits differ in every step."""
     from paper_2604_26209_amd import binding as B
     hq, header, n = {"two_blocks": (64, 0, 32), "header": (64, 7, 32), "names": (32, 0, 64), "names_g2": (16, 0, 128)}[case]
-    prompts, steps = 48, 26
+    steps = 26
     blen = np.full(prompts * n, steps)
     blen[4::11] = 13
     attr = np.ones(prompts * n, np.int32)
     wl = W.make_workload("few_blocks", "bf16", hq, 8, 128, 500000.0, steps, [header] * prompts, [1] * prompts, [20] * prompts, [n] * prompts, blen)
     kw = dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=attr, mask_mode=B.HPD_MASK_PAPER)
-    _say(f"literal mask, few shared blocks: {case}")
+    _say(f"literal mask, few shared blocks: {case}, {prompts} prompts")
     a = H.run_hip(wl, fused=True, **kw)
-    H.check_all(wl, a, prompts=[0, 31], label=case, pos_mode="paper_gap", attr_len=attr, mask_mode="paper")
+    H.check_all(wl, a, prompts=[0, 31 % prompts], label=case, pos_mode="paper_gap", attr_len=attr, mask_mode="paper")
     b = H.run_hip(wl, inputs=a["inputs"], **kw)
     c = H.run_hip(wl, inputs=a["inputs"], fused=True, kernel_mode=3, **kw)
     for t, (x, y, z) in enumerate(zip(a["out"], b["out"], c["out"])):
@@ -429,17 +430,18 @@ def test_block_mask_decode_of_many_rows_through_large_pages(page):
 
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
 @pytest.mark.parametrize("literal", [False, True])
-def test_non_finite_values_of_a_branch_in_decode_with_many_rows(literal, value):
+@pytest.mark.parametrize("prompts", [24, 48])
+def test_non_finite_values_of_a_branch_in_decode_with_many_rows(prompts, literal, value):
     """One value of one branch at one step.  Literal mask: the outputs that are not finite are those of the generic kernel: rows of
     the branch and of later ones.  Block mask: no rows but those that the streaming kernel has (branches that share a tile
-    of 32 keys with it).  All others keep the bits of a run without it."""
+    of 32 keys with it).  All others keep the bits of a run without it.  384 workgroups, two per CU at a time, and 768, three."""
     from paper_2604_26209_amd import binding as B
-    prompts, n, steps, at = 48, 32, 12, 2
+    n, steps, at = 32, 12, 2
     attr = np.ones(prompts * n, np.int32)
     wl = W.make_workload("non_finite", "bf16", 64, 8, 128, 500000.0, steps, [7] * prompts, [1] * prompts, [40] * prompts, [n] * prompts,
                          np.full(prompts * n, steps))
     kw = dict(pos_mode=B.HPD_POS_PAPER_GAP, attr_len=attr, mask_mode=B.HPD_MASK_PAPER) if literal else {}
-    _say(f"non-finite value, literal={literal}: {value}")
+    _say(f"non-finite value, literal={literal}, {prompts} prompts: {value}")
     clean = H.run_hip(wl, fused=True, **kw)
     inputs = clean["inputs"]
     inputs.v_new[at][3 * n + 5, 1, 3] = value
