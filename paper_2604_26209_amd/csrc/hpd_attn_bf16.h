@@ -8,7 +8,7 @@
 // What the lookup of a workgroup's descriptor takes stands in front of these in a kernel's arguments, which the build has
 // loaded into registers before the kernel starts: the descriptor is requested at once instead of behind a trip for the
 // arguments (us a step, before -> now: fp32, 8 prompts x 12 branches 11.4 -> 11.1; 32 prompts x 16 branches 24.4 -> 24.0;
-// launches of several rounds as before: there the arguments are in the scalar cache).
+// launches of several rounds as before: there the arguments are in the scalar cache)  The launch functions take them from here.
 struct StreamArgs {
   hpd_dev_tables tb;
   int32_t step, Hq, Hkv, Tcap, RG, n_groups, out_f32, fused, live_base;
@@ -18,9 +18,8 @@ struct StreamArgs {
   float scale_log2;
 };
 
-// decode attention of launches with many rows per unit (hpd_attn_dense.hip); G, max_nblk: the kernel's rows per branch,
-// the most row blocks of any unit; workgroups: those that have rows
-hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32_t max_nblk, int32_t workgroups, int32_t n_cus, const void* q,
+// decode attention of launches with many rows per unit (hpd_attn_dense.hip); G: the kernel's rows per branch
+hipError_t hpd_launch_attention_dense(const hpd_layout* L, StreamArgs a, int32_t G, bool paper, const void* q,
                                       const void* k_prefix, const void* v_prefix, void* k_tail, void* v_tail,
                                       const void* k_new, const void* v_new, void* out, hipStream_t s);
 

@@ -5,7 +5,7 @@
 // What bounds such a launch is the compute waves.  attn_stream_kernel has six of them on a CU's four SIMDs beside two
 // loaders: a block of 32 keys took 184 ns per row block and CU (70B-like, in-kernel timestamps), 129 ns here, and its one
 // workgroup per CU leaves the CU idle while it starts and ends (18 of 93 us), where here the others work.
-//  * Two or three workgroups per CU (WGS; the rule is at the launch), as in the prefill: rounds of two blocks and a ring of four, or
+//  * Two or three workgroups per CU (WGS; the rule is hpd_plan_dense_launch's), as in the prefill: rounds of two blocks and a ring of four, or
 //    rounds of one block, a ring of three, 168 registers.  For those what only the tails need of a lane is formed behind the prefix
 //    (again()), a row's branch waits in LDS, a tile's values are read 16 keys at a time, and the start value of the scores is
 //    two registers (MinusPoint).  No register may be left over for scratch memory: the compiler does not see the loads that are
@@ -36,7 +36,7 @@
 
 namespace {
 
-constexpr int DENSE_WAVES = 4;  // row blocks per workgroup
+constexpr int DENSE_WAVES = HPD_DENSE_ROWS / 32;  // row blocks per workgroup
 
 // Minus the reference point of a row, 16 times in the start value of its scores.  With two workgroups per CU the 16
 // registers are kept, and the first matrix instruction of a chain reads them as its addend; with three they are two, and
@@ -831,38 +831,27 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   }
 }
 
-template <int G, bool PAPER, bool PAGED>
-hipError_t launch_dense(const StreamArgs& a, int64_t items, bool three, const void* q, const void* k_prefix, const void* v_prefix,
-                        void* k_tail, void* v_tail, const void* k_new, const void* v_new, void* out, hipStream_t s) {
-  if (three)
-    attn_dense_kernel<G, PAPER, PAGED, 3><<<dim3((unsigned)items), DENSE_WAVES * 64, 0, s>>>(
-        PAPER ? a.tb.punit_desc : a.tb.unit_desc, a.n_groups, a.RG, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail,
-        (const uint16_t*)k_new, (const uint16_t*)v_new, out);
-  else
-    attn_dense_kernel<G, PAPER, PAGED, 2><<<dim3((unsigned)items), DENSE_WAVES * 64, 0, s>>>(
-        PAPER ? a.tb.punit_desc : a.tb.unit_desc, a.n_groups, a.RG, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix, (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail,
-        (const uint16_t*)k_new, (const uint16_t*)v_new, out);
+template <int G, bool PAPER, bool PAGED, int WGS>
+hipError_t launch_dense(const StreamArgs& a, int64_t items, const void* q, const void* k_prefix, const void* v_prefix, void* k_tail,
+                        void* v_tail, const void* k_new, const void* v_new, void* out, hipStream_t s) {
+  attn_dense_kernel<G, PAPER, PAGED, WGS><<<dim3((unsigned)items), DENSE_WAVES * 64, 0, s>>>(
+      PAPER ? a.tb.punit_desc : a.tb.unit_desc, a.n_groups, a.RG, a.Hkv, a, (const uint16_t*)q, (const uint16_t*)k_prefix,
+      (const uint16_t*)v_prefix, (uint16_t*)k_tail, (uint16_t*)v_tail, (const uint16_t*)k_new, (const uint16_t*)v_new, out);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32_t max_nblk, int32_t workgroups, int32_t n_cus, const void* q,
-                                      const void* k_prefix, const void* v_prefix, void* k_tail, void* v_tail,
-                                      const void* k_new, const void* v_new, void* out, hipStream_t s) {
-  a.RG = (max_nblk + DENSE_WAVES - 1) / DENSE_WAVES;
-  const int64_t items = ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
-  if (items > 0x7fffffff) return hipErrorInvalidValue;
-  // Three workgroups per CU where all of them run at a time that two per CU would leave to a second round, and from more than
-  // four per CU on; between them the third would only leave a longer last round.  Time with two per CU over time with three,
-  // geometric means of 3220 random batches, block mask | literal mask: up to 256 workgroups 0.90 | 0.88, 256-512 0.97 | 0.96, 512-768
-  // 1.12 | 1.19, 768-1024 0.97 | 0.99, 1024-1600 1.05 | 1.07, 1600-3000 1.07 | 1.09, more 1.11 | 1.10.  In the first of these ranges the
-  // grid has to have few workgroups without rows, which upset where the others go: the figures are for up to 1.25 times as many in
-  // the grid; with more 1.04 | 1.03, in a quarter of them below 0.97, down to 0.84.
-  const int64_t cu = n_cus;
-  const bool three = (workgroups > 2 * cu && workgroups <= 3 * cu && 4 * items <= 5 * (int64_t)workgroups) || workgroups > 4 * cu;
-  a.at_once = workgroups <= 3 * cu;
-#define HPD_DENSE_M(GG, PP, TT) launch_dense<GG, PP, TT>(a, items, three, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s)
+hipError_t hpd_launch_attention_dense(const hpd_layout* L, StreamArgs a, int32_t G, bool paper, const void* q, const void* k_prefix,
+                                      const void* v_prefix, void* k_tail, void* v_tail, const void* k_new, const void* v_new,
+                                      void* out, hipStream_t s) {
+  const hpd_dense_launch x = hpd_plan_dense_launch(L, a.step);
+  if (x.grid > 0x7fffffff) return hipErrorInvalidValue;
+  a.n_groups = x.n_groups;
+  a.RG = x.row_groups;
+  a.at_once = x.at_once;
+#define HPD_DENSE_W(GG, PP, TT, WW) launch_dense<GG, PP, TT, WW>(a, x.grid, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s)
+#define HPD_DENSE_M(GG, PP, TT) (x.per_cu == 3 ? HPD_DENSE_W(GG, PP, TT, 3) : HPD_DENSE_W(GG, PP, TT, 2))
 #define HPD_DENSE(GG)                                                                   \
   (paper ? a.tb.tail_pages ? HPD_DENSE_M(GG, true, true) : HPD_DENSE_M(GG, true, false) \
          : a.tb.tail_pages ? HPD_DENSE_M(GG, false, true) : HPD_DENSE_M(GG, false, false))
@@ -875,4 +864,5 @@ hipError_t hpd_launch_attention_dense(StreamArgs a, int32_t G, bool paper, int32
   }
 #undef HPD_DENSE
 #undef HPD_DENSE_M
+#undef HPD_DENSE_W
 }

@@ -1440,7 +1440,7 @@ hipError_t hpd_launch_attention_stream(const hpd_layout* L, int32_t step, const 
   a.n_groups = (int32_t)(n_units * a.Hkv);
   // the plan is that of the layout's own lists; a launch on the device-side ones has the rows that are left by then
   const bool dense = !dynamic && (L->kernel_mode == 0 || L->kernel_mode == 2) && L->dense_steps[step];
-  if (dense) return hpd_launch_attention_dense(a, G, paper, max_nblk, L->dense_workgroups[step], L->n_cus, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s);
+  if (dense) return hpd_launch_attention_dense(L, a, G, paper, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s);
   const int64_t items = ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
 #define HPD_LAUNCH_M(GG, PP)                                                                            \
   (narrow ? launch_g<GG, NarrowShape, PP>(a, items, q, k_prefix, v_prefix, k_tail, v_tail, k_new, v_new, out, s) \
@@ -1479,9 +1479,13 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
   // kernel, which was faster in every call measured: one prompt of 200 tokens 13.6 -> 9.3 us, and the
   // larger ones at the kernel.
   const bool narrow = L->kernel_mode == 4, wide = L->kernel_mode == 3, own = !narrow && !wide;
-  const int32_t shape_blocks = narrow ? NarrowShape::MAX_BLOCKS : own ? PREFILL_WAVES : WideShape::MAX_BLOCKS;
-  a.RG = (max_nblk + shape_blocks - 1) / shape_blocks;
-  a.n_groups = (int32_t)(n_units * a.Hkv);
+  if (own) {  // takes its row groups from the list
+    a.RG = a.n_groups = 0;
+  } else {
+    const int32_t shape_blocks = narrow ? NarrowShape::MAX_BLOCKS : WideShape::MAX_BLOCKS;
+    a.RG = (max_nblk + shape_blocks - 1) / shape_blocks;
+    a.n_groups = (int32_t)(n_units * a.Hkv);
+  }
   const int64_t items = own ? (int64_t)L->fgroup_desc.size() / 8 * a.Hkv : ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
   if (items > 0x7fffffff) return hipErrorInvalidValue;
   const bool list = L->cfg.mask_mode == HPD_MASK_PAPER;

@@ -336,6 +336,26 @@ struct IntArena {
 
 }  // namespace
 
+// Three workgroups per CU where all of them run at a time that two per CU would leave to a second round, and from more than
+// four per CU on; between them the third would only leave a longer last round.  Time with two per CU over time with three,
+// geometric means of 3220 random batches, block mask | literal mask: up to 256 workgroups 0.90 | 0.88, 256-512 0.97 | 0.96, 512-768
+// 1.12 | 1.19, 768-1024 0.97 | 0.99, 1024-1600 1.05 | 1.07, 1600-3000 1.07 | 1.09, more 1.11 | 1.10.  In the first of these ranges the
+// grid has to have few workgroups without rows, which upset where the others go: the figures are for up to 1.25 times as many in
+// the grid; with more 1.04 | 1.03, in a quarter of them below 0.97, down to 0.84.
+hpd_dense_launch hpd_plan_dense_launch(const hpd_layout* L, int32_t step) {
+  const bool paper = paper_mode(L);
+  const int32_t Hkv = L->cfg.n_kv_heads, Gr = L->cfg.n_q_heads / Hkv, G = Gr <= 2 ? Gr : Gr <= 4 ? 4 : 8;
+  const int32_t n_units = paper ? L->punit_ptr[step + 1] - L->punit_ptr[step] : L->unit_ptr[step + 1] - L->unit_ptr[step];
+  hpd_dense_launch d;
+  d.n_groups = n_units * Hkv;
+  d.row_groups = ((paper ? L->pmax_rows[step] : L->max_rows[step]) * G + HPD_DENSE_ROWS - 1) / HPD_DENSE_ROWS;
+  d.grid = ((int64_t)d.n_groups + 7) / 8 * 8 * d.row_groups;
+  const int64_t cu = L->n_cus, workgroups = L->dense_workgroups[step];
+  d.per_cu = (workgroups > 2 * cu && workgroups <= 3 * cu && 4 * d.grid <= 5 * workgroups) || workgroups > 4 * cu ? 3 : 2;
+  d.at_once = workgroups <= 3 * cu;
+  return d;
+}
+
 extern "C" {
 
 const char* hpd_status_string(int status) {

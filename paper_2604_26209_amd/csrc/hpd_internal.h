@@ -147,6 +147,7 @@ hipError_t hpd_launch_finetune_mask(const int32_t* table, int32_t S, int32_t* po
 // fp32 decode attention (hpd_attn_f32.hip): block mask, 32, 64 or 128 channels; one row group of 16
 // rows holds the query heads of at least one branch; 16-byte loads from the pools.  kernel_mode 1 forces the generic kernel.
 constexpr int32_t HPD_PREFILL_ROWS = 128;  // query rows per workgroup of attn_prefill_kernel
+constexpr int32_t HPD_DENSE_ROWS = 128;    // ... and of attn_dense_kernel
 constexpr int32_t HPD_F32_ROWS = 16;
 constexpr int32_t HPD_F32_PAD = 4;  // floats between the rows of a wave's share of the result in LDS
 // waves of a workgroup: at most 16, and their tiles fit 128 of the 160 KB of LDS
@@ -163,6 +164,16 @@ hipError_t hpd_launch_attention_f32(const hpd_layout* L, int32_t step, const voi
 
 // most keys any row of the step has in the generic kernel (it keeps one score per key in LDS)
 int64_t hpd_generic_max_keys(const hpd_layout* L, int32_t step);
+
+// A launch of attn_dense_kernel: its (unit, kv head), the row groups of the widest unit, the workgroups of the grid, how many of them
+// run on a CU at a time (2 or 3), and whether three per CU are all that have rows
+struct hpd_dense_launch {
+  int32_t n_groups, row_groups;
+  int64_t grid;
+  int32_t per_cu;
+  bool at_once;
+};
+hpd_dense_launch hpd_plan_dense_launch(const hpd_layout* L, int32_t step);
 
 bool hpd_stream_supported(const hpd_layout* L);
 hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const void* k_prefix,

@@ -195,6 +195,69 @@ static int dense_steps(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t P,
   return n == 0 ? NONE : n == T ? ALL : SOME;
 }
 
+// workgroups per CU at a time in the steps of a bf16 batch, 0 where the streaming kernel runs; branch b ends after blen(b) steps
+// and has attr(b) name tokens (literal mask)
+static std::vector<int> workgroups_per_cu(int32_t hq, int32_t hkv, int32_t T, const std::vector<int32_t>& header, int32_t docs,
+                                          const std::vector<int32_t>& doc, const std::vector<int32_t>& branches, bool paper,
+                                          const std::function<int32_t(int32_t)>& blen, const std::function<int32_t(int32_t)>& attr) {
+  hpd_config cfg{};
+  cfg.n_q_heads = hq; cfg.n_kv_heads = hkv; cfg.head_dim = 128; cfg.dtype = HPD_BF16; cfg.rope_base = 500000.0; cfg.max_new = T;
+  cfg.flags = HPD_FLAG_HOST_ONLY;
+  cfg.pos_mode = paper ? HPD_POS_PAPER_GAP : HPD_POS_CONTIG;
+  cfg.mask_mode = paper ? HPD_MASK_PAPER : HPD_MASK_BLOCK;
+  std::vector<int32_t> doc_ptr{0}, branch_ptr{0}, lens, names;
+  for (size_t p = 0; p < header.size(); ++p) doc_ptr.push_back(doc_ptr.back() + docs);
+  for (int32_t n : branches) branch_ptr.push_back(branch_ptr.back() + n);
+  for (int32_t b = 0; b < branch_ptr.back(); ++b) {
+    lens.push_back(blen(b));
+    names.push_back(attr(b));
+  }
+  hpd_layout* L = nullptr;
+  CHECK(hpd_build_layout(&cfg, (int32_t)header.size(), header.data(), doc_ptr.data(), doc.data(), branch_ptr.data(), lens.data(),
+                         paper ? names.data() : nullptr, nullptr, &L) == HPD_OK);
+  CHECK(L->n_cus == 256);
+  std::vector<int> per_cu;
+  for (int32_t t = 0; t < T; ++t) per_cu.push_back(L->dense_steps[t] ? hpd_plan_dense_launch(L, t).per_cu : 0);
+  hpd_layout_free(L);
+  return per_cu;
+}
+
+// the batches of the GPU tests that are there for one of the two shapes of the kernel for many rows per unit: what they run
+static void many_rows_of_the_gpu_tests() {
+  auto steps_of = [](const std::vector<int>& v, int per_cu) { return std::count(v.begin(), v.end(), per_cu); };
+  // test_decode_of_many_rows_per_unit_by_workgroups_per_cu
+  const struct { int g, tenths; } shapes[] = {{1, 15}, {2, 25}, {8, 25}, {3, 25}, {8, 50}, {1, 50}, {2, 50}};
+  for (const auto& x : shapes)
+    for (bool literal : {false, true}) {
+      const int pad = x.g <= 2 ? x.g : x.g <= 4 ? 4 : 8, n = 256 / pad, prompts = x.tenths * 256 / 160, per = literal ? 1 : 2;
+      const int heads[] = {0, 33, 64, 7, 95}, docs[] = {1, 31, 64, 33, 97, 32};
+      std::vector<int32_t> header, doc, branches;
+      for (int p = 0; p < (literal ? prompts : prompts / 2); ++p) header.push_back(heads[p % 5]);
+      for (int d = 0; d < (int)header.size() * per; ++d) {
+        doc.push_back(docs[d % 6]);
+        branches.push_back(n - d % 3 % 2);
+      }
+      const auto v = workgroups_per_cu(x.g * 8, 8, 21, header, per, doc, branches, literal,
+                                       [](int32_t b) { return b % 11 == 7 ? 18 : b % 9 == 5 ? 14 : 21; },
+                                       [](int32_t b) { return 1 + b % 4; });
+      const int want = x.tenths < 20 ? 2 : 3;
+      CHECK(steps_of(v, want) >= 7 && steps_of(v, 5 - want) == 0);
+      if (x.g > 1) CHECK(steps_of(v, want) >= 15);
+    }
+  // test_non_finite_values_of_a_branch_in_decode_with_many_rows, test_literal_decode_of_many_rows_and_few_shared_blocks
+  for (int prompts : {24, 48}) {
+    const int want = prompts == 24 ? 2 : 3;
+    const std::vector<int32_t> doc40(prompts, 40), doc20(prompts, 20);
+    for (bool literal : {false, true})
+      CHECK(steps_of(workgroups_per_cu(64, 8, 12, std::vector<int32_t>(prompts, 7), 1, doc40, std::vector<int32_t>(prompts, 32), literal,
+                                       [](int32_t) { return 12; }, [](int32_t) { return 1; }), want) == 12);
+    const struct { int hq, header, n; } few[] = {{64, 0, 32}, {64, 7, 32}, {32, 0, 64}, {16, 0, 128}};
+    for (const auto& x : few)
+      CHECK(steps_of(workgroups_per_cu(x.hq, 8, 26, std::vector<int32_t>(prompts, x.header), 1, doc20, std::vector<int32_t>(prompts, x.n),
+                                       true, [](int32_t b) { return b % 11 == 4 ? 13 : 26; }, [](int32_t) { return 1; }), want) == 26);
+  }
+}
+
 // random batches of the bf16 kernels' shape, from fewer row groups than CUs to more than 16 per CU
 static void prefill_lists() {
   std::mt19937 rng(30);
@@ -343,6 +406,7 @@ int main() {
   }
   CHECK(with_list >= 10);
   prefill_lists();
+  many_rows_of_the_gpu_tests();
   // short workgroups: four waves where all of them are at work at once, two where they queue up; a wave per tile and one
   // for the newest tokens where there are few workgroups
   CHECK(f32_waves(8, 2, 32, 1, 500, 5, 4) == 4);

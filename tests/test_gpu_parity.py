@@ -276,10 +276,10 @@ def test_decode_of_many_rows_per_unit(g, literal):
 
 
 @pytest.mark.parametrize("literal", [False, True])
-@pytest.mark.parametrize("g,of_cus", [(1, 1.5), (8, 2.5), (3, 2.5), (8, 5), (1, 5)])
+@pytest.mark.parametrize("g,of_cus", [(1, 1.5), (2, 2.5), (8, 2.5), (3, 2.5), (8, 5), (1, 5), (2, 5)])
 def test_decode_of_many_rows_per_unit_by_workgroups_per_cu(g, of_cus, literal):
     """The kernel for many rows per unit in launches of 1.5 workgroups per CU (two at a time), of 2.5 (three, priorities by
-    progress) and of 5 (three).  Documents of one token and around one block, row blocks that do not fill a workgroup, branches that
+    progress) and of 5 (three); that the plan has them run so, the host test of the layouts says for the same batches.  Documents of one token and around one block, row blocks that do not fill a workgroup, branches that
     end, 21 steps: three chunks of tails, so that every piece of LDS that three workgroups per CU leave a wave holds keys and
     values; pools of NaN.  Oracle, two-call sequence and pages of 8 tokens (the same bits), the other kernel."""
     from paper_2604_26209_amd import binding as B
@@ -1063,7 +1063,7 @@ def test_prefill_attention_at_the_edges_of_its_blocks(g, literal):
 
 
 @pytest.mark.parametrize("literal", [False, True])
-@pytest.mark.parametrize("g,hkv", [(1, 16), (3, 6), (4, 8), (8, 3)])
+@pytest.mark.parametrize("g,hkv", [(1, 16), (2, 5), (3, 6), (4, 8), (8, 3)])
 def test_prefill_attention_with_three_workgroups_per_cu(g, hkv, literal):
     """The same edges in a launch of more than two row groups per CU, which runs rounds of one block; a number of kv heads
     that is no multiple of 8 deals the row groups to several lanes."""
