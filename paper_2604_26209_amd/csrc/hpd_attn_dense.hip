@@ -85,6 +85,10 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   constexpr int SB = WGS == 2 ? 2 : 1;      // blocks per round
   constexpr int SLOTS = WGS == 2 ? 4 : 3;   // blocks in the ring
   constexpr uint32_t RING = SLOTS * BLK;
+  // Two workgroups per CU, block mask: what most rounds of the prefix do lies in one piece, the rest behind the loop.  A branch that is
+  // taken costs a round 2 % where a SIMD has one wave (the loop had one more than with two per CU alone: up to 256 workgroups 0.987
+  // of its speed, so 1.002).  Three per CU: paged tails 0.5 % slower so; literal mask: registers spill.
+  constexpr bool STRAIGHT = !PAPER && WGS == 2;
   __shared__ uint4 ring[SLOTS * SLOT_U4];
   constexpr int MAX_KEY_BRANCHES = 256;
   __shared__ int32_t klen[PAPER ? MAX_KEY_BRANCHES : 1];  // tokens in memory of every key branch
@@ -390,7 +394,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[b][i] = S[i];
       }
-      if (masked) {
+      if (STRAIGHT ? __builtin_expect(masked, 0) : masked) {
 #pragma unroll
         for (int b = 0; b < N; ++b)
 #pragma unroll
@@ -403,7 +407,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
     for (int b = 0; b < N; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) bm = fmaxf(bm, s[b][i]);
-    if (__any(bm > slack)) {
+    if (STRAIGHT ? __builtin_expect(__any(bm > slack), 0) : __any(bm > slack)) {
       bm = fmaxf(bm, __shfl_xor(bm, 32));
       // (a row that has seen no key yet keeps its empty state)
       const bool none = bm <= NEG_BIG, first = slack < 0.f;
@@ -414,7 +418,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
       const bool again = __any(fabsf(m_old) > fmaxf(128.f, fabsf(m_new)));
       minus_m.set(m_new);
       const float shift = again ? 0.f : d;
-      if (again) scores();
+      if (STRAIGHT ? __builtin_expect(again, 0) : again) scores();
 #pragma unroll
       for (int b = 0; b < N; ++b)
 #pragma unroll
@@ -650,11 +654,11 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
   }
   for (int32_t r = 0; r < r_plain; ++r) {
     open_round(r, at);
-    if (!PAPER && r == NR - 1) issue_own_keys(my_free, my_free + 4096, 0, own_tile(0));
+    if (!PAPER && (STRAIGHT ? __builtin_expect(r == NR - 1, 0) : r == NR - 1)) issue_own_keys(my_free, my_free + 4096, 0, own_tile(0));
     const int32_t vA = keys_of(SB * r), vB = SB == 2 ? keys_of(2 * r + 1) : 32;
     const bool masked = (vA & vB) != 32;
     uint32_t ok0 = 0, ok1 = 0;
-    if (masked) { ok0 = ok_bits(vA); ok1 = ok_bits(vB); }
+    if (STRAIGHT ? __builtin_expect(masked, 0) : masked) { ok0 = ok_bits(vA); ok1 = ok_bits(vB); }
     compute(std::integral_constant<int, SB>{}, at, masked, ok0, ok1, -1, false);
     at = behind(at);
   }
