@@ -8,7 +8,7 @@
 // What the lookup of a workgroup's descriptor takes stands in front of these in a kernel's arguments, which the build has
 // loaded into registers before the kernel starts: the descriptor is requested at once instead of behind a trip for the
 // arguments (us a step, before -> now: fp32, 8 prompts x 12 branches 11.4 -> 11.1; 32 prompts x 16 branches 24.4 -> 24.0;
-// launches of several rounds as before: there the arguments are in the scalar cache)  The launch functions take them from here.
+// launches of several rounds as before: there the arguments are in the scalar cache).  The launch functions take them from here, so that both are the same.
 struct StreamArgs {
   hpd_dev_tables tb;
   int32_t step, Hq, Hkv, Tcap, RG, n_groups, out_f32, fused, live_base;

@@ -27,7 +27,7 @@
 //  * Paged tails: the page table's entries for a tile come by DMA ahead of it.
 // Measured (us per hpd_decode_step, the other kernel -> two workgroups per CU -> this): 16 prompts x 2 documents of 2048 tokens,
 // 48 branches, 64/8 heads, step 17, 160 -> 142 -> 135 (768 workgroups); literal mask, 64 prompts x 4 documents of 384 tokens, 96
-// branches, 32/8 heads, step 7, 369 -> 323 -> 312.  Outputs differ from the other kernel's by rounding (relative 7e-4 in bf16);
+// branches, 32/8 heads, step 7, 369 -> 315 -> 305.  Outputs differ from the other kernel's by rounding (relative 7e-4 in bf16);
 // error against 64 bits 1.7e-3 for both.
 #include <algorithm>
 #include <type_traits>

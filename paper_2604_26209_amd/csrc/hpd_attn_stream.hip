@@ -1019,15 +1019,17 @@ attn_stream_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t 
 // the LDS reads of their operands, 1.20 with the softmax, 1.13 with the loads to LDS (loops without start and end, clock
 // 1.6-1.7 of 2.4 GHz: cycles saved lower the clock, only work saved gains), and a launch waits for the XCD whose clock is
 // lowest (5 % below the highest).
-// Measured (us per call with hpd_prefix_fill, one card; the general kernel -> rounds of two blocks, two workgroups per CU, unit
-// after unit -> this): 32 prompts x (64 + 512 tokens), 32/8 heads 207 -> 175 -> 162; 16 prompts x (128 + 2 x 2048),
-// 64/8 heads 3238 -> 2763 -> 2582; literal mask, 16 ragged prompts of up to 8 documents 4465 -> 3742 -> 3524.
+// Measured (us per call with hpd_prefix_fill): 32 prompts x (64 + 512 tokens), 32/8 heads; 16 prompts x (128 + 2 x 2048), 64/8
+// heads; literal mask, 16 ragged prompts of up to 8 documents: the general kernel -> rounds of two blocks, two workgroups per CU, unit
+// after unit 207 -> 177, 3238 -> 2706, 4465 -> 3724; that -> this, another card, 171 -> 158, 2624 -> 2501, 3640 -> 3493.  Over 2782
+// random batches 1.24 times the speed of that in the mean; 11 slower by more than 3 %, down to 0.87 (3 kv heads, four units).
 // A wave whose rows lie behind the segment's end loads and meets the barriers, and its products are
 // thrown away; the general kernel gave it a share of the keys.  Calls of such segments are faster all the
 // same (us, the general kernel -> rounds of two blocks, 32/8 heads): one prompt of 64 + 100 tokens 11.8 -> 8.3; 2 x (1000 + 300 documents
 // of 8, 16, 32 tokens) 1403 -> 1093, 1470 -> 1096, 1521 -> 1110; 1 x (8000 + 8) 649 -> 525; 16/16 heads, 2 x
 // (1000 + 300 x 32) 2670 -> 2041; literal mask, 16 x (64 + 4 x 500, 8 tokens of names) 785 -> 664.
-// The outputs differ from the general kernel's by rounding (relative 5e-4 in bf16).  Error against 64 bits on N(0,1) inputs, fp32 outputs: 2.42e-4, general kernel 2.44e-4.
+// The outputs differ from the general kernel's by rounding (relative 5e-4 in bf16).  Error against 64 bits on N(0,1) inputs, fp32 outputs: 2.42e-4, general
+// kernel 2.44e-4; one prompt of 64 + 512 tokens with two workgroups per CU 2.331e-4, with three 2.313e-4.
 // ---------------------------------------------------------------------------------------
 constexpr int PREFILL_WAVES = HPD_PREFILL_ROWS / 32;  // row blocks per workgroup
 // WGS = workgroups per CU
@@ -1494,8 +1496,9 @@ hipError_t hpd_launch_prefill_stream(const hpd_layout* L, const void* q, const v
   const int64_t items = own ? (int64_t)L->fgroup_desc.size() / 8 * a.Hkv : ((int64_t)(a.n_groups + 7) / 8 * 8) * a.RG;
   if (items > 0x7fffffff) return hipErrorInvalidValue;
   const bool list = L->cfg.mask_mode == HPD_MASK_PAPER;
-  // Up to two workgroups per CU none is a third, and rounds of two blocks are the faster ones (time of the kernel before over
-  // two / three per CU: up to 256 row groups 1.03 / 1.01, 256-320 1.14 / 1.13, 450-512 1.22 / 1.23; above: 512-768 1.15 / 1.28).
+  // Up to two workgroups per CU none is a third, and rounds of two blocks are the faster ones or as fast (time of the kernel before
+  // over two / three per CU, the latter without the second block's reference point: up to 256 row groups 1.03 / 1.01, 256-320 1.14 /
+  // 1.13, 450-512 1.22 / 1.23; above: 512-768 1.15 / 1.28).
   const bool three = L->prefill_groups > 2 * (int64_t)L->n_cus;
 #define HPD_LAUNCH_M(GG, PP)                                                                   \
   (narrow ? launch_g<GG, NarrowShape, PP>(a, items, q, k_prefix, v_prefix, nullptr, nullptr,  \

@@ -143,7 +143,7 @@ void plan_f32(hpd_layout* L, int32_t n_cus) {
 }
 
 // The steps that run attn_dense_kernel (hpd_attn_dense.hip).  Against the kernel with loader waves it has the faster
-// loop for many rows (four waves that load and compute, two workgroups per CU), and the start and end of a workgroup under
+// loop for many rows (four waves that load and compute, two or three workgroups per CU), and the start and end of a workgroup under
 // another's work; but it reads the prefix once per 128 rows, keeps fewer bytes in flight, and a wave without rows idles where
 // the other kernel gives it a share of the keys.  Which one is faster depends on how the units' rows divide, on their
 // lengths and on how many workgroups there are, so both are estimated from the units: the time of a workgroup (start, blocks
@@ -338,7 +338,7 @@ struct IntArena {
 
 // Three workgroups per CU where all of them run at a time that two per CU would leave to a second round, and from more than
 // four per CU on; between them the third would only leave a longer last round.  Time with two per CU over time with three,
-// geometric means of 3220 random batches, block mask | literal mask: up to 256 workgroups 0.90 | 0.88, 256-512 0.97 | 0.96, 512-768
+// geometric means of 3220 random batches, block mask | literal mask: up to 256 workgroups 0.89 | 0.88, 256-512 0.97 | 0.96, 512-768
 // 1.12 | 1.19, 768-1024 0.97 | 0.99, 1024-1600 1.05 | 1.07, 1600-3000 1.07 | 1.09, more 1.11 | 1.10.  In the first of these ranges the
 // grid has to have few workgroups without rows, which upset where the others go: the figures are for up to 1.25 times as many in
 // the grid; with more 1.04 | 1.03, in a quarter of them below 0.97, down to 0.84.
