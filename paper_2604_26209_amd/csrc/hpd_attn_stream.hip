@@ -1021,8 +1021,8 @@ attn_stream_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t 
 // lowest (5 % below the highest).
 // Measured (us per call with hpd_prefix_fill): 32 prompts x (64 + 512 tokens), 32/8 heads; 16 prompts x (128 + 2 x 2048), 64/8
 // heads; literal mask, 16 ragged prompts of up to 8 documents: the general kernel -> rounds of two blocks, two workgroups per CU, unit
-// after unit 207 -> 177, 3238 -> 2706, 4465 -> 3724; that -> this, another card, 171 -> 158, 2624 -> 2501, 3640 -> 3493.  Over 2782
-// random batches 1.24 times the speed of that in the mean; 11 slower by more than 3 %, down to 0.87 (3 kv heads, four units).
+// after unit 207 -> 177, 3238 -> 2706, 4465 -> 3724; that -> this, another card, 171 -> 158, 2624 -> 2501, 3640 -> 3493.  Over 3478
+// random batches 1.2 times the speed of that in the mean; 11 slower by more than 3 %, down to 0.92 (most of 512 to 768 row groups).
 // A wave whose rows lie behind the segment's end loads and meets the barriers, and its products are
 // thrown away; the general kernel gave it a share of the keys.  Calls of such segments are faster all the
 // same (us, the general kernel -> rounds of two blocks, 32/8 heads): one prompt of 64 + 100 tokens 11.8 -> 8.3; 2 x (1000 + 300 documents

@@ -244,11 +244,16 @@ void plan_dense(hpd_layout* L, int32_t n_cus) {
 //    groups: 512-1000 1.25 / 1.33, 1000-2000 1.21 / 1.30, 2000-4000 1.24 / 1.26.
 //  * Up to two per CU: all start at once, the second half where the first one's workgroups are, in their order.  The shortest
 //    join each other - the longest of them the shortest -, and the longest have a CU to themselves: longest first 1.05-1.17, so
-//    1.14-1.22 (280 row groups of one prompt of 115 + 345 tokens, literal mask: 17.4 us, so 16.2).
+//    1.14-1.22 (280 row groups of one prompt of 115 + 345 tokens, literal mask: 17.4 us, so 16.2).  No lanes (below): dealt to
+//    them, the row groups of a few units load some XCDs twice as much as others, and the records that fill up start in front of row
+//    groups.  Against the same grid, up to 256 | 256-512 row groups, in lanes -> so: 1 kv head 1.06 -> 1.07 | 1.21 -> 1.35, 2: 1.07
+//    -> 1.07 | 1.22 -> 1.26, 3: 1.08 -> 1.09 | 1.18 -> 1.22, 4: 1.09 -> 1.09 | 1.25 -> 1.24, 5 to 7: 1.09 -> 1.11 | 1.26 -> 1.29, 12:
+//    1.14 -> 1.15 | 1.32 -> 1.35; 84 documents of 59 tokens, 12/3 heads, 12.6 -> 8.9 us (grid 9.6).
 //  * More than 16: unit after unit, so that the row groups that run at a time read the same keys out of the L2 (all of 28000 row
 //    groups longest first: 3349 us, unit after unit 2078); the heaviest unit first, in each the longest row group first.
-// Workgroup b runs on XCD b % 8, and takes kv head b % Hkv of record b / Hkv: with fewer than 8 kv heads the records are dealt
-// to 8 / gcd(8, Hkv) lanes in turn, and the row groups of a unit stay in one lane, hence those of a (unit, kv head) on one XCD.
+// Workgroup b runs on XCD b % 8, and takes kv head b % Hkv of record b / Hkv: with more than two row groups per CU and a number of kv
+// heads that is no multiple of 8 the records are dealt to 8 / gcd(8, Hkv) lanes in turn, and the row groups of a unit stay in one
+// lane, hence those of a (unit, kv head) on one XCD.
 // More than 16 row groups per CU are written straight to their places; collected and copied twice, they made building slower by up to a
 // third.  What is left is one pass over the memory (ms of hpd_build_layout, without the list -> collected -> so: 256 x 2 x 4000
 // tokens, 64/8 heads 3.97 -> 4.52 -> 4.18; 1000 x 4 x 500, 32/8 heads 1.20 -> 1.57 -> 1.24; that one has the sorting of the documents
@@ -263,8 +268,11 @@ void list_prefill_groups(hpd_layout* L, int32_t n_cus) {
   auto unit = [&](size_t u) { return L->funit_desc.data() + u * 8; };
   auto groups = [&](size_t u) { return ceil_div(unit(u)[5], per); };
   auto seen_in_full = [&](size_t u) { return list ? unit(u)[1] : ceil_div(unit(u)[1], HPD_KEY_BLOCK); };  // blocks
+  int64_t all = 0;
+  for (size_t u = 0; u < n_units; ++u) all += groups(u);
+  L->prefill_groups = all * Hkv;
   struct Lane { int64_t load = 0, n = 0; };
-  std::vector<Lane> lanes(8 / std::gcd(8, Hkv));
+  std::vector<Lane> lanes(L->prefill_groups <= 2 * (int64_t)n_cus ? 1 : 8 / std::gcd(8, Hkv));
   std::vector<uint8_t> lane_of(lanes.size() > 1 ? n_units : 0);
   for (size_t u = 0; u < n_units; ++u) {
     size_t to = 0;
@@ -279,12 +287,8 @@ void list_prefill_groups(hpd_layout* L, int32_t n_cus) {
     }
     lanes[to].n += groups(u);
   }
-  int64_t most = 0, all = 0;
-  for (const Lane& l : lanes) {
-    most = std::max(most, l.n);
-    all += l.n;
-  }
-  L->prefill_groups = all * Hkv;
+  int64_t most = 0;
+  for (const Lane& l : lanes) most = std::max(most, l.n);
   L->fgroup_desc.resize(most * lanes.size() * 8);
   auto put = [&](size_t lane, size_t k, size_t u, int32_t tok) {
     int32_t* o = L->fgroup_desc.data() + (k * lanes.size() + lane) * 8;

@@ -98,8 +98,9 @@ static int32_t f32_waves(int32_t hq, int32_t hkv, int32_t D, int32_t T, int32_t 
 
 // the steps of an even bf16 batch that run the kernel for many rows per unit: all of them, some, none
 enum { NONE = 0, SOME = 1, ALL = 2 };
-// attn_prefill_kernel's list: every row group of every segment once, with its segment's words; the row groups of a segment are
-// dealt to one XCD for every kv head (workgroup b: record b / Hkv, kv head b % Hkv, XCD b % 8)
+// attn_prefill_kernel's list: every row group of every segment once, with its segment's words.  With more than two row groups per CU
+// those of a segment are dealt to one XCD for every kv head (workgroup b: record b / Hkv, kv head b % Hkv, XCD b % 8); otherwise no
+// record is without tokens, so that every XCD has the same number of row groups, or one more.
 static void check_prefill_groups(const hpd_layout* L) {
   const int32_t Hkv = L->cfg.n_kv_heads, Gr = L->cfg.n_q_heads / Hkv;
   if (L->cfg.dtype != HPD_BF16 || L->cfg.head_dim != 128 || Gr > 8) {
@@ -110,10 +111,14 @@ static void check_prefill_groups(const hpd_layout* L) {
   const size_t n_units = L->funit_desc.size() / 8;
   std::vector<std::vector<int>> seen(n_units), xcd(n_units, std::vector<int>(Hkv, -1));
   int64_t n = 0;
+  const bool few = L->prefill_groups <= 2 * (int64_t)L->n_cus;
   for (size_t u = 0; u < n_units; ++u) seen[u].assign((L->funit_desc[u * 8 + 5] + per - 1) / per, 0);
   for (size_t r = 0; r < L->fgroup_desc.size() / 8; ++r) {
     const int32_t* d = L->fgroup_desc.data() + r * 8;
-    if (d[5] == 0) continue;
+    if (d[5] == 0) {
+      CHECK(!few);
+      continue;
+    }
     size_t u = 0;  // (a segment is told by its first pool slot and its kind)
     while (u < n_units && !std::equal(d, d + 7, L->funit_desc.data() + u * 8)) ++u;
     CHECK(u < n_units && d[7] % per == 0 && d[7] >= 0 && d[7] < d[5]);
@@ -121,7 +126,7 @@ static void check_prefill_groups(const hpd_layout* L) {
     for (int32_t hk = 0; hk < Hkv; ++hk, ++n) {
       int& x = xcd[u][hk];
       const int now = (int)((r * Hkv + hk) % 8);
-      CHECK(x < 0 || x == now);
+      CHECK(few || x < 0 || x == now);
       x = now;
     }
   }
@@ -129,7 +134,7 @@ static void check_prefill_groups(const hpd_layout* L) {
     for (int c : s) CHECK(c == 1);
   CHECK(n == L->prefill_groups);
   // the order of each lane, and that the lanes are as even as their units allow
-  const size_t lanes = 8 / std::gcd(8, Hkv), row = (size_t)L->n_cus / lanes / Hkv;
+  const size_t lanes = few ? 1 : 8 / std::gcd(8, Hkv), row = (size_t)L->n_cus / lanes / Hkv;
   auto blocks = [&](const int32_t* d, int32_t tok) {
     return (L->cfg.mask_mode == HPD_MASK_PAPER ? d[1] : (d[1] + 31) / 32) + (std::min(tok + per, d[5]) + 31) / 32;
   };
