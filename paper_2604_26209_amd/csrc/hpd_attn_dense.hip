@@ -413,7 +413,7 @@ attn_dense_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t r
       const bool none = bm <= NEG_BIG, first = slack < 0.f;
       const float d = none ? 0.f : first ? bm : fmaxf(bm, 0.f);
       const float alpha = first ? 0.f : fast_exp2(-d);
-      slack = none && first ? slack : WGS == 3 && N == 1 && first ? 0.f : MAX_SLACK;  // (a first block by itself: as there)
+      slack = none && first ? slack : WGS == 3 && N == 1 && first ? 0.f : MAX_SLACK;  // (the second block moves a first one's point)
       const float m_old = minus_m.get(), m_new = m_old - d;
       const bool again = __any(fabsf(m_old) > fmaxf(128.f, fabsf(m_new)));
       minus_m.set(m_new);

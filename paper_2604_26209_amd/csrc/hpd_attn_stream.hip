@@ -1021,7 +1021,7 @@ attn_stream_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t 
 // lowest (5 % below the highest).
 // Measured (us per call with hpd_prefix_fill): 32 prompts x (64 + 512 tokens), 32/8 heads; 16 prompts x (128 + 2 x 2048), 64/8
 // heads; literal mask, 16 ragged prompts of up to 8 documents: the general kernel -> rounds of two blocks, two workgroups per CU, unit
-// after unit 207 -> 177, 3238 -> 2706, 4465 -> 3724; that -> this, another card, 171 -> 155, 2624 -> 2468, 3640 -> 3478.  Over 3478
+// after unit 207 -> 177, 3238 -> 2706, 4465 -> 3724; that -> this, another card, 171 -> 157, 2660 -> 2488, 3647 -> 3438.  Over 3478
 // random batches 1.2 times the speed of that in the mean; 11 slower by more than 3 %, down to 0.92 (most of 512 to 768 row groups).
 // A wave whose rows lie behind the segment's end loads and meets the barriers, and its products are
 // thrown away; the general kernel gave it a share of the keys.  Calls of such segments are faster all the
@@ -1029,7 +1029,7 @@ attn_stream_kernel(const int32_t* __restrict__ descs, int32_t n_groups, int32_t 
 // of 8, 16, 32 tokens) 1403 -> 1093, 1470 -> 1096, 1521 -> 1110; 1 x (8000 + 8) 649 -> 525; 16/16 heads, 2 x
 // (1000 + 300 x 32) 2670 -> 2041; literal mask, 16 x (64 + 4 x 500, 8 tokens of names) 785 -> 664.
 // The outputs differ from the general kernel's by rounding (relative 5e-4 in bf16).  Error against 64 bits on N(0,1) inputs, fp32 outputs: 2.42e-4, general
-// kernel 2.44e-4; one prompt of 64 + 512 tokens with two workgroups per CU 2.331e-4, with three 2.321e-4.
+// kernel 2.44e-4; one prompt of 64 + 512 tokens with two workgroups per CU and with three 2.331e-4.
 // ---------------------------------------------------------------------------------------
 constexpr int PREFILL_WAVES = HPD_PREFILL_ROWS / 32;  // row blocks per workgroup
 // WGS = workgroups per CU
@@ -1191,10 +1191,7 @@ attn_prefill_kernel(const int32_t* __restrict__ descs, int32_t kv_heads, StreamA
       // infinite, and infinity times 0 is NaN.
       const bool first = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, slack))) < 0.f;  // (all rows alike)
       const float d = first ? bm : fmaxf(bm, 0.f);
-      // A first block by itself: the second one moves the point too, as a point over 64 keys has the largest weight of more rows be
-      // exactly 1.  With the first block's alone the error against 64 bits was 0.4 to 1 % larger than with rounds of two blocks (fp32
-      // outputs, 11 random batches), so it is 0.3 to 1 % smaller; 0.5 % of the time, in segments of a few blocks up to 6.
-      slack = WGS == 3 && N == 1 && first ? 0.f : MAX_SLACK;
+      slack = MAX_SLACK;
       // These scores were added up on top of the old reference point and carry its rounding.  Where it is farther
       // from 0 than the new one and large (up to 128 that rounding is a sixteenth of the weights'), once
       // more from there.  (Whenever the point moves: 2701 -> 2992 us on 16 prompts x (128 + 2 x 2048), 64/8 heads,
@@ -1279,10 +1276,11 @@ attn_prefill_kernel(const int32_t* __restrict__ descs, int32_t kv_heads, StreamA
   };
   uint32_t at = 0;
   int32_t r = 0;
-  // Rounds of one block: the first two at once, where all rows see both, so that the point is that of 64 keys without being moved.
-  // The third is on its way meanwhile, the fourth is requested a round late.  Against moving it with the second block: 1.008x (block
-  // mask) and 1.019x (literal) in the mean of 1100 random batches; the three calls above 1.01 to 1.02x.
-  if (WGS == 3 && NBh >= 2) {
+  // Rounds of one block: the first two at once, where all rows see both, so that the reference point is that of 64 keys as in rounds
+  // of two: more rows' largest weight is exactly 1.  With the first block's alone the error against 64 bits was 0.4 to 1 % larger (fp32
+  // outputs, 11 random batches).  The third block is on its way meanwhile, the fourth is requested a round late.  Time of moving the
+  // point with the second block over this: 1.008 (block mask), 1.019 (literal) in the mean of 1100 random batches.
+  if (WGS == 3 && plain_end >= 2) {
     issue(nA, 2 * BLK);
     nA = slot_of(min(3, NB - 1));
     asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
